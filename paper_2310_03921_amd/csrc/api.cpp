@@ -166,16 +166,20 @@ gap_status drain_dev_err(gap_handle* h) {
   return GAP_OK;
 }
 
-// Workspace slices of the pair transposition.
+// Workspace slices of the pair transposition (`order` only where the targets
+// are wanted by decreasing in-degree, `list` unless the caller lends a buffer
+// of n_pairs words that is free until the transposition is done).
 struct PairWs {
-  size_t tgt_ptr, tgt_pair, src, order, scratch;
+  size_t tgt_ptr = 0, tgt_pair = 0, src = 0, order = 0, scratch = 0, list = 0;
 };
-void layout_pairs(Layout& L, int64_t n_atoms, int64_t n_pairs, PairWs& p) {
+void layout_pairs(Layout& L, int64_t n_atoms, int64_t n_pairs, PairWs& p, bool want_order = false,
+                  bool own_list = true) {
   p.tgt_ptr = L.take(sizeof(int64_t) * (n_atoms + 1));
   p.tgt_pair = L.take(sizeof(int32_t) * std::max<int64_t>(n_pairs, 1));
   p.src = L.take(sizeof(int32_t) * std::max<int64_t>(n_pairs, 1));
-  p.order = L.take(sizeof(int32_t) * std::max<int64_t>(n_atoms, 1));
-  p.scratch = L.take(sizeof(int32_t) * (n_atoms + 2048));
+  if (want_order) p.order = L.take(sizeof(int32_t) * std::max<int64_t>(n_atoms, 1));
+  p.scratch = L.take(sizeof(int32_t) * gapk::pair_scratch_ints(n_atoms, want_order));
+  if (own_list) p.list = L.take(sizeof(int32_t) * std::max<int64_t>(n_pairs, 1));
 }
 
 void run_pairs(gap_handle* h, const gap_atoms* a, const PairWs& p, bool want_order,
@@ -187,7 +191,7 @@ void run_pairs(gap_handle* h, const gap_atoms* a, const PairWs& p, bool want_ord
   gapk::pair_transpose(a->pair_ptr, a->pair_j, a->n_atoms, a->n_pairs, at<int64_t>(h, p.tgt_ptr),
                        at<int32_t>(h, p.tgt_pair), at<int32_t>(h, p.src),
                        want_order ? at<int32_t>(h, p.order) : nullptr, at<int32_t>(h, p.scratch),
-                       h->dev_err, st);
+                       at<int32_t>(h, p.list), h->dev_err, st);
   h->timer.end(gapk::TM_PAIRS);
   h->timer.st = timer_st;
 }
@@ -469,11 +473,13 @@ gap_status gap_pair_transpose(gap_handle* h, const gap_atoms* a, int64_t* tgt_pt
     return fail(h, GAP_E_INVALID, "bad sizes");
   Layout L;
   const size_t src = L.take(sizeof(int32_t) * std::max<int64_t>(a->n_pairs, 1));
-  const size_t scr = L.take(sizeof(int32_t) * (a->n_atoms + 2048));
+  const size_t scr = L.take(sizeof(int32_t) * gapk::pair_scratch_ints(a->n_atoms, false));
+  const size_t lst = L.take(sizeof(int32_t) * std::max<int64_t>(a->n_pairs, 1));
   s = ensure_ws(h, L.off);
   if (s != GAP_OK) return s;
   gapk::pair_transpose(a->pair_ptr, a->pair_j, a->n_atoms, a->n_pairs, tgt_ptr, tgt_pair,
-                       at<int32_t>(h, src), nullptr, at<int32_t>(h, scr), h->dev_err, h->stream);
+                       at<int32_t>(h, src), nullptr, at<int32_t>(h, scr), at<int32_t>(h, lst),
+                       h->dev_err, h->stream);
   HIP_TRY(h, hipGetLastError());
   return GAP_OK;
 }
@@ -514,7 +520,7 @@ gap_status build_knm_impl(gap_handle* h, const gap_atoms* a, const gap_sparse* s
   if (prec != GAP_FP64 && prec != GAP_BF16X3) return fail(h, GAP_E_INVALID, "bad precision");
   Layout L;
   PairWs p;
-  layout_pairs(L, N, a->n_pairs, p);
+  layout_pairs(L, N, a->n_pairs, p, true);
   const size_t S = L.take(sizeof(double) * std::max<int64_t>(N * ld4(M), 1));
   SplitWs sw;
   size_t jh = 0, jl = 0;
@@ -1491,7 +1497,7 @@ gap_status gap_forces_noalloc(gap_handle* h, const gap_atoms* a, const double* d
   const bool direct = aligned32(dEdd) && a->D % 4 == 0;
   Layout L;
   PairWs p;
-  layout_pairs(L, a->n_atoms, a->n_pairs, p);
+  layout_pairs(L, a->n_atoms, a->n_pairs, p, false, false);  // (list: the f_pair slice)
   const size_t fp = L.take(sizeof(double) * std::max<int64_t>(3 * a->n_pairs, 1));
   const size_t gp = direct ? 0 : L.take(sizeof(double) * std::max<int64_t>(a->n_atoms * ld4(a->D), 1));
   if (L.off > kNoAllocScratchBytes)
@@ -1512,7 +1518,8 @@ gap_status gap_forces_noalloc(gap_handle* h, const gap_atoms* a, const double* d
                        reinterpret_cast<int64_t*>(base + p.tgt_ptr),
                        reinterpret_cast<int32_t*>(base + p.tgt_pair),
                        reinterpret_cast<int32_t*>(base + p.src), nullptr,
-                       reinterpret_cast<int32_t*>(base + p.scratch), h->dev_err, h->stream);
+                       reinterpret_cast<int32_t*>(base + p.scratch),
+                       reinterpret_cast<int32_t*>(base + fp), h->dev_err, h->stream);
   gapk::forces_f64(a->jac, f32(a->jac_dt), a->ld_jac, a->D, g, ldg,
                    reinterpret_cast<int32_t*>(base + p.src), a->n_atoms, a->n_pairs,
                    reinterpret_cast<int64_t*>(base + p.tgt_ptr),

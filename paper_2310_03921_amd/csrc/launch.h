@@ -59,10 +59,13 @@ struct Timer {
 
 // ---- pairs.hip ------------------------------------------------------------
 // tgt_ptr/tgt_pair (target-major pair view), pair_src, and the targets sorted
-// by decreasing in-degree (order).  scratch_i32 needs n_atoms + 2048 ints.
+// by decreasing in-degree (order, may be NULL).  list: n_pairs words of scratch.
 void pair_transpose(const int64_t* pair_ptr, const int32_t* pair_j, int64_t n_atoms,
                     int64_t n_pairs, int64_t* tgt_ptr, int32_t* tgt_pair, int32_t* pair_src,
-                    int32_t* order, int32_t* scratch_i32, int* dev_err, hipStream_t st);
+                    int32_t* order, int32_t* scratch_i32, int32_t* list, int* dev_err,
+                    hipStream_t st);
+// int32 words of pair_transpose's scratch_i32.
+int64_t pair_scratch_ints(int64_t n_atoms, bool want_order);
 // Configuration index of each atom (atom_cfg[i] = c for cfg_ptr[c] <= i < cfg_ptr[c+1]).
 void atom_config(const int64_t* cfg_ptr, int64_t n_cfg, int64_t n_atoms, int32_t* atom_cfg,
                  hipStream_t st);

@@ -3,10 +3,11 @@
 // The descriptor derivatives come as a source-major pair list (atom i, slot k)
 // pointing at atoms j(i,k).  A force observation on atom j sums over every pair
 // pointing at j (Sec. "Theory", operator L-hat), so the force-row and force
-// kernels walk a target-major view.  The view is built by a counting sort:
-// per-target counts (integer atomics), an exclusive scan, placement with
-// per-target cursors, and a per-target insertion sort that restores increasing
-// pair order, so the result does not depend on atomic ordering.
+// kernels walk a target-major view.  The view is built by a counting sort: the
+// per-target counting atomics also give every pair a slot in its target's
+// segment, an exclusive scan gives the segments, and a rank sort of each
+// segment restores increasing pair order, so the result does not depend on the
+// order in which the atomics arrived.
 //
 // Targets are also ordered by decreasing in-degree: the force-row kernel
 // processes 16 targets per wavefront, one incoming pair of each per step, and
@@ -14,6 +15,8 @@
 // Within one degree the order is increasing atom index, so the 16 targets of
 // a wavefront usually come from one or two neighbouring configurations and
 // their incoming pairs' Jacobian rows lie close together in memory.
+#include <algorithm>
+
 #include "common.h"
 #include "launch.h"
 
@@ -22,6 +25,11 @@ namespace gapk {
 namespace {
 
 constexpr int kDegBuckets = 1024;
+constexpr int kScanPer = 4096;      // counts scanned by one block
+constexpr int kWaveRankMax = 2048;  // segments up to this length are rank-sorted by one wave
+constexpr int kSmallAtoms = 1024;   // limits of the one-block form
+constexpr int kSmallPer = 12;       // pairs per thread
+constexpr int kSmallPairs = 1024 * kSmallPer;
 
 __global__ void k_fill_i32(int32_t* p, int64_t n, int32_t v) {
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
@@ -29,144 +37,299 @@ __global__ void k_fill_i32(int32_t* p, int64_t n, int32_t v) {
     p[i] = v;
 }
 
-__global__ void k_count_targets(const int32_t* __restrict__ pair_j, int64_t n_pairs,
-                                int64_t n_atoms, int32_t* __restrict__ cnt, int* dev_err) {
-  for (int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; p < n_pairs;
-       p += (int64_t)gridDim.x * blockDim.x) {
+// src[p] = i for the pairs p of atom i: sixteen lanes per atom.
+GAP_DEV void write_pair_src(const int64_t* __restrict__ pair_ptr, int64_t i, int64_t n_pairs,
+                            int32_t* __restrict__ src, int* dev_err) {
+  int64_t lo = pair_ptr[i], hi = pair_ptr[i + 1];
+  if (lo < 0 || hi > n_pairs || hi < lo) {
+    atomicOr(dev_err, GAP_DEVERR_INDEX);
+    lo = max((int64_t)0, min(lo, n_pairs));
+    hi = max(lo, min(hi, n_pairs));
+  }
+  for (int64_t p = lo + (threadIdx.x & 15); p < hi; p += 16) src[p] = (int32_t)i;
+}
+
+// Inclusive scan of one value per thread over the 1024 threads of a block.
+template <typename T>
+GAP_DEV T block_scan_1024(T v, T* wave_tot) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const T u = __shfl_up(v, o);
+    if (lane >= o) v += u;
+  }
+  if (lane == 63) wave_tot[wave] = v;
+  __syncthreads();
+  T base = 0;
+#pragma unroll
+  for (int w = 0; w < 16; ++w) base += (w < wave) ? wave_tot[w] : 0;
+  __syncthreads();
+  return v + base;
+}
+
+// Rank of this lane's value v (one of the n valid values of the wave, lanes
+// 0 .. n - 1) among the wave's values.
+GAP_DEV int wave_rank(int32_t v, int n) {
+  int r = 0;
+  for (int q = 0; q < n; ++q) r += __builtin_amdgcn_readlane(v, q) < v ? 1 : 0;
+  return r;
+}
+
+// Rank sort of one segment of n distinct values by one wave, in -> out.
+GAP_DEV void wave_sort_segment(const int32_t* in, int n_, int32_t* __restrict__ out) {
+  const int lane = threadIdx.x & 63;
+  const int n = __builtin_amdgcn_readfirstlane(n_);
+  if (n <= 64) {
+    const int32_t v = lane < n ? in[lane] : 0;
+    const int r = wave_rank(v, n);
+    if (lane < n) out[r] = v;
+    return;
+  }
+  for (int a = 0; a < n; a += 64) {
+    const int32_t v = a + lane < n ? in[a + lane] : 0;
+    int r = 0;
+    for (int b = 0; b < n; b += 64) {
+      const int32_t w = b + lane < n ? in[b + lane] : INT32_MAX;  // never below a pair index
+      const int nb = min(64, n - b);
+      for (int q = 0; q < nb; ++q) r += __builtin_amdgcn_readlane(w, q) < v ? 1 : 0;
+    }
+    if (a + lane < n) out[r] = v;
+  }
+}
+
+// The whole transposition in one block, for lists that fit its LDS and
+// registers: a molecular-dynamics cell of 64 atoms and 1,900 pairs took nine
+// launches and 189 us as separate kernels (most of it the serial sort of each
+// segment by one thread), and one launch here (the whole energy-and-force call
+// 389 -> 233 us).  Bound by latency: one round
+// trip to memory for the pair list, then LDS.
+__global__ __launch_bounds__(1024) void k_pairs_small(
+    const int64_t* __restrict__ pair_ptr, const int32_t* __restrict__ pair_j, int n_atoms,
+    int n_pairs, int64_t* __restrict__ tgt_ptr, int32_t* __restrict__ tgt_pair,
+    int32_t* __restrict__ pair_src, int32_t* __restrict__ order, int* dev_err) {
+  __shared__ int32_t cnt[kSmallAtoms], start[kSmallAtoms + 1], wave_tot[16];
+  __shared__ int32_t list[kSmallPairs];
+  const int t = threadIdx.x, wave = t >> 6;
+  int32_t jv[kSmallPer];
+#pragma unroll
+  for (int q = 0; q < kSmallPer; ++q) jv[q] = pair_j[min(t + 1024 * q, max(n_pairs, 1) - 1)];
+  cnt[t] = 0;
+#pragma unroll
+  for (int q = 0; q < kSmallPer; ++q)
+    if (t + 1024 * q < n_pairs) pair_src[t + 1024 * q] = -1;
+  __syncthreads();
+  bool bad = false;
+  int32_t pos[kSmallPer];
+#pragma unroll
+  for (int q = 0; q < kSmallPer; ++q) {
+    pos[q] = -1;
+    if (t + 1024 * q < n_pairs) {
+      if (jv[q] < 0 || jv[q] >= n_atoms)
+        bad = true;
+      else
+        pos[q] = atomicAdd(&cnt[jv[q]], 1);
+    }
+  }
+  if (bad) atomicOr(dev_err, GAP_DEVERR_INDEX);
+  for (int i = t >> 4; i < n_atoms; i += 64)
+    write_pair_src(pair_ptr, i, n_pairs, pair_src, dev_err);
+  __syncthreads();
+  const int32_t c = t < n_atoms ? cnt[t] : 0;
+  const int32_t incl = block_scan_1024(c, wave_tot);
+  start[t] = incl - c;
+  if (t == 1023) start[1024] = incl;
+  if (t < n_atoms) tgt_ptr[t] = incl - c;
+  if (t == 1023) tgt_ptr[n_atoms] = incl;
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < kSmallPer; ++q)
+    if (pos[q] >= 0) list[start[jv[q]] + pos[q]] = t + 1024 * q;
+  __syncthreads();
+  for (int j = wave; j < n_atoms; j += 16) {
+    const int lo = start[j];
+    wave_sort_segment(list + lo, start[j + 1] - lo, tgt_pair + lo);
+  }
+  for (int p = start[1024] + t; p < n_pairs; p += 1024) tgt_pair[p] = 0;  // dropped pairs
+  if (order != nullptr && t < n_atoms) {
+    const int32_t d = min(c, kDegBuckets - 1);
+    int r = 0;
+    for (int i = 0; i < n_atoms; ++i) {
+      const int32_t e = min(cnt[i], kDegBuckets - 1);
+      r += (e > d || (e == d && i < t)) ? 1 : 0;
+    }
+    order[r] = t;
+  }
+}
+
+__global__ void k_pairs_init(int32_t* __restrict__ cnt, int64_t n_cnt, int32_t* __restrict__ src,
+                             int64_t n_pairs) {
+  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < max(n_cnt, n_pairs);
+       i += (int64_t)gridDim.x * blockDim.x) {
+    if (i < n_cnt) cnt[i] = 0;
+    if (i < n_pairs) src[i] = -1;
+  }
+}
+
+// Count the pairs of every target; the counting atomic's old value is the
+// pair's slot in its target's segment.  The same launch writes the sources.
+__global__ void k_count_targets(const int64_t* __restrict__ pair_ptr,
+                                const int32_t* __restrict__ pair_j, int64_t n_pairs,
+                                int64_t n_atoms, int32_t* __restrict__ cnt,
+                                int32_t* __restrict__ slot, int32_t* __restrict__ src,
+                                int* dev_err) {
+  const int64_t t0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  const int64_t nt = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t p = t0; p < n_pairs; p += nt) {
     const int32_t j = pair_j[p];
     if (j < 0 || j >= n_atoms) {
       atomicOr(dev_err, GAP_DEVERR_INDEX);
       continue;
     }
-    atomicAdd(&cnt[j], 1);
+    slot[p] = atomicAdd(&cnt[j], 1);
   }
+  for (int64_t i = t0 >> 4; i < n_atoms; i += nt >> 4)
+    write_pair_src(pair_ptr, i, n_pairs, src, dev_err);
 }
 
-// Exclusive scan of n int32 counts into n+1 int64 offsets; one block of 1024.
+// Exclusive scan of n int32 counts into n + 1 int64 offsets: block b scans
+// counts [4096 b, 4096 (b + 1)) after summing all counts before them itself
+// (coalesced 16-byte reads that hit L2), so no pass waits for another block.
+// One block walking the whole list took 275 us for 116,000 counts.
 __global__ __launch_bounds__(1024) void k_scan_counts(const int32_t* __restrict__ cnt, int64_t n,
                                                       int64_t* __restrict__ ptr) {
-  __shared__ int64_t part[1024];
+  __shared__ int64_t wave_tot[16];
+  __shared__ int64_t base_s;
   const int t = threadIdx.x;
-  const int64_t chunk = (n + 1023) / 1024;
-  const int64_t lo = min(n, t * chunk), hi = min(n, lo + chunk);
-  int64_t s = 0;
-  for (int64_t i = lo; i < hi; ++i) s += cnt[i];
-  part[t] = s;
+  const int64_t lo = (int64_t)blockIdx.x * kScanPer;
+  const int4* c4 = reinterpret_cast<const int4*>(cnt);
+  int64_t before = 0;
+#pragma unroll 8
+  for (int64_t e = t; e < lo / 4; e += 1024) {
+    const int4 v = c4[e];
+    before += (int64_t)v.x + v.y + v.z + v.w;
+  }
+  before = block_scan_1024(before, wave_tot);
+  if (t == 1023) base_s = before;
   __syncthreads();
-  for (int off = 1; off < 1024; off <<= 1) {
-    int64_t v = (t >= off) ? part[t - off] : 0;
-    __syncthreads();
-    part[t] += v;
-    __syncthreads();
+  int32_t v[4];
+  int64_t s = 0;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int64_t i = lo + 4 * t + q;
+    v[q] = i < n ? cnt[i] : 0;
+    s += v[q];
   }
-  int64_t run = part[t] - s;
-  for (int64_t i = lo; i < hi; ++i) {
-    ptr[i] = run;
-    run += cnt[i];
+  const int64_t incl = block_scan_1024(s, wave_tot) + base_s;
+  int64_t run = incl - s;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int64_t i = lo + 4 * t + q;
+    if (i < n) ptr[i] = run;
+    run += v[q];
   }
-  if (t == 1023) ptr[n] = part[1023];
+  if (blockIdx.x == gridDim.x - 1 && t == 1023) ptr[n] = incl;
 }
 
 __global__ void k_place_pairs(const int32_t* __restrict__ pair_j, int64_t n_pairs, int64_t n_atoms,
-                              const int64_t* __restrict__ tgt_ptr, int32_t* __restrict__ cursor,
-                              int32_t* __restrict__ tgt_pair) {
+                              const int64_t* __restrict__ tgt_ptr,
+                              const int32_t* __restrict__ slot, int32_t* __restrict__ list) {
   for (int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; p < n_pairs;
        p += (int64_t)gridDim.x * blockDim.x) {
     const int32_t j = pair_j[p];
     if (j < 0 || j >= n_atoms) continue;
-    const int32_t pos = atomicAdd(&cursor[j], 1);
-    tgt_pair[tgt_ptr[j] + pos] = (int32_t)p;
+    list[tgt_ptr[j] + slot[p]] = (int32_t)p;
   }
 }
 
-__global__ void k_sort_segments(const int64_t* __restrict__ tgt_ptr, int64_t n_atoms,
-                                int32_t* __restrict__ tgt_pair) {
-  for (int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; j < n_atoms;
-       j += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t lo = tgt_ptr[j], hi = tgt_ptr[j + 1];
-    for (int64_t a = lo + 1; a < hi; ++a) {
-      const int32_t v = tgt_pair[a];
-      int64_t b = a - 1;
-      while (b >= lo && tgt_pair[b] > v) {
-        tgt_pair[b + 1] = tgt_pair[b];
-        --b;
-      }
-      tgt_pair[b + 1] = v;
+// Restore increasing pair order in every segment, list -> tgt_pair: one wave
+// per target ranks its values in registers (a serial insertion sort by one
+// thread per target took 1.27 ms for 116,000 targets of 30 pairs).  A segment
+// longer than kWaveRankMax is rebuilt by its wave from the pair list in order
+// instead (a pass over the list, not the square of the segment).  Entries past
+// the last segment (pairs dropped for an out-of-range target) hold pair 0, a
+// valid index for readers that clamp a slot to the end of the list.
+__global__ __launch_bounds__(256) void k_sort_segments(const int64_t* __restrict__ tgt_ptr,
+                                                       int64_t n_atoms, int64_t n_pairs,
+                                                       const int32_t* __restrict__ pair_j,
+                                                       const int32_t* __restrict__ list,
+                                                       int32_t* __restrict__ tgt_pair) {
+  const int lane = threadIdx.x & 63;
+  const int64_t nw = (int64_t)gridDim.x * 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  for (int64_t j = (int64_t)blockIdx.x * 4 + wave; j < n_atoms; j += nw) {
+    const int64_t lo = tgt_ptr[j], n = tgt_ptr[j + 1] - lo;
+    if (n <= kWaveRankMax) {
+      wave_sort_segment(list + lo, (int)n, tgt_pair + lo);
+      continue;
+    }
+    int64_t out = lo;
+    for (int64_t p0 = 0; p0 < n_pairs; p0 += 64) {
+      const bool mine = p0 + lane < n_pairs && pair_j[p0 + lane] == (int32_t)j;
+      const uint64_t m = __ballot(mine);
+      if (mine) tgt_pair[out + __popcll(m & ((1ull << lane) - 1))] = (int32_t)(p0 + lane);
+      out += __popcll(m);
     }
   }
+  for (int64_t p = tgt_ptr[n_atoms] + blockIdx.x * (int64_t)256 + threadIdx.x; p < n_pairs;
+       p += (int64_t)gridDim.x * 256)
+    tgt_pair[p] = 0;
 }
 
-__global__ void k_pair_src(const int64_t* __restrict__ pair_ptr, int64_t n_atoms, int64_t n_pairs,
-                           int32_t* __restrict__ src, int* dev_err) {
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n_atoms;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    int64_t lo = pair_ptr[i], hi = pair_ptr[i + 1];
-    if (lo < 0 || hi > n_pairs || hi < lo) {
-      atomicOr(dev_err, GAP_DEVERR_INDEX);
-      lo = max((int64_t)0, min(lo, n_pairs));
-      hi = max(lo, min(hi, n_pairs));
-    }
-    for (int64_t p = lo; p < hi; ++p) src[p] = (int32_t)i;
-  }
-}
-
-__global__ void k_degree_hist(const int64_t* __restrict__ tgt_ptr, int64_t n_atoms,
-                              int32_t* __restrict__ hist) {
-  for (int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; j < n_atoms;
-       j += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t d = tgt_ptr[j + 1] - tgt_ptr[j];
-    atomicAdd(&hist[d < kDegBuckets ? d : kDegBuckets - 1], 1);
-  }
-}
-
-// Turn the degree histogram into start offsets for decreasing degree.
-__global__ __launch_bounds__(kDegBuckets) void k_degree_offsets(int32_t* __restrict__ hist) {
-  __shared__ int32_t s[kDegBuckets];
-  const int t = threadIdx.x;
-  const int b = kDegBuckets - 1 - t;  // position t holds bucket b (decreasing degree)
-  s[t] = hist[b];
+// Stable counting sort of the atoms by decreasing degree, 1024 atoms per
+// block.  A wave finds each atom's place among its equals by comparing degrees
+// lane by lane, a block adds up its waves, and a scan over blocks and degrees
+// in between (k_degree_scan) gives every (block, degree) its start.  One
+// workgroup walking all atoms took 5.7 ms for 116,000 atoms.
+template <bool PLACE>
+__global__ __launch_bounds__(1024) void k_degree_block(const int64_t* __restrict__ tgt_ptr,
+                                                       int64_t n_atoms, int32_t* __restrict__ hist,
+                                                       int32_t* __restrict__ order) {
+  __shared__ uint16_t wh[16][kDegBuckets];
+  const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
+  const int64_t j = (int64_t)blockIdx.x * 1024 + t;
+  const int d = j < n_atoms ? (int)min(tgt_ptr[j + 1] - tgt_ptr[j], (int64_t)kDegBuckets - 1) : -1;
+  for (int e = t; e < 16 * kDegBuckets / 2; e += 1024) reinterpret_cast<uint32_t*>(wh)[e] = 0;
   __syncthreads();
-  for (int off = 1; off < kDegBuckets; off <<= 1) {
-    int32_t v = (t >= off) ? s[t - off] : 0;
-    __syncthreads();
-    s[t] += v;
-    __syncthreads();
+  int lower = 0, same = 0;
+#pragma unroll 8
+  for (int q = 0; q < 64; ++q) {
+    const bool eq = __builtin_amdgcn_readlane(d, q) == d;
+    same += eq ? 1 : 0;
+    lower += (eq && q < lane) ? 1 : 0;
   }
-  hist[b] = s[t] - hist[b];
+  if (d >= 0 && lower == 0) wh[wave][d] = (uint16_t)same;
+  __syncthreads();
+  int run = 0;
+#pragma unroll
+  for (int w = 0; w < 16; ++w) {
+    const int c = wh[w][t];
+    wh[w][t] = (uint16_t)run;
+    run += c;
+  }
+  int32_t* h = hist + (int64_t)blockIdx.x * kDegBuckets;
+  if (!PLACE) {
+    h[t] = run;
+    return;
+  }
+  __syncthreads();
+  if (d >= 0) order[h[d] + wh[wave][d] + lower] = (int32_t)j;
 }
 
-// Stable placement: one workgroup, thread b owns degree bucket b and walks the
-// atoms in index order, a chunk of kDegBuckets degrees at a time staged in
-// LDS.  Waves whose 64 buckets are all empty only help with the staging.
-__global__ __launch_bounds__(kDegBuckets) void k_degree_place(const int64_t* __restrict__ tgt_ptr,
-                                                              int64_t n_atoms,
-                                                              const int32_t* __restrict__ off,
-                                                              int32_t* __restrict__ order) {
-  __shared__ int16_t deg[kDegBuckets];
-  const int b = threadIdx.x;
-  int32_t pos = off[b];
-  const int32_t end = b > 0 ? off[b - 1] : (int32_t)n_atoms;  // buckets laid out decreasing
-  const bool busy = __any(pos < end);
-  for (int64_t base = 0; base < n_atoms; base += kDegBuckets) {
-    const int64_t j = base + b;
-    int d = -1;
-    if (j < n_atoms) d = (int)min(tgt_ptr[j + 1] - tgt_ptr[j], (int64_t)kDegBuckets - 1);
-    deg[b] = (int16_t)d;
-    __syncthreads();
-    if (busy) {
-      const int n = (int)min((int64_t)kDegBuckets, n_atoms - base);
-      const int4* d8 = reinterpret_cast<const int4*>(deg);
-      for (int i8 = 0; i8 < (n + 7) / 8; ++i8) {
-        const int4 v = d8[i8];  // eight degrees (entries past n hold -1)
-        const int w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-          const int dq = (int16_t)(w[q >> 1] >> (16 * (q & 1)));
-          if (dq == b) order[pos++] = (int32_t)(base + 8 * i8 + q);
-        }
-      }
-    }
-    __syncthreads();
+// hist[block][degree] -> start of that block's atoms of that degree in the
+// order of decreasing degree, then increasing block.
+__global__ __launch_bounds__(kDegBuckets) void k_degree_scan(int32_t* __restrict__ hist,
+                                                             int64_t n_blk) {
+  __shared__ int32_t wave_tot[16];
+  const int b = kDegBuckets - 1 - (int)threadIdx.x;  // decreasing degree
+  int32_t tot = 0;
+#pragma unroll 8
+  for (int64_t q = 0; q < n_blk; ++q) tot += hist[q * kDegBuckets + b];
+  int32_t run = block_scan_1024(tot, wave_tot) - tot;
+#pragma unroll 8
+  for (int64_t q = 0; q < n_blk; ++q) {
+    const int32_t c = hist[q * kDegBuckets + b];
+    hist[q * kDegBuckets + b] = run;
+    run += c;
   }
 }
 
@@ -188,38 +351,42 @@ inline unsigned grid_for(int64_t n, int block = 256) {
 
 }  // namespace
 
+int64_t pair_scratch_ints(int64_t n_atoms, bool want_order) {
+  const int64_t cnt = (n_atoms + 63) / 64 * 64;
+  return cnt + (want_order ? (n_atoms + 1023) / 1024 * kDegBuckets : 0);
+}
+
 void pair_transpose(const int64_t* pair_ptr, const int32_t* pair_j, int64_t n_atoms,
                     int64_t n_pairs, int64_t* tgt_ptr, int32_t* tgt_pair, int32_t* pair_src,
-                    int32_t* order, int32_t* scratch, int* dev_err, hipStream_t st) {
-  int32_t* cnt = scratch;                   // n_atoms
-  int32_t* hist = scratch + n_atoms;        // kDegBuckets
-  hipLaunchKernelGGL(k_fill_i32, dim3(grid_for(n_atoms + kDegBuckets)), dim3(256), 0, st, cnt,
-                     n_atoms + kDegBuckets, 0);
-  if (n_pairs > 0) {
-    hipLaunchKernelGGL(k_fill_i32, dim3(grid_for(n_pairs)), dim3(256), 0, st, pair_src, n_pairs,
-                       -1);
-    // entries past the last valid target's segment (pairs dropped for an
-    // out-of-range target) hold pair 0, a valid index for readers that clamp
-    // a slot to the end of the list
-    hipLaunchKernelGGL(k_fill_i32, dim3(grid_for(n_pairs)), dim3(256), 0, st, tgt_pair, n_pairs, 0);
-    hipLaunchKernelGGL(k_count_targets, dim3(grid_for(n_pairs)), dim3(256), 0, st, pair_j, n_pairs,
-                       n_atoms, cnt, dev_err);
+                    int32_t* order, int32_t* scratch, int32_t* list, int* dev_err,
+                    hipStream_t st) {
+  if (n_pairs > 0 && n_atoms > 0 && n_atoms <= kSmallAtoms && n_pairs <= kSmallPairs) {
+    hipLaunchKernelGGL(k_pairs_small, dim3(1), dim3(1024), 0, st, pair_ptr, pair_j, (int)n_atoms,
+                       (int)n_pairs, tgt_ptr, tgt_pair, pair_src, order, dev_err);
+    return;
   }
-  hipLaunchKernelGGL(k_scan_counts, dim3(1), dim3(1024), 0, st, cnt, n_atoms, tgt_ptr);
+  int32_t* cnt = scratch;                               // n_atoms
+  int32_t* hist = scratch + (n_atoms + 63) / 64 * 64;   // 1024 per 1024 atoms
+  hipLaunchKernelGGL(k_pairs_init, dim3(grid_for(std::max(n_atoms, n_pairs))), dim3(256), 0, st,
+                     cnt, n_atoms, pair_src, n_pairs);
+  if (n_pairs > 0)
+    hipLaunchKernelGGL(k_count_targets, dim3(grid_for(n_pairs)), dim3(256), 0, st, pair_ptr,
+                       pair_j, n_pairs, n_atoms, cnt, tgt_pair, pair_src, dev_err);
+  hipLaunchKernelGGL(k_scan_counts,
+                     dim3((unsigned)std::max<int64_t>(1, (n_atoms + kScanPer - 1) / kScanPer)),
+                     dim3(1024), 0, st, cnt, n_atoms, tgt_ptr);
   if (n_pairs > 0) {
-    hipLaunchKernelGGL(k_fill_i32, dim3(grid_for(n_atoms)), dim3(256), 0, st, cnt, n_atoms, 0);
     hipLaunchKernelGGL(k_place_pairs, dim3(grid_for(n_pairs)), dim3(256), 0, st, pair_j, n_pairs,
-                       n_atoms, tgt_ptr, cnt, tgt_pair);
-    hipLaunchKernelGGL(k_sort_segments, dim3(grid_for(n_atoms)), dim3(256), 0, st, tgt_ptr,
-                       n_atoms, tgt_pair);
-    hipLaunchKernelGGL(k_pair_src, dim3(grid_for(n_atoms)), dim3(256), 0, st, pair_ptr, n_atoms,
-                       n_pairs, pair_src, dev_err);
+                       n_atoms, tgt_ptr, tgt_pair, list);
+    hipLaunchKernelGGL(k_sort_segments, dim3(grid_for(n_atoms, 4)), dim3(256), 0, st, tgt_ptr,
+                       n_atoms, n_pairs, pair_j, list, tgt_pair);
   }
   if (order != nullptr && n_atoms > 0) {
-    hipLaunchKernelGGL(k_degree_hist, dim3(grid_for(n_atoms)), dim3(256), 0, st, tgt_ptr, n_atoms,
-                       hist);
-    hipLaunchKernelGGL(k_degree_offsets, dim3(1), dim3(kDegBuckets), 0, st, hist);
-    hipLaunchKernelGGL(k_degree_place, dim3(1), dim3(kDegBuckets), 0, st, tgt_ptr, n_atoms, hist,
+    const unsigned nb = (unsigned)((n_atoms + 1023) / 1024);
+    hipLaunchKernelGGL(k_degree_block<false>, dim3(nb), dim3(1024), 0, st, tgt_ptr, n_atoms, hist,
+                       order);
+    hipLaunchKernelGGL(k_degree_scan, dim3(1), dim3(kDegBuckets), 0, st, hist, (int64_t)nb);
+    hipLaunchKernelGGL(k_degree_block<true>, dim3(nb), dim3(1024), 0, st, tgt_ptr, n_atoms, hist,
                        order);
   }
 }
