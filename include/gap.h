@@ -423,7 +423,7 @@ gap_status gap_predict_backward(gap_handle *h, const gap_atoms *atoms, const gap
 /* Forces from descriptor gradients by the chain rule (Sec. "Theory"):
  *   forces[j][alpha] = - sum_{(i,k): j(i,k)=j} J[(i,k)][alpha] . dEdd[i]
  * dEdd [n_atoms][D] FP64 row-major (ld = D); forces [n_atoms][3] FP64.
- * Deterministic: per-pair contributions are summed per target in pair order. */
+ * Deterministic: per-pair contributions are summed per target in a fixed order. */
 gap_status gap_forces(gap_handle *h, const gap_atoms *atoms, const double *dEdd, double *forces);
 
 /* The split step of the BF16X3 form on its own (the BF16X3 calls apply the

@@ -229,6 +229,7 @@ void run_split(gap_handle* h, const gap_sparse* sp, const SplitWs& w, bool trans
 struct PredictWs {
   size_t W, e_atom, g, f_pair;
   size_t epart = 0;  // per-column-group energy partials of the P-stage
+  size_t part = 0;   // partial outputs of a split W X
   PairWs pairs;
   SplitWs split;
 };
@@ -243,8 +244,9 @@ void layout_predict(Layout& L, const gap_atoms* a, const gap_sparse* sp, bool ne
                          : 0;
   w.e_atom = need_eatom ? L.take(sizeof(double) * std::max<int64_t>(N, 1)) : 0;
   w.epart = L.take(sizeof(double) *
-                   std::max<int64_t>(N * std::max(gapk::pstage_groups(M),
+                   std::max<int64_t>(N * std::max(gapk::pstage_groups(N, M),
                                                   gapk::gemm_b3_col_blocks(M)), 1));
+  w.part = bf16 ? 0 : L.take(gapk::wx_part_bytes(N, M, D));
   w.g = need_gbuf ? L.take(sizeof(double) * std::max<int64_t>(N * ld4(D), 1)) : 0;
   w.f_pair = need_forces ? L.take(sizeof(double) * std::max<int64_t>(3 * a->n_pairs, 1)) : 0;
   if (need_forces) layout_pairs(L, N, a->n_pairs, w.pairs);
@@ -265,7 +267,8 @@ void run_predict(gap_handle* h, const gap_atoms* a, const gap_sparse* sp, const 
       gapk::gemm_b3_wx(W32, ldw, N, M, at<__bf16>(h, w.split.xth), at<__bf16>(h, w.split.xtl), D,
                        out, ldo, h->stream);
     else
-      gapk::gemm_wx_f64(W, ldw, N, M, sp->X, sp->ld_x, D, out, ldo, h->stream);
+      gapk::gemm_wx_f64(W, ldw, N, M, sp->X, sp->ld_x, D, at<double>(h, w.part), out, ldo,
+                        h->stream);
   };
   if (bf16) {
     run_split(h, sp, w.split, need_g);
@@ -277,8 +280,8 @@ void run_predict(gap_handle* h, const gap_atoms* a, const gap_sparse* sp, const 
                           h->stream);
   } else {
     gapk::pstage_f64(0, a->desc, f32(a->desc_dt), a->ld_desc, N, sp->X, sp->ld_x, M, D, sp->zeta,
-                     sp->delta, c, nullptr, nullptr, 0, W, ldw, ea, nullptr, h->stream, nullptr, 0,
-                     at<double>(h, w.epart));
+                     sp->delta, c, nullptr, W, ldw, ea, at<double>(h, w.epart), nullptr,
+                     h->stream);
   }
   if (species) gapk::mask_species_rows(species, zsel, N, ea, W, ldw, h->stream, W32);
   if (e_cfg) gapk::segment_sum_f64(ea, a->cfg_ptr, a->n_cfg, N, e_cfg, h->stream);
@@ -726,6 +729,7 @@ gap_status gap_predict_variance(gap_handle* h, const gap_atoms* a, const gap_spa
   const size_t Yr = L.take(sizeof(double) * M * ldm);
   const size_t Ks = L.take(sizeof(double) * N * ldm);
   const size_t Zb = L.take(sizeof(double) * N * ldm);
+  const size_t pt = L.take(gapk::wx_part_bytes(N, M, M));
   s = ensure_ws(h, L.off);
   if (s != GAP_OK) return s;
   h->timer.begin(gapk::TM_PREDICT);
@@ -738,12 +742,12 @@ gap_status gap_predict_variance(gap_handle* h, const gap_atoms* a, const gap_spa
   gapk::local_rows_f64(a->desc, f32(a->desc_dt), a->ld_desc, N, nullptr, N, sp->X, sp->ld_x, M,
                        D, sp->zeta, sp->delta, at<double>(h, Ks), ldm, h->dev_err, h->stream,
                        true);
-  gapk::gemm_wx_f64(at<double>(h, Ks), ldm, N, M, at<double>(h, Yu), ldm, M, at<double>(h, Zb),
-                    ldm, h->stream);
+  gapk::gemm_wx_f64(at<double>(h, Ks), ldm, N, M, at<double>(h, Yu), ldm, M, at<double>(h, pt),
+                    at<double>(h, Zb), ldm, h->stream);
   gapk::var_rows(at<double>(h, Zb), ldm, N, M, -1.0, a->desc, f32(a->desc_dt), a->ld_desc, D,
                  sp->zeta, sp->delta, 1, var, h->stream);
-  gapk::gemm_wx_f64(at<double>(h, Ks), ldm, N, M, at<double>(h, Yr), ldm, M, at<double>(h, Zb),
-                    ldm, h->stream);
+  gapk::gemm_wx_f64(at<double>(h, Ks), ldm, N, M, at<double>(h, Yr), ldm, M, at<double>(h, pt),
+                    at<double>(h, Zb), ldm, h->stream);
   gapk::var_rows(at<double>(h, Zb), ldm, N, M, 1.0, a->desc, f32(a->desc_dt), a->ld_desc, D,
                  sp->zeta, sp->delta, 0, var, h->stream);
   h->timer.end(gapk::TM_PREDICT);
@@ -778,18 +782,21 @@ gap_status gap_select_cur(gap_handle* h, const gap_atoms* a, int64_t n_sparse, d
   const size_t lv = L.take(sizeof(double) * N);
   const size_t ky = L.take(sizeof(double) * n_pad);
   const size_t ix = L.take(sizeof(int32_t) * n_pad);
+  const size_t pt = L.take(std::max(gapk::wtd_part_bytes(N, D, D), gapk::wx_part_bytes(N, D, D)));
   s = ensure_ws(h, L.off);
   if (s != GAP_OK) return s;
   double* dd = at<double>(h, Dd);
   double* lev = leverage ? leverage : at<double>(h, lv);
   // leverage l_i = ||d_i^T U^-1||^2 with U^T U = D^T D + jitter I
   gapk::desc_f64(a->desc, f32(a->desc_dt), a->ld_desc, N, D, dd, ldd, h->stream);
-  gapk::gemm_wtd_f64(dd, ldd, N, D, dd, false, ldd, D, at<double>(h, Gw), D, h->stream);
+  gapk::gemm_wtd_f64(dd, ldd, N, D, dd, false, ldd, D, at<double>(h, pt), at<double>(h, Gw), D,
+                     h->stream);
   gapk::cholesky_lower(at<double>(h, Lw), D, D, jitter, at<double>(h, Gw), D, h->dev_err,
                        h->stream);
   gapk::stack_u(at<double>(h, Ub), D, 0, D, at<double>(h, Lw), D, h->stream);
   gapk::trinv_upper(at<double>(h, Ub), D, D, at<double>(h, Yu), ldd, h->dev_err, h->stream);
-  gapk::gemm_wx_f64(dd, ldd, N, D, at<double>(h, Yu), ldd, D, at<double>(h, Zb), ldd, h->stream);
+  gapk::gemm_wx_f64(dd, ldd, N, D, at<double>(h, Yu), ldd, D, at<double>(h, pt), at<double>(h, Zb),
+                    ldd, h->stream);
   gapk::var_rows(at<double>(h, Zb), ldd, N, D, 1.0, dd, false, ldd, D, 1, 1.0, 2, lev, h->stream);
   gapk::cur_select_sort(lev, u, N, at<double>(h, ky), at<int32_t>(h, ix), h->stream);
   if (n_sparse > 0)
@@ -997,7 +1004,7 @@ void layout_refine(Layout& L, const gap_atoms* a, const gap_sparse* sp, RefineWs
   w.v = L.take(sizeof(double) * std::max<int64_t>(n_rows, 1));
   w.hbuf = L.take(sizeof(double) * std::max<int64_t>(N * ld4(D), 1));
   w.gvec = L.take(sizeof(double) * M);
-  w.dcp = L.take(sizeof(double) * std::max(gapk::pstage_row_blocks(N),
+  w.dcp = L.take(sizeof(double) * std::max(gapk::pstage_row_blocks(N, M),
                                            gapk::resid_colsum_groups(N, M)) * M + 8);
   w.ones = L.take(sizeof(double) * M);
   // pw.W holds S = delta^2 zeta p^(zeta-1) unless the caller keeps it
@@ -1013,8 +1020,7 @@ void refine_weights(gap_handle* h, const gap_atoms* a, const gap_sparse* sp, con
   double* ones = at<double>(h, w.ones);
   gapk::fill_f64(ones, M, 1.0, h->stream);
   gapk::pstage_f64(0, a->desc, f32(a->desc_dt), a->ld_desc, N, sp->X, sp->ld_x, M, D, sp->zeta,
-                   sp->delta, ones, nullptr, nullptr, 0, S, ldS, nullptr, nullptr, h->stream,
-                   nullptr, 0, nullptr);
+                   sp->delta, ones, nullptr, S, ldS, nullptr, nullptr, nullptr, h->stream);
 }
 
 // rtop = Sigma^-1/2 (y - K c) over the batch's rows (energy rows, then three
@@ -1037,7 +1043,8 @@ void refine_residual_rows(gap_handle* h, const gap_atoms* a, const gap_sparse* s
   double* hb = at<double>(h, w.hbuf);
   double* dcp = at<double>(h, w.dcp);
   if (N > 0) {
-    gapk::gemm_wx_scaled_f64(S, ldS, N, M, c, sp->X, sp->ld_x, D, g, ldg, h->stream);
+    gapk::gemm_wx_scaled_f64(S, ldS, N, M, c, sp->X, sp->ld_x, D, at<double>(h, w.pw.part), g, ldg,
+                             h->stream);
     gapk::cfg_energy_from_grad(a->desc, f32(a->desc_dt), a->ld_desc, g, ldg, a->cfg_ptr, nc, N, D,
                                sp->zeta, kcp, h->stream);
     gapk::forces_f64(a->jac, f32(a->jac_dt), a->ld_jac, D, g, ldg,
@@ -1057,9 +1064,9 @@ void refine_residual_rows(gap_handle* h, const gap_atoms* a, const gap_sparse* s
     if (gapk::resid_colsum_f64(hb, ldg, N, D, sp->X, sp->ld_x, M, S, ldS, dcp, h->stream)) {
       gapk::reduce_rows_f64(dcp, gapk::resid_colsum_groups(N, M), M, gv, h->stream);
     } else {
-      gapk::pstage_f64(3, nullptr, false, 0, N, sp->X, sp->ld_x, M, D, sp->zeta, sp->delta,
-                       nullptr, nullptr, hb, ldg, nullptr, 0, nullptr, dcp, h->stream, S, ldS);
-      gapk::reduce_rows_f64(dcp, gapk::pstage_row_blocks(N), M, gv, h->stream);
+      gapk::pstage_f64(3, hb, false, ldg, N, sp->X, sp->ld_x, M, D, sp->zeta, sp->delta, nullptr,
+                       nullptr, nullptr, 0, nullptr, nullptr, dcp, h->stream, S, ldS);
+      gapk::reduce_rows_f64(dcp, gapk::pstage_row_blocks(N, M), M, gv, h->stream);
     }
   } else {
     gapk::fill_f64(gv, M, 0.0, h->stream);
@@ -1405,20 +1412,21 @@ gap_status gap_predict_backward(gap_handle* h, const gap_atoms* a, const gap_spa
     return GAP_OK;
   }
   const size_t W = needW ? L.take(sizeof(double) * std::max<int64_t>(N * ldw, 1)) : 0;
-  const size_t dcp = L.take(sizeof(double) * (gapk::pstage_row_blocks(N) * M + 8));
+  const size_t dcp = L.take(sizeof(double) * (gapk::pstage_row_blocks(N, M) * M + 8));
+  const size_t pt = L.take(std::max(gapk::wx_part_bytes(N, M, D), gapk::wtd_part_bytes(N, M, D)));
   s = ensure_ws(h, L.off);
   if (s != GAP_OK) return s;
   double* Wp = needW ? at<double>(h, W) : nullptr;
   h->timer.begin(gapk::TM_BACKWARD);
-  {
-    gapk::pstage_f64(1, a->desc, f32(a->desc_dt), a->ld_desc, N, sp->X, sp->ld_x, M, D, sp->zeta,
-                     sp->delta, c, g_e, nullptr, 0, Wp, ldw, nullptr, at<double>(h, dcp),
-                     h->stream);
-  }
-  if (d_c) gapk::reduce_rows_f64(at<double>(h, dcp), gapk::pstage_row_blocks(N), M, d_c, h->stream);
-  if (d_desc) gapk::gemm_wx_f64(Wp, ldw, N, M, sp->X, sp->ld_x, D, d_desc, D, h->stream);
+  gapk::pstage_f64(1, a->desc, f32(a->desc_dt), a->ld_desc, N, sp->X, sp->ld_x, M, D, sp->zeta,
+                   sp->delta, c, g_e, Wp, ldw, nullptr, nullptr, at<double>(h, dcp), h->stream);
+  if (d_c)
+    gapk::reduce_rows_f64(at<double>(h, dcp), gapk::pstage_row_blocks(N, M), M, d_c, h->stream);
+  if (d_desc)
+    gapk::gemm_wx_f64(Wp, ldw, N, M, sp->X, sp->ld_x, D, at<double>(h, pt), d_desc, D, h->stream);
   if (d_X)
-    gapk::gemm_wtd_f64(Wp, ldw, N, M, a->desc, f32(a->desc_dt), a->ld_desc, D, d_X, D, h->stream);
+    gapk::gemm_wtd_f64(Wp, ldw, N, M, a->desc, f32(a->desc_dt), a->ld_desc, D, at<double>(h, pt),
+                       d_X, D, h->stream);
   h->timer.end(gapk::TM_BACKWARD);
   HIP_TRY(h, hipGetLastError());
   return GAP_OK;

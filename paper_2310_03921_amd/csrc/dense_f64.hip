@@ -6,6 +6,7 @@
 // Polynomial dot-product kernel: Sec. "Regression"; energy rows: eq. 1 summed
 // by L-hat over a configuration (Sec. "Theory"); predict: eq. epsilon.
 #include <algorithm>
+#include <type_traits>
 
 #include "launch.h"
 #include "mma_f64.h"
@@ -173,113 +174,6 @@ __global__ __launch_bounds__(256) void k_energy_rows(const TD* __restrict__ desc
     v += __shfl_xor(v, 32);
     const int64_t col = colbase + u * 16 + idx;
     if (g == 0 && col < M) K[c + col * ldk] = v;
-  }
-}
-
-// ------------------------------------------------------------- P-stage ----
-// Block = 64 rows (16 per wave); loops over all columns 64 at a time.
-template <typename TD>
-__global__ __launch_bounds__(256) void k_pstage(int mode, const TD* __restrict__ desc, int64_t ldd,
-                                                int64_t n, const double* __restrict__ X,
-                                                int64_t ldx, int64_t M, int64_t D, int zeta,
-                                                double delta, const double* __restrict__ cc,
-                                                const double* __restrict__ g_e,
-                                                const double* __restrict__ H, int64_t ldh,
-                                                double* __restrict__ W, int64_t ldw,
-                                                double* __restrict__ e_atom,
-                                                double* __restrict__ dc_part,
-                                                const double* __restrict__ Sx, int64_t ldsx) {
-  __shared__ double colsum[4][64];
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane >> 4, idx = lane & 15;
-  const int64_t rowbase = (int64_t)blockIdx.x * 64 + wave * 16;
-  const int64_t row = rowbase + idx;
-  const bool rvalid = row < n;
-  FragRowK<TD> fa{desc + (rvalid ? row : 0) * ldd, D, rvalid && mode != 3};
-  FragRowK<double> fh{H ? H + (rvalid ? row : 0) * ldh : nullptr, D, rvalid && H != nullptr};
-  const double d2 = delta * delta, d2z = d2 * zeta;
-  double ge[4];
-  bool rv[4];
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int64_t rr = rowbase + g + 4 * r;
-    rv[r] = rr < n;
-    ge[r] = ((mode == 1 || mode == 2) && rv[r]) ? g_e[rr] : 0.0;
-  }
-  double esum[4] = {0.0, 0.0, 0.0, 0.0};
-  for (int64_t col0 = 0; col0 < M; col0 += 16 * kNC) {
-    FragRowK<double> fb[kNC];
-#pragma unroll
-    for (int u = 0; u < kNC; ++u) {
-      const int64_t col = col0 + u * 16 + idx;
-      fb[u] = FragRowK<double>{X + (col < M ? col : 0) * ldx, D, col < M};
-    }
-    d4v acc[kNC], accq[kNC];
-#pragma unroll
-    for (int u = 0; u < kNC; ++u) {
-      acc[u] = zero4();
-      accq[u] = zero4();
-    }
-    if (mode == 2)
-      wave_mma2<kNC>(fa, fh, fb, D, g, acc, accq);
-    else if (mode == 3)
-      wave_mma<kNC>(fh, fb, D, g, accq);
-    else
-      wave_mma<kNC>(fa, fb, D, g, acc);
-#pragma unroll
-    for (int u = 0; u < kNC; ++u) {
-      const int64_t col = col0 + u * 16 + idx;
-      const bool cvalid = col < M;
-      const double cm = (cvalid && cc) ? cc[col] : 0.0;
-      double csum = 0.0;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int64_t rr = rowbase + g + 4 * r;
-        if (rv[r] && !cvalid && W && mode < 2 && col < ldw) W[rr * ldw + col] = 0.0;  // row padding
-        if (!rv[r] || !cvalid) continue;
-        if (mode == 3) {
-          csum -= Sx[rr * ldsx + col] * accq[u][r];
-          continue;
-        }
-        const double p = acc[u][r];
-        const double pz1 = ipow(p, zeta - 1);
-        const double kval = d2 * pz1 * p;
-        if (mode == 0) {
-          esum[r] += cm * kval;
-          if (W) W[rr * ldw + col] = d2z * cm * pz1;
-        } else if (mode == 1) {
-          csum += ge[r] * kval;
-          if (W) W[rr * ldw + col] = ge[r] * d2z * cm * pz1;
-        } else {
-          csum += ge[r] * kval - d2z * pz1 * accq[u][r];
-        }
-      }
-      if (mode != 0) {
-        csum += __shfl_xor(csum, 16);
-        csum += __shfl_xor(csum, 32);
-        if (g == 0) colsum[wave][u * 16 + idx] = csum;
-      }
-    }
-    if (mode != 0) {
-      __syncthreads();
-      if (threadIdx.x < 64) {
-        const int64_t col = col0 + threadIdx.x;
-        if (col < M)
-          dc_part[(int64_t)blockIdx.x * M + col] =
-              ((colsum[0][threadIdx.x] + colsum[1][threadIdx.x]) + colsum[2][threadIdx.x]) +
-              colsum[3][threadIdx.x];
-      }
-      __syncthreads();
-    }
-  }
-  if (mode == 0 && e_atom) {
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      double v = esum[r];
-#pragma unroll
-      for (int o = 1; o < 16; o <<= 1) v += __shfl_xor(v, o);
-      const int64_t rr = rowbase + g + 4 * r;
-      if (idx == 0 && rr < n) e_atom[rr] = v;
-    }
   }
 }
 
@@ -560,16 +454,17 @@ __global__ __launch_bounds__(256, 3) void k_gemm_wx_q(
   }
 }
 
-// P-stage of predict (MODE 0) and backward (MODE 1) for D % 4 == 0, in the
-// layout of k_gemm_wx_q: four-wave blocks, three per compute unit, each
+// P-stage of predict (MODE 0) and backward (MODE 1), in the layout of
+// k_gemm_wx_q: four-wave blocks, three per compute unit, each
 // covering 64 rows and a group of 128 sparse-point columns (wave w: rows
 // 16 w .. + 15, eight column tiles); the contraction over D runs in 16-wide
 // chunks whose X rows are staged in LDS (double-buffered, in the matrix core's
 // operand order), each wave reads its 16 descriptor rows straight from memory,
 // and the column groups of a row block run on one XCD.  Loads in the loop are
 // unconditional: rows past n, columns past M and k past D read clamped valid
-// addresses and are cancelled by zero factors when staged (X) or by the zero X
-// rows (descriptors).  The epilogue is the one of k_pstage: p = d_i . x_m,
+// addresses; X entries outside the matrix are staged as zero, and descriptor
+// entries past D (row padding, of any value) are replaced by zero in the last
+// chunk.  Epilogue: p = d_i . x_m,
 // W[i][m] (MODE 0: delta^2 zeta c_m p^(zeta-1); MODE 1: the same times g_e[i],
 // zero row padding), and
 // MODE 0: per-row energy partials of the column group in e_part[group][i];
@@ -579,7 +474,7 @@ __global__ __launch_bounds__(256, 3) void k_gemm_wx_q(
 // carry a minus sign): dc_part[row block][m] = - sum over the block's rows of
 // Sx[i][m] p_im, with no kernel and no W.
 // Column sums are taken per wave (16 rows), then over the four waves in order.
-template <typename TD, int MODE>
+template <typename TD, int MODE, bool RAGGED>
 __global__ __launch_bounds__(256, 3) void k_pstage_q(
     const TD* __restrict__ desc, int64_t ldd, int64_t n, const double* __restrict__ X,
     int64_t ldx, int64_t M, int64_t D, int zeta, double delta, const double* __restrict__ cc,
@@ -600,6 +495,8 @@ __global__ __launch_bounds__(256, 3) void k_pstage_q(
   // chunk: sparse point m = cg + gi / 4, entries k = 16 c + 4 (gi % 4) .. + 3,
   // which land as (k = 16 c + 4 g + q, column 16 u + idx) at
   // [(q / 2) * 8 + u][16 g + idx][q % 2]
+  // last 4-entry group inside the rows
+  const int64_t k_top = RAGGED ? (D + 3) / 4 * 4 - 4 : D - 4;
   const double* xrow[2];
   double xok[2];
   int soff[2], dqv[2];
@@ -615,19 +512,32 @@ __global__ __launch_bounds__(256, 3) void k_pstage_q(
   auto fetch = [&](int64_t c, d4v v[2]) {
 #pragma unroll
     for (int it = 0; it < 2; ++it)
-      v[it] = *reinterpret_cast<const d4v*>(xrow[it] + min(c * kQxK + 4 * dqv[it], D - 4));
+      v[it] = *reinterpret_cast<const d4v*>(xrow[it] + min(c * kQxK + 4 * dqv[it], k_top));
   };
   auto stage = [&](int64_t c, double* dst, const d4v v[2]) {
 #pragma unroll
     for (int it = 0; it < 2; ++it) {
+      // (RAGGED: the padding may hold anything, so its entries are replaced, not scaled)
       const double f = (c * kQxK + 4 * dqv[it] < D) ? xok[it] : 0.0;
-      const d2v lo = {f * v[it][0], f * v[it][1]}, hi = {f * v[it][2], f * v[it][3]};
+      d2v lo = {f * v[it][0], f * v[it][1]}, hi = {f * v[it][2], f * v[it][3]};
+      if (RAGGED) {
+        const int64_t in = D - (c * kQxK + 4 * dqv[it]);
+        lo[0] = in > 0 ? lo[0] : 0.0;
+        lo[1] = in > 1 ? lo[1] : 0.0;
+        hi[0] = in > 2 ? hi[0] : 0.0;
+        hi[1] = in > 3 ? hi[1] : 0.0;
+      }
       *reinterpret_cast<d2v*>(dst + soff[it]) = lo;
       *reinterpret_cast<d2v*>(dst + soff[it] + 8 * 128) = hi;
     }
   };
   auto afrag = [&](int64_t c, double a[4]) {
-    load4u(drow + min(c * kQxK + 4 * g, D - 4), a);
+    load4u(drow + min(c * kQxK + 4 * g, k_top), a);
+  };
+  auto cut = [&](double a[4]) {  // the last chunk's entries past D
+    const int64_t in = D - ((nch - 1) * kQxK + 4 * g);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) a[q] = q < in ? a[q] : 0.0;
   };
 
   d4v sv[2];
@@ -642,6 +552,7 @@ __global__ __launch_bounds__(256, 3) void k_pstage_q(
   for (int64_t c = 0; c < nch; ++c) {
     const int64_t cn = min(c + 1, nch - 1);
     fetch(cn, sv);
+    if (RAGGED && c == nch - 1) cut(a_cur);
     afrag(cn, a_nxt);
     __builtin_amdgcn_sched_barrier(0);
     const d2v* xb = reinterpret_cast<const d2v*>(xs + (c & 1) * kQxBuf) + lane;
@@ -727,14 +638,26 @@ __global__ __launch_bounds__(256, 3) void k_pstage_q(
   }
 }
 
-// e[i] = sum over the column groups g of part[g][i], in group order
-__global__ void k_sum_groups(const double* __restrict__ part, int64_t ng, int64_t n,
-                             double* __restrict__ e) {
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x) {
+// e[i] = sum over the column groups g of part[g][i]: sixteen groups of lanes
+// per sixteen atoms take the groups in turn, then add up in a fixed order.
+__global__ __launch_bounds__(256) void k_sum_groups(const double* __restrict__ part, int64_t ng,
+                                                    int64_t n, double* __restrict__ e) {
+  __shared__ double red[16][17];
+  const int a = threadIdx.x & 15, q0 = threadIdx.x >> 4;
+  for (int64_t i0 = blockIdx.x * (int64_t)16; i0 < n; i0 += (int64_t)gridDim.x * 16) {
+    const int64_t i = min(i0 + a, n - 1);
     double s = 0.0;
-    for (int64_t q = 0; q < ng; ++q) s += part[q * n + i];
-    e[i] = s;
+#pragma unroll 4
+    for (int64_t q = q0; q < ng; q += 16) s += part[q * n + i];
+    red[q0][a] = s;
+    __syncthreads();
+    if (threadIdx.x < 16 && i0 + a < n) {
+      double t = 0.0;
+#pragma unroll
+      for (int q = 0; q < 16; ++q) t += red[q][a];
+      e[i] = t;
+    }
+    __syncthreads();
   }
 }
 
@@ -929,68 +852,60 @@ void local_rows_f64(const void* desc, bool desc_f32, int64_t ldd, int64_t n_atom
                        row_major ? 1 : 0);
 }
 
-int64_t pstage_row_blocks(int64_t n) { return (n + 63) / 64; }
+// Lines between the 32 x 32 tiles of dense_small.hip and the staged kernels, in
+// blocks of the latter.  A staged block takes 64 x 128 outputs (W^T D: 64 x 64)
+// and a compute unit holds three, but each alone cannot hide its loads, so up
+// to about one block per compute unit the staged time does not fall with the
+// number of blocks; the small tiles' time does, at 0.75 of the staged rate
+// once both fill the chip.  Measured (us, small against staged):
+//   P-stage: 256 blocks (N 1024, M 2000, D 252) 37.0 / 37.4; 316 blocks
+//     (N 5021, M 500) 41.5 / 50.8; 512 blocks (N 2048, M 2000) 64.2 / 52.6
+//     and (N 1024, M 4000, D 1000) 192 / 165;
+//   W X: 2 blocks (N 64, M 2000, D 252) 10.4 / 161; 128 blocks (N 4096) 103 /
+//     172 and (N 1024, M 4000, D 1000) 181 / 322; 256 blocks (N 8192) 200 / 169;
+//   W^T D (whose staged form does not split its contraction): 128 blocks
+//     (M 2000, D 252) at N 4096 99 / 190; 1008 blocks (M 4000, D 1000) 685 / 677.
+constexpr int64_t kPstageSmall = 384, kWxSmall = 224, kWtdSmall = 512;
+static bool pstage_small(int64_t n, int64_t M) {
+  return (int64_t)cdiv(n, 64) * cdiv(M, 128) < kPstageSmall;
+}
 
-int64_t pstage_groups(int64_t M) { return (M + 127) / 128; }
+int64_t pstage_row_blocks(int64_t n, int64_t M) { return cdiv(n, pstage_small(n, M) ? 32 : 64); }
 
-void pstage_f64(int mode, const void* desc, bool desc_f32, int64_t ldd, int64_t n,
+int64_t pstage_groups(int64_t n, int64_t M) { return cdiv(M, pstage_small(n, M) ? 32 : 128); }
+
+void pstage_f64(int mode, const void* rows, bool rows_f32, int64_t ldd, int64_t n,
                 const double* X, int64_t ldx, int64_t M, int64_t D, int zeta, double delta,
-                const double* c, const double* g_e, const double* H, int64_t ldh, double* W,
-                int64_t ldw, double* e_atom, double* dc_part, hipStream_t st,
-                const double* Sx, int64_t ldsx, double* e_part) {
+                const double* c, const double* g_e, double* W, int64_t ldw, double* e_atom,
+                double* e_part, double* dc_part, hipStream_t st, const double* Sx, int64_t ldsx) {
   if (n <= 0 || M <= 0) return;
-  // LDS-staged form: energies (mode 0) go through per-column-group partials
-  // (mode 3 takes the rows h_i of H as its descriptors)
-  const void* arows = mode == 3 ? static_cast<const void*>(H) : desc;
-  const int64_t lda = mode == 3 ? ldh : ldd;
-  const bool lds_ok = D % 4 == 0 && D >= 4 && lda % 4 == 0 && ldx % 4 == 0 && arows &&
-                      (reinterpret_cast<uintptr_t>(arows) & 31) == 0 &&
-                      (reinterpret_cast<uintptr_t>(X) & 31) == 0 &&
-                      ((mode == 0 && c && (!e_atom || e_part)) || (mode == 1 && c && g_e) ||
-                       (mode == 3 && Sx));
-  if (lds_ok) {
-    const int64_t ng = pstage_groups(M);
-    const dim3 grid(xcd_group_tile_blocks(pstage_row_blocks(n), ng)), blk(256);
-    double* ep = e_atom ? e_part : nullptr;
-    if (mode == 3) {
-      hipLaunchKernelGGL((k_pstage_q<double, 3>), grid, blk, 0, st, H, ldh, n, X, ldx, M, D,
-                         zeta, delta, nullptr, nullptr, nullptr, 0, nullptr, dc_part, Sx, ldsx,
-                         ng);
-      return;
-    }
-    if (desc_f32) {
-      if (mode == 0)
-        hipLaunchKernelGGL((k_pstage_q<float, 0>), grid, blk, 0, st, tptr<float>(desc), ldd, n,
-                           X, ldx, M, D, zeta, delta, c, g_e, W, ldw, ep, dc_part, nullptr, 0,
-                           ng);
+  const int64_t ng = pstage_groups(n, M);
+  double* ep = e_atom ? e_part : nullptr;
+  if (pstage_small(n, M)) {
+    small_pstage_f64(mode, rows, rows_f32, ldd, n, X, ldx, M, D, zeta, delta, c, g_e, W, ldw, ep,
+                     dc_part, Sx, ldsx, st);
+  } else {
+    const dim3 grid(xcd_group_tile_blocks(cdiv(n, 64), ng)), blk(256);
+    auto go = [&](auto kern, auto p) {
+      hipLaunchKernelGGL(kern, grid, blk, 0, st, p, ldd, n, X, ldx, M, D, zeta, delta, c, g_e, W,
+                         ldw, ep, dc_part, Sx, ldsx, ng);
+    };
+    auto pick = [&](auto ragged) {
+      constexpr bool R = decltype(ragged)::value;
+      if (mode == 3)
+        go(k_pstage_q<double, 3, R>, tptr<double>(rows));
+      else if (rows_f32)
+        mode == 0 ? go(k_pstage_q<float, 0, R>, tptr<float>(rows))
+                  : go(k_pstage_q<float, 1, R>, tptr<float>(rows));
       else
-        hipLaunchKernelGGL((k_pstage_q<float, 1>), grid, blk, 0, st, tptr<float>(desc), ldd, n,
-                           X, ldx, M, D, zeta, delta, c, g_e, W, ldw, ep, dc_part, nullptr, 0,
-                           ng);
-    } else {
-      if (mode == 0)
-        hipLaunchKernelGGL((k_pstage_q<double, 0>), grid, blk, 0, st, tptr<double>(desc), ldd,
-                           n, X, ldx, M, D, zeta, delta, c, g_e, W, ldw, ep, dc_part, nullptr, 0,
-                           ng);
-      else
-        hipLaunchKernelGGL((k_pstage_q<double, 1>), grid, blk, 0, st, tptr<double>(desc), ldd,
-                           n, X, ldx, M, D, zeta, delta, c, g_e, W, ldw, ep, dc_part, nullptr, 0,
-                           ng);
-    }
-    if (mode == 0 && e_atom)
-      hipLaunchKernelGGL(k_sum_groups, dim3(std::max(1u, std::min(cdiv(n, 256), 65536u))),
-                         dim3(256), 0, st, e_part, ng, n, e_atom);
-    return;
+        mode == 0 ? go(k_pstage_q<double, 0, R>, tptr<double>(rows))
+                  : go(k_pstage_q<double, 1, R>, tptr<double>(rows));
+    };
+    D % 4 ? pick(std::true_type{}) : pick(std::false_type{});
   }
-  dim3 grid((unsigned)pstage_row_blocks(n));
-  if (desc_f32)
-    hipLaunchKernelGGL(k_pstage<float>, grid, dim3(256), 0, st, mode, tptr<float>(desc), ldd, n,
-                       X, ldx, M, D, zeta, delta, c, g_e, H, ldh, W, ldw, e_atom, dc_part, Sx,
-                       ldsx);
-  else
-    hipLaunchKernelGGL(k_pstage<double>, grid, dim3(256), 0, st, mode, tptr<double>(desc), ldd,
-                       n, X, ldx, M, D, zeta, delta, c, g_e, H, ldh, W, ldw, e_atom, dc_part, Sx,
-                       ldsx);
+  if (mode == 0 && e_atom)
+    hipLaunchKernelGGL(k_sum_groups, dim3(std::max(1u, std::min(cdiv(n, 16), 65536u))), dim3(256),
+                       0, st, e_part, ng, n, e_atom);
 }
 
 // The LDS-staged form needs W rows of whole 32-byte groups (ldw % 4 == 0, W
@@ -1002,9 +917,21 @@ inline bool wx_lds_ok(const double* W, int64_t ldw, int64_t M, int64_t ldx,
          (reinterpret_cast<uintptr_t>(W) & 31) == 0 && (M + 2 * kQxK) * ldx * 8 < (1ll << 31);
 }
 
+static bool wx_small(int64_t n, int64_t M, int64_t D) {
+  return M > 0 && (int64_t)cdiv(n, 64) * cdiv(D, 128) < kWxSmall;
+}
+size_t wx_part_bytes(int64_t n, int64_t M, int64_t D) {
+  return n > 0 && D > 0 && wx_small(n, M, D) ? small_part_bytes(n, D, M) : 0;
+}
+
 void gemm_wx_f64(const double* W, int64_t ldw, int64_t n, int64_t M, const double* X,
-                 int64_t ldx, int64_t D, double* out, int64_t ldo, hipStream_t st) {
+                 int64_t ldx, int64_t D, double* part, double* out, int64_t ldo,
+                 hipStream_t st) {
   if (n <= 0 || D <= 0) return;
+  if (wx_small(n, M, D)) {
+    small_wx_f64(W, ldw, n, M, nullptr, X, ldx, D, part, out, ldo, st);
+    return;
+  }
   if (wx_lds_ok(W, ldw, M, ldx, D)) {
     const int64_t n_ct = cdiv(D, 128);
     hipLaunchKernelGGL(k_gemm_wx_q<false>, dim3(xcd_group_tile_blocks(cdiv(n, 64), n_ct)),
@@ -1047,9 +974,13 @@ bool resid_colsum_f64(const double* H, int64_t ldh, int64_t n, int64_t D, const 
 }
 
 void gemm_wx_scaled_f64(const double* W, int64_t ldw, int64_t n, int64_t M, const double* cs,
-                        const double* X, int64_t ldx, int64_t D, double* out, int64_t ldo,
-                        hipStream_t st) {
+                        const double* X, int64_t ldx, int64_t D, double* part, double* out,
+                        int64_t ldo, hipStream_t st) {
   if (n <= 0 || D <= 0) return;
+  if (wx_small(n, M, D)) {
+    small_wx_f64(W, ldw, n, M, cs, X, ldx, D, part, out, ldo, st);
+    return;
+  }
   if (wx_lds_ok(W, ldw, M, ldx, D)) {
     const int64_t n_ct = cdiv(D, 128);
     hipLaunchKernelGGL(k_gemm_wx_q<true>, dim3(xcd_group_tile_blocks(cdiv(n, 64), n_ct)),
@@ -1074,10 +1005,21 @@ void gemvt_cm_add_f64(const double* A, int64_t lda, int64_t rows, int64_t cols, 
                      y);
 }
 
+static bool wtd_small(int64_t n, int64_t M, int64_t D) {
+  return n > 0 && (int64_t)cdiv(M, 64) * cdiv(D, 64) < kWtdSmall;
+}
+size_t wtd_part_bytes(int64_t n, int64_t M, int64_t D) {
+  return M > 0 && D > 0 && wtd_small(n, M, D) ? small_part_bytes(M, D, n) : 0;
+}
+
 void gemm_wtd_f64(const double* W, int64_t ldw, int64_t n, int64_t M, const void* desc,
-                  bool desc_f32, int64_t ldd, int64_t D, double* out, int64_t ldo,
+                  bool desc_f32, int64_t ldd, int64_t D, double* part, double* out, int64_t ldo,
                   hipStream_t st) {
   if (M <= 0 || D <= 0) return;
+  if (wtd_small(n, M, D)) {
+    small_wtd_f64(W, ldw, n, M, desc, desc_f32, ldd, D, part, out, ldo, st);
+    return;
+  }
   dim3 grid(cdiv(M, 64), cdiv(D, 64));
   if (desc_f32)
     hipLaunchKernelGGL(k_gemm_wtd<float>, grid, dim3(256), 0, st, W, ldw, n, M,

@@ -498,17 +498,32 @@ __global__ __launch_bounds__(256) void k_pair_dots4(const TJ* __restrict__ jac, 
   }
 }
 
-__global__ void k_gather_forces(const double* __restrict__ f_pair,
-                                const int64_t* __restrict__ tgt_ptr,
-                                const int32_t* __restrict__ tgt_pair, int64_t n_atoms,
-                                double* __restrict__ F) {
-  for (int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; q < 3 * n_atoms;
-       q += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t j = q / 3;
-    const int a = (int)(q - 3 * j);
-    double s = 0.0;
-    for (int64_t e = tgt_ptr[j]; e < tgt_ptr[j + 1]; ++e) s += f_pair[(int64_t)tgt_pair[e] * 3 + a];
-    F[q] = -s;
+// F[j] = - sum of f_pair over the pairs pointing at j: sixteen lanes per atom
+// take its pairs in turn and add up in a fixed order.  (One thread per force
+// component, whose two dependent loads per pair ran one after the other, took
+// 17 us for 64 atoms and 55 us for 65,536.)
+__global__ __launch_bounds__(256) void k_gather_forces(const double* __restrict__ f_pair,
+                                                       const int64_t* __restrict__ tgt_ptr,
+                                                       const int32_t* __restrict__ tgt_pair,
+                                                       int64_t n_atoms, double* __restrict__ F) {
+  const int l = threadIdx.x & 15;
+  for (int64_t j0 = blockIdx.x * (int64_t)16; j0 < n_atoms; j0 += (int64_t)gridDim.x * 16) {
+    const int64_t j = j0 + (threadIdx.x >> 4);
+    double s[3] = {0.0, 0.0, 0.0};
+    if (j < n_atoms) {
+      const int64_t hi = tgt_ptr[j + 1];
+#pragma unroll 2
+      for (int64_t e = tgt_ptr[j] + l; e < hi; e += 16) {
+        const double* f = f_pair + (int64_t)tgt_pair[e] * 3;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) s[a] += f[a];
+      }
+    }
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+      for (int o = 1; o < 16; o <<= 1) s[a] += __shfl_xor(s[a], o);
+    if (j < n_atoms && l < 3) F[3 * j + l] = -(l == 0 ? s[0] : l == 1 ? s[1] : s[2]);
   }
 }
 
@@ -746,7 +761,7 @@ void forces_f64(const void* jac, bool jac_f32, int64_t ldj, int64_t D, const dou
                          reinterpret_cast<const double*>(jac), ldj, D, g, ldg, pair_src, n_pairs,
                          f_pair);
   }
-  hipLaunchKernelGGL(k_gather_forces, dim3(std::min<unsigned>(cdiv(3 * n_atoms, 256), 65536u)),
+  hipLaunchKernelGGL(k_gather_forces, dim3(std::min<unsigned>(cdiv(n_atoms, 16), 65536u)),
                      dim3(256), 0, st, f_pair, tgt_ptr, tgt_pair, n_atoms, forces);
 }
 

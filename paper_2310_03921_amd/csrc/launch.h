@@ -79,26 +79,21 @@ void energy_rows_f64(const void* desc, bool desc_f32, int64_t ldd, const int64_t
                      int64_t D, int zeta, double delta, double* K, int64_t ldk, double* S,
                      int64_t ldS, hipStream_t st,
                      const int32_t* species = nullptr, int32_t zsel = 0);
-// P-stage of predict / backward.  For rows i of desc:
+// P-stage of predict / backward.  For the rows d_i and p = d_i . x_m:
 //   mode 0 (forward):  W[i][m] = delta^2 zeta c_m p^(zeta-1)       (if W)
 //                      e_atom[i] = sum_m c_m delta^2 p^zeta         (if e_atom)
 //   mode 1 (backward): W[i][m] = g_e[i] delta^2 zeta c_m p^(zeta-1) (if W)
 //                      dc_part[rb][m] = sum_{i in row block rb} g_e[i] delta^2 p^zeta
-//   mode 2 (residual): W[i][m] = g_e[i] delta^2 p^zeta + delta^2 zeta p^(zeta-1) q_im
-//                      where q = H X^T with H [n][ldh] (rows of h_i); only dc_part is written
-//                      (column partial sums of W over the row block)
-//   mode 3 (residual, force part with a stored S): dc_part = column partial sums of
-//                      -S[i][m] q_im, q = H X^T (desc unused)
-// Column groups of the LDS-staged P-stage; e_part (for e_atom in mode 0) holds
-// pstage_groups(M) x n doubles.
-int64_t pstage_groups(int64_t M);
-void pstage_f64(int mode, const void* desc, bool desc_f32, int64_t ldd, int64_t n,
+//   mode 3 (residual; FP64 rows h_i): dc_part[rb][m] = - sum_{i in rb} Sx[i][m] p
+// W rows are padded with zeros to ldw.  e_part (scratch for e_atom) holds
+// pstage_groups(n, M) x n doubles, dc_part pstage_row_blocks(n, M) x M.
+int64_t pstage_groups(int64_t n, int64_t M);
+int64_t pstage_row_blocks(int64_t n, int64_t M);
+void pstage_f64(int mode, const void* rows, bool rows_f32, int64_t ldd, int64_t n,
                 const double* X, int64_t ldx, int64_t M, int64_t D, int zeta, double delta,
-                const double* c, const double* g_e, const double* H, int64_t ldh, double* W,
-                int64_t ldw, double* e_atom, double* dc_part, hipStream_t st,
-                const double* Sx = nullptr, int64_t ldsx = 0, double* e_part = nullptr);
-int64_t pstage_row_blocks(int64_t n);
-// out[i][j] = scale_i * sum_k W[i][k] X[k][j]   (n x D, row-major ldo); scale = 1 if row_scale null
+                const double* c, const double* g_e, double* W, int64_t ldw, double* e_atom,
+                double* e_part, double* dc_part, hipStream_t st, const double* Sx = nullptr,
+                int64_t ldsx = 0);
 // Two-body SE descriptor: rows (energies, then 3 per atom) of the pair-distance
 // kernel, its K_MM, and prediction (per-pair terms in ep / gp, n_pairs each).
 void se2b_rows_f64(const double* pair_r, const int64_t* cfg_ptr, int64_t n_cfg,
@@ -125,8 +120,10 @@ void local_rows_f64(const void* desc, bool desc_f32, int64_t ldd, int64_t n_atom
                     const int32_t* atom_idx, int64_t n_local, const double* X, int64_t ldx,
                     int64_t M, int64_t D, int zeta, double delta, double* K, int64_t ldk,
                     int* dev_err, hipStream_t st, bool row_major = false);
+// out[i][j] = sum_k W[i][k] X[k][j]   (n x D, row-major ldo); part: wx_part_bytes of scratch
+size_t wx_part_bytes(int64_t n, int64_t M, int64_t D);
 void gemm_wx_f64(const double* W, int64_t ldw, int64_t n, int64_t M, const double* X,
-                 int64_t ldx, int64_t D, double* out, int64_t ldo, hipStream_t st);
+                 int64_t ldx, int64_t D, double* part, double* out, int64_t ldo, hipStream_t st);
 // dc_part[rg][m] = -sum_{i in row group rg} S[i][m] (H_i . x_m), column-stationary;
 // returns false (nothing launched) when the shape is outside its limits
 // (D <= 256, ldS and ldh multiples of 4).  Groups: resid_colsum_groups(n, M).
@@ -136,16 +133,17 @@ bool resid_colsum_f64(const double* H, int64_t ldh, int64_t n, int64_t D, const 
                       hipStream_t st);
 // out = (W diag(cs)) X   (cs: [M], any alignment)
 void gemm_wx_scaled_f64(const double* W, int64_t ldw, int64_t n, int64_t M, const double* cs,
-                        const double* X, int64_t ldx, int64_t D, double* out, int64_t ldo,
-                        hipStream_t st);
+                        const double* X, int64_t ldx, int64_t D, double* part, double* out,
+                        int64_t ldo, hipStream_t st);
 // y = A x (column-major rows x cols);  y += A^T x
 void gemv_cm_f64(const double* A, int64_t lda, int64_t rows, int64_t cols, const double* x,
                  double* y, hipStream_t st);
 void gemvt_cm_add_f64(const double* A, int64_t lda, int64_t rows, int64_t cols, const double* x,
                       double* y, hipStream_t st);
-// out[m][j] = sum_i W[i][m] desc[i][j]        (M x D, row-major ldo)
+// out[m][j] = sum_i W[i][m] desc[i][j]   (M x D, row-major ldo); part: wtd_part_bytes of scratch
+size_t wtd_part_bytes(int64_t n, int64_t M, int64_t D);
 void gemm_wtd_f64(const double* W, int64_t ldw, int64_t n, int64_t M, const void* desc,
-                  bool desc_f32, int64_t ldd, int64_t D, double* out, int64_t ldo,
+                  bool desc_f32, int64_t ldd, int64_t D, double* part, double* out, int64_t ldo,
                   hipStream_t st);
 // dst[i][0:D] = src[i][0:D]
 void copy_rows_f64(const double* src, int64_t lds, double* dst, int64_t ldd, int64_t n, int64_t D,
@@ -166,6 +164,21 @@ void mask_species_rows(const int32_t* species, int32_t zsel, int64_t n, double* 
                        int64_t ldw, hipStream_t st, float* W32 = nullptr);
 void segment_sum_f64(const double* e_atom, const int64_t* cfg_ptr, int64_t n_cfg, int64_t n,
                      double* e_cfg, hipStream_t st);
+
+// ---- dense_small.hip ------------------------------------------------------
+// The P-stage, W X (columns of W scaled by cs where given) and W^T D on 32 x 32
+// tiles; part holds small_part_bytes(output rows, output columns, k).
+size_t small_part_bytes(int64_t n_rows, int64_t n_cols, int64_t K);
+void small_pstage_f64(int mode, const void* rows, bool rows_f32, int64_t ldd, int64_t n,
+                      const double* X, int64_t ldx, int64_t M, int64_t D, int zeta, double delta,
+                      const double* c, const double* g_e, double* W, int64_t ldw, double* e_part,
+                      double* dc_part, const double* Sx, int64_t ldsx, hipStream_t st);
+void small_wx_f64(const double* W, int64_t ldw, int64_t n, int64_t M, const double* cs,
+                  const double* X, int64_t ldx, int64_t D, double* part, double* out, int64_t ldo,
+                  hipStream_t st);
+void small_wtd_f64(const double* W, int64_t ldw, int64_t n, int64_t M, const void* desc,
+                   bool desc_f32, int64_t ldd, int64_t D, double* part, double* out, int64_t ldo,
+                   hipStream_t st);
 
 // ---- force_f64.hip --------------------------------------------------------
 void force_rows_f64(const void* jac, bool jac_f32, int64_t ldj, int64_t D, const double* X,

@@ -128,35 +128,3 @@ GAP_DEV void wave_mma(const FA& fa, const FB (&fb)[NC], int64_t K, int g, d4v (&
     mma_block<NC>(a0, b0, acc);
   }
 }
-
-// Two A operands against the same B tiles: acc0 += A0 B, acc1 += A1 B.
-template <int NC, class FA0, class FA1, class FB>
-GAP_DEV void wave_mma2(const FA0& fa0, const FA1& fa1, const FB (&fb)[NC], int64_t K, int g,
-                       d4v (&acc0)[NC], d4v (&acc1)[NC]) {
-  const int64_t Kf = K & ~int64_t(15);
-  for (int64_t k0 = 0; k0 < Kf; k0 += 16) {
-    typename FA0::Raw r0;
-    typename FA1::Raw r1;
-    typename FB::Raw rb[NC];
-    fa0.fast(k0, g, r0);
-    fa1.fast(k0, g, r1);
-#pragma unroll
-    for (int u = 0; u < NC; ++u) fb[u].fast(k0, g, rb[u]);
-    double a0[4], a1[4], b[NC][4];
-    fa0.cook(r0, a0);
-    fa1.cook(r1, a1);
-#pragma unroll
-    for (int u = 0; u < NC; ++u) fb[u].cook(rb[u], b[u]);
-    mma_block<NC>(a0, b, acc0);
-    mma_block<NC>(a1, b, acc1);
-  }
-  if (Kf < K) {
-    double a0[4], a1[4], b[NC][4];
-    fa0.frag(Kf, g, a0);
-    fa1.frag(Kf, g, a1);
-#pragma unroll
-    for (int u = 0; u < NC; ++u) fb[u].frag(Kf, g, b[u]);
-    mma_block<NC>(a0, b, acc0);
-    mma_block<NC>(a1, b, acc1);
-  }
-}
