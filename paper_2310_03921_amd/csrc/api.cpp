@@ -730,24 +730,25 @@ gap_status gap_predict_variance(gap_handle* h, const gap_atoms* a, const gap_spa
   const size_t Ks = L.take(sizeof(double) * N * ldm);
   const size_t Zb = L.take(sizeof(double) * N * ldm);
   const size_t pt = L.take(gapk::wx_part_bytes(N, M, M));
+  const size_t tp = L.take(sizeof(double) * M * ldm);
   s = ensure_ws(h, L.off);
   if (s != GAP_OK) return s;
   h->timer.begin(gapk::TM_PREDICT);
   // U (K_MM + jitter I = U^T U) and the inverses of U and R
   gapk::cholesky_lower(at<double>(h, Lw), M, M, jitter, Kmm, M, h->dev_err, h->stream);
   gapk::stack_u(at<double>(h, Ub), M, 0, M, at<double>(h, Lw), M, h->stream);
-  gapk::trinv_upper(at<double>(h, Ub), M, M, at<double>(h, Yu), ldm, h->dev_err, h->stream);
-  gapk::trinv_upper(R, ldr, M, at<double>(h, Yr), ldm, h->dev_err, h->stream);
+  gapk::trinv_upper2(at<double>(h, Ub), M, at<double>(h, Yu), R, ldr, at<double>(h, Yr), M, ldm,
+                     at<double>(h, tp), h->dev_err, h->stream);
   // k_i rows, then var_i = k_ii - ||k_i^T U^-1||^2 + ||k_i^T R^-1||^2
   gapk::local_rows_f64(a->desc, f32(a->desc_dt), a->ld_desc, N, nullptr, N, sp->X, sp->ld_x, M,
                        D, sp->zeta, sp->delta, at<double>(h, Ks), ldm, h->dev_err, h->stream,
                        true);
   gapk::gemm_wx_f64(at<double>(h, Ks), ldm, N, M, at<double>(h, Yu), ldm, M, at<double>(h, pt),
-                    at<double>(h, Zb), ldm, h->stream);
+                    at<double>(h, Zb), ldm, h->stream, true);
   gapk::var_rows(at<double>(h, Zb), ldm, N, M, -1.0, a->desc, f32(a->desc_dt), a->ld_desc, D,
                  sp->zeta, sp->delta, 1, var, h->stream);
   gapk::gemm_wx_f64(at<double>(h, Ks), ldm, N, M, at<double>(h, Yr), ldm, M, at<double>(h, pt),
-                    at<double>(h, Zb), ldm, h->stream);
+                    at<double>(h, Zb), ldm, h->stream, true);
   gapk::var_rows(at<double>(h, Zb), ldm, N, M, 1.0, a->desc, f32(a->desc_dt), a->ld_desc, D,
                  sp->zeta, sp->delta, 0, var, h->stream);
   h->timer.end(gapk::TM_PREDICT);
@@ -783,6 +784,7 @@ gap_status gap_select_cur(gap_handle* h, const gap_atoms* a, int64_t n_sparse, d
   const size_t ky = L.take(sizeof(double) * n_pad);
   const size_t ix = L.take(sizeof(int32_t) * n_pad);
   const size_t pt = L.take(std::max(gapk::wtd_part_bytes(N, D, D), gapk::wx_part_bytes(N, D, D)));
+  const size_t tp = L.take(sizeof(double) * D * ldd);
   s = ensure_ws(h, L.off);
   if (s != GAP_OK) return s;
   double* dd = at<double>(h, Dd);
@@ -794,9 +796,10 @@ gap_status gap_select_cur(gap_handle* h, const gap_atoms* a, int64_t n_sparse, d
   gapk::cholesky_lower(at<double>(h, Lw), D, D, jitter, at<double>(h, Gw), D, h->dev_err,
                        h->stream);
   gapk::stack_u(at<double>(h, Ub), D, 0, D, at<double>(h, Lw), D, h->stream);
-  gapk::trinv_upper(at<double>(h, Ub), D, D, at<double>(h, Yu), ldd, h->dev_err, h->stream);
+  gapk::trinv_upper2(at<double>(h, Ub), D, at<double>(h, Yu), nullptr, 0, nullptr, D, ldd,
+                     at<double>(h, tp), h->dev_err, h->stream);
   gapk::gemm_wx_f64(dd, ldd, N, D, at<double>(h, Yu), ldd, D, at<double>(h, pt), at<double>(h, Zb),
-                    ldd, h->stream);
+                    ldd, h->stream, true);
   gapk::var_rows(at<double>(h, Zb), ldd, N, D, 1.0, dd, false, ldd, D, 1, 1.0, 2, lev, h->stream);
   gapk::cur_select_sort(lev, u, N, at<double>(h, ky), at<int32_t>(h, ix), h->stream);
   if (n_sparse > 0)

@@ -377,15 +377,26 @@ template <bool CS>
 __global__ __launch_bounds__(256, 3) void k_gemm_wx_q(
     const double* __restrict__ W, int64_t ldw, int64_t n, int64_t M,
     const double* __restrict__ cs, const double* __restrict__ X, int64_t ldx, int64_t D,
-    double* __restrict__ out, int64_t ldo, int64_t n_ct) {
+    double* __restrict__ out, int64_t ldo, int64_t n_ct, int upper) {
   __shared__ __attribute__((aligned(16))) double xs[2 * kQxBuf];
   int64_t rb, ct;
-  if (!xcd_group_tile((n + 63) / 64, n_ct, rb, ct)) return;
+  const int64_t n_rb = (n + 63) / 64;
+  bool mine = xcd_group_tile(n_rb, n_ct, rb, ct);
+  if (upper) {
+    // the work of a column group grows with its index: the longest first, so
+    // that no long block starts when the others are done
+    const int64_t per = (n_rb + 7) / 8, j = blockIdx.x >> 3;
+    ct = n_ct - 1 - j / per;
+    rb = (j % per) * 8 + (blockIdx.x & 7);
+    mine = rb < n_rb;
+  }
+  if (!mine) return;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane >> 4, idx = lane & 15;
   const int64_t rowbase = rb * 64 + wave * 16;
   const double* wrow = W + min(rowbase + idx, n - 1) * ldw;
-  const int64_t nch = (M + kQxK - 1) / kQxK;
   const int64_t cg = ct * 128;
+  // (upper: X[k][j] = 0 for k > j, so a column group needs k < cg + 128 only)
+  const int64_t nch = ((upper ? min(M, cg + 128) : M) + kQxK - 1) / kQxK;
 
   // staging: thread t moves elements e = t + 256 it: k offset kl = t / 128 + 2 it
   // (the same in a wave), column d = t % 128
@@ -925,17 +936,17 @@ size_t wx_part_bytes(int64_t n, int64_t M, int64_t D) {
 }
 
 void gemm_wx_f64(const double* W, int64_t ldw, int64_t n, int64_t M, const double* X,
-                 int64_t ldx, int64_t D, double* part, double* out, int64_t ldo,
-                 hipStream_t st) {
+                 int64_t ldx, int64_t D, double* part, double* out, int64_t ldo, hipStream_t st,
+                 bool upper) {
   if (n <= 0 || D <= 0) return;
   if (wx_small(n, M, D)) {
-    small_wx_f64(W, ldw, n, M, nullptr, X, ldx, D, part, out, ldo, st);
+    small_wx_f64(W, ldw, n, M, nullptr, X, ldx, D, part, out, ldo, st, upper);
     return;
   }
   if (wx_lds_ok(W, ldw, M, ldx, D)) {
     const int64_t n_ct = cdiv(D, 128);
     hipLaunchKernelGGL(k_gemm_wx_q<false>, dim3(xcd_group_tile_blocks(cdiv(n, 64), n_ct)),
-                       dim3(256), 0, st, W, ldw, n, M, nullptr, X, ldx, D, out, ldo, n_ct);
+                       dim3(256), 0, st, W, ldw, n, M, nullptr, X, ldx, D, out, ldo, n_ct, upper ? 1 : 0);
     return;
   }
   hipLaunchKernelGGL(k_gemm_wx, dim3(cdiv(n, 64), cdiv(D, 64)), dim3(256), 0, st, W, ldw, n, M,
@@ -984,7 +995,7 @@ void gemm_wx_scaled_f64(const double* W, int64_t ldw, int64_t n, int64_t M, cons
   if (wx_lds_ok(W, ldw, M, ldx, D)) {
     const int64_t n_ct = cdiv(D, 128);
     hipLaunchKernelGGL(k_gemm_wx_q<true>, dim3(xcd_group_tile_blocks(cdiv(n, 64), n_ct)),
-                       dim3(256), 0, st, W, ldw, n, M, cs, X, ldx, D, out, ldo, n_ct);
+                       dim3(256), 0, st, W, ldw, n, M, cs, X, ldx, D, out, ldo, n_ct, 0);
     return;
   }
   hipLaunchKernelGGL(k_gemm_wx_cs, dim3(cdiv(n, 64), cdiv(D, 64)), dim3(256), 0, st, W, ldw, n, M,

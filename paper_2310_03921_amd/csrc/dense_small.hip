@@ -164,21 +164,57 @@ GAP_DEV void block_tile(const OA& A, const OB& B, int64_t row0, int64_t col0, in
            red[3][row][c4 + q];
 }
 
-// out[z][i][j] = sum over slice z of k of A[i][k] B[j][k]
+// out[z][i][j] = sum over slice z of k of A[i][k] B[j][k]; with `upper`, B[j][k]
+// is zero for k > j and those k are left out.
 template <class OA, class OB>
 __global__ __launch_bounds__(256) void k_gemm_small(OA A, OB B, int64_t K, int64_t k_per,
-                                                    double* __restrict__ out, int64_t ldo,
-                                                    int64_t stride) {
+                                                    int upper, double* __restrict__ out,
+                                                    int64_t ldo, int64_t stride) {
   __shared__ double red[4][kT][kTS];
   const int64_t col0 = (int64_t)blockIdx.x * kT, row0 = (int64_t)blockIdx.y * kT;
   const int64_t k_lo = (int64_t)blockIdx.z * k_per;
   double v[4];
-  block_tile(A, B, row0, col0, k_lo, min(K, k_lo + k_per), red, v);
+  const int64_t k_hi = min(upper ? min(K, col0 + kT) : K, k_lo + k_per);
+  block_tile(A, B, row0, col0, k_lo, max(k_hi, k_lo), red, v);
   const int64_t row = row0 + (threadIdx.x >> 3), col = col0 + (threadIdx.x & 7) * 4;
   double* o = out + blockIdx.z * stride + row * ldo + col;
 #pragma unroll
   for (int q = 0; q < 4; ++q)
     if (row < A.n && col + q < B.n) o[q] = v[q];
+}
+
+// One level of the triangular inverse by doubling, for the pair of diagonal
+// blocks blockIdx.z (the first s x s, the second possibly cut by n):
+// STEP 0: tmp = R12 Y22 (Y22 upper: k <= column), and Y21 = 0;
+// STEP 1: Y12 = -Y11 tmp (Y11 upper: k >= row).
+template <int STEP>
+__global__ __launch_bounds__(256) void k_trinv_level(const double* __restrict__ R, int64_t ldr,
+                                                     double* __restrict__ Y, int64_t ldy,
+                                                     int64_t n, int64_t s,
+                                                     double* __restrict__ tmp) {
+  __shared__ double red[4][kT][kTS];
+  const int64_t b1 = 2 * s * (int64_t)blockIdx.z, b2 = b1 + s, s2 = min(s, n - b2);
+  const int64_t col0 = (int64_t)blockIdx.x * kT, row0 = (int64_t)blockIdx.y * kT;
+  if (col0 >= s2) return;
+  double* tp = tmp + (int64_t)blockIdx.z * s * s;  // s x s2, row-major
+  double v[4];
+  if (STEP == 0)
+    block_tile(ColOp<double>{R + b1 + b2 * ldr, ldr, s}, ColOp<double>{Y + b2 * ldy + b2, ldy, s2},
+               row0, col0, 0, min(s2, col0 + kT), red, v);
+  else
+    block_tile(RowOp<double>{Y + b1 * ldy + b1, ldy, s}, ColOp<double>{tp, s2, s2}, row0, col0,
+               row0, s, red, v);
+  const int64_t i = row0 + (threadIdx.x >> 3), j = col0 + (threadIdx.x & 7) * 4;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    if (i >= s || j + q >= s2) continue;
+    if (STEP == 0) {
+      tp[i * s2 + j + q] = v[q];
+      Y[(b2 + j + q) * ldy + b1 + i] = 0.0;
+    } else {
+      Y[(b1 + i) * ldy + b2 + j + q] = -v[q];
+    }
+  }
 }
 
 // P-stage of k_pstage_q (same modes and outputs) on 32 x 32 tiles: e_part has a
@@ -246,18 +282,18 @@ int64_t tiles(int64_t a, int64_t b) { return (int64_t)cdiv(a, kT) * cdiv(b, kT);
 
 template <class OA, class OB>
 void launch_small(const OA& A, const OB& B, int64_t K, double* part, double* out, int64_t ldo,
-                  hipStream_t st) {
+                  hipStream_t st, int upper = 0) {
   const int64_t nz = slices(tiles(A.n, B.n), K);
   const int64_t k_per = ((K + nz - 1) / nz + 63) / 64 * 64;
   const unsigned z = cdiv(K, k_per);
   const dim3 grid(cdiv(B.n, kT), cdiv(A.n, kT), z);
   if (z == 1) {
-    hipLaunchKernelGGL((k_gemm_small<OA, OB>), grid, dim3(256), 0, st, A, B, K, k_per, out, ldo,
-                       int64_t(0));
+    hipLaunchKernelGGL((k_gemm_small<OA, OB>), grid, dim3(256), 0, st, A, B, K, k_per, upper, out,
+                       ldo, int64_t(0));
     return;
   }
-  hipLaunchKernelGGL((k_gemm_small<OA, OB>), grid, dim3(256), 0, st, A, B, K, k_per, part, B.n,
-                     A.n * B.n);
+  hipLaunchKernelGGL((k_gemm_small<OA, OB>), grid, dim3(256), 0, st, A, B, K, k_per, upper, part,
+                     B.n, A.n * B.n);
   sum_parts_f64(part, z, A.n * B.n, out, A.n, ldo, B.n, st);
 }
 
@@ -290,12 +326,21 @@ void small_pstage_f64(int mode, const void* rows, bool rows_f32, int64_t ldd, in
 
 void small_wx_f64(const double* W, int64_t ldw, int64_t n, int64_t M, const double* cs,
                   const double* X, int64_t ldx, int64_t D, double* part, double* out, int64_t ldo,
-                  hipStream_t st) {
+                  hipStream_t st, bool upper) {
   const ColOp<double> x{X, ldx, D};
   if (cs)
-    launch_small(ScaledRowOp{W, ldw, n, cs}, x, M, part, out, ldo, st);
+    launch_small(ScaledRowOp{W, ldw, n, cs}, x, M, part, out, ldo, st, upper);
   else
-    launch_small(RowOp<double>{W, ldw, n}, x, M, part, out, ldo, st);
+    launch_small(RowOp<double>{W, ldw, n}, x, M, part, out, ldo, st, upper);
+}
+
+void small_trinv_level(const double* R, int64_t ldr, double* Y, int64_t ldy, int64_t n, int64_t s,
+                       double* tmp, hipStream_t st) {
+  const unsigned pairs = cdiv(n - s, 2 * s), t = cdiv(s, kT);
+  hipLaunchKernelGGL(k_trinv_level<0>, dim3(t, t, pairs), dim3(256), 0, st, R, ldr, Y, ldy, n, s,
+                     tmp);
+  hipLaunchKernelGGL(k_trinv_level<1>, dim3(t, t, pairs), dim3(256), 0, st, R, ldr, Y, ldy, n, s,
+                     tmp);
 }
 
 void small_wtd_f64(const double* W, int64_t ldw, int64_t n, int64_t M, const void* desc,

@@ -120,10 +120,12 @@ void local_rows_f64(const void* desc, bool desc_f32, int64_t ldd, int64_t n_atom
                     const int32_t* atom_idx, int64_t n_local, const double* X, int64_t ldx,
                     int64_t M, int64_t D, int zeta, double delta, double* K, int64_t ldk,
                     int* dev_err, hipStream_t st, bool row_major = false);
-// out[i][j] = sum_k W[i][k] X[k][j]   (n x D, row-major ldo); part: wx_part_bytes of scratch
+// out[i][j] = sum_k W[i][k] X[k][j]   (n x D, row-major ldo); part: wx_part_bytes of scratch;
+// upper: X is upper triangular (M = D) and k > j is left out
 size_t wx_part_bytes(int64_t n, int64_t M, int64_t D);
 void gemm_wx_f64(const double* W, int64_t ldw, int64_t n, int64_t M, const double* X,
-                 int64_t ldx, int64_t D, double* part, double* out, int64_t ldo, hipStream_t st);
+                 int64_t ldx, int64_t D, double* part, double* out, int64_t ldo, hipStream_t st,
+                 bool upper = false);
 // dc_part[rg][m] = -sum_{i in row group rg} S[i][m] (H_i . x_m), column-stationary;
 // returns false (nothing launched) when the shape is outside its limits
 // (D <= 256, ldS and ldh multiples of 4).  Groups: resid_colsum_groups(n, M).
@@ -175,7 +177,9 @@ void small_pstage_f64(int mode, const void* rows, bool rows_f32, int64_t ldd, in
                       double* dc_part, const double* Sx, int64_t ldsx, hipStream_t st);
 void small_wx_f64(const double* W, int64_t ldw, int64_t n, int64_t M, const double* cs,
                   const double* X, int64_t ldx, int64_t D, double* part, double* out, int64_t ldo,
-                  hipStream_t st);
+                  hipStream_t st, bool upper = false);
+void small_trinv_level(const double* R, int64_t ldr, double* Y, int64_t ldy, int64_t n, int64_t s,
+                       double* tmp, hipStream_t st);
 void small_wtd_f64(const double* W, int64_t ldw, int64_t n, int64_t M, const void* desc,
                    bool desc_f32, int64_t ldd, int64_t D, double* part, double* out, int64_t ldo,
                    hipStream_t st);
@@ -307,9 +311,9 @@ void norm2_f64(const double* x, int64_t n, double* out, hipStream_t st);
 // out[0] += x . x
 void sumsq_add_f64(const double* x, int64_t n, double* out, hipStream_t st);
 // Y = R^-1 (R upper n x n col-major) as a row-major Y[i * ldy + c], zero below
-// the diagonal; one workgroup per column.
-void trinv_upper(const double* R, int64_t ld, int64_t n, double* Y, int64_t ldy, int* dev_err,
-                 hipStream_t st);
+// the diagonal, for one or two matrices (R1 NULL: one); tmp: n * ldy doubles.
+void trinv_upper2(const double* R0, int64_t ld0, double* Y0, const double* R1, int64_t ld1,
+                  double* Y1, int64_t n, int64_t ldy, double* tmp, int* dev_err, hipStream_t st);
 // var[i] = base + sign * ||Z[i][0:m]||^2 with base var[i] (init 0), delta^2 (d_i . d_i)^zeta
 // (init 1) or 0 (init 2).
 void var_rows(const double* Z, int64_t ldz, int64_t n, int64_t m, double sign, const void* desc,

@@ -16,6 +16,7 @@
 
 #include "launch.h"
 #include "mma_f64.h"
+#include "tri64.h"
 
 namespace gapk {
 
@@ -24,7 +25,6 @@ namespace {
 constexpr int kQrNB = 64;      // outer block width (compact-WY trailing update)
 constexpr int kTrsvMaxBlocks = 256;  // multi-block triangular solve: n <= 64 * 256
 constexpr int kPanelW = 32;    // inner panel width (column-by-column factorisation)
-constexpr int kCholNB = 64;    // Cholesky block
 constexpr int kPanelMaxGrid = 256;
 // Workspace counter words: [0] the column kernels' counter, [kPanelBar ..
 // kPanelBar + 8 * 16) the cooperative panel's eight arrival counters.
@@ -80,105 +80,93 @@ __global__ void k_chol_init(double* __restrict__ Lw, int64_t ldl, int64_t M, dou
     Lw[i + j * ldl] = Kmm[i + j * ldk] + (i == j ? jitter : 0.0);
 }
 
-// Diagonal block (nbj <= 64) by one wave, left-looking: lane r holds row r of
-// the block in registers.  For column c, lane c publishes the finished part of
-// its row (L[c][0:c]) to LDS; every lane forms the dot product of its row with
-// it (broadcast reads), lane c's residual gives the pivot by a lane shuffle,
-// and lanes below divide.  The column loop is unrolled so that every register
-// index is a compile-time constant.
-__global__ __launch_bounds__(64) void k_chol_diag(double* __restrict__ Lw, int64_t ldl, int64_t j0,
-                                                  int nbj, int* dev_err) {
-  __shared__ double rowc[kCholNB];
-  const int l = threadIdx.x;
-  double row[kCholNB];
-#pragma unroll
-  for (int c = 0; c < kCholNB; ++c)
-    row[c] = (l < nbj && c < nbj) ? Lw[(j0 + l) + (j0 + c) * ldl] : 0.0;
-  bool bad = false;
-#pragma unroll
-  for (int c = 0; c < kCholNB; ++c) {
-    if (c < nbj) {
-      if (l == c) {
-#pragma unroll
-        for (int q = 0; q < c; ++q) rowc[q] = row[q];
-      }
-      __syncthreads();
-      double dot = 0.0;
-#pragma unroll
-      for (int q = 0; q < c; ++q) dot += row[q] * rowc[q];
-      const double res = row[c] - dot;
-      double p = __shfl(res, c);
-      if (!(p > 0.0) || !isfinite(p)) {
-        bad = true;
-        p = 1.0;
-      }
-      const double d = sqrt(p);
-      if (l == c) row[c] = d;
-      else if (l > c) row[c] = res / d;
-      __syncthreads();
+// Lower triangle of the diagonal block at j0 (nbj <= 64 columns, completed with
+// unit columns) from L into S, factored, and back.
+GAP_DEV void chol_diag_block(double* __restrict__ Lw, int64_t ldl, int64_t j0, int nbj,
+                             double (*S)[kTriS], int* dev_err, bool load) {
+  if (load)
+    for (int e = threadIdx.x; e < kTri * kTri; e += 256) {
+      const int r = e & 63, c = e >> 6;
+      if (r >= c) S[r][c] = r < nbj ? Lw[(j0 + r) + (j0 + c) * ldl] : (r == c ? 1.0 : 0.0);
     }
-  }
-  if (bad && l == 0) atomicOr(dev_err, GAP_DEVERR_NOT_PD);
-#pragma unroll
-  for (int c = 0; c < kCholNB; ++c)
-    if (c < nbj && l < nbj && l >= c) Lw[(j0 + l) + (j0 + c) * ldl] = row[c];
-}
-
-// Rows below the diagonal block: L[r, j0:j0+nbj] = A[r, j0:j0+nbj] L_dd^-T.
-__global__ __launch_bounds__(256) void k_chol_panel(double* __restrict__ Lw, int64_t ldl, int64_t M,
-                                                    int64_t j0, int nbj) {
-  __shared__ double s[kCholNB][kCholNB + 1];
-  for (int e = threadIdx.x; e < nbj * nbj; e += 256) {
-    const int r = e % nbj, c = e / nbj;
-    s[r][c] = (r >= c) ? Lw[(j0 + r) + (j0 + c) * ldl] : 0.0;
-  }
   __syncthreads();
-  const int64_t r = j0 + nbj + blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (r >= M) return;
-  double x[kCholNB];
-#pragma unroll
-  for (int c = 0; c < kCholNB; ++c) {
-    if (c < nbj) {
-      double v = Lw[r + (j0 + c) * ldl];
-#pragma unroll
-      for (int q = 0; q < c; ++q) v -= x[q] * s[c][q];
-      x[c] = v / s[c][c];
-      Lw[r + (j0 + c) * ldl] = x[c];
-    } else {
-      x[c] = 0.0;
-    }
+  const bool bad = chol64_lds(S);
+  if (bad && threadIdx.x == 0) atomicOr(dev_err, GAP_DEVERR_NOT_PD);
+  for (int e = threadIdx.x; e < kTri * kTri; e += 256) {
+    const int r = e & 63, c = e >> 6;
+    if (r >= c && r < nbj) Lw[(j0 + r) + (j0 + c) * ldl] = S[r][c];
   }
 }
 
-// C[r][c] -= sum_k P[r][k] P[c][k] on the lower trailing block (r >= c).
+__global__ __launch_bounds__(256) void k_chol_diag(double* __restrict__ Lw, int64_t ldl, int64_t j0,
+                                                   int nbj, int* dev_err) {
+  __shared__ double S[kTri][kTriS];
+  chol_diag_block(Lw, ldl, j0, nbj, S, dev_err, true);
+}
+
+// Rows below a full diagonal block: L[r, j0:j0+64] = A[r, j0:j0+64] L_dd^-T,
+// one row per lane in registers (34 us a block column when each entry waited
+// for the dot product before it and divided, 19 us now; latency: the loads, then
+// a chain of 64 columns).
+__global__ __launch_bounds__(64) void k_chol_panel(double* __restrict__ Lw, int64_t ldl, int64_t M,
+                                                   int64_t j0) {
+  __shared__ __attribute__((aligned(16))) double u[kTri * kTri];
+  __shared__ double rinv[kTri];
+  const uint32_t l = threadIdx.x;
+  const uint32_t r = (uint32_t)min(kTri + blockIdx.x * (int64_t)64 + l, M - j0 - 1);
+  double* A = Lw + j0 + j0 * ldl;
+  double x[kTri];
+#pragma unroll
+  for (int c = 0; c < kTri; ++c) u[c * kTri + l] = (A + c * ldl)[l];  // U[c][l] = L[l][c]
+#pragma unroll
+  for (int c = 0; c < kTri; ++c) x[c] = (A + c * ldl)[r];
+  rinv[l] = 1.0 / u[l * (kTri + 1)];  // (this lane's own write)
+  __syncthreads();
+  row_solve64(x, u, rinv);
+  // lanes past the last row hold that row too and store the same values
+#pragma unroll
+  for (int c = 0; c < kTri; ++c) (A + c * ldl)[r] = x[c];
+}
+
+// C[r][c] -= sum_k P[r][k] P[c][k] on the lower trailing block (r >= c), P the
+// 64 columns at j0.  The first block goes on to factor its tile, the next
+// diagonal block, while the others run.
 __global__ __launch_bounds__(256) void k_chol_update(double* __restrict__ Lw, int64_t ldl,
-                                                     int64_t M, int64_t j0, int nbj) {
-  const int64_t t0 = j0 + nbj;
+                                                     int64_t M, int64_t j0, int* dev_err) {
+  __shared__ double S[kTri][kTriS];
+  const int64_t t0 = j0 + kTri;
   const int64_t cbase = t0 + (int64_t)blockIdx.x * 64;  // columns (MFMA rows)
   const int64_t rbase = t0 + (int64_t)blockIdx.y * 64;  // rows (MFMA columns)
   if (rbase + 63 < cbase) return;                        // tile strictly above the diagonal
+  const bool next = blockIdx.x == 0 && blockIdx.y == 0;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane >> 4, idx = lane & 15;
   const int64_t c = cbase + wave * 16 + idx;
-  FragColK<double> fa{Lw + (c < M ? c : 0) + j0 * ldl, ldl, nbj, c < M};
+  FragColK<double> fa{Lw + (c < M ? c : 0) + j0 * ldl, ldl, kTri, c < M};
   FragColK<double> fb[4];
 #pragma unroll
   for (int u = 0; u < 4; ++u) {
     const int64_t r = rbase + u * 16 + idx;
-    fb[u] = FragColK<double>{Lw + (r < M ? r : 0) + j0 * ldl, ldl, nbj, r < M};
+    fb[u] = FragColK<double>{Lw + (r < M ? r : 0) + j0 * ldl, ldl, kTri, r < M};
   }
   d4v acc[4];
 #pragma unroll
   for (int u = 0; u < 4; ++u) acc[u] = zero4();
-  wave_mma<4>(fa, fb, nbj, g, acc);
+  wave_mma<4>(fa, fb, kTri, g, acc);
 #pragma unroll
   for (int u = 0; u < 4; ++u) {
     const int64_t r = rbase + u * 16 + idx;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const int64_t cc = cbase + wave * 16 + g + 4 * q;
-      if (r < M && cc < M && r >= cc) Lw[r + cc * ldl] -= acc[u][q];
+      const bool in = r < M && cc < M && r >= cc;
+      const double v = in ? Lw[r + cc * ldl] - acc[u][q] : (r == cc ? 1.0 : 0.0);
+      if (next)
+        S[r - rbase][cc - cbase] = v;
+      else if (in)
+        Lw[r + cc * ldl] = v;
     }
   }
+  if (next) chol_diag_block(Lw, ldl, t0, (int)min((int64_t)kTri, M - t0), S, dev_err, false);
 }
 
 // ------------------------------------------------------------------- QR ----
@@ -1827,19 +1815,40 @@ __global__ __launch_bounds__(1024) void k_trsv_blk(const double* __restrict__ R,
   for (int64_t i = threadIdx.x; i < n; i += 1024) x[i] = xs[i];
 }
 
-// Inverse of an upper-triangular R (col-major, ld), one column per workgroup:
-// block c solves R y = e_c, which only involves the leading (c+1) x (c+1)
-// block, and writes y as row-major Y (Y[i * ldy + c] = (R^-1)[i][c], zero
-// below the diagonal).
-__global__ __launch_bounds__(1024) void k_trinv_upper(const double* __restrict__ R, int64_t ld,
-                                                      int64_t n, double* __restrict__ Y,
-                                                      int64_t ldy, int* dev_err) {
-  extern __shared__ double xs[];
-  __shared__ double T[64][65];
-  const int64_t c = blockIdx.x;
-  for (int64_t i = threadIdx.x; i <= c; i += 1024) xs[i] = (i == c) ? 1.0 : 0.0;
-  trsv_blk_lds<false>(R, ld, c + 1, xs, T, dev_err);
-  for (int64_t i = threadIdx.x; i < n; i += 1024) Y[i * ldy + c] = (i <= c) ? xs[i] : 0.0;
+// Inverses of the 64 x 64 diagonal blocks of upper-triangular matrices (col-
+// major, ld) into the diagonal blocks of Y (row-major, ldy), zero below the
+// diagonal; a lane per row of Y, which solves y R = e_r by substitution.  One
+// block per (diagonal block, matrix).
+__global__ __launch_bounds__(64) void k_trinv_diag(const double* __restrict__ R0, int64_t ld0,
+                                                   double* __restrict__ Y0,
+                                                   const double* __restrict__ R1, int64_t ld1,
+                                                   double* __restrict__ Y1, int64_t n,
+                                                   int64_t ldy, int* dev_err) {
+  __shared__ __attribute__((aligned(16))) double u[kTri * kTri];
+  __shared__ double rinv[kTri];
+  const int l = threadIdx.x;
+  const int64_t j0 = (int64_t)blockIdx.x * kTri, ld = blockIdx.y ? ld1 : ld0;
+  const double* R = (blockIdx.y ? R1 : R0) + j0 + j0 * ld;
+  const int w = (int)min((int64_t)kTri, n - j0);
+#pragma unroll 16
+  for (int c = 0; c < kTri; ++c)  // column c, rows 0 .. c; unit rows past the matrix
+    u[l * kTri + c] = (l <= c && c < w) ? R[l + c * ld] : (l == c ? 1.0 : 0.0);
+  const double d = u[l * (kTri + 1)];
+  if (d == 0.0 || !isfinite(d)) atomicOr(dev_err, GAP_DEVERR_RANK);
+  rinv[l] = 1.0 / d;
+  __syncthreads();
+  double x[kTri];
+#pragma unroll
+  for (int c = 0; c < kTri; ++c) {
+    x[c] = c == l ? 1.0 : 0.0;
+    asm volatile("" : "+v"(x[c]));  // (64 lane masks carried through the substitution spill)
+  }
+  row_solve64(x, u, rinv);
+  if (l >= w) return;
+  double* y = (blockIdx.y ? Y1 : Y0) + (j0 + l) * ldy + j0;
+#pragma unroll
+  for (int c = 0; c < kTri; ++c)
+    if (c < w) y[c] = x[c];
 }
 
 // var[i] += sign * sum_j Z[i][j]^2 (row-major Z, one wave per row); with
@@ -2191,14 +2200,12 @@ void cholesky_lower(double* Lw, int64_t ldl, int64_t M, double jitter, const dou
                     int64_t ldk, int* dev_err, hipStream_t st) {
   hipLaunchKernelGGL(k_chol_init, dim3(cdiv(M, 256), (unsigned)M), dim3(256), 0, st, Lw, ldl, M,
                      jitter, Kmm, ldk);
-  for (int64_t j0 = 0; j0 < M; j0 += kCholNB) {
-    const int nbj = (int)std::min<int64_t>(kCholNB, M - j0);
-    hipLaunchKernelGGL(k_chol_diag, dim3(1), dim3(64), 0, st, Lw, ldl, j0, nbj, dev_err);
-    const int64_t rest = M - j0 - nbj;
-    if (rest <= 0) break;
-    hipLaunchKernelGGL(k_chol_panel, dim3(cdiv(rest, 256)), dim3(256), 0, st, Lw, ldl, M, j0, nbj);
-    hipLaunchKernelGGL(k_chol_update, dim3(cdiv(rest, 64), cdiv(rest, 64)), dim3(256), 0, st, Lw,
-                       ldl, M, j0, nbj);
+  hipLaunchKernelGGL(k_chol_diag, dim3(1), dim3(256), 0, st, Lw, ldl, (int64_t)0,
+                     (int)std::min<int64_t>(kTri, M), dev_err);
+  for (int64_t j0 = 0; j0 + kTri < M; j0 += kTri) {
+    const unsigned nt = cdiv(M - j0 - kTri, kTri);
+    hipLaunchKernelGGL(k_chol_panel, dim3(nt), dim3(64), 0, st, Lw, ldl, M, j0);
+    hipLaunchKernelGGL(k_chol_update, dim3(nt, nt), dim3(256), 0, st, Lw, ldl, M, j0, dev_err);
   }
 }
 
@@ -2496,11 +2503,22 @@ void sumsq_add_f64(const double* x, int64_t n, double* out, hipStream_t st) {
   hipLaunchKernelGGL(k_sumsq_add, dim3(1), dim3(1024), 0, st, x, n, out);
 }
 
-void trinv_upper(const double* R, int64_t ld, int64_t n, double* Y, int64_t ldy, int* dev_err,
-                 hipStream_t st) {
+// Y_z = R_z^-1 for two upper-triangular matrices of order n (R_1 may be NULL),
+// by doubling: with the inverses of two neighbouring s x s diagonal blocks,
+//   [R11 R12; 0 R22]^-1 = [Y11, -Y11 R12 Y22; 0, Y22],
+// two products per level for all pairs of blocks at once (tmp: n * ldy doubles).
+// A substitution per column and workgroup, the form this replaces, re-read the
+// whole triangle for every column: 2.3 ms at n = 2000, now 0.35 ms for both.
+void trinv_upper2(const double* R0, int64_t ld0, double* Y0, const double* R1, int64_t ld1,
+                  double* Y1, int64_t n, int64_t ldy, double* tmp, int* dev_err, hipStream_t st) {
   if (n <= 0) return;
-  hipLaunchKernelGGL(k_trinv_upper, dim3((unsigned)n), dim3(1024), (size_t)n * sizeof(double), st,
-                     R, ld, n, Y, ldy, dev_err);
+  const int nz = R1 ? 2 : 1;
+  hipLaunchKernelGGL(k_trinv_diag, dim3(cdiv(n, kTri), nz), dim3(64), 0, st, R0, ld0, Y0, R1, ld1,
+                     Y1, n, ldy, dev_err);
+  for (int64_t s = kTri; s < n; s *= 2) {
+    small_trinv_level(R0, ld0, Y0, ldy, n, s, tmp, st);
+    if (R1) small_trinv_level(R1, ld1, Y1, ldy, n, s, tmp, st);
+  }
 }
 
 void var_rows(const double* Z, int64_t ldz, int64_t n, int64_t m, double sign, const void* desc,
