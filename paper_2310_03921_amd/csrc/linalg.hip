@@ -564,16 +564,6 @@ __global__ __launch_bounds__(kRRT) void k_qr_panel_rr(double* __restrict__ A, in
   }
 }
 
-__global__ void k_sum_slabs(const double* __restrict__ part, int64_t nslab, int64_t n,
-                            double* __restrict__ W) {
-  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < n;
-       e += (int64_t)gridDim.x * blockDim.x) {
-    double s = 0.0;
-    for (int64_t q = 0; q < nslab; ++q) s += part[q * n + e];
-    W[e] = s;
-  }
-}
-
 // sum_{q0 <= q < q1} a(q) b(q) with four independent partial sums, so that the
 // LDS reads of four terms are in flight together (a single running sum waits
 // for each read in turn)
@@ -2209,21 +2199,29 @@ void cholesky_lower(double* Lw, int64_t ldl, int64_t M, double jitter, const dou
   }
 }
 
-static int64_t qr_slab_rows(int64_t m) {
-  // slabs of >= 2048 rows (a multiple of 32), at most 256 of them
-  int64_t s = (m + 255) / 256;
-  s = std::max<int64_t>(s, 2048);
-  return (s + 31) / 32 * 32;
+// Rows per slab of the 128-wide W = V^T C of rows [j0, m) and nct columns: at
+// most 256 slabs, of >= 2048 rows where those alone give about two blocks per
+// compute unit, else shorter ones (>= 256 rows, whose partials still cost less
+// than reading V and C) until they do.  With 2048-row slabs a factorisation of
+// 6,000 rows and 200 columns ran this product on 8 blocks in 305 us; 50 blocks
+// take 48 us.
+static int64_t qr_slab_rows(int64_t m, int64_t j0, int64_t nct) {
+  const int64_t rows = m - j0, n_ct = (nct + kVC - 1) / kVC;
+  const int64_t large = std::max<int64_t>((m + 255) / 256, 2048);
+  const int64_t fill = std::max<int64_t>(rows * n_ct / 512, 256);
+  return (std::min(large, fill) + 31) / 32 * 32;
 }
 
 // Elements of the split-K partials buffer: those of the 128-wide updates, or
 // of the 16- and 64-wide ones over short slabs (at most 64 reflectors x 128
 // columns).  Both the workspace size and its binding use this one count.
 static int64_t qr_part_elems(int64_t m, int64_t n) {
-  const int64_t ncols = n + 1;
-  const int64_t nslab = (m + qr_slab_rows(m) - 1) / qr_slab_rows(m);
-  return std::max(nslab * kQrOB * ncols,
-                  ((m + kNarrowSlab - 1) / kNarrowSlab + 1) * (int64_t)kQrNB * 2 * kQrNB);
+  int64_t e = ((m + kNarrowSlab - 1) / kNarrowSlab + 1) * (int64_t)kQrNB * 2 * kQrNB;
+  for (int64_t j0 = 0; j0 < n; j0 += kQrOB) {
+    const int64_t nct = n + 1 - j0, slab = qr_slab_rows(m, j0, nct);
+    e = std::max(e, (m - j0 + slab - 1) / slab * kQrOB * nct);
+  }
+  return e;
 }
 
 size_t qr_workspace_bytes(int64_t m, int64_t n) {
@@ -2264,7 +2262,7 @@ void qr_bind_workspace(void* base, int64_t m, int64_t n, QrWork* w) {
 // columns [j0, j0 + pw): W = V^T A[j0:m, j0:c_end) (Gram V^T V included),
 // T from the Gram and tau, then A[j0:m, c0:c_end) -= V (T^T W).
 static void qr_wy_update(double* A, int64_t ld, int64_t m, int64_t j0, int pw, int64_t c_end,
-                         int64_t slab, QrWork* w, hipStream_t st) {
+                         QrWork* w, hipStream_t st) {
   const int64_t nct = c_end - j0;
   if (nct <= pw) return;
   if (pw <= 16 && nct <= 64) {
@@ -2282,7 +2280,6 @@ static void qr_wy_update(double* A, int64_t ld, int64_t m, int64_t j0, int pw, i
     // Short slabs: a 64-wide update has one column tile, so the slabs alone
     // must give enough blocks to fill the device; the many partials are summed
     // by the multi-block row reduction.
-    (void)slab;
     const int64_t nslab = (m - j0 + kNarrowSlab - 1) / kNarrowSlab;
     const int64_t n_ct = (nct + kVC - 1) / kVC;
     const int64_t total = nslab * n_ct, per_xcd = (total + 7) / 8;
@@ -2299,9 +2296,10 @@ static void qr_wy_update(double* A, int64_t ld, int64_t m, int64_t j0, int pw, i
 
 // The same update for an outer block of up to kQrOB reflectors.
 static void qr_wy_update_ob(double* A, int64_t ld, int64_t m, int64_t j0, int pw, int64_t c_end,
-                            int64_t slab, QrWork* w, hipStream_t st) {
+                            QrWork* w, hipStream_t st) {
   const int64_t nct = c_end - j0;
   if (nct <= pw) return;
+  const int64_t slab = qr_slab_rows(m, j0, nct);
   const int64_t nslab = (m - j0 + slab - 1) / slab;
   const int64_t n_ct = (nct + kVC - 1) / kVC;
   const int64_t total = nslab * n_ct, per_xcd = (total + 7) / 8;
@@ -2312,8 +2310,7 @@ static void qr_wy_update_ob(double* A, int64_t ld, int64_t m, int64_t j0, int pw
   else
     hipLaunchKernelGGL(k_qr_vtc3<false>, dim3((unsigned)(8 * per_xcd)), dim3(512), 0, st, A, ld,
                        m, j0, pw, nct, slab, n_ct, total, per_xcd, w->part);
-  hipLaunchKernelGGL(k_sum_slabs, dim3(g256(pw * nct)), dim3(256), 0, st, w->part, nslab,
-                     (int64_t)pw * nct, w->W);
+  reduce_rows_f64(w->part, nslab, (int64_t)pw * nct, w->W, st);
   hipLaunchKernelGGL(k_qr_larft_half, dim3(2), dim3(256), 0, st, w->W, nct, pw, w->tau + j0,
                      w->T);
   if (pw > kQrNB)
@@ -2350,7 +2347,6 @@ void qr_factor(double* A, int64_t ld, int64_t m, int64_t ncols, int64_t n, QrWor
   Timer dummy;
   if (!tm) tm = &dummy;
   hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(1), 0, st, w->counter);
-  const int64_t slab = qr_slab_rows(m);
   const int cap = rr_capacity();
   // Three levels: 16-wide register-resident panels inside 64-wide blocks
   // (compact-WY updates within the block), 64-wide blocks inside 128-wide outer
@@ -2397,19 +2393,19 @@ void qr_factor(double* A, int64_t ld, int64_t m, int64_t ncols, int64_t n, QrWor
           }
         }
         // rest of the 64-wide block with this inner panel's reflectors
-        qr_wy_update(A, ld, m, i0, pw, j0 + bw, slab, w, st);
+        qr_wy_update(A, ld, m, i0, pw, j0 + bw, w, st);
         tm->end(TM_QR_PANEL);
         i0 += pw;
       }
       if (j0 + bw >= o0 + ow) continue;
       // rest of the outer block with this 64-wide block's reflectors
       tm->begin(TM_QR_UPDATE);
-      qr_wy_update(A, ld, m, j0, bw, o0 + ow, slab, w, st);
+      qr_wy_update(A, ld, m, j0, bw, o0 + ow, w, st);
       tm->end(TM_QR_UPDATE);
     }
     if (o0 + ow >= ncols) continue;
     tm->begin(TM_QR_UPDATE);
-    qr_wy_update_ob(A, ld, m, o0, ow, ncols, slab, w, st);
+    qr_wy_update_ob(A, ld, m, o0, ow, ncols, w, st);
     tm->end(TM_QR_UPDATE);
   }
 }
