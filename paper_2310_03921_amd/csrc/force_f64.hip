@@ -14,6 +14,9 @@
 // kernel.  Each output row is written once, no atomics, so results do not
 // depend on scheduling.  The four waves of a block share the slot group (their
 // Jacobian rows hit L1) and cover consecutive column ranges.
+#include <algorithm>
+#include <type_traits>
+
 #include "launch.h"
 #include "mma_f64.h"
 
@@ -125,125 +128,6 @@ __global__ __launch_bounds__(256) void k_force_rows(
   }
 }
 
-// LDS-resident forms for D <= 256: the block's 64 sparse-point columns of X
-// stay in LDS for its whole lifetime, stored in the order the matrix core
-// consumes them.  A block covers 64 targets (four 16-target slot groups) x 64
-// columns.  Consecutive logical blocks on one XCD walk the column tiles of the
-// same 64 targets, so their Jacobian rows are fetched from HBM once and then
-// served mostly from that XCD's L2.
-constexpr int kLdsNC = 4;
-constexpr int kLdsMaxKb = 16;  // D <= 256
-
-// Twelve-wave form: wave w handles Jacobian component alpha = w % 3 of slot
-// group w / 3, so three waves share a SIMD and hide each other's Jacobian load
-// latency.  X in LDS per 16-k block, per 16-column tile, per lane: 4 doubles.
-// (Used when D is not a multiple of 4; k_force_rows_lds12f below otherwise.)
-constexpr int kW12 = 12;
-template <typename TJ>
-__global__ __launch_bounds__(64 * kW12) void k_force_rows_lds12(
-    const TJ* __restrict__ jac, int64_t ldj, int64_t D, const double* __restrict__ X,
-    int64_t ldx, int64_t M, const double* __restrict__ S, int64_t ldS,
-    const int64_t* __restrict__ tgt_ptr, const int32_t* __restrict__ tgt_pair,
-    const int32_t* __restrict__ pair_src, const int32_t* __restrict__ order, int64_t n_atoms,
-    int64_t row0, double* __restrict__ K, int64_t ldk, int64_t n_ct, int64_t n_grp, int nkb) {
-  extern __shared__ double xs[];  // [nkb][kLdsNC][64 lanes][4]
-  int64_t ct, tgb;
-  if (!xcd_group_tile(n_grp, n_ct, tgb, ct)) return;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane >> 4, idx = lane & 15;
-  const int alpha = wave % 3, grp = wave / 3;
-  const int64_t colbase = ct * (16 * kLdsNC);
-
-  for (int e = threadIdx.x; e < nkb * kLdsNC * 64; e += 64 * kW12) {
-    const int kb = e / (kLdsNC * 64), rem = e % (kLdsNC * 64);
-    const int u = rem / 64, ln = rem % 64;
-    const int64_t col = colbase + u * 16 + (ln & 15);
-    double v[4];
-    if (col < M)
-      load4(X + col * ldx, (int64_t)kb * 16 + 4 * (ln >> 4), D, v);
-    else
-      zero_frag(v);
-    d4v w = {v[0], v[1], v[2], v[3]};
-    *reinterpret_cast<d4v*>(xs + (size_t)e * 4) = w;
-  }
-  __syncthreads();
-
-  const int64_t slot = (tgb * 4 + grp) * 16 + idx;
-  const int target = slot < n_atoms ? order[slot] : -1;
-  const int64_t seg0 = target >= 0 ? tgt_ptr[target] : 0;
-  const int deg = target >= 0 ? (int)(tgt_ptr[target + 1] - seg0) : 0;
-  const int maxdeg = wave_max16(deg);
-  int64_t colr[kLdsNC];
-#pragma unroll
-  for (int u = 0; u < kLdsNC; ++u) colr[u] = colbase + u * 16 + idx;
-  d4v acc[kLdsNC];
-#pragma unroll
-  for (int u = 0; u < kLdsNC; ++u) acc[u] = zero4();
-  const d4v* xb = reinterpret_cast<const d4v*>(xs) + lane;
-  auto pair_at = [&](int t) -> int { return t < deg ? tgt_pair[seg0 + t] : -1; };
-  int pair = maxdeg > 0 ? pair_at(0) : -1;
-  int src = pair >= 0 ? pair_src[pair] : -1;
-  if (src < 0) pair = -1;
-  double a0[4], a1[4];
-  if (pair >= 0) load4(jac + (int64_t)pair * 3 * ldj + alpha * ldj, 4 * g, D, a0); else zero_frag(a0);
-  for (int t = 0; t < maxdeg; ++t) {
-    const bool pv = pair >= 0;
-    const TJ* jr = jac + (int64_t)(pv ? pair : 0) * 3 * ldj + alpha * ldj;
-    int pair_n = pair_at(t + 1);
-    int src_n = -1;
-    d4v G[kLdsNC];
-#pragma unroll
-    for (int u = 0; u < kLdsNC; ++u) G[u] = zero4();
-    for (int kb = 0; kb < nkb; kb += 2) {  // nkb is even
-      if (pv) load4(jr, (int64_t)(kb + 1) * 16 + 4 * g, D, a1); else zero_frag(a1);
-      if (kb == 0) src_n = pair_n >= 0 ? pair_src[pair_n] : -1;
-      {
-        d4v b[kLdsNC];
-#pragma unroll
-        for (int u = 0; u < kLdsNC; ++u) b[u] = xb[(kb * kLdsNC + u) * 64];
-#pragma unroll
-        for (int s4 = 0; s4 < 4; ++s4)
-#pragma unroll
-          for (int u = 0; u < kLdsNC; ++u) G[u] = mfma_f64(a0[s4], b[u][s4], G[u]);
-      }
-      if (kb + 2 < nkb) {
-        if (pv) load4(jr, (int64_t)(kb + 2) * 16 + 4 * g, D, a0); else zero_frag(a0);
-      } else {
-        if (src_n < 0) pair_n = -1;
-        if (pair_n >= 0) load4(jac + (int64_t)pair_n * 3 * ldj + alpha * ldj, 4 * g, D, a0);
-        else zero_frag(a0);
-      }
-      {
-        d4v b[kLdsNC];
-#pragma unroll
-        for (int u = 0; u < kLdsNC; ++u) b[u] = xb[((kb + 1) * kLdsNC + u) * 64];
-#pragma unroll
-        for (int s4 = 0; s4 < 4; ++s4)
-#pragma unroll
-          for (int u = 0; u < kLdsNC; ++u) G[u] = mfma_f64(a1[s4], b[u][s4], G[u]);
-      }
-    }
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int src_r = __shfl(src, g + 4 * r);
-#pragma unroll
-      for (int u = 0; u < kLdsNC; ++u) {
-        const double sv = (src_r >= 0 && colr[u] < M) ? S[(int64_t)src_r * ldS + colr[u]] : 0.0;
-        acc[u][r] += sv * G[u][r];
-      }
-    }
-    pair = pair_n;
-    src = src_n;
-  }
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int tr = __shfl(target, g + 4 * r);
-    if (tr < 0) continue;
-#pragma unroll
-    for (int u = 0; u < kLdsNC; ++u)
-      if (colr[u] < M) K[(row0 + 3 * (int64_t)tr + alpha) + colr[u] * ldk] = -acc[u][r];
-  }
-}
-
 // Unconditional 4-wide loads of a Jacobian row segment (32-byte aligned).
 GAP_DEV void ldj4(const double* p, double out[4]) {
   const d4v v = *reinterpret_cast<const d4v*>(p);
@@ -254,39 +138,57 @@ GAP_DEV void ldj4(const float* p, double out[4]) {
   out[0] = v[0]; out[1] = v[1]; out[2] = v[2]; out[3] = v[3];
 }
 
-// The twelve-wave kernel for D % 4 == 0 with no guarded load on its hot path.
+// LDS-resident form for D <= 256: the block's 16 NC sparse-point columns of X
+// stay in LDS for its whole lifetime, in the order the matrix core consumes
+// them.  A block covers 16 NG targets (NG slot groups); wave w handles Jacobian
+// component alpha = w % 3 of slot group w / 3, so that three waves share a SIMD
+// and hide each other's Jacobian load latency.  Consecutive logical blocks on
+// one XCD walk the column tiles of the same targets, so their Jacobian rows are
+// fetched from HBM once and then served mostly from that XCD's L2.  With 12
+// waves and 128 KB of X a block has a compute unit to itself.
+// NG = 4: a wave walks all pairs of its targets.  NG = 1: SP = 4 waves share
+// them (wave s the steps s, s + 4, ...) and their sums are added in LDS in wave
+// order at the end: blocks a quarter as long, for calls whose few blocks of the
+// first form would leave compute units idle behind the targets of the highest
+// degree (kForceSplit).
+// There is no guarded load on the hot path.
 // A load under a condition compiles to a branch whose join waits for the load
 // at once, which would serialise the Jacobian stream; here every load reads a
 // valid address and invalid data is cancelled arithmetically:
-//  - k blocks beyond D read the row's last 4 elements and meet zero rows of X;
+//  - k blocks beyond D read the row's last 4 elements and meet zero rows of X
+//    (RAGGED, D % 4 != 0: the row's padding may hold anything, so entries past D
+//    are replaced by zero where they are used);
 //  - a slot past its degree (or a target past n_atoms) reads a valid pair of
 //    the same target (or pair 0) and its step result is multiplied by a zero S;
 //  - S is read at a clamped (source, column) and multiplied by the validity.
 // Matrix data are finite, so garbage * 0 == 0.  Results equal those of the
 // guarded form up to the order of FP64 additions (identical here: the zero
 // contributions add exact zeros).
-template <typename TJ>
-__global__ __launch_bounds__(64 * kW12) void k_force_rows_lds12f(
+constexpr int kLdsMaxKb = 16;  // D <= 256
+constexpr int kLdsNC = 4;      // 16-column tiles per block
+template <typename TJ, bool RAGGED, int NG>
+__global__ __launch_bounds__(768) void k_force_rows_lds(
     const TJ* __restrict__ jac, int64_t ldj, int64_t D, const double* __restrict__ X,
     int64_t ldx, int64_t M, const double* __restrict__ S, int64_t ldS,
     const int64_t* __restrict__ tgt_ptr, const int32_t* __restrict__ tgt_pair,
     const int32_t* __restrict__ pair_src, const int32_t* __restrict__ order, int64_t n_atoms,
     int64_t n_pairs, int64_t row0, double* __restrict__ K, int64_t ldk, int64_t n_ct,
     int64_t n_grp, int nkb) {
-  // X tiles in LDS: [nkb][kLdsNC][2 halves][64 lanes][2 doubles]: a lane's four
+  // X tiles in LDS: [nkb][NC][2 halves][64 lanes][2 doubles]: a lane's four
   // k values of one fragment are split into two 16-byte halves stored 1 KB
   // apart, so each 16-byte LDS read of the wave is contiguous (no bank conflict)
+  constexpr int NC = kLdsNC, SP = 4 / NG;
   extern __shared__ double xs[];
   int64_t ct, tgb;
   if (!xcd_group_tile(n_grp, n_ct, tgb, ct)) return;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane >> 4, idx = lane & 15;
-  const int alpha = wave % 3, grp = wave / 3;
-  const int64_t colbase = ct * (16 * kLdsNC);
+  const int alpha = wave % 3, grp = wave / 3 / SP, sp = wave / 3 % SP;
+  const int64_t colbase = ct * (16 * NC);
 
-  for (int e = threadIdx.x; e < nkb * kLdsNC * 64; e += 64 * kW12) {
-    const int kb = e / (kLdsNC * 64), rem = e % (kLdsNC * 64);
+  for (int e = threadIdx.x; e < nkb * NC * 64; e += 768) {
+    const int kb = e / (NC * 64), rem = e % (NC * 64);
     const int u = rem / 64, ln = rem % 64;
-    const int64_t col = colbase + 4 * (ln & 15) + u;  // lane idx of tile u: column 4 idx + u
+    const int64_t col = colbase + NC * (ln & 15) + u;  // lane idx of tile u: column NC idx + u
     double v[4];
     if (col < M)
       load4(X + col * ldx, (int64_t)kb * 16 + 4 * (ln >> 4), D, v);
@@ -299,7 +201,7 @@ __global__ __launch_bounds__(64 * kW12) void k_force_rows_lds12f(
   }
   __syncthreads();
 
-  const int64_t slot = (tgb * 4 + grp) * 16 + idx;
+  const int64_t slot = (tgb * NG + grp) * 16 + idx;
   const int target = slot < n_atoms ? order[slot] : -1;
   const int64_t seg0 = target >= 0 ? tgt_ptr[target] : 0;
   const int deg = target >= 0 ? (int)(tgt_ptr[target + 1] - seg0) : 0;
@@ -307,70 +209,77 @@ __global__ __launch_bounds__(64 * kW12) void k_force_rows_lds12f(
   // step t of this slot reads tgt_pair[pair_slot(t)], always a valid entry
   const int64_t last = min(seg0 + max(deg - 1, 0), n_pairs - 1);
   auto pair_slot = [&](int t) -> int64_t { return min(seg0 + t, last); };
-  const int64_t kmax4 = D - 4;
-  // the four columns of a lane are consecutive (4 idx + u), so its S values
-  // for one source are one 32-byte load (S rows padded with zeros to ldS)
-  int64_t colr[kLdsNC];
+  const int64_t kmax4 = RAGGED ? (D + 3) / 4 * 4 - 4 : D - 4;
+  auto cut = [&](int kb, double a[4]) {  // the k block's entries past D
 #pragma unroll
-  for (int u = 0; u < kLdsNC; ++u) colr[u] = colbase + 4 * idx + u;
-  const int64_t scol = min(colbase + 4 * idx, ldS - 4);
-  d4v acc[kLdsNC];
+    for (int q = 0; q < 4; ++q) a[q] = kb * 16 + 4 * g + q < D ? a[q] : 0.0;
+  };
+  // the NC columns of a lane are consecutive (NC idx + u), so its S values
+  // for one source are one load (S rows padded with zeros to ldS)
+  typedef double dNv __attribute__((ext_vector_type(NC)));
+  int64_t colr[NC];
 #pragma unroll
-  for (int u = 0; u < kLdsNC; ++u) acc[u] = zero4();
+  for (int u = 0; u < NC; ++u) colr[u] = colbase + NC * idx + u;
+  const int64_t scol = min(colbase + NC * idx, ldS - NC);
+  d4v acc[NC];
+#pragma unroll
+  for (int u = 0; u < NC; ++u) acc[u] = zero4();
   const d2v* xb = reinterpret_cast<const d2v*>(xs) + lane;
   auto xfrag = [&](int tile) -> d4v {
     const d2v lo = xb[tile * 128], hi = xb[tile * 128 + 64];
     const d4v f = {lo[0], lo[1], hi[0], hi[1]};
     return f;
   };
-  if (maxdeg <= 0) {
-    // no pair reaches any of these targets: the rows are zero
+  if (maxdeg <= sp) {
+    // no step of this wave
   } else {
-    // Pair metadata runs one step ahead of its use: at step t the pair of
-    // step t + 1 is known, so its source and the pair of step t + 2 are
-    // loaded now and first needed a whole step later.
-    int pair = tgt_pair[pair_slot(0)];
-    int pair_n = tgt_pair[pair_slot(1)];
+    // Pair metadata runs one step ahead of its use: at a step the pair of the
+    // wave's next step is known, so its source and the pair of the step after
+    // that are loaded now and first needed a whole step later.
+    int pair = tgt_pair[pair_slot(sp)];
+    int pair_n = tgt_pair[pair_slot(sp + SP)];
     int src = pair_src[pair];
     double a0[4], a1[4];
     const TJ* jr = jac + (int64_t)pair * 3 * ldj + alpha * ldj;
     ldj4(jr + min((int64_t)4 * g, kmax4), a0);
-    for (int t = 0; t < maxdeg; ++t) {
-      const int pair_nn = tgt_pair[pair_slot(t + 2)];
+    for (int t = sp; t < maxdeg; t += SP) {
+      const int pair_nn = tgt_pair[pair_slot(t + 2 * SP)];
       const int src_n = pair_src[pair_n];
       const TJ* jn = jac + (int64_t)pair_n * 3 * ldj + alpha * ldj;
-      d4v G[kLdsNC];
+      d4v G[NC];
 #pragma unroll
-      for (int u = 0; u < kLdsNC; ++u) G[u] = zero4();
+      for (int u = 0; u < NC; ++u) G[u] = zero4();
       for (int kb = 0; kb < nkb; kb += 2) {  // nkb is even
         ldj4(jr + min((int64_t)(kb + 1) * 16 + 4 * g, kmax4), a1);
+        if (RAGGED) cut(kb, a0);
         {
-          d4v b[kLdsNC];
+          d4v b[NC];
 #pragma unroll
-          for (int u = 0; u < kLdsNC; ++u) b[u] = xfrag(kb * kLdsNC + u);
+          for (int u = 0; u < NC; ++u) b[u] = xfrag(kb * NC + u);
 #pragma unroll
           for (int s4 = 0; s4 < 4; ++s4)
 #pragma unroll
-            for (int u = 0; u < kLdsNC; ++u) G[u] = mfma_f64(a0[s4], b[u][s4], G[u]);
+            for (int u = 0; u < NC; ++u) G[u] = mfma_f64(a0[s4], b[u][s4], G[u]);
         }
         // the next block of this step, or the first block of the next step
         const TJ* jp = (kb + 2 < nkb) ? jr + (int64_t)(kb + 2) * 16 : jn;
         ldj4(jp + min((int64_t)4 * g, kmax4 - ((kb + 2 < nkb) ? (int64_t)(kb + 2) * 16 : 0)), a0);
+        if (RAGGED) cut(kb + 1, a1);
         {
-          d4v b[kLdsNC];
+          d4v b[NC];
 #pragma unroll
-          for (int u = 0; u < kLdsNC; ++u) b[u] = xfrag((kb + 1) * kLdsNC + u);
+          for (int u = 0; u < NC; ++u) b[u] = xfrag((kb + 1) * NC + u);
 #pragma unroll
           for (int s4 = 0; s4 < 4; ++s4)
 #pragma unroll
-            for (int u = 0; u < kLdsNC; ++u) G[u] = mfma_f64(a1[s4], b[u][s4], G[u]);
+            for (int u = 0; u < NC; ++u) G[u] = mfma_f64(a1[s4], b[u][s4], G[u]);
         }
       }
-      d4v sv[4];
+      dNv sv[4];
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int src_r = __shfl(src, g + 4 * r);
-        sv[r] = *reinterpret_cast<const d4v*>(S + (int64_t)max(src_r, 0) * ldS + scol);
+        sv[r] = *reinterpret_cast<const dNv*>(S + (int64_t)max(src_r, 0) * ldS + scol);
       }
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
@@ -378,7 +287,7 @@ __global__ __launch_bounds__(64 * kW12) void k_force_rows_lds12f(
         const int deg_r = __shfl(deg, g + 4 * r);
         const bool ok_r = t < deg_r && src_r >= 0;
 #pragma unroll
-        for (int u = 0; u < kLdsNC; ++u)
+        for (int u = 0; u < NC; ++u)
           acc[u][r] += sv[r][u] * ((ok_r && colr[u] < M) ? 1.0 : 0.0) * G[u][r];
       }
       jr = jn;
@@ -386,12 +295,26 @@ __global__ __launch_bounds__(64 * kW12) void k_force_rows_lds12f(
       src = src_n;
     }
   }
+  if (SP > 1) {
+    __syncthreads();  // X is no longer read: its LDS holds the other waves' sums
+    d4v* part = reinterpret_cast<d4v*>(xs) + ((grp * 3 + alpha) * (SP - 1)) * NC * 64 + lane;
+    if (sp > 0) {
+#pragma unroll
+      for (int u = 0; u < NC; ++u) part[((sp - 1) * NC + u) * 64] = acc[u];
+    }
+    __syncthreads();
+    if (sp > 0) return;
+#pragma unroll
+    for (int w = 0; w < SP - 1; ++w)
+#pragma unroll
+      for (int u = 0; u < NC; ++u) acc[u] += part[(w * NC + u) * 64];
+  }
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
     const int tr = __shfl(target, g + 4 * r);
     if (tr < 0) continue;
 #pragma unroll
-    for (int u = 0; u < kLdsNC; ++u)
+    for (int u = 0; u < NC; ++u)
       if (colr[u] < M) K[(row0 + 3 * (int64_t)tr + alpha) + colr[u] * ldk] = -acc[u][r];
   }
 }
@@ -632,6 +555,12 @@ __global__ __launch_bounds__(256) void k_jac_t_apply4(const TJ* __restrict__ jac
 
 inline unsigned cdiv(int64_t a, int64_t b) { return (unsigned)((a + b - 1) / b); }
 
+// Below this many 64 x 64 blocks the split form of k_force_rows_lds runs (us,
+// split against not): 128 blocks (2022 atoms, M 200, D 252, 20 pairs an atom)
+// 403 / 824; 476 blocks (4321 atoms, M 400, 30 pairs) 1545 / 1713; 1088 blocks
+// (M 1000) 3310 / 3651; 2816 blocks (11,222 atoms) 8244 / 8094.
+constexpr int64_t kForceSplit = 1536;
+
 }  // namespace
 
 void force_rows_f64(const void* jac, bool jac_f32, int64_t ldj, int64_t D, const double* X,
@@ -640,67 +569,30 @@ void force_rows_f64(const void* jac, bool jac_f32, int64_t ldj, int64_t D, const
                     int64_t n_atoms, int64_t n_pairs, int64_t row0, double* K, int64_t ldk,
                     hipStream_t st) {
   if (n_atoms <= 0 || M <= 0) return;
-  if (D <= 16 * kLdsMaxKb && D % 4 == 0 && ldS % 4 == 0 && ldS >= 4 && n_pairs > 0) {
+  if (D <= 16 * kLdsMaxKb) {  // (S rows are padded to a multiple of four)
     const int nkb = (int)(((D + 15) / 16 + 1) / 2 * 2);  // even number of 16-k blocks
-    const int64_t n_ct = (M + 16 * kLdsNC - 1) / (16 * kLdsNC);
-    const int64_t n_tgb = (n_atoms + 63) / 64;
-    const unsigned blocks = xcd_group_tile_blocks(n_tgb, n_ct);
-    const size_t lds = (size_t)nkb * kLdsNC * 64 * 4 * sizeof(double);
-    const int lds_max = 16 * kLdsNC * 64 * 4 * 8;
-    dim3 grid(blocks);
-    if (jac_f32) {
-      static bool attr = false;
-      if (!attr) {
-        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_force_rows_lds12f<float>),
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, lds_max);
-        attr = true;
-      }
-      hipLaunchKernelGGL(k_force_rows_lds12f<float>, grid, dim3(64 * kW12), lds, st,
-                         reinterpret_cast<const float*>(jac), ldj, D, X, ldx, M, S, ldS, tgt_ptr,
-                         tgt_pair, pair_src, order, n_atoms, n_pairs, row0, K, ldk, n_ct, n_tgb,
-                         nkb);
-    } else {
-      static bool attr = false;
-      if (!attr) {
-        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_force_rows_lds12f<double>),
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, lds_max);
-        attr = true;
-      }
-      hipLaunchKernelGGL(k_force_rows_lds12f<double>, grid, dim3(64 * kW12), lds, st,
-                         reinterpret_cast<const double*>(jac), ldj, D, X, ldx, M, S, ldS, tgt_ptr,
-                         tgt_pair, pair_src, order, n_atoms, n_pairs, row0, K, ldk, n_ct, n_tgb,
-                         nkb);
-    }
-    return;
-  }
-  if (D <= 16 * kLdsMaxKb) {
-    const int nkb = (int)(((D + 15) / 16 + 1) / 2 * 2);  // even number of 16-k blocks
-    const int64_t n_ct = (M + 16 * kLdsNC - 1) / (16 * kLdsNC);
-    const int64_t n_tgb = (n_atoms + 63) / 64;
-    const unsigned blocks = xcd_group_tile_blocks(n_tgb, n_ct);
-    const size_t lds = (size_t)nkb * kLdsNC * 64 * 4 * sizeof(double);
-    dim3 grid(blocks);
-    if (jac_f32) {
-      static bool attr_f = false;
-      if (!attr_f) {
-        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_force_rows_lds12<float>),
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, 16 * kLdsNC * 64 * 4 * 8);
-        attr_f = true;
-      }
-      hipLaunchKernelGGL(k_force_rows_lds12<float>, grid, dim3(64 * kW12), lds, st,
-                         reinterpret_cast<const float*>(jac), ldj, D, X, ldx, M, S, ldS, tgt_ptr,
-                         tgt_pair, pair_src, order, n_atoms, row0, K, ldk, n_ct, n_tgb, nkb);
-    } else {
-      static bool attr_d = false;
-      if (!attr_d) {
-        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_force_rows_lds12<double>),
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, 16 * kLdsNC * 64 * 4 * 8);
-        attr_d = true;
-      }
-      hipLaunchKernelGGL(k_force_rows_lds12<double>, grid, dim3(64 * kW12), lds, st,
-                         reinterpret_cast<const double*>(jac), ldj, D, X, ldx, M, S, ldS, tgt_ptr,
-                         tgt_pair, pair_src, order, n_atoms, row0, K, ldk, n_ct, n_tgb, nkb);
-    }
+    const int64_t n_ct = cdiv(M, 16 * kLdsNC);
+    const bool split = (int64_t)cdiv(n_atoms, 64) * n_ct < kForceSplit;
+    const int64_t n_tgb = cdiv(n_atoms, split ? 16 : 64);
+    // (the split form also keeps nine waves' sums there)
+    const size_t tile = (size_t)kLdsNC * 64 * 4 * sizeof(double);
+    const size_t lds = std::max((size_t)nkb * tile, split ? 9 * tile : 0);
+    auto go = [&](auto kern, auto j) {
+      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)(kLdsMaxKb * tile));
+      hipLaunchKernelGGL(kern, dim3(xcd_group_tile_blocks(n_tgb, n_ct)), dim3(768), lds, st, j,
+                         ldj, D, X, ldx, M, S, ldS, tgt_ptr, tgt_pair, pair_src, order, n_atoms,
+                         n_pairs, row0, K, ldk, n_ct, n_tgb, nkb);
+    };
+    auto pick = [&](auto j) {
+      using T = std::remove_const_t<std::remove_pointer_t<decltype(j)>>;
+      if (D % 4)
+        split ? go(k_force_rows_lds<T, true, 1>, j) : go(k_force_rows_lds<T, true, 4>, j);
+      else
+        split ? go(k_force_rows_lds<T, false, 1>, j) : go(k_force_rows_lds<T, false, 4>, j);
+    };
+    jac_f32 ? pick(static_cast<const float*>(jac)) : pick(static_cast<const double*>(jac));
     return;
   }
   const int64_t n_ct = (M + 4 * 16 * kFNC - 1) / (4 * 16 * kFNC);

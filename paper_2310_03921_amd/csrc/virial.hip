@@ -19,6 +19,8 @@
 // step covers a D that is not a multiple of 16), and accumulates the nine
 // weighted sums in registers.  One cross-lane and cross-wave reduction in a
 // fixed order ends the block, so results do not depend on scheduling.
+#include <type_traits>
+
 #include "launch.h"
 #include "mma_f64.h"
 
@@ -163,36 +165,37 @@ GAP_DEV void ldj4(const float* p, double out[4]) {
   out[0] = v[0]; out[1] = v[1]; out[2] = v[2]; out[3] = v[3];
 }
 
-// The same rows for D % 4 == 0 and D <= 256 with the block's 64 columns of X
-// resident in LDS for its lifetime, stored in the matrix core's operand order
-// (as in the force-row kernel): twelve waves, wave w taking Jacobian component
-// beta = w % 3 of pair stream w / 3, so three waves share a SIMD.  Every load
-// in the pair loop reads a valid address (pairs past the configuration read
-// its last pair, k blocks past D the row's last four elements against zero
-// rows of X) and invalid data are cancelled by zero weights; the next k
-// block's (or the next chunk's first) Jacobian fragment is loaded before the
-// current block's matrix work.
-constexpr int kVW = 12;
-constexpr int kVNC = 4;      // 16-column tiles per block
+// The same rows for D <= 256 with the block's 64 columns of X resident in LDS for
+// its lifetime, stored in the matrix core's operand order (as in the force-row
+// kernel): twelve waves, wave w taking Jacobian component beta = w % 3 of pair
+// stream w / 3, so three waves share a SIMD.  Every load in the pair loop reads
+// a valid address (pairs past the configuration read its last pair, k blocks
+// past D the row's last four elements against zero rows of X) and invalid data
+// are cancelled by zero weights, or for D % 4 != 0 (RAGGED), where the row's
+// padding may hold anything, replaced by zero; the next k block's (or the next
+// chunk's first) Jacobian fragment is loaded before the current block's matrix
+// work.
+constexpr int kVNC = 4;  // 16-column tiles per block
+constexpr int kVNG = 4;  // pair streams
 constexpr int kVMaxKb = 16;  // D <= 256
-template <typename TJ>
-__global__ __launch_bounds__(64 * kVW) void k_virial_rows_lds(
+template <typename TJ, bool RAGGED>
+__global__ __launch_bounds__(192 * kVNG) void k_virial_rows_lds(
     const TJ* __restrict__ jac, int64_t ldj, int64_t D, const double* __restrict__ X,
     int64_t ldx, int64_t M, const double* __restrict__ S, int64_t ldS,
     const int64_t* __restrict__ cfg_ptr, const int64_t* __restrict__ pair_ptr,
     const int32_t* __restrict__ pair_src, const double* __restrict__ pair_r, int64_t n_atoms,
     int64_t n_pairs, double* __restrict__ K, int64_t ldk, int64_t n_ct, int64_t n_cfg, int nkb) {
   extern __shared__ double xs[];  // [nkb][kVNC][2 halves][64 lanes][2]
-  __shared__ double red[4][9][64];
+  __shared__ double red[kVNG][9][16 * kVNC];
   int64_t c, ct;
   if (!xcd_group_tile(n_cfg, n_ct, c, ct)) return;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane >> 4, idx = lane & 15;
   const int beta = wave % 3, stream = wave / 3;
   const int64_t colbase = ct * (16 * kVNC);
-  for (int e = threadIdx.x; e < nkb * kVNC * 64; e += 64 * kVW) {
+  for (int e = threadIdx.x; e < nkb * kVNC * 64; e += 192 * kVNG) {
     const int kb = e / (kVNC * 64), rem = e % (kVNC * 64);
     const int u = rem / 64, ln = rem % 64;
-    const int64_t col = colbase + 4 * (ln & 15) + u;  // lane idx of tile u: column 4 idx + u
+    const int64_t col = colbase + kVNC * (ln & 15) + u;  // lane idx of tile u: column kVNC idx + u
     double v[4];
     if (col < M)
       load4(X + col * ldx, (int64_t)kb * 16 + 4 * (ln >> 4), D, v);
@@ -209,11 +212,15 @@ __global__ __launch_bounds__(64 * kVW) void k_virial_rows_lds(
   const int64_t a1 = min(max(cfg_ptr[c + 1], a0), n_atoms);
   const int64_t p_lo = min(max(pair_ptr[a0], (int64_t)0), n_pairs);
   const int64_t p_hi = min(max(pair_ptr[a1], p_lo), n_pairs);
-  const int64_t kmax4 = D - 4;
+  const int64_t kmax4 = RAGGED ? (D + 3) / 4 * 4 - 4 : D - 4;
+  auto cut = [&](int kb, double a[4]) {  // the k block's entries past D
+#pragma unroll
+    for (int q = 0; q < 4; ++q) a[q] = kb * 16 + 4 * g + q < D ? a[q] : 0.0;
+  };
   double cm[kVNC];
 #pragma unroll
-  for (int u = 0; u < kVNC; ++u) cm[u] = colbase + 4 * idx + u < M ? 1.0 : 0.0;
-  const int64_t scol = min(colbase + 4 * idx, ldS - 4);
+  for (int u = 0; u < kVNC; ++u) cm[u] = colbase + kVNC * idx + u < M ? 1.0 : 0.0;
+  const int64_t scol = min(colbase + kVNC * idx, ldS - kVNC);
   double acc[3][kVNC];
 #pragma unroll
   for (int al = 0; al < 3; ++al)
@@ -233,14 +240,15 @@ __global__ __launch_bounds__(64 * kVW) void k_virial_rows_lds(
     const TJ* jr = row_of(p0);
     double fa[4], fb[4];
     ldj4(jr + min((int64_t)4 * g, kmax4), fa);
-    for (; p0 < p_hi; p0 += 64) {
-      const int64_t pn = p0 + 64;
+    for (; p0 < p_hi; p0 += 16 * kVNG) {
+      const int64_t pn = p0 + 16 * kVNG;
       const TJ* jn = row_of(pn < p_hi ? pn : p0);
       d4v G[kVNC];
 #pragma unroll
       for (int u = 0; u < kVNC; ++u) G[u] = zero4();
       for (int kb = 0; kb < nkb; kb += 2) {  // nkb is even
         ldj4(jr + min((int64_t)(kb + 1) * 16 + 4 * g, kmax4), fb);
+        if (RAGGED) cut(kb, fa);
         {
           d4v b[kVNC];
 #pragma unroll
@@ -253,6 +261,7 @@ __global__ __launch_bounds__(64 * kVW) void k_virial_rows_lds(
         const bool more = kb + 2 < nkb;
         const TJ* jp = more ? jr + (int64_t)(kb + 2) * 16 : jn;
         ldj4(jp + min((int64_t)4 * g, kmax4 - (more ? (int64_t)(kb + 2) * 16 : 0)), fa);
+        if (RAGGED) cut(kb + 1, fb);
         {
           d4v b[kVNC];
 #pragma unroll
@@ -296,16 +305,17 @@ __global__ __launch_bounds__(64 * kVW) void k_virial_rows_lds(
 #pragma unroll
     for (int al = 0; al < 3; ++al)
 #pragma unroll
-      for (int u = 0; u < kVNC; ++u) red[stream][3 * al + beta][4 * idx + u] = acc[al][u];
+      for (int u = 0; u < kVNC; ++u) red[stream][3 * al + beta][kVNC * idx + u] = acc[al][u];
   }
   __syncthreads();
-  if (threadIdx.x < 64) {
+  if (threadIdx.x < 16 * kVNC) {
     const int64_t col = colbase + threadIdx.x;
     if (col < M) {
 #pragma unroll
       for (int q = 0; q < 9; ++q) {
-        const double t = red[0][q][threadIdx.x] + red[1][q][threadIdx.x] +
-                         red[2][q][threadIdx.x] + red[3][q][threadIdx.x];
+        double t = red[0][q][threadIdx.x];
+#pragma unroll
+        for (int w = 1; w < kVNG; ++w) t += red[w][q][threadIdx.x];
         K[(9 * c + q) + col * ldk] = -t;
       }
     }
@@ -325,26 +335,22 @@ void virial_rows_f64(const void* jac, bool jac_f32, int64_t ldj, int64_t D, cons
   // dealt to the XCDs in turn
   const int64_t n_ct = (M + 63) / 64;
   dim3 grid(xcd_group_tile_blocks(n_cfg, n_ct));
-  if (D % 4 == 0 && D >= 4 && D <= 16 * kVMaxKb && ldS % 4 == 0 && ldS >= 4) {
+  if (D <= 16 * kVMaxKb) {  // (S rows are padded to a multiple of four)
     const int nkb = 2 * (int)((D + 31) / 32);  // even, 16-deep blocks
-    const size_t lds = (size_t)nkb * kVNC * 64 * 4 * sizeof(double);
-    static bool attr = false;
-    if (!attr) {
-      const int mx = (int)((size_t)kVMaxKb * kVNC * 64 * 4 * sizeof(double));
-      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_virial_rows_lds<float>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, mx);
-      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_virial_rows_lds<double>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, mx);
-      attr = true;
-    }
-    if (jac_f32)
-      hipLaunchKernelGGL(k_virial_rows_lds<float>, grid, dim3(64 * kVW), lds, st,
-                         reinterpret_cast<const float*>(jac), ldj, D, X, ldx, M, S, ldS, cfg_ptr,
-                         pair_ptr, pair_src, pair_r, n_atoms, n_pairs, K, ldk, n_ct, n_cfg, nkb);
-    else
-      hipLaunchKernelGGL(k_virial_rows_lds<double>, grid, dim3(64 * kVW), lds, st,
-                         reinterpret_cast<const double*>(jac), ldj, D, X, ldx, M, S, ldS, cfg_ptr,
-                         pair_ptr, pair_src, pair_r, n_atoms, n_pairs, K, ldk, n_ct, n_cfg, nkb);
+    const size_t tile = (size_t)kVNC * 64 * 4 * sizeof(double);
+    auto go = [&](auto kern, auto j) {
+      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)(kVMaxKb * tile));
+      hipLaunchKernelGGL(kern, grid, dim3(192 * kVNG), nkb * tile, st,
+                         j, ldj, D, X, ldx, M, S, ldS, cfg_ptr, pair_ptr, pair_src, pair_r,
+                         n_atoms, n_pairs, K, ldk, n_ct, n_cfg, nkb);
+    };
+    auto pick = [&](auto j) {
+      using T = std::remove_const_t<std::remove_pointer_t<decltype(j)>>;
+      D % 4 ? go(k_virial_rows_lds<T, true>, j) : go(k_virial_rows_lds<T, false>, j);
+    };
+    jac_f32 ? pick(static_cast<const float*>(jac)) : pick(static_cast<const double*>(jac));
     return;
   }
   if (jac_f32)

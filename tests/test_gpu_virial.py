@@ -78,3 +78,28 @@ def test_fit_with_virial_rows(gapx, gap):
     c, _ = gap.fit(A, n, gap.build_kmm(sp), torch.tensor(y, device="cuda"),
                    torch.tensor(sig, device="cuda"), w.jitter, sp)
     close(c.cpu().numpy(), c_ref, TOL, "c")
+
+
+@pytest.mark.parametrize("D", [1, 33, 150, 255, 256])
+def test_rows_at_descriptor_edges(gapx, gap, D):
+    """Virial and force rows of the LDS-resident kernels at descriptor lengths off
+    their 4-, 16- and 32-entry steps, with row padding that is never read, and a
+    target of a degree far above the others."""
+    w = synth.Workload("edge", 77, n_cfg=5, atoms_lo=1, atoms_hi=40, D=D, nb=6, M=70)
+    b = synth.generate(w)
+    X = synth.sparse_points(w, b)
+    pair_j = b.pair_j.copy()
+    first = b.pair_ptr[b.cfg_ptr[3]], b.pair_ptr[b.cfg_ptr[4]]
+    pair_j[first[0]:first[1]:2] = b.cfg_ptr[3]
+    r = synth.pair_vectors(w, b)
+    atoms = gapx.Atoms.from_host(b.cfg_ptr, b.desc, b.pair_ptr, pair_j, b.jac)
+    sp = gapx.Sparse.from_host(X, w.zeta, w.delta)
+    if D % 4:
+        atoms.jac[:, :, D:] = float("nan")
+    Kv = gap.build_virial_rows(atoms, sp, torch.tensor(r, device="cuda"))
+    ref = oracle.build_virial_rows(b.cfg_ptr, b.desc, b.pair_ptr, b.jac, r, X, w.zeta, w.delta)
+    got = Kv[:, :9 * b.n_cfg].T.cpu().numpy()
+    assert np.abs(got - ref).max() <= 1e-10 * np.abs(ref).max()
+    K = gap.build_knm(atoms, sp)[:w.M, :b.n_rows].T.cpu().numpy()
+    kref = oracle.build_knm(b.cfg_ptr, b.desc, b.pair_ptr, pair_j, b.jac, X, w.zeta, w.delta)
+    assert np.abs(K - kref).max() <= 1e-10 * np.abs(kref).max()
