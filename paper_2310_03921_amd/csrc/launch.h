@@ -271,8 +271,9 @@ struct QrWork {
   double* W;          // nb x (n+1) reduced V^T C
   double* Wt;         // T^T W
   double* T;          // nb x nb
-  double* colstate;   // per column: tau, beta, scale, then tw[nb]
-  double* red;        // panel reduction partials
+  double* Q;          // a panel's orthonormal columns, 64 x (m rounded up to 4)
+  double* pan;        // a panel's small matrices
+  double* red;        // reduction partials and pivot rows of the column-by-column panel
   double* tau;        // tau of every reflector [n]
   unsigned int* counter;
   unsigned int* flags;  // per-block completion flags of the multi-block triangular solves

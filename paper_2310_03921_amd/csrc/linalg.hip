@@ -4,11 +4,10 @@
 // plus the pieces of FP64 iterative refinement (semi-normal equations).
 //
 // Householder QR, right-looking and blocked (compact WY, Q = I - V T V^T):
-//   panel: one launch per column; every launch applies the previous reflector
-//          to the rest of the panel and, in the same pass over the rows,
-//          accumulates the norm and dot products that define the next
-//          reflector; the last block to finish reduces the per-block partial
-//          sums in a fixed order (no atomics on data, deterministic).
+//   panel: 64 columns at once, by Cholesky QR twice and the reconstruction of
+//          the Householder vectors (all products on FP64 MFMA, three small
+//          one-block steps); a column-by-column cooperative kernel takes a
+//          panel whose columns are numerically dependent.
 //   trailing update: W = V^T C (split over row slabs on FP64 MFMA, then a
 //          fixed-order reduction), T from the Gram V^T V and tau, and
 //          C -= V (T^T W) on FP64 MFMA.  b rides along as the last column.
@@ -24,11 +23,11 @@ namespace {
 
 constexpr int kQrNB = 64;      // outer block width (compact-WY trailing update)
 constexpr int kTrsvMaxBlocks = 256;  // multi-block triangular solve: n <= 64 * 256
-constexpr int kPanelW = 32;    // inner panel width (column-by-column factorisation)
 constexpr int kPanelMaxGrid = 256;
-// Workspace counter words: [0] the column kernels' counter, [kPanelBar ..
-// kPanelBar + 8 * 16) the cooperative panel's eight arrival counters.
+// Workspace counter words: [0] the panel's state (1: it needs the column-by-
+// column kernel), [kPanelBar ..) that kernel's eight arrival counters.
 constexpr int kPanelBar = 64;
+constexpr int kPanelBarWords = 8 * 16;
 constexpr int kCounterWords = 256;
 
 inline unsigned cdiv(int64_t a, int64_t b) { return (unsigned)((a + b - 1) / b); }
@@ -170,195 +169,6 @@ __global__ __launch_bounds__(256) void k_chol_update(double* __restrict__ Lw, in
 }
 
 // ------------------------------------------------------------------- QR ----
-// Column state of the current inner panel, per column: tau, beta, scale,
-// tw[kPanelW] where tw[j] = tau * (v^T a_j) for the panel columns j to its right.
-constexpr int kCS = kPanelW + 3;
-
-__global__ __launch_bounds__(256) void k_qr_col(double* __restrict__ A, int64_t ld, int64_t m,
-                                                int64_t j0, int pw, int64_t k,
-                                                double* __restrict__ colstate,
-                                                double* __restrict__ red,
-                                                unsigned int* __restrict__ counter,
-                                                double* __restrict__ tau_all) {
-  __shared__ double s_tw[kPanelW];
-  __shared__ double s_red[4][kPanelW];
-  __shared__ double s_tot[kPanelW];
-  __shared__ int s_last;
-  __shared__ double s_par[2];
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int64_t pend = j0 + pw;
-  const bool has_prev = k > j0;
-  const bool has_next = k < pend;
-  const int64_t prev = k - 1;
-  double beta_p = 0.0, scale_p = 0.0;
-  if (has_prev) {
-    const double* cs = colstate + (prev - j0) * kCS;
-    beta_p = cs[1];
-    scale_p = cs[2];
-    for (int j = threadIdx.x; j < kPanelW; j += 256) s_tw[j] = cs[3 + j];
-  }
-  __syncthreads();
-  const int ncnt = has_next ? (int)(pend - k) : 0;  // sigma, then d_{k+1} .. d_{pend-1}
-  double part[kPanelW];
-#pragma unroll
-  for (int jj = 0; jj < kPanelW; ++jj) part[jj] = 0.0;
-
-  const int64_t r_lo = has_prev ? prev : k;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  // Columns touched this pass: jb .. pend-1 (jb = prev when a reflector is applied).
-  const int64_t jb = has_prev ? prev : k;
-  const int nc = (int)(pend - jb);
-  for (int64_t r = r_lo + blockIdx.x * (int64_t)blockDim.x + threadIdx.x; r < m; r += stride) {
-    // all loads of the row first (independent, issued together), then compute, then store
-    double a[kPanelW + 1];
-    double* rp = A + jb * ld + r;  // column offsets jj * ld are uniform across the wave
-#pragma unroll
-    for (int jj = 0; jj <= kPanelW; ++jj) a[jj] = (jj < nc) ? rp[jj * ld] : 0.0;
-    const bool acc_row = has_next && r > k;
-    int o = 0;  // offset of column k in a[]
-    if (has_prev) {
-      double v;
-      if (r == prev) {
-        v = 1.0;
-        a[0] = beta_p;
-      } else {
-        v = a[0] * scale_p;
-        a[0] = v;
-      }
-#pragma unroll
-      for (int jj = 1; jj <= kPanelW; ++jj)
-        if (jj < nc) a[jj] -= s_tw[jb + jj - j0] * v;
-      o = 1;
-    }
-    if (acc_row) {
-      const double ak = has_prev ? a[1] : a[0];
-      part[0] += ak * ak;
-#pragma unroll
-      for (int jj = 1; jj < kPanelW; ++jj)
-        if (jj < ncnt) part[jj] += ak * (has_prev ? a[jj + 1] : a[jj]);
-    }
-    if (has_prev) {
-      if (r == k) {  // the next pivot row is read by the last block of this launch
-#pragma unroll
-        for (int jj = 0; jj <= kPanelW; ++jj)
-          if (jj < nc) xstore(rp + jj * ld, a[jj]);
-      } else {
-#pragma unroll
-        for (int jj = 0; jj <= kPanelW; ++jj)
-          if (jj < nc) rp[jj * ld] = a[jj];
-      }
-    }
-    (void)o;
-  }
-  if (!has_next) return;
-
-  // block partial sums -> red[v * gridDim.x + block]
-#pragma unroll
-  for (int v = 0; v < kPanelW; ++v) {
-    if (v < ncnt) {
-      const double s = wave_sum(part[v]);
-      if (lane == 0) s_red[wave][v] = s;
-    }
-  }
-  __syncthreads();
-  const int G = gridDim.x;
-  for (int v = threadIdx.x; v < ncnt; v += 256)
-    xstore(red + (int64_t)v * G + blockIdx.x,
-           ((s_red[0][v] + s_red[1][v]) + s_red[2][v]) + s_red[3][v]);
-  wait_mem();
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    const unsigned t =
-        __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    s_last = (t == (unsigned)G - 1u);
-  }
-  __syncthreads();
-  if (!s_last) return;
-  // Fixed-order reduction of the per-block partials: thread t sums blocks
-  // t, t + 256, ... (loads issued together), then a wave and block tree.
-  double tot[kPanelW];
-#pragma unroll
-  for (int v = 0; v < kPanelW; ++v) tot[v] = 0.0;
-  for (int b = threadIdx.x; b < G; b += 256) {
-#pragma unroll
-    for (int v = 0; v < kPanelW; ++v)
-      if (v < ncnt) tot[v] += vload(red + (int64_t)v * G + b);
-  }
-#pragma unroll
-  for (int v = 0; v < kPanelW; ++v) {
-    if (v < ncnt) {
-      const double s = wave_sum(tot[v]);
-      if (lane == 0) s_red[wave][v] = s;
-    }
-  }
-  __syncthreads();
-  for (int v = threadIdx.x; v < ncnt; v += 256)
-    s_tot[v] = ((s_red[0][v] + s_red[1][v]) + s_red[2][v]) + s_red[3][v];
-  __syncthreads();
-  double* cs = colstate + (k - j0) * kCS;
-  if (threadIdx.x == 0) {
-    const double alpha = vload(A + k + k * ld);
-    const double xnorm = sqrt(s_tot[0]);
-    double tau = 0.0, beta = alpha, scale = 0.0;
-    if (xnorm > 0.0) {
-      beta = -copysign(hypot(alpha, xnorm), alpha);
-      tau = (beta - alpha) / beta;
-      scale = 1.0 / (alpha - beta);
-    }
-    cs[0] = tau;
-    cs[1] = beta;
-    cs[2] = scale;
-    tau_all[k] = tau;
-    s_par[0] = tau;
-    s_par[1] = scale;
-    __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
-  __syncthreads();
-  for (int jj = 1 + threadIdx.x; jj < ncnt; jj += 256) {
-    const int64_t j = k + jj;
-    const double w = vload(A + k + j * ld) + s_par[1] * s_tot[jj];
-    cs[3 + (j - j0)] = s_par[0] * w;
-  }
-}
-
-// ------------------------------------------------ register-resident panel ----
-// Householder factorisation of an inner panel of width <= kRRW with the whole
-// panel held in registers across a cooperative grid: thread t of block b owns
-// the panel rows i0 + (b * 512 + t) + q * (grid * 512), q < kRRQ.  Every column
-// step applies the previous reflector to the thread's rows, forms per-block
-// partial sums of the next column's norm and dot products, publishes them, and
-// waits at a grid barrier; every block then reduces all partials in the same
-// fixed order, so all blocks derive identical reflector parameters without a
-// second barrier.  Partials alternate between two buffers so a block that is
-// one step ahead never overwrites values a slower block is still reading.
-static_assert(kPanelMaxGrid <= 256, "the panel reduction reads at most 4 partials per lane");
-constexpr int kRRW = 16;    // panel width
-constexpr int kRRQ = 4;     // rows per thread
-constexpr int kRRT = 512;   // threads per block
-static_assert(kRRW == 16, "the panel's wave reduction is a 16-value butterfly");
-
-GAP_DEV void grid_barrier(unsigned int* arrive, unsigned int target, int* dev_err) {
-  wait_mem();  // this wave's cross-block stores (device-scope atomics) have completed
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    __hip_atomic_fetch_add(arrive, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    uint64_t spins = 0;
-    // Bounded wait: a barrier that does not complete within ~0.2 s sets the
-    // error bit, and every later barrier returns at once once the bit is set,
-    // so a failed co-residency assumption costs one timeout, never a hang.
-    while (__hip_atomic_load(arrive, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT) < target) {
-      if (__hip_atomic_load(dev_err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & GAP_DEVERR_SYNC)
-        break;
-      __builtin_amdgcn_s_sleep(2);
-      if (++spins > (1ull << 22)) {
-        atomicOr(dev_err, GAP_DEVERR_SYNC);
-        break;
-      }
-    }
-  }
-  __syncthreads();
-}
-
 // Grid barrier on eight arrival counters, one per XCD slot of the block index
 // (64 bytes apart), instead of one: the atomic adds of a few hundred blocks on a
 // single address serialise at the memory-side atomic unit.  `round` counts the
@@ -378,8 +188,9 @@ GAP_DEV void grid_barrier_x8(unsigned int* arrive, unsigned int round, int* dev_
     const unsigned x = threadIdx.x & 7;
     const unsigned target = round * (G > x ? (G - x + 7) / 8 : 0u);
     uint64_t spins = 0;
-    // Bounded wait, as in grid_barrier: a timeout sets the error bit, and a
-    // set bit (checked every 64 polls) ends every later wait at once.
+    // Bounded wait: a barrier that does not complete within ~0.2 s sets the
+    // error bit, and a set bit (checked every 64 polls) ends every later wait at
+    // once, so a failed co-residency assumption costs one timeout, never a hang.
     for (;;) {
       const unsigned c =
           __hip_atomic_load(arrive + x * kBarStride, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT);
@@ -398,143 +209,403 @@ GAP_DEV void grid_barrier_x8(unsigned int* arrive, unsigned int round, int* dev_
   __syncthreads();
 }
 
-__global__ __launch_bounds__(kRRT) void k_qr_panel_rr(double* __restrict__ A, int64_t ld,
-                                                      int64_t m, int64_t i0, int pw,
-                                                      double* __restrict__ red,
-                                                      double* __restrict__ piv,
-                                                      unsigned int* __restrict__ arrive,
-                                                      double* __restrict__ tau_all,
-                                                      int* __restrict__ dev_err) {
-  __shared__ double s_wred[kRRT / 64][kRRW];
-  __shared__ double s_tot[kRRW];
-  __shared__ double s_tw[kRRW];
-  __shared__ double s_par[3];  // tau, beta, scale of the reflector just formed
-  __shared__ double s_pv[kRRW];  // the pivot row of the current column
-  const int G = gridDim.x;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int64_t stride = (int64_t)G * kRRT;
-  int64_t lrow[kRRQ];  // local row index (row - i0), or -1
-  double a[kRRQ][kRRW];
+// ------------------------------------------------------ 64-column panels ----
+// P (rows j0 .. m - 1 of bw <= 64 columns) = Q R by Cholesky QR, twice, and the
+// Householder vectors of that factorisation from Q (Ballard et al., Euro-Par /
+// IPDPS 2014, "Reconstructing Householder vectors from Tall-Skinny QR"):
+//   G1 = P^T P = R1^T R1, Q <- P R1^-1;  G2 = Q^T Q = R2^T R2, Q^ = Q R2^-1;
+//   Q^ - [S; 0] = V U with V unit lower trapezoidal, U upper triangular and the
+//   signs S_jj = -sign of the pivot's diagonal (LU without pivoting of the top
+//   64 rows, |U_jj| >= 1), so that P = H [S R2 R1; 0], H = I - V T V^T,
+//   tau_j = -U_jj S_jj.
+// The first pass leaves |Q^T Q - I| about cond(P)^2 u (columns scaled); while
+// its entries are below 1/64 the second makes Q^ orthonormal to rounding, and the factors
+// are as accurate as those of the column-by-column reduction (residual, Gram
+// matrix and solutions agree with LAPACK's to rounding for condition numbers up
+// to 1e12 over all columns).  A panel that fails the test (its columns dependent
+// to about 1e-8, a zero column, an overflow) is left as it is and factored by
+// k_qr_panel_col.  One grid barrier and one reduction over blocks per column, as
+// in the register-resident reduction this replaces, cost 6.8 us a column at
+// 26,000 rows and 9.7 us at 353,000 (0.43 and 0.62 ms per 64 columns, and 0.13
+// and 0.34 ms more for the updates between its 16-column steps); this takes
+// 0.15 and 0.36 ms, at the small end the latency of its one-block steps
+// (k_panel_vectors 60 us, k_panel_chol 18 us), at the large end the passes over
+// the panel.
+constexpr int kGramTiles = 10;                // lower 16 x 16 tiles of a 64 x 64 Gram
+constexpr int kGram = kGramTiles * 256;       // their values
+constexpr int kGramMaxBlocks = 256;
+// What the panel kernels keep between launches (doubles).
+constexpr int kPanU1 = 0;                     // R1, row-major upper, 64 x 64
+constexpr int kPanRinv1 = kPanU1 + 4096;      // 1 / its diagonal
+constexpr int kPanZ = kPanRinv1 + 64;         // U R2, row-major upper
+constexpr int kPanRinvZ = kPanZ + 4096;
+constexpr int kPanG = kPanRinvZ + 64;         // reduced Gram
+constexpr int kPanDoubles = kPanG + kGram;
+
+// Gram partials of up to 64 columns (col-major, rows 16-byte groups aligned):
+// wave w of the grid takes the 16-row chunks w, w + waves, ...; a lane holds
+// four consecutive rows of its column of each 16-column tile, which serve as
+// both operands; the block's four waves add up in LDS.
+__global__ __launch_bounds__(256) void k_panel_gram(const double* __restrict__ P, int64_t ld,
+                                                    int64_t rows, int bw,
+                                                    double* __restrict__ part) {
+  __shared__ double red[3][kGram];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane >> 4, idx = lane & 15;
+  const double* col[4];
 #pragma unroll
-  for (int q = 0; q < kRRQ; ++q) {
-    const int64_t lr = (int64_t)blockIdx.x * kRRT + threadIdx.x + q * stride;
-    lrow[q] = (i0 + lr < m) ? lr : -1;
+  for (int u = 0; u < 4; ++u) col[u] = P + (int64_t)min(16 * u + idx, bw - 1) * ld + 4 * g;
+  d4v acc[kGramTiles];
 #pragma unroll
-    for (int j = 0; j < kRRW; ++j)
-      a[q][j] = (lrow[q] >= 0 && j < pw) ? A[(i0 + lr) + (i0 + j) * ld] : 0.0;
+  for (int t = 0; t < kGramTiles; ++t) acc[t] = zero4();
+  const int64_t nch = (rows + 15) / 16, full = rows / 16, nw = (int64_t)gridDim.x * 4;
+  auto products = [&](const d4v (&a)[4]) {
+    int t = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j <= i; ++j, ++t)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) acc[t] = mfma_f64(a[i][q], a[j][q], acc[t]);
+  };
+  int64_t c = (int64_t)blockIdx.x * 4 + wave;
+  d4v cur[4], nxt[4];
+  if (c < full) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) cur[u] = *reinterpret_cast<const d4v*>(col[u] + 16 * c);
+    for (; c < full; c += nw) {
+      const int64_t cn = c + nw < full ? c + nw : c;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) nxt[u] = *reinterpret_cast<const d4v*>(col[u] + 16 * cn);
+      __builtin_amdgcn_sched_barrier(0);
+      products(cur);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) cur[u] = nxt[u];
+    }
   }
-  double beta_p = 0.0, scale_p = 0.0;
-  for (int k = 0; k <= pw; ++k) {
-    // 1. apply reflector k-1 to rows >= k-1.  Register arrays are indexed by
-    //    absolute column only (selects against k), never by a k-relative
-    //    index, which would force them out of registers.  tw[j] is zero for
-    //    j <= k-1, and v is zero on rows above the reflector, so the update
-    //    needs no condition.
-    if (k > 0) {
-      double tw[kRRW];
+  if (c < nch) {  // the last, partial chunk
+    const int64_t left = rows - 16 * c - 4 * g;
 #pragma unroll
-      for (int j = 0; j < kRRW; ++j) tw[j] = s_tw[j];
+    for (int u = 0; u < 4; ++u)
 #pragma unroll
-      for (int q = 0; q < kRRQ; ++q) {
-        const bool at = lrow[q] == k - 1, below = lrow[q] > k - 1;
-        double ak1 = 0.0;
+      for (int q = 0; q < 4; ++q) cur[u][q] = q < left ? col[u][16 * c + q] : 0.0;
+    products(cur);
+  }
+  if (wave > 0) {
 #pragma unroll
-        for (int j = 0; j < kRRW; ++j) ak1 = (j == k - 1) ? a[q][j] : ak1;
-        const double v = at ? 1.0 : (below ? ak1 * scale_p : 0.0);
-        const double nk1 = at ? beta_p : (below ? v : ak1);
+    for (int t = 0; t < kGramTiles; ++t)
 #pragma unroll
-        for (int j = 0; j < kRRW; ++j) {
-          a[q][j] = (j == k - 1) ? nk1 : a[q][j];
-          a[q][j] -= tw[j] * v;
+      for (int q = 0; q < 4; ++q) red[wave - 1][t * 256 + q * 64 + lane] = acc[t][q];
+  }
+  __syncthreads();
+  if (wave == 0) {
+#pragma unroll
+    for (int t = 0; t < kGramTiles; ++t)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int e = t * 256 + q * 64 + lane;
+        part[(int64_t)blockIdx.x * kGram + e] =
+            ((acc[t][q] + red[0][e]) + red[1][e]) + red[2][e];
+      }
+  }
+}
+
+// The reduced Gram (layout of k_panel_gram) into the lower triangle of S, with
+// unit columns from bw on.
+GAP_DEV void gram_to_lds(const double* __restrict__ G, int bw, double (*S)[kTriS]) {
+  for (int e = threadIdx.x; e < kGram; e += 256) {
+    const int t = e >> 8, q = (e >> 6) & 3, lane = e & 63;
+    const int i = t < 1 ? 0 : t < 3 ? 1 : t < 6 ? 2 : 3, j = t - i * (i + 1) / 2;
+    const int r = 16 * i + (lane >> 4) + 4 * q, c = 16 * j + (lane & 15);
+    if (r >= c) S[r][c] = r < bw ? G[e] : (r == c ? 1.0 : 0.0);
+  }
+}
+
+// R1 of the first Gram; clears the panel's state word and the barrier counters
+// of k_qr_panel_col.
+__global__ __launch_bounds__(256) void k_panel_chol(int bw, double* __restrict__ pan,
+                                                    unsigned int* __restrict__ state,
+                                                    unsigned int* __restrict__ arrive) {
+  __shared__ double S[kTri][kTriS];
+  gram_to_lds(pan + kPanG, bw, S);
+  __syncthreads();
+  const bool bad = chol64_lds(S);
+  if (threadIdx.x == 0) *state = bad ? 1u : 0u;
+  if (threadIdx.x < kPanelBarWords) arrive[threadIdx.x] = 0u;
+  for (int e = threadIdx.x; e < kTri * kTri; e += 256) {
+    const int c = e >> 6, q = e & 63;  // U1[c][q] = L[q][c]
+    pan[kPanU1 + e] = q >= c ? S[q][c] : 0.0;
+  }
+  if (threadIdx.x < kTri) pan[kPanRinv1 + threadIdx.x] = 1.0 / S[threadIdx.x][threadIdx.x];
+}
+
+// Rows x of src (col-major) <- x U^-1 into dst, a row per lane; U and its
+// reciprocal diagonal from global memory into LDS.
+__global__ __launch_bounds__(256) void k_panel_solve(const double* __restrict__ src, int64_t lds,
+                                                     double* __restrict__ dst, int64_t ldd,
+                                                     int64_t rows, int bw,
+                                                     const double* __restrict__ u_g,
+                                                     const double* __restrict__ rinv_g,
+                                                     const unsigned int* __restrict__ state) {
+  __shared__ __attribute__((aligned(16))) double u[kTri * kTri];
+  __shared__ double rinv[kTri];
+  if (*state) return;
+  const uint32_t r = (uint32_t)min((int64_t)blockIdx.x * 256 + threadIdx.x, rows - 1);
+  double x[kTri];
+#pragma unroll
+  for (int c = 0; c < kTri; ++c) x[c] = (src + (int64_t)min(c, bw - 1) * lds)[r];
+  for (int e = threadIdx.x; e < kTri * kTri / 2; e += 256)
+    reinterpret_cast<d2v*>(u)[e] = reinterpret_cast<const d2v*>(u_g)[e];
+  if (threadIdx.x < kTri) rinv[threadIdx.x] = rinv_g[threadIdx.x];
+  __syncthreads();
+#pragma unroll
+  for (int c = 0; c < kTri; ++c) x[c] = c < bw ? x[c] : 0.0;
+  row_solve64(x, u, rinv);
+  // lanes past the last row hold that row too and store the same values
+#pragma unroll
+  for (int c = 0; c < kTri; ++c)
+    if (c < bw) (dst + c * ldd)[r] = x[c];
+}
+
+// LU without pivoting of B - diag(sg) for B (64 x 64, in LDS), sg_j = -sign of
+// the pivot: U in and above the diagonal, unit L below.  256 threads, four steps
+// of 16 columns: one wave factors them with a row per lane, then solves the
+// rows to their right with a column per lane; the four waves update the rest.
+GAP_DEV void lu64_signs(double (*B)[kTriS], double* sg) {
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int g = lane >> 4, idx = lane & 15;
+  for (int s = 0; s < 4; ++s) {
+    const int c0 = 16 * s;
+    if (wave == 0) {
+      double v[16];
+#pragma unroll
+      for (int c = 0; c < 16; ++c) v[c] = B[lane][c0 + c];
+#pragma unroll
+      for (int c = 0; c < 16; ++c) {
+        const double p = readlane_f64(v[c], c0 + c);
+        const double sign = p >= 0.0 ? -1.0 : 1.0;
+        const double piv = p - sign;
+        const double l = v[c] * rcp_f64(piv);
+        v[c] = lane == c0 + c ? piv : (lane > c0 + c ? l : v[c]);
+        const double lv = lane > c0 + c ? l : 0.0;
+#pragma unroll
+        for (int q = c + 1; q < 16; ++q) v[q] -= lv * readlane_f64(v[q], c0 + c);
+        if (lane == 0) sg[c0 + c] = sign;
+      }
+      if (lane >= c0) {
+#pragma unroll
+        for (int c = 0; c < 16; ++c) B[lane][c0 + c] = v[c];
+      }
+    }
+    __syncthreads();
+    if (wave == 0 && s < 3) {  // U12 = L11^-1 B12, a column per lane
+      const int col = min(c0 + 16 + lane, kTri - 1);
+      double y[16];
+#pragma unroll
+      for (int i = 0; i < 16; ++i) y[i] = B[c0 + i][col];
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+#pragma unroll
+        for (int k = i + 1; k < 16; ++k) y[k] -= B[c0 + k][c0 + i] * y[i];
+      if (c0 + 16 + lane < kTri) {
+#pragma unroll
+        for (int i = 1; i < 16; ++i) B[c0 + i][col] = y[i];
+      }
+    }
+    __syncthreads();
+    int t = 0;
+    for (int ti = s + 1; ti < 4; ++ti)
+      for (int tj = s + 1; tj < 4; ++tj, ++t) {
+        if ((t & 3) != wave) continue;
+        d4v acc;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[r] = B[16 * ti + g + 4 * r][16 * tj + idx];
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          acc = mfma_f64(-B[16 * ti + idx][c0 + 4 * g + q], B[c0 + 4 * g + q][16 * tj + idx], acc);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) B[16 * ti + g + 4 * r][16 * tj + idx] = acc[r];
+      }
+    __syncthreads();
+  }
+}
+
+// Upper triangle of the product of two upper triangles given by element
+// functions a(i, k) (i <= k) and b(k, j) (k <= j), handed to put(i, j, value)
+// for every i <= j; 256 threads.
+template <class FA, class FB, class FP>
+GAP_DEV void upper_product64(FA a, FB b, FP put) {
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int g = lane >> 4, idx = lane & 15;
+  int t = 0;
+  for (int ti = 0; ti < 4; ++ti)
+    for (int tj = ti; tj < 4; ++tj, ++t) {
+      if ((t & 3) != wave) continue;
+      d4v acc = zero4();
+      for (int tk = ti; tk <= tj; ++tk)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int i = 16 * ti + idx, k = 16 * tk + 4 * g + q, j = 16 * tj + idx;
+          acc = mfma_f64(i <= k ? a(i, k) : 0.0, k <= j ? b(k, j) : 0.0, acc);
+        }
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int i = 16 * ti + g + 4 * r, j = 16 * tj + idx;
+        if (i <= j) put(i, j, acc[r]);
+      }
+    }
+}
+
+// The one-block middle of the panel: R2 from the second Gram, the test that Q
+// was near enough to orthonormal, the signs and L, U of Q^'s top rows, and from
+// them R and V's top in A, tau, and Z = U R2 (V's other rows are q Z^-1).
+__global__ __launch_bounds__(256) void k_panel_vectors(double* __restrict__ A, int64_t ld,
+                                                       int64_t rows, int bw,
+                                                       const double* __restrict__ Q, int64_t ldq,
+                                                       double* __restrict__ pan,
+                                                       double* __restrict__ tau,
+                                                       unsigned int* __restrict__ state) {
+  __shared__ double S[kTri][kTriS], B[kTri][kTriS];
+  __shared__ __attribute__((aligned(16))) double u[kTri * kTri];
+  __shared__ double rinv[kTri], sg[kTri];
+  __shared__ int s_bad;
+  if (*state) return;  // uniform: a whole-grid condition
+  if (threadIdx.x == 0) s_bad = 0;
+  gram_to_lds(pan + kPanG, bw, S);
+  __syncthreads();
+  bool far = false;
+  for (int e = threadIdx.x; e < kTri * kTri; e += 256) {
+    const int r = e & 63, c = e >> 6;
+    if (r >= c) far |= !(fabs(S[r][c] - (r == c ? 1.0 : 0.0)) < 1.0 / 64);
+  }
+  if (far) s_bad = 1;
+  __syncthreads();
+  if (s_bad) {
+    if (threadIdx.x == 0) *state = 1u;
+    return;
+  }
+  (void)chol64_lds(S);  // diagonally dominant: no bad pivot
+  for (int e = threadIdx.x; e < kTri * kTri; e += 256) {
+    const int c = e >> 6, q = e & 63;
+    u[e] = q >= c ? S[q][c] : 0.0;  // R2
+  }
+  if (threadIdx.x < kTri) rinv[threadIdx.x] = 1.0 / S[threadIdx.x][threadIdx.x];
+  __syncthreads();
+  if (threadIdx.x < 64) {  // Q^'s top rows, one per lane
+    const int l = threadIdx.x;
+    double x[kTri];
+#pragma unroll
+    for (int c = 0; c < kTri; ++c)
+      x[c] = Q[(int64_t)min(c, bw - 1) * ldq + min((int64_t)l, rows - 1)];
+#pragma unroll
+    for (int c = 0; c < kTri; ++c) x[c] = c < bw && l < rows ? x[c] : 0.0;
+    row_solve64(x, u, rinv);
+#pragma unroll
+    for (int c = 0; c < kTri; ++c) B[l][c] = x[c];
+  }
+  __syncthreads();
+  lu64_signs(B, sg);
+  // V's top rows (unit lower) and R = S R2 R1
+  for (int e = threadIdx.x; e < kTri * kTri; e += 256) {
+    const int r = e & 63, c = e >> 6;
+    if (r > c && r < rows && c < bw) A[r + c * ld] = B[r][c];
+  }
+  if (threadIdx.x < bw) tau[threadIdx.x] = -B[threadIdx.x][threadIdx.x] * sg[threadIdx.x];
+  const double* u1 = pan + kPanU1;
+  upper_product64([&](int i, int k) { return u[i * kTri + k]; },
+                  [&](int k, int j) { return u1[k * kTri + j]; },
+                  [&](int i, int j, double v) {
+                    if (j < bw) A[i + j * ld] = sg[i] * v;
+                  });
+  upper_product64([&](int i, int k) { return B[i][k]; },
+                  [&](int k, int j) { return u[k * kTri + j]; },
+                  [&](int i, int j, double v) { pan[kPanZ + i * kTri + j] = v; });
+  if (threadIdx.x < kTri)
+    pan[kPanRinvZ + threadIdx.x] =
+        1.0 / (B[threadIdx.x][threadIdx.x] * u[threadIdx.x * (kTri + 1)]);
+}
+
+// Householder factorisation of a panel column by column in memory, for the
+// panels whose state word is set (the launch ends at once otherwise): a
+// cooperative grid, one pass over the rows per column that applies the previous
+// reflector and accumulates the norm and dot products of the next, one grid
+// barrier per column.  Rows belong to threads for the whole kernel.  It also
+// runs as a single ordinary block.
+constexpr int kColT = 256;
+__global__ __launch_bounds__(kColT) void k_qr_panel_col(double* __restrict__ A, int64_t ld,
+                                                        int64_t rows, int bw,
+                                                        double* __restrict__ red,
+                                                        double* __restrict__ piv,
+                                                        unsigned int* __restrict__ arrive,
+                                                        const unsigned int* __restrict__ state,
+                                                        double* __restrict__ tau_all,
+                                                        int* __restrict__ dev_err) {
+  if (*state == 0u) return;
+  __shared__ double s_wred[kColT / 64][kTri];
+  __shared__ double s_tw[kTri], s_pv[kTri], s_tot[kTri];
+  __shared__ double s_par[3];  // tau, beta, scale of the reflector just formed
+  const int G = gridDim.x, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int64_t stride = (int64_t)G * kColT;
+  for (int k = 0; k <= bw; ++k) {
+    double part[kTri];
+#pragma unroll
+    for (int j = 0; j < kTri; ++j) part[j] = 0.0;
+    for (int64_t r = (int64_t)blockIdx.x * kColT + threadIdx.x; r < rows; r += stride) {
+      if (r < k - 1) continue;
+      double* row = A + r;
+      double a[kTri], v = 0.0, ak = 0.0;
+#pragma unroll
+      for (int j = 0; j < kTri; ++j) a[j] = (j >= k - 1 && j < bw) ? row[j * ld] : 0.0;
+      if (k > 0) {  // reflector k - 1
+#pragma unroll
+        for (int j = 0; j < kTri; ++j)
+          if (j == k - 1) {
+            v = r == k - 1 ? 1.0 : a[j] * s_par[2];
+            row[j * ld] = r == k - 1 ? s_par[1] : v;
+          }
+#pragma unroll
+        for (int j = 0; j < kTri; ++j)
+          if (j >= k && j < bw) {
+            a[j] -= s_tw[j] * v;
+            row[j * ld] = a[j];
+          }
+      }
+      if (k < bw && r >= k) {
+#pragma unroll
+        for (int j = 0; j < kTri; ++j) ak = (j == k) ? a[j] : ak;
+        if (r == k) {
+          double* pv = piv + (k & 1) * kTri;
+#pragma unroll
+          for (int j = 0; j < kTri; ++j) xstore(pv + j, a[j]);
+        } else {
+#pragma unroll
+          for (int j = 0; j < kTri; ++j) part[j] += ak * a[j];
         }
       }
     }
-    if (k == pw) break;
-    // 2. partial sums for column k over rows > k, by absolute column:
-    //    part[k] = sum a_k^2, part[j] = sum a_k a_j (j > k); pivot row published
-    double part[kRRW];
+    if (k == bw) break;
 #pragma unroll
-    for (int j = 0; j < kRRW; ++j) part[j] = 0.0;
-#pragma unroll
-    for (int q = 0; q < kRRQ; ++q) {
-      double ak = 0.0;
-#pragma unroll
-      for (int j = 0; j < kRRW; ++j) ak = (j == k) ? a[q][j] : ak;
-      ak = (lrow[q] > k) ? ak : 0.0;
-      // columns j < k are summed too (no select per register) and never used
-#pragma unroll
-      for (int j = 0; j < kRRW; ++j) part[j] += ak * a[q][j];
-      if (lrow[q] == k) {
-        double* pv = piv + (k & 1) * kRRW;
-#pragma unroll
-        for (int j = 0; j < kRRW; ++j) xstore(pv + j, a[q][j]);
-      }
+    for (int j = 0; j < kTri; ++j) {
+      const double t = wave_sum(part[j]);
+      if (lane == 0) s_wred[wave][j] = t;
     }
-    // wave sums of the 16 partials by a halving butterfly (17 lane exchanges
-    // instead of 16 separate 6-step reductions): lane l ends with the total of
-    // column 8 b5 + 4 b4 + 2 b3 + b2 of its lane bits
-    {
-      double t8[8], t4[4], t2[2], t1;
-      const bool u5 = lane & 32, u4 = lane & 16, u3 = lane & 8, u2 = lane & 4;
-#pragma unroll
-      for (int i = 0; i < 8; ++i)
-        t8[i] = (u5 ? part[i + 8] : part[i]) + __shfl_xor(u5 ? part[i] : part[i + 8], 32);
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        t4[i] = (u4 ? t8[i + 4] : t8[i]) + __shfl_xor(u4 ? t8[i] : t8[i + 4], 16);
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-        t2[i] = (u3 ? t4[i + 2] : t4[i]) + __shfl_xor(u3 ? t4[i] : t4[i + 2], 8);
-      t1 = (u2 ? t2[1] : t2[0]) + __shfl_xor(u2 ? t2[0] : t2[1], 4);
-      t1 += __shfl_xor(t1, 2);
-      t1 += __shfl_xor(t1, 1);
-      const int jj = (u5 ? 8 : 0) + (u4 ? 4 : 0) + (u3 ? 2 : 0) + (u2 ? 1 : 0);
-      if ((lane & 3) == 0 && jj >= k && jj < pw) s_wred[wave][jj - k] = t1;
-    }
-    const int ncnt = pw - k;
     __syncthreads();
-    double* rb = red + (size_t)(k & 1) * kRRW * G;
-    if (threadIdx.x < ncnt) {
-      double s = 0.0;
+    double* rb = red + (size_t)(k & 1) * kTri * kPanelMaxGrid;
+    if (threadIdx.x < kTri) {
+      double t = 0.0;
 #pragma unroll
-      for (int w = 0; w < kRRT / 64; ++w) s += s_wred[w][threadIdx.x];
-      xstore(rb + (int64_t)threadIdx.x * G + blockIdx.x, s);
+      for (int w = 0; w < kColT / 64; ++w) t += s_wred[w][threadIdx.x];
+      xstore(rb + threadIdx.x * kPanelMaxGrid + blockIdx.x, t);
     }
     grid_barrier_x8(arrive, (unsigned)(k + 1), dev_err);
-    // the pivot row, read together with the partials below (one round trip)
-    const double* pv = piv + (k & 1) * kRRW;
-    if (threadIdx.x < kRRW) s_pv[threadIdx.x] = vload(pv + threadIdx.x);
-    // 3. every block reduces all partials in the same order.  A wave reads the
-    //    G <= 256 partials of its two columns (wave, wave + 8) with all eight
-    //    loads in flight together (clamped addresses, out-of-range ones scaled
-    //    by zero), so the reads cost one memory round trip, not one per load.
-    if (wave < ncnt) {
-      const int v0 = wave, v1 = min(wave + kRRT / 64, ncnt - 1);
-      double x0[4], x1[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int b = min(lane + 64 * i, G - 1);
-        x0[i] = vload(rb + (int64_t)v0 * G + b);
-        x1[i] = vload(rb + (int64_t)v1 * G + b);
-      }
-      double s0 = 0.0, s1 = 0.0;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const double w = (lane + 64 * i < G) ? 1.0 : 0.0;
-        s0 += w * x0[i];
-        s1 += w * x1[i];
-      }
-      s0 = wave_sum(s0);
-      s1 = wave_sum(s1);
-      if (lane == 0) {
-        s_tot[v0] = s0;
-        if (wave + kRRT / 64 < ncnt) s_tot[wave + kRRT / 64] = s1;
-      }
+    if (threadIdx.x < kTri) {
+      double t = 0.0;
+      for (int b = 0; b < G; ++b) t += vload(rb + threadIdx.x * kPanelMaxGrid + b);
+      s_tot[threadIdx.x] = t;
+      s_pv[threadIdx.x] = vload(piv + (k & 1) * kTri + threadIdx.x);
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-      const double alpha = s_pv[k];
-      const double xnorm = sqrt(s_tot[0]);
+      const double alpha = s_pv[k], xnorm = sqrt(s_tot[k]);
       double tau = 0.0, beta = alpha, scale = 0.0;
       if (xnorm > 0.0) {
         beta = -copysign(hypot(alpha, xnorm), alpha);
@@ -544,23 +615,14 @@ __global__ __launch_bounds__(kRRT) void k_qr_panel_rr(double* __restrict__ A, in
       s_par[0] = tau;
       s_par[1] = beta;
       s_par[2] = scale;
-      if (blockIdx.x == 0) tau_all[i0 + k] = tau;
+      if (blockIdx.x == 0) tau_all[k] = tau;
     }
     __syncthreads();
-    if (threadIdx.x < kRRW) {
+    if (threadIdx.x < kTri) {
       const int j = threadIdx.x;
-      s_tw[j] = (j > k && j < pw) ? s_par[0] * (s_pv[j] + s_par[2] * s_tot[j - k]) : 0.0;
+      s_tw[j] = (j > k && j < bw) ? s_par[0] * (s_pv[j] + s_par[2] * s_tot[j]) : 0.0;
     }
-    beta_p = s_par[1];
-    scale_p = s_par[2];
     __syncthreads();
-  }
-#pragma unroll
-  for (int q = 0; q < kRRQ; ++q) {
-    if (lrow[q] < 0) continue;
-#pragma unroll
-    for (int j = 0; j < kRRW; ++j)
-      if (j < pw) A[(i0 + lrow[q]) + (i0 + j) * ld] = a[q][j];
   }
 }
 
@@ -620,44 +682,6 @@ __global__ void k_qr_tw(const double* __restrict__ W, int64_t nct, int pw,
     double s = 0.0;
     for (int l = 0; l <= kk; ++l) s += T[l * kQrNB + kk] * W[(int64_t)l * nct + cp];
     Wt[(int64_t)kk * nct + cp] = -s;
-  }
-}
-
-// T and Wt = -T^T W of a narrow reflector block (pw <= 16, nct <= 64) in one
-// wave: the same sums in the same order as k_qr_larft followed by k_qr_tw, in
-// one launch instead of two.  W's pw rows and tau are staged in LDS first with
-// all loads in flight at once; the rest works from LDS with a one-wave barrier
-// per column.
-__global__ __launch_bounds__(64) void k_qr_larft_tw16(const double* __restrict__ W, int64_t nct,
-                                                      int pw, const double* __restrict__ tau,
-                                                      double* __restrict__ T,
-                                                      double* __restrict__ Wt) {
-  __shared__ double sW[16][65];
-  __shared__ double sT[16][17];
-  __shared__ double sTau[16];
-  const int l = threadIdx.x;
-#pragma unroll
-  for (int r = 0; r < 16; ++r)
-    sW[r][l] = (r < pw && l < nct) ? W[(int64_t)r * nct + l] : 0.0;
-  if (l < 16) sTau[l] = l < pw ? tau[l] : 0.0;
-  for (int e = l; e < 256; e += 64) sT[e / 16][e % 16] = 0.0;
-  __syncthreads();
-  for (int i = 0; i < pw; ++i) {
-    const double ti = sTau[i];
-    double z = 0.0;
-    if (l < i) z = dot4(l, i, [&](int q) { return sT[l][q]; }, [&](int q) { return sW[q][i]; });
-    __syncthreads();
-    if (l < i) sT[l][i] = -ti * z;
-    if (l == i) sT[i][i] = ti;
-    __syncthreads();
-  }
-  for (int e = l; e < pw * pw; e += 64) T[(e / pw) * kQrNB + e % pw] = sT[e / pw][e % pw];
-  const int ntr = (int)(nct - pw);
-  for (int e = l; e < pw * ntr; e += 64) {
-    const int kk = e / ntr, cp = pw + (e - kk * ntr);
-    const double acc =
-        dot4(0, kk + 1, [&](int q) { return sT[q][kk]; }, [&](int q) { return sW[q][cp]; });
-    Wt[(int64_t)kk * nct + cp] = -acc;
   }
 }
 
@@ -933,70 +957,7 @@ __global__ __launch_bounds__(512) void k_qr_vtc2(const double* __restrict__ A, i
     }
 }
 
-// W = V^T C for a narrow reflector block (pw <= 16) and a narrow C (nct <= 64
-// columns, the panel's own columns first): the update inside a 64-column block
-// after each 16-wide panel.  This is a memory-bound pass over m x nct doubles,
-// so it has no LDS staging: wave u of a block owns C columns [16 u, 16 u + 16)
-// and all 16 V columns, reads 4 consecutive rows of its columns per lane
-// (32-byte loads, K-permuted so lane group g holds rows 4 g .. 4 g + 3 of a
-// 16-row chunk), and keeps two chunks in flight.  Slabs are short (kNarrowSlab
-// rows) so that many blocks stream at once; chunks clear of the V triangle and
-// of the slab end load with no condition.
-constexpr int kNarrowSlab = 512;
-__global__ __launch_bounds__(256) void k_qr_vtc_narrow(const double* __restrict__ A, int64_t ld,
-                                                       int64_t m, int64_t j0, int pw, int64_t nct,
-                                                       double* __restrict__ part) {
-  const int64_t s = blockIdx.x;
-  const int64_t r0 = j0 + s * kNarrowSlab, r1 = std::min(m, r0 + kNarrowSlab);
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane >> 4, idx = lane & 15;
-  const int64_t cp = (int64_t)wave * 16 + idx;  // this lane's C column (relative to j0)
-  if ((int64_t)wave * 16 >= nct) return;
-  const double* vcol = A + (j0 + min(idx, pw - 1)) * ld;
-  const double* ccol = A + (j0 + min(cp, nct - 1)) * ld;
-  d4v acc = zero4();
-  auto chunk = [&](int64_t rk, double (&va)[4], double (&cb)[4]) {
-    const int64_t r = rk + 4 * g;
-    if (rk - j0 >= 16 && rk + 16 <= r1) {  // uniform over the wave
-      const d4v v = *reinterpret_cast<const d4v*>(vcol + r);
-      const d4v c = *reinterpret_cast<const d4v*>(ccol + r);
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        va[q] = v[q];
-        cb[q] = c[q];
-      }
-    } else {
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int64_t rq = r + q, rr = rq - j0;
-        const bool in = rq < r1;
-        const double v = in ? vcol[rq] : 0.0;
-        const double c = in ? ccol[rq] : 0.0;
-        va[q] = (!in || idx >= pw) ? 0.0 : (rr == idx ? 1.0 : (rr > idx ? v : 0.0));
-        cb[q] = (!in || cp >= nct) ? 0.0
-                                   : (cp < pw ? (rr == cp ? 1.0 : (rr > cp ? c : 0.0)) : c);
-      }
-    }
-  };
-  const int64_t nch = (r1 - r0 + 15) / 16;
-  double va0[4], cb0[4], va1[4], cb1[4];
-  if (nch > 0) chunk(r0, va0, cb0);
-  if (nch > 1) chunk(r0 + 16, va1, cb1);
-  for (int64_t c = 0; c < nch; c += 2) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) acc = mfma_f64(va0[q], cb0[q], acc);
-    if (c + 2 < nch) chunk(r0 + (c + 2) * 16, va0, cb0);
-    if (c + 1 >= nch) break;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) acc = mfma_f64(va1[q], cb1[q], acc);
-    if (c + 3 < nch) chunk(r0 + (c + 3) * 16, va1, cb1);
-  }
-  // D layout: lane (g, idx) holds W[V column g + 4 q][C column idx of the tile]
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int ii = g + 4 * q;
-    if (ii < pw && cp < nct) part[(s * pw + ii) * nct + cp] = acc[q];
-  }
-}
+constexpr int kNarrowSlab = 512;  // rows per slab of a 64-wide update
 
 // ---------------------------------------------- outer (128-wide) WY update ----
 // The same two products as above for a reflector block up to kQrOB = 128 wide:
@@ -2167,7 +2128,6 @@ __global__ void k_fill_u32(unsigned int* __restrict__ p, int64_t n, unsigned int
     p[i] = v;
 }
 
-__global__ void k_zero_u32(unsigned int* p) { *p = 0u; }
 
 inline unsigned g256(int64_t n) { return std::max(1u, std::min(cdiv(n, 256), 65536u)); }
 
@@ -2212,11 +2172,14 @@ static int64_t qr_slab_rows(int64_t m, int64_t j0, int64_t nct) {
   return (std::min(large, fill) + 31) / 32 * 32;
 }
 
-// Elements of the split-K partials buffer: those of the 128-wide updates, or
+static int64_t qr_ldq(int64_t m) { return (m + 3) & ~int64_t(3); }
+
+// Elements of the split-K partials buffer: the Gram partials of a panel, those of the 128-wide updates, or
 // of the 16- and 64-wide ones over short slabs (at most 64 reflectors x 128
 // columns).  Both the workspace size and its binding use this one count.
 static int64_t qr_part_elems(int64_t m, int64_t n) {
-  int64_t e = ((m + kNarrowSlab - 1) / kNarrowSlab + 1) * (int64_t)kQrNB * 2 * kQrNB;
+  int64_t e = std::max(((m + kNarrowSlab - 1) / kNarrowSlab + 1) * (int64_t)kQrNB * 2 * kQrNB,
+                       (int64_t)kGramMaxBlocks * kGram);
   for (int64_t j0 = 0; j0 < n; j0 += kQrOB) {
     const int64_t nct = n + 1 - j0, slab = qr_slab_rows(m, j0, nct);
     e = std::max(e, (m - j0 + slab - 1) / slab * kQrOB * nct);
@@ -2227,33 +2190,33 @@ static int64_t qr_part_elems(int64_t m, int64_t n) {
 size_t qr_workspace_bytes(int64_t m, int64_t n) {
   const int64_t ncols = n + 1;
   size_t d = 0;
-  d += (size_t)qr_part_elems(m, n);           // part
-  d += (size_t)kQrOB * ncols * 2;            // W, Wt
-  d += (size_t)kQrOB * kQrOB;                // T
-  d += (size_t)kQrNB * kCS;                  // colstate
-  d += (size_t)kQrNB * kPanelMaxGrid;        // red
-  d += (size_t)n + 8;                        // tau
+  d += (size_t)qr_part_elems(m, n);            // part
+  d += (size_t)kQrOB * ncols * 2;              // W, Wt
+  d += (size_t)kQrOB * kQrOB;                  // T
+  d += (size_t)kTri * qr_ldq(m);               // Q of a panel
+  d += (size_t)kPanDoubles;                    // pan
+  d += (size_t)2 * kTri * (kPanelMaxGrid + 1); // red and piv of the column kernel
+  d += (size_t)n + 8;                          // tau
   return d * sizeof(double) + sizeof(unsigned int) * (kCounterWords + kTrsvMaxBlocks);  // counters, flags
 }
 
 void qr_bind_workspace(void* base, int64_t m, int64_t n, QrWork* w) {
   const int64_t ncols = n + 1;
   double* p = reinterpret_cast<double*>(base);
-  w->part = p;
+  auto take = [&](int64_t k) {
+    double* q = p;
+    p += k;
+    return q;
+  };
+  w->Q = take(kTri * qr_ldq(m));  // (first: 32-byte aligned columns)
+  w->pan = take(kPanDoubles);
   w->part_elems = qr_part_elems(m, n);
-  p += w->part_elems;
-  w->W = p;
-  p += kQrOB * ncols;
-  w->Wt = p;
-  p += kQrOB * ncols;
-  w->T = p;
-  p += kQrOB * kQrOB;
-  w->colstate = p;
-  p += kQrNB * kCS;
-  w->red = p;
-  p += kQrNB * kPanelMaxGrid;
-  w->tau = p;
-  p += n + 8;
+  w->part = take(w->part_elems);
+  w->W = take(kQrOB * ncols);
+  w->Wt = take(kQrOB * ncols);
+  w->T = take(kQrOB * kQrOB);
+  w->red = take(2 * kTri * (kPanelMaxGrid + 1));
+  w->tau = take(n + 8);
   w->counter = reinterpret_cast<unsigned int*>(p);
   w->flags = w->counter + kCounterWords;
 }
@@ -2265,18 +2228,7 @@ static void qr_wy_update(double* A, int64_t ld, int64_t m, int64_t j0, int pw, i
                          QrWork* w, hipStream_t st) {
   const int64_t nct = c_end - j0;
   if (nct <= pw) return;
-  if (pw <= 16 && nct <= 64) {
-    const int64_t nslab = (m - j0 + kNarrowSlab - 1) / kNarrowSlab;
-    hipLaunchKernelGGL(k_qr_vtc_narrow, dim3((unsigned)nslab), dim3(256), 0, st, A, ld, m, j0, pw,
-                       nct, w->part);
-    // many slabs, few outputs: 16 waves per 64 outputs split the slab sum
-    reduce_rows_f64(w->part, nslab, (int64_t)pw * nct, w->W, st);
-    hipLaunchKernelGGL(k_qr_larft_tw16, dim3(1), dim3(64), 0, st, w->W, nct, pw, w->tau + j0,
-                       w->T, w->Wt);
-    hipLaunchKernelGGL(k_qr_upd<16>, dim3(cdiv(m - j0, kUR)), dim3(512), 0, st, A, ld, m, j0,
-                       pw, c_end, nct, w->Wt);
-    return;
-  } else {
+  {
     // Short slabs: a 64-wide update has one column tile, so the slabs alone
     // must give enough blocks to fill the device; the many partials are summed
     // by the multi-block row reduction.
@@ -2327,76 +2279,72 @@ static void qr_wy_update_ob(double* A, int64_t ld, int64_t m, int64_t j0, int pw
                        c_end, nct, w->Wt);
 }
 
-// Number of k_qr_panel_rr blocks that are co-resident on the current device (0 if unknown).
-static int rr_capacity() {
+// Number of k_qr_panel_col blocks that are co-resident on the current device (0 if unknown).
+static int col_capacity() {
   static int cap = -1;
   if (cap < 0) {
     cap = 0;
     int dev = 0, nb = 0;
     hipDeviceProp_t p;
     if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&p, dev) == hipSuccess &&
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_qr_panel_rr, kRRT, 0) == hipSuccess &&
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_qr_panel_col, kColT, 0) == hipSuccess &&
         nb > 0)
       cap = std::min(nb * p.multiProcessorCount, kPanelMaxGrid);
   }
   return cap;
 }
 
+// Householder factors of the bw <= 64 columns at j0, rows j0 .. m - 1.
+static void qr_panel(double* A_, int64_t ld, int64_t m, int64_t j0, int bw, QrWork* w,
+                     hipStream_t st, int* dev_err) {
+  double* A = A_ + j0 + j0 * ld;
+  double* tau = w->tau + j0;
+  int64_t rows = m - j0, ldq = qr_ldq(m);
+  unsigned int *state = w->counter, *arrive = w->counter + kPanelBar;
+  const unsigned gb = (unsigned)std::max<int64_t>(
+      1, std::min<int64_t>(kGramMaxBlocks, (rows + 127) / 128));
+  auto gram = [&](const double* P, int64_t ldp) {
+    hipLaunchKernelGGL(k_panel_gram, dim3(gb), dim3(256), 0, st, P, ldp, rows, bw, w->part);
+    reduce_rows_f64(w->part, gb, kGram, w->pan + kPanG, st);
+  };
+  gram(A, ld);
+  hipLaunchKernelGGL(k_panel_chol, dim3(1), dim3(256), 0, st, bw, w->pan, state, arrive);
+  hipLaunchKernelGGL(k_panel_solve, dim3(cdiv(rows, 256)), dim3(256), 0, st, A, ld, w->Q, ldq,
+                     rows, bw, w->pan + kPanU1, w->pan + kPanRinv1, state);
+  gram(w->Q, ldq);
+  hipLaunchKernelGGL(k_panel_vectors, dim3(1), dim3(256), 0, st, A, ld, rows, bw, w->Q, ldq,
+                     w->pan, tau, state);
+  if (rows > kTri)
+    hipLaunchKernelGGL(k_panel_solve, dim3(cdiv(rows - kTri, 256)), dim3(256), 0, st, w->Q + kTri,
+                       ldq, A + kTri, ld, rows - kTri, bw, w->pan + kPanZ, w->pan + kPanRinvZ,
+                       state);
+  // ends at once unless the panel's columns are numerically dependent
+  double *red = w->red, *piv = w->red + 2 * kTri * kPanelMaxGrid;
+  const int64_t G = std::min<int64_t>(col_capacity(), (rows + kColT - 1) / kColT);
+  void* args[] = {&A, &ld, &rows, &bw, &red, &piv, &arrive, &state, &tau, &dev_err};
+  if (G < 1 || hipLaunchCooperativeKernel(reinterpret_cast<const void*>(&k_qr_panel_col),
+                                          dim3((unsigned)G), dim3(kColT), args, 0,
+                                          st) != hipSuccess) {
+    (void)hipGetLastError();
+    hipLaunchKernelGGL(k_qr_panel_col, dim3(1), dim3(kColT), 0, st, A, ld, rows, bw, red, piv,
+                       arrive, state, tau, dev_err);
+  }
+}
+
 void qr_factor(double* A, int64_t ld, int64_t m, int64_t ncols, int64_t n, QrWork* w,
                hipStream_t st, int* dev_err, Timer* tm) {
   Timer dummy;
   if (!tm) tm = &dummy;
-  hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(1), 0, st, w->counter);
-  const int cap = rr_capacity();
-  // Three levels: 16-wide register-resident panels inside 64-wide blocks
-  // (compact-WY updates within the block), 64-wide blocks inside 128-wide outer
-  // blocks (one 64-wide update of the outer block's second half), and one
-  // 128-wide update of the trailing matrix per outer block.
+  // Two levels: 64-wide panels inside 128-wide outer blocks (one 64-wide compact-
+  // WY update of the outer block's second half), one 128-wide update of the
+  // trailing matrix per outer block.
   for (int64_t o0 = 0; o0 < n; o0 += kQrOB) {
     const int ow = (int)std::min<int64_t>(kQrOB, n - o0);
     for (int64_t j0 = o0; j0 < o0 + ow; j0 += kQrNB) {
       const int bw = (int)std::min<int64_t>(kQrNB, o0 + ow - j0);
-      int64_t i0 = j0;
-      while (i0 < j0 + bw) {
-        const int64_t rows = m - i0;
-        // as few blocks as hold the panel: every column costs one grid barrier
-        // and a reduction over the blocks' partials, both growing with the grid
-        const int64_t G_rr = std::min<int64_t>(cap, (rows + kRRT * kRRQ - 1) / (kRRT * kRRQ));
-        const bool rr = cap > 0 && rows <= G_rr * kRRT * kRRQ;
-        const int pw = (int)std::min<int64_t>(rr ? kRRW : kPanelW, j0 + bw - i0);
-        tm->begin(TM_QR_PANEL);
-        bool done = false;
-        if (rr) {
-          hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(256), 0, st, w->counter + kPanelBar,
-                             (int64_t)8 * kBarStride, 0u);
-          int64_t ld_ = ld, m_ = m, i0_ = i0;
-          int pw_ = pw;
-          double* A_ = A;
-          double* red_ = w->red;
-          double* piv_ = w->T;  // the T scratch is free while a panel is factored
-          unsigned int* arr_ = w->counter + kPanelBar;
-          double* tau_ = w->tau;
-          int* err_ = dev_err;
-          void* args[] = {&A_, &ld_, &m_, &i0_, &pw_, &red_, &piv_, &arr_, &tau_, &err_};
-          done = hipLaunchCooperativeKernel(reinterpret_cast<const void*>(&k_qr_panel_rr),
-                                            dim3((unsigned)G_rr), dim3(kRRT), args, 0,
-                                            st) == hipSuccess;
-          if (!done) (void)hipGetLastError();
-        }
-        if (!done) {
-          for (int64_t k = i0; k <= i0 + pw; ++k) {
-            const int64_t r_lo = (k > i0) ? k - 1 : k;
-            const int64_t rr_rows = m - r_lo;
-            const unsigned G = std::max(1u, std::min(cdiv(rr_rows, 512), (unsigned)kPanelMaxGrid));
-            hipLaunchKernelGGL(k_qr_col, dim3(G), dim3(256), 0, st, A, ld, m, i0, pw, k,
-                               w->colstate, w->red, w->counter, w->tau);
-          }
-        }
-        // rest of the 64-wide block with this inner panel's reflectors
-        qr_wy_update(A, ld, m, i0, pw, j0 + bw, w, st);
-        tm->end(TM_QR_PANEL);
-        i0 += pw;
-      }
+      tm->begin(TM_QR_PANEL);
+      qr_panel(A, ld, m, j0, bw, w, st, dev_err);
+      tm->end(TM_QR_PANEL);
       if (j0 + bw >= o0 + ow) continue;
       // rest of the outer block with this 64-wide block's reflectors
       tm->begin(TM_QR_UPDATE);

@@ -1,0 +1,88 @@
+"""Householder QR panels at their edges, through gap_lstsq: widths and heights
+around the 64- and 128-wide blocks, square matrices, and panels whose columns
+are numerically dependent (factored column by column).
+
+Bounds: a backward-stable QR has |R^T R - A^T A| <= c(m, n) u |A|_F^2 with c a
+low-degree polynomial, here taken as 1e-12 / u = 4500 for n <= 300; solutions of
+well-conditioned systems agree to 1e-10 as everywhere in these tests."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def gapx():
+    import paper_2310_03921_amd as g
+    assert torch.cuda.is_available(), "GPU tests need a gfx950 device"
+    return g
+
+
+@pytest.fixture(scope="module")
+def gap(gapx):
+    return gapx.Gap(0)
+
+
+def device_matrix(gapx, K, y):
+    m, n = K.shape
+    A = gapx.colmajor(m, n + 1)
+    A[:n, :m] = torch.tensor(K.T)
+    A[n, :m] = torch.tensor(y)
+    return A
+
+
+def factor_error(A, K):
+    n = K.shape[1]
+    R = np.triu(A[:n, :n].T.cpu().numpy())
+    return np.linalg.norm(R.T @ R - K.T @ K) / np.linalg.norm(K) ** 2
+
+
+@pytest.mark.parametrize("m,n", [
+    (1, 1), (5, 1), (17, 16), (63, 63), (64, 64), (65, 64), (100, 65), (128, 128), (129, 127),
+    (400, 129), (1000, 200), (2049, 256), (4100, 63), (30000, 70), (5003, 300)])
+def test_lstsq_shapes(gapx, gap, m, n):
+    print(f"m {m} n {n}", flush=True)
+    rng = np.random.default_rng([m, n])
+    # column scales over twelve decades: the factorisation is invariant to them
+    scale = 10.0 ** rng.uniform(-6, 6, n)
+    K = rng.standard_normal((m, n)) + (np.eye(m, n) * 3 if m < 2 * n else 0)
+    y = rng.standard_normal(m)
+    A = device_matrix(gapx, K * scale, y)
+    x, _ = gap.lstsq(A, m, n)
+    ref = np.linalg.lstsq(K, y, rcond=None)[0]
+    got = x.cpu().numpy() * scale
+    assert np.linalg.norm(got - ref) <= 1e-10 * np.linalg.norm(ref) * np.linalg.cond(K)
+    assert factor_error(A, K * scale) <= 1e-12
+
+
+@pytest.mark.parametrize("m,n", [(300, 64), (700, 100), (5000, 200)])
+@pytest.mark.parametrize("eps", [1e-4, 1e-7, 1e-9, 0.0])
+def test_dependent_columns_in_a_panel(gapx, gap, m, n, eps):
+    """Columns equal up to eps, in the first and in the last panel: the factor stays
+    backward stable, and the rest of the matrix is not disturbed."""
+    print(f"m {m} n {n} eps {eps}", flush=True)
+    rng = np.random.default_rng([m, n])
+    K = rng.standard_normal((m, n))
+    for a, b in ((3, 40), (n - 1, n - 9)):
+        K[:, a] = K[:, b] + eps * rng.standard_normal(m)
+    y = rng.standard_normal(m)
+    A = device_matrix(gapx, K, y)
+    try:
+        x, _ = gap.lstsq(A, m, n)
+    except gapx.GapError as e:  # an exactly zero pivot is allowed for equal columns only
+        assert eps == 0.0 and e.status == gapx.GAP_E_RANK
+    assert factor_error(A, K) <= 1e-12
+    if eps >= 1e-7:
+        r = y - K @ x.cpu().numpy()
+        xn = np.linalg.norm(K) * np.linalg.norm(x.cpu().numpy()) + np.linalg.norm(y)
+        assert np.linalg.norm(K.T @ r) <= 1e-12 * np.linalg.norm(K) * xn
+
+
+def test_zero_column_is_reported(gapx, gap):
+    rng = np.random.default_rng(5)
+    K = rng.standard_normal((500, 90))
+    K[:, 70] = 0.0
+    with pytest.raises(gapx.GapError) as e:
+        gap.lstsq(device_matrix(gapx, K, rng.standard_normal(500)), 500, 90)
+    assert e.value.status == gapx.GAP_E_RANK
