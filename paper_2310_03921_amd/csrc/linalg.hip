@@ -24,8 +24,8 @@ namespace {
 constexpr int kQrNB = 64;      // outer block width (compact-WY trailing update)
 constexpr int kTrsvMaxBlocks = 256;  // multi-block triangular solve: n <= 64 * 256
 constexpr int kPanelMaxGrid = 256;
-// Workspace counter words: [0] the panel's state (1: it needs the column-by-
-// column kernel), [kPanelBar ..) that kernel's eight arrival counters.
+// Workspace counter words: [0], [1] the states of an outer block's two panels (1:
+// the panel needs the column-by-column kernel), [kPanelBar ..) that kernel's eight arrival counters.
 constexpr int kPanelBar = 64;
 constexpr int kPanelBarWords = 8 * 16;
 constexpr int kCounterWords = 256;
@@ -217,7 +217,7 @@ GAP_DEV void grid_barrier_x8(unsigned int* arrive, unsigned int round, int* dev_
 //   Q^ - [S; 0] = V U with V unit lower trapezoidal, U upper triangular and the
 //   signs S_jj = -sign of the pivot's diagonal (LU without pivoting of the top
 //   64 rows, |U_jj| >= 1), so that P = H [S R2 R1; 0], H = I - V T V^T,
-//   tau_j = -U_jj S_jj.
+//   T = -U S V1^-T (V1 the top block of V), tau_j = T_jj = -U_jj S_jj.
 // The first pass leaves |Q^T Q - I| about cond(P)^2 u (columns scaled); while
 // its entries are below 1/64 the second makes Q^ orthonormal to rounding, and the factors
 // are as accurate as those of the column-by-column reduction (residual, Gram
@@ -239,7 +239,9 @@ constexpr int kPanU1 = 0;                     // R1, row-major upper, 64 x 64
 constexpr int kPanRinv1 = kPanU1 + 4096;      // 1 / its diagonal
 constexpr int kPanZ = kPanRinv1 + 64;         // U R2, row-major upper
 constexpr int kPanRinvZ = kPanZ + 4096;
-constexpr int kPanG = kPanRinvZ + 64;         // reduced Gram
+constexpr int kPanV1 = kPanRinvZ + 64;        // V's top block transposed, row-major upper
+constexpr int kPanUS = kPanV1 + 4096;         // -U S, col-major
+constexpr int kPanG = kPanUS + 4096;          // reduced Gram
 constexpr int kPanDoubles = kPanG + kGram;
 
 // Gram partials of up to 64 columns (col-major, rows 16-byte groups aligned):
@@ -338,32 +340,40 @@ __global__ __launch_bounds__(256) void k_panel_chol(int bw, double* __restrict__
   if (threadIdx.x < kTri) pan[kPanRinv1 + threadIdx.x] = 1.0 / S[threadIdx.x][threadIdx.x];
 }
 
-// Rows x of src (col-major) <- x U^-1 into dst, a row per lane; U and its
-// reciprocal diagonal from global memory into LDS.
-__global__ __launch_bounds__(256) void k_panel_solve(const double* __restrict__ src, int64_t lds,
-                                                     double* __restrict__ dst, int64_t ldd,
-                                                     int64_t rows, int bw,
-                                                     const double* __restrict__ u_g,
-                                                     const double* __restrict__ rinv_g,
+// dst <- src U^-1 (both col-major), a row per lane; U row-major and the
+// reciprocals of its diagonal (NULL: ones) go through LDS.  Blocks from na on
+// take problem b.
+struct PanelSolve {
+  const double* src;
+  int64_t lds;
+  double* dst;
+  int64_t ldd, rows;
+  int bw;
+  const double *u, *rinv;
+};
+__global__ __launch_bounds__(256) void k_panel_solve(PanelSolve pa, PanelSolve pb, int na,
                                                      const unsigned int* __restrict__ state) {
   __shared__ __attribute__((aligned(16))) double u[kTri * kTri];
   __shared__ double rinv[kTri];
   if (*state) return;
-  const uint32_t r = (uint32_t)min((int64_t)blockIdx.x * 256 + threadIdx.x, rows - 1);
+  const bool second = (int)blockIdx.x >= na;
+  const PanelSolve p = second ? pb : pa;
+  const int64_t b = second ? (int)blockIdx.x - na : (int)blockIdx.x;
+  const uint32_t r = (uint32_t)min(b * 256 + threadIdx.x, p.rows - 1);
   double x[kTri];
 #pragma unroll
-  for (int c = 0; c < kTri; ++c) x[c] = (src + (int64_t)min(c, bw - 1) * lds)[r];
+  for (int c = 0; c < kTri; ++c) x[c] = (p.src + (int64_t)min(c, p.bw - 1) * p.lds)[r];
   for (int e = threadIdx.x; e < kTri * kTri / 2; e += 256)
-    reinterpret_cast<d2v*>(u)[e] = reinterpret_cast<const d2v*>(u_g)[e];
-  if (threadIdx.x < kTri) rinv[threadIdx.x] = rinv_g[threadIdx.x];
+    reinterpret_cast<d2v*>(u)[e] = reinterpret_cast<const d2v*>(p.u)[e];
+  if (threadIdx.x < kTri) rinv[threadIdx.x] = p.rinv ? p.rinv[threadIdx.x] : 1.0;
   __syncthreads();
 #pragma unroll
-  for (int c = 0; c < kTri; ++c) x[c] = c < bw ? x[c] : 0.0;
+  for (int c = 0; c < kTri; ++c) x[c] = c < p.bw ? x[c] : 0.0;
   row_solve64(x, u, rinv);
   // lanes past the last row hold that row too and store the same values
 #pragma unroll
   for (int c = 0; c < kTri; ++c)
-    if (c < bw) (dst + c * ldd)[r] = x[c];
+    if (c < p.bw) (p.dst + c * p.ldd)[r] = x[c];
 }
 
 // LU without pivoting of B - diag(sg) for B (64 x 64, in LDS), sg_j = -sign of
@@ -522,6 +532,12 @@ __global__ __launch_bounds__(256) void k_panel_vectors(double* __restrict__ A, i
   if (threadIdx.x < kTri)
     pan[kPanRinvZ + threadIdx.x] =
         1.0 / (B[threadIdx.x][threadIdx.x] * u[threadIdx.x * (kTri + 1)]);
+  // T = (-U S) V1^-T: the rows of -U S and V1^T for the substitution
+  for (int e = threadIdx.x; e < kTri * kTri; e += 256) {
+    const int c = e >> 6, q = e & 63;
+    pan[kPanV1 + e] = q > c ? B[q][c] : (q == c ? 1.0 : 0.0);
+    pan[kPanUS + e] = q <= c ? -B[q][c] * sg[c] : 0.0;
+  }
 }
 
 // Householder factorisation of a panel column by column in memory, for the
@@ -641,48 +657,6 @@ GAP_DEV double dot4(int q0, int q1, FA a, FB b) {
   }
   for (; q < q1; ++q) s0 += a(q) * b(q);
   return (s0 + s1) + (s2 + s3);
-}
-
-// T (pw x pw upper, row-major ld kQrNB): T_ii = tau_i, T[0:i, i] = -tau_i T[0:i, 0:i] G[0:i, i]
-__global__ __launch_bounds__(256) void k_qr_larft(const double* __restrict__ W, int64_t nct, int pw,
-                                                  const double* __restrict__ tau,
-                                                  double* __restrict__ T) {
-  __shared__ double sT[kQrNB][kQrNB + 1];
-  __shared__ double sG[kQrNB][kQrNB + 1];
-  __shared__ double sTau[kQrNB];  // staged once: a load per column would cost a round trip each
-  if (threadIdx.x < kQrNB) sTau[threadIdx.x] = (int)threadIdx.x < pw ? tau[threadIdx.x] : 0.0;
-  for (int e = threadIdx.x; e < kQrNB * kQrNB; e += 256) {
-    const int l = e / kQrNB, i = e % kQrNB;
-    sG[l][i] = (l < pw && i < pw) ? W[(int64_t)l * nct + i] : 0.0;
-    sT[l][i] = 0.0;
-  }
-  __syncthreads();
-  for (int i = 0; i < pw; ++i) {
-    const double ti = sTau[i];
-    double z = 0.0;
-    const int l = threadIdx.x;
-    if (l < i) z = dot4(l, i, [&](int q) { return sT[l][q]; }, [&](int q) { return sG[q][i]; });
-    __syncthreads();
-    if (l < i) sT[l][i] = -ti * z;
-    if (l == i) sT[i][i] = ti;
-    __syncthreads();
-  }
-  for (int e = threadIdx.x; e < kQrNB * kQrNB; e += 256) T[e] = sT[e / kQrNB][e % kQrNB];
-}
-
-// Wt[kk][c'] = sum_{l <= kk} T[l][kk] W[l][c']  for c' in [pw, nct)
-// Wt[kk][cp] = -(T^T W)[kk][cp] for cp in [pw, nct) (negated: the update adds V Wt)
-__global__ void k_qr_tw(const double* __restrict__ W, int64_t nct, int pw,
-                        const double* __restrict__ T, double* __restrict__ Wt) {
-  const int64_t ntr = nct - pw;
-  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < (int64_t)pw * ntr;
-       e += (int64_t)gridDim.x * blockDim.x) {
-    const int kk = (int)(e / ntr);
-    const int64_t cp = pw + (e - (int64_t)kk * ntr);
-    double s = 0.0;
-    for (int l = 0; l <= kk; ++l) s += T[l * kQrNB + kk] * W[(int64_t)l * nct + cp];
-    Wt[(int64_t)kk * nct + cp] = -s;
-  }
 }
 
 // Trailing update, persistent over a 128-row block of C: the block stages
@@ -1327,22 +1301,19 @@ __global__ __launch_bounds__(256, 2) void k_qr_vtc5(const double* __restrict__ A
     }
 }
 
-// T (pw x pw upper triangular, ld kQrOB) of a reflector block from the Gram
-// G = V^T V held in the first pw columns of W (row l at W + l * nct), in two
-// steps.  The diagonal 64 x 64 blocks come from the column recursion
-// T[0:i, i] = -tau_i T[0:i, 0:i] G[0:i, i], T[i][i] = tau_i, one block per half
-// (k_qr_larft_half); the coupling block is T12 = -T11 G12 T22 (k_qr_tcouple),
-// since for H = H1 H2 with H_k = I - V_k T_k V_k^T the product is
-// I - [V1 V2] [[T1, -T1 V1^T V2 T2], [0, T2]] [V1 V2]^T.
-__global__ __launch_bounds__(256) void k_qr_larft_half(const double* __restrict__ W,
-                                                       int64_t nct, int pw,
-                                                       const double* __restrict__ tau,
-                                                       double* __restrict__ T) {
+// T of a 64-wide half whose panel was factored column by column (its state word
+// is set; other panels bring their T along), from the Gram G = V^T V held in W
+// (row l at W + l * nct): T[0:i, i] = -tau_i T[0:i, 0:i] G[0:i, i], T[i][i] =
+// tau_i.  Col-major, ld 64, one block per half; zero below the diagonal.
+__global__ __launch_bounds__(256) void k_qr_larft(const double* __restrict__ W, int64_t nct,
+                                                  int pw, const double* __restrict__ tau,
+                                                  double* __restrict__ T,
+                                                  const unsigned int* __restrict__ state) {
   __shared__ double sT[kQrNB][kQrNB + 1];
   __shared__ double sG[kQrNB][kQrNB + 1];
+  if (state[blockIdx.x] == 0u) return;
   const int o = blockIdx.x * kQrNB;
   const int w = min(kQrNB, pw - o);
-  if (w <= 0) return;
   __shared__ double sTau[kQrNB];  // staged once: a load per column would cost a round trip each
   if (threadIdx.x < kQrNB) sTau[threadIdx.x] = (int)threadIdx.x < w ? tau[o + threadIdx.x] : 0.0;
   for (int e = threadIdx.x; e < kQrNB * kQrNB; e += 256) {
@@ -1361,63 +1332,78 @@ __global__ __launch_bounds__(256) void k_qr_larft_half(const double* __restrict_
     if (l == i) sT[i][i] = ti;
     __syncthreads();
   }
-  for (int e = threadIdx.x; e < kQrNB * kQrNB; e += 256) {
-    const int r = e / kQrNB, c = e % kQrNB;
-    T[(int64_t)(o + r) * kQrOB + (o + c)] = sT[r][c];
-    if (blockIdx.x == 1) T[(int64_t)(o + r) * kQrOB + c] = 0.0;  // lower-left block
-  }
+  for (int e = threadIdx.x; e < kQrNB * kQrNB; e += 256)
+    T[blockIdx.x * kQrNB * kQrNB + e] = sT[e % kQrNB][e / kQrNB];
 }
 
-__global__ __launch_bounds__(256) void k_qr_tcouple(const double* __restrict__ W, int64_t nct,
-                                                    int pw, double* __restrict__ T) {
-  __shared__ double sA[kQrNB][kQrNB + 1];  // T11, then X = G12 T22
-  __shared__ double sB[kQrNB][kQrNB + 1];  // G12
-  __shared__ double sC[kQrNB][kQrNB + 1];  // T22
-  const int w2 = pw - kQrNB;  // width of the second half (> 0)
-  for (int e = threadIdx.x; e < kQrNB * kQrNB; e += 256) {
-    const int r = e / kQrNB, c = e % kQrNB;
-    sB[r][c] = (c < w2) ? W[(int64_t)r * nct + (kQrNB + c)] : 0.0;
-    sC[r][c] = (r < w2 && c < w2) ? T[(int64_t)(kQrNB + r) * kQrOB + (kQrNB + c)] : 0.0;
-  }
-  __syncthreads();
-  // X = G12 T22 (T22 upper triangular)
-  double x[16];
+// Wt = -T^T W over the trailing columns [pw, nct), T the factor of up to two
+// 64-wide halves H = H1 H2: with T1, T2 (col-major, ld 64) and the coupling
+// G12 = V1^T V2 that W holds in its own columns,
+//   Wt1 = -T1^T W1,  Wt2 = -T2^T (W2 + G12^T Wt1),
+// which is -T^T W for T = [T1, -T1 G12 T2; 0, T2] without forming it.  (The
+// negated product, so that the update kernel adds V Wt to C.)  A block takes 64
+// columns, a wave 16 of them; each product's result is the next one's operand in
+// the registers it is in (lane group g holds rows g + 4 r, so step r contracts
+// those rows).  The one-block products for T and the element-wise product this
+// replaces took 140 us per 128 columns; this takes 10.
+__global__ __launch_bounds__(256) void k_qr_wt(const double* __restrict__ W, int64_t nct, int pw,
+                                               const double* __restrict__ T,
+                                               double* __restrict__ Wt) {
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane >> 4, idx = lane & 15;
+  const int64_t cp = pw + (int64_t)blockIdx.x * 64 + wave * 16 + idx;
+  if (cp - idx >= nct) return;
+  const double* wc = W + min(cp, nct - 1);
+  // rows l = o + 16 t + g + 4 r of W's column, zero from pw on
+  auto load_w = [&](int o, d4v (&x)[4]) {
 #pragma unroll
-  for (int u = 0; u < 16; ++u) {
-    const int e = threadIdx.x + u * 256, r = e / kQrNB, c = e % kQrNB;
-    x[u] = dot4(0, c + 1, [&](int q) { return sB[r][q]; }, [&](int q) { return sC[q][c]; });
-  }
-  __syncthreads();
+    for (int t = 0; t < 4; ++t)
 #pragma unroll
-  for (int u = 0; u < 16; ++u) {
-    const int e = threadIdx.x + u * 256;
-    sB[e / kQrNB][e % kQrNB] = x[u];  // sB now holds X
-    sA[e / kQrNB][e % kQrNB] = T[(int64_t)(e / kQrNB) * kQrOB + (e % kQrNB)];
+      for (int r = 0; r < 4; ++r) {
+        const int l = o + 16 * t + g + 4 * r;
+        const double v = wc[(int64_t)min(l, pw - 1) * nct];
+        x[t][r] = l < pw ? v : 0.0;
+      }
+  };
+  // y = -T^T x (T[l][kk] at T[kk * 64 + l], zero for l > kk)
+  auto times_t = [&](const double* Th, const d4v (&x)[4], d4v (&y)[4]) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      y[u] = zero4();
+#pragma unroll
+      for (int t = 0; t <= u; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          y[u] = mfma_f64(-Th[(16 * u + idx) * kQrNB + 16 * t + g + 4 * r], x[t][r], y[u]);
+    }
+  };
+  auto store = [&](int o, const d4v (&y)[4]) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int kk = o + 16 * u + g + 4 * r;
+        if (kk < pw && cp < nct) Wt[(int64_t)kk * nct + cp] = y[u][r];
+      }
+  };
+  d4v x[4], y[4];
+  load_w(0, x);
+  times_t(T, x, y);
+  store(0, y);
+  if (pw <= kQrNB) return;
+  load_w(kQrNB, x);
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {  // x += G12^T y
+    const int k2 = kQrNB + 16 * u + idx;
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const double v = W[(int64_t)(16 * t + g + 4 * r) * nct + min(k2, pw - 1)];
+        x[u] = mfma_f64(k2 < pw ? v : 0.0, y[t][r], x[u]);
+      }
   }
-  __syncthreads();
-  // T12 = -T11 X (T11 upper triangular)
-  for (int u = 0; u < 16; ++u) {
-    const int e = threadIdx.x + u * 256, r = e / kQrNB, c = e % kQrNB;
-    const double acc =
-        dot4(r, kQrNB, [&](int q) { return sA[r][q]; }, [&](int q) { return sB[q][c]; });
-    T[(int64_t)r * kQrOB + (kQrNB + c)] = -acc;
-  }
-}
-
-// Wn[kk][cp] = -sum_{l <= kk} T[l][kk] W[l][cp] for cp in [pw, nct)  (T with ld ldt):
-// the negated W' = T^T W, so the update kernel adds V Wn to C without a negation
-// on the freshly loaded value (which would wait for the load at once)
-__global__ void k_qr_tw_ld(const double* __restrict__ W, int64_t nct, int pw,
-                           const double* __restrict__ T, int ldt, double* __restrict__ Wt) {
-  const int64_t ntr = nct - pw;
-  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < (int64_t)pw * ntr;
-       e += (int64_t)gridDim.x * blockDim.x) {
-    const int kk = (int)(e / ntr);
-    const int64_t cp = pw + (e - (int64_t)kk * ntr);
-    double s = 0.0;
-    for (int l = 0; l <= kk; ++l) s += T[l * ldt + kk] * W[(int64_t)l * nct + cp];
-    Wt[(int64_t)kk * nct + cp] = -s;
-  }
+  times_t(T + kQrNB * kQrNB, x, y);
+  store(kQrNB, y);
 }
 
 // C -= V W' for a reflector block up to 128 wide, persistent over a 128-row
@@ -2239,8 +2225,9 @@ static void qr_wy_update(double* A, int64_t ld, int64_t m, int64_t j0, int pw, i
                        pw, nct, (int64_t)kNarrowSlab, n_ct, total, per_xcd, w->part);
     reduce_rows_f64(w->part, nslab, (int64_t)pw * nct, w->W, st);
   }
-  hipLaunchKernelGGL(k_qr_larft, dim3(1), dim3(256), 0, st, w->W, nct, pw, w->tau + j0, w->T);
-  hipLaunchKernelGGL(k_qr_tw, dim3(g256(pw * (nct - pw))), dim3(256), 0, st, w->W, nct, pw, w->T,
+  hipLaunchKernelGGL(k_qr_larft, dim3(1), dim3(256), 0, st, w->W, nct, pw, w->tau + j0, w->T,
+                     w->counter);
+  hipLaunchKernelGGL(k_qr_wt, dim3(cdiv(nct - pw, 64)), dim3(256), 0, st, w->W, nct, pw, w->T,
                      w->Wt);
   hipLaunchKernelGGL(k_qr_upd<kQrNB>, dim3(cdiv(m - j0, kUR)), dim3(512), 0, st, A, ld, m, j0, pw, c_end,
                      nct, w->Wt);
@@ -2263,12 +2250,10 @@ static void qr_wy_update_ob(double* A, int64_t ld, int64_t m, int64_t j0, int pw
     hipLaunchKernelGGL(k_qr_vtc3<false>, dim3((unsigned)(8 * per_xcd)), dim3(512), 0, st, A, ld,
                        m, j0, pw, nct, slab, n_ct, total, per_xcd, w->part);
   reduce_rows_f64(w->part, nslab, (int64_t)pw * nct, w->W, st);
-  hipLaunchKernelGGL(k_qr_larft_half, dim3(2), dim3(256), 0, st, w->W, nct, pw, w->tau + j0,
-                     w->T);
-  if (pw > kQrNB)
-    hipLaunchKernelGGL(k_qr_tcouple, dim3(1), dim3(256), 0, st, w->W, nct, pw, w->T);
-  hipLaunchKernelGGL(k_qr_tw_ld, dim3(g256(pw * (nct - pw))), dim3(256), 0, st, w->W, nct, pw,
-                     w->T, kQrOB, w->Wt);
+  hipLaunchKernelGGL(k_qr_larft, dim3(cdiv(pw, kQrNB)), dim3(256), 0, st, w->W, nct, pw,
+                     w->tau + j0, w->T, w->counter);
+  hipLaunchKernelGGL(k_qr_wt, dim3(cdiv(nct - pw, 64)), dim3(256), 0, st, w->W, nct, pw, w->T,
+                     w->Wt);
   // the barrier-light kernel needs a full block, a full tile of trailing
   // columns and a 64-column tile of C within 31-bit offsets
   if (pw == kQrOB && nct - pw >= kU5C && ld < (int64_t)(1 << 22))
@@ -2294,13 +2279,14 @@ static int col_capacity() {
   return cap;
 }
 
-// Householder factors of the bw <= 64 columns at j0, rows j0 .. m - 1.
-static void qr_panel(double* A_, int64_t ld, int64_t m, int64_t j0, int bw, QrWork* w,
+// Householder factors of the bw <= 64 columns at j0, rows j0 .. m - 1, half `half`
+// of its outer block.
+static void qr_panel(double* A_, int64_t ld, int64_t m, int64_t j0, int bw, int half, QrWork* w,
                      hipStream_t st, int* dev_err) {
   double* A = A_ + j0 + j0 * ld;
   double* tau = w->tau + j0;
   int64_t rows = m - j0, ldq = qr_ldq(m);
-  unsigned int *state = w->counter, *arrive = w->counter + kPanelBar;
+  unsigned int *state = w->counter + half, *arrive = w->counter + kPanelBar;
   const unsigned gb = (unsigned)std::max<int64_t>(
       1, std::min<int64_t>(kGramMaxBlocks, (rows + 127) / 128));
   auto gram = [&](const double* P, int64_t ldp) {
@@ -2309,15 +2295,18 @@ static void qr_panel(double* A_, int64_t ld, int64_t m, int64_t j0, int bw, QrWo
   };
   gram(A, ld);
   hipLaunchKernelGGL(k_panel_chol, dim3(1), dim3(256), 0, st, bw, w->pan, state, arrive);
-  hipLaunchKernelGGL(k_panel_solve, dim3(cdiv(rows, 256)), dim3(256), 0, st, A, ld, w->Q, ldq,
-                     rows, bw, w->pan + kPanU1, w->pan + kPanRinv1, state);
+  const unsigned n1 = cdiv(rows, 256), n2 = rows > kTri ? cdiv(rows - kTri, 256) : 0;
+  const PanelSolve q1{A, ld, w->Q, ldq, rows, bw, w->pan + kPanU1, w->pan + kPanRinv1};
+  hipLaunchKernelGGL(k_panel_solve, dim3(n1), dim3(256), 0, st, q1, q1, (int)n1, state);
   gram(w->Q, ldq);
   hipLaunchKernelGGL(k_panel_vectors, dim3(1), dim3(256), 0, st, A, ld, rows, bw, w->Q, ldq,
                      w->pan, tau, state);
-  if (rows > kTri)
-    hipLaunchKernelGGL(k_panel_solve, dim3(cdiv(rows - kTri, 256)), dim3(256), 0, st, w->Q + kTri,
-                       ldq, A + kTri, ld, rows - kTri, bw, w->pan + kPanZ, w->pan + kPanRinvZ,
-                       state);
+  // V's other rows, and T in one block more
+  const PanelSolve v{w->Q + kTri, ldq, A + kTri, ld, rows - kTri, bw, w->pan + kPanZ,
+                     w->pan + kPanRinvZ};
+  const PanelSolve t{w->pan + kPanUS, kTri, w->T + half * kTri * kTri, kTri, kTri, kTri,
+                     w->pan + kPanV1, nullptr};
+  hipLaunchKernelGGL(k_panel_solve, dim3(n2 + 1), dim3(256), 0, st, v, t, (int)n2, state);
   // ends at once unless the panel's columns are numerically dependent
   double *red = w->red, *piv = w->red + 2 * kTri * kPanelMaxGrid;
   const int64_t G = std::min<int64_t>(col_capacity(), (rows + kColT - 1) / kColT);
@@ -2343,7 +2332,7 @@ void qr_factor(double* A, int64_t ld, int64_t m, int64_t ncols, int64_t n, QrWor
     for (int64_t j0 = o0; j0 < o0 + ow; j0 += kQrNB) {
       const int bw = (int)std::min<int64_t>(kQrNB, o0 + ow - j0);
       tm->begin(TM_QR_PANEL);
-      qr_panel(A, ld, m, j0, bw, w, st, dev_err);
+      qr_panel(A, ld, m, j0, bw, j0 > o0 ? 1 : 0, w, st, dev_err);
       tm->end(TM_QR_PANEL);
       if (j0 + bw >= o0 + ow) continue;
       // rest of the outer block with this 64-wide block's reflectors
