@@ -455,7 +455,7 @@ gap_status gap_workspace_query(gap_handle* h, const gap_atoms* a, const gap_spar
   L.take(sizeof(double) * N * M);  // S
   size_t knm = L.off;
   Layout F;
-  F.take(sizeof(double) * M * M);
+  F.take(sizeof(double) * gapk::chol_doubles(M));
   F.take(gapk::qr_workspace_bytes(n_rows + M, M));
   PredictWs pw;
   layout_predict(F, a, sp, true, true, true, true, pw);
@@ -723,7 +723,7 @@ gap_status gap_predict_variance(gap_handle* h, const gap_atoms* a, const gap_spa
   if (N == 0) return GAP_OK;
   const int64_t ldm = ld4(M);
   Layout L;
-  const size_t Lw = L.take(sizeof(double) * M * M);
+  const size_t Lw = L.take(sizeof(double) * gapk::chol_doubles(M));
   const size_t Ub = L.take(sizeof(double) * M * (M + 1));
   const size_t Yu = L.take(sizeof(double) * M * ldm);
   const size_t Yr = L.take(sizeof(double) * M * ldm);
@@ -776,7 +776,7 @@ gap_status gap_select_cur(gap_handle* h, const gap_atoms* a, int64_t n_sparse, d
   Layout L;
   const size_t Dd = L.take(sizeof(double) * N * ldd);
   const size_t Gw = L.take(sizeof(double) * D * D);
-  const size_t Lw = L.take(sizeof(double) * D * D);
+  const size_t Lw = L.take(sizeof(double) * gapk::chol_doubles(D));
   const size_t Ub = L.take(sizeof(double) * D * (D + 1));
   const size_t Yu = L.take(sizeof(double) * D * ldd);
   const size_t Zb = L.take(sizeof(double) * N * ldd);
@@ -917,7 +917,7 @@ gap_status gap_fold_init(gap_handle* h, double* T, int64_t ld, int64_t M, const 
   if (!Kmm) return fail(h, GAP_E_INVALID, "Kmm is NULL");
   if (!(jitter >= 0.0) || !std::isfinite(jitter)) return fail(h, GAP_E_INVALID, "bad jitter");
   Layout L;
-  const size_t Lw = L.take(sizeof(double) * M * M);
+  const size_t Lw = L.take(sizeof(double) * gapk::chol_doubles(M));
   s = ensure_ws(h, L.off);
   if (s != GAP_OK) return s;
   double* Lm = at<double>(h, Lw);
@@ -1100,7 +1100,7 @@ gap_status gap_fit(gap_handle* h, double* A, int64_t ld, int64_t n_rows, const d
     if (D > 2048) return fail(h, GAP_E_UNSUPPORTED, "refinement needs D <= 2048");
   }
   Layout L;
-  const size_t Lw = L.take(sizeof(double) * M * M);
+  const size_t Lw = L.take(sizeof(double) * gapk::chol_doubles(M));
   const size_t q = L.take(gapk::qr_workspace_bytes(m, M));
   size_t rbot = 0;
   RefineWs rw;

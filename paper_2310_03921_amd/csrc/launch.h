@@ -263,6 +263,8 @@ void stack_u(double* A, int64_t ld, int64_t n_rows, int64_t M, const double* L, 
              hipStream_t st);
 // In-place lower Cholesky of the M x M col-major matrix Lw (ld = ldl) after adding
 // jitter to its diagonal; the strict upper part is left untouched.
+// Lw holds chol_doubles(M) (with ldl = M), the factor first.
+int64_t chol_doubles(int64_t M);
 void cholesky_lower(double* Lw, int64_t ldl, int64_t M, double jitter, const double* Kmm,
                     int64_t ldk, int* dev_err, hipStream_t st);
 struct QrWork {

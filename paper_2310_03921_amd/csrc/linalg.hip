@@ -80,9 +80,11 @@ __global__ void k_chol_init(double* __restrict__ Lw, int64_t ldl, int64_t M, dou
 }
 
 // Lower triangle of the diagonal block at j0 (nbj <= 64 columns, completed with
-// unit columns) from L into S, factored, and back.
+// unit columns) from L into S, factored, and back; the inverses of its transposed
+// factor's 16 x 16 diagonal blocks go to inv (1024 doubles).
 GAP_DEV void chol_diag_block(double* __restrict__ Lw, int64_t ldl, int64_t j0, int nbj,
-                             double (*S)[kTriS], int* dev_err, bool load) {
+                             double (*S)[kTriS], double* __restrict__ inv, int* dev_err,
+                             bool load) {
   if (load)
     for (int e = threadIdx.x; e < kTri * kTri; e += 256) {
       const int r = e & 63, c = e >> 6;
@@ -91,6 +93,7 @@ GAP_DEV void chol_diag_block(double* __restrict__ Lw, int64_t ldl, int64_t j0, i
   __syncthreads();
   const bool bad = chol64_lds(S);
   if (bad && threadIdx.x == 0) atomicOr(dev_err, GAP_DEVERR_NOT_PD);
+  if (threadIdx.x < 64) tri_inv16([&](int i, int j) { return S[j][i]; }, inv);
   for (int e = threadIdx.x; e < kTri * kTri; e += 256) {
     const int r = e & 63, c = e >> 6;
     if (r >= c && r < nbj) Lw[(j0 + r) + (j0 + c) * ldl] = S[r][c];
@@ -98,40 +101,45 @@ GAP_DEV void chol_diag_block(double* __restrict__ Lw, int64_t ldl, int64_t j0, i
 }
 
 __global__ __launch_bounds__(256) void k_chol_diag(double* __restrict__ Lw, int64_t ldl, int64_t j0,
-                                                   int nbj, int* dev_err) {
+                                                   int nbj, double* __restrict__ inv,
+                                                   int* dev_err) {
   __shared__ double S[kTri][kTriS];
-  chol_diag_block(Lw, ldl, j0, nbj, S, dev_err, true);
+  chol_diag_block(Lw, ldl, j0, nbj, S, inv, dev_err, true);
 }
 
 // Rows below a full diagonal block: L[r, j0:j0+64] = A[r, j0:j0+64] L_dd^-T,
-// one row per lane in registers (34 us a block column when each entry waited
-// for the dot product before it and divided, 19 us now; latency: the loads, then
-// a chain of 64 columns).
-__global__ __launch_bounds__(64) void k_chol_panel(double* __restrict__ Lw, int64_t ldl, int64_t M,
-                                                   int64_t j0) {
-  __shared__ __attribute__((aligned(16))) double u[kTri * kTri];
-  __shared__ double rinv[kTri];
-  const uint32_t l = threadIdx.x;
-  const uint32_t r = (uint32_t)min(kTri + blockIdx.x * (int64_t)64 + l, M - j0 - 1);
+// sixteen rows per wave (34 us a block column when each entry waited for the dot
+// product before it and divided).
+__global__ __launch_bounds__(256) void k_chol_panel(double* __restrict__ Lw, int64_t ldl,
+                                                    int64_t M, int64_t j0,
+                                                    const double* __restrict__ inv) {
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane >> 4, idx = lane & 15;
+  const int64_t r0 = j0 + kTri + (blockIdx.x * (int64_t)4 + wave) * 16;
+  if (r0 >= M) return;
   double* A = Lw + j0 + j0 * ldl;
-  double x[kTri];
+  double* row = Lw + min(r0 + idx, M - 1) + j0 * ldl;
+  d4v x[4];
 #pragma unroll
-  for (int c = 0; c < kTri; ++c) u[c * kTri + l] = (A + c * ldl)[l];  // U[c][l] = L[l][c]
+  for (int b = 0; b < 4; ++b)
 #pragma unroll
-  for (int c = 0; c < kTri; ++c) x[c] = (A + c * ldl)[r];
-  rinv[l] = 1.0 / u[l * (kTri + 1)];  // (this lane's own write)
-  __syncthreads();
-  row_solve64(x, u, rinv);
+    for (int r = 0; r < 4; ++r) x[b][r] = row[(16 * b + g + 4 * r) * ldl];
+  TriOps t;
+  tri_ops(t, [&](int i, int j) { return A[j + i * ldl]; },  // U[i][j] = L[j][i]
+          [&](int e) { return inv[e]; });
+  tri_solve16(t, x);
   // lanes past the last row hold that row too and store the same values
 #pragma unroll
-  for (int c = 0; c < kTri; ++c) (A + c * ldl)[r] = x[c];
+  for (int b = 0; b < 4; ++b)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) row[(16 * b + g + 4 * r) * ldl] = x[b][r];
 }
 
 // C[r][c] -= sum_k P[r][k] P[c][k] on the lower trailing block (r >= c), P the
 // 64 columns at j0.  The first block goes on to factor its tile, the next
 // diagonal block, while the others run.
 __global__ __launch_bounds__(256) void k_chol_update(double* __restrict__ Lw, int64_t ldl,
-                                                     int64_t M, int64_t j0, int* dev_err) {
+                                                     int64_t M, int64_t j0,
+                                                     double* __restrict__ inv, int* dev_err) {
   __shared__ double S[kTri][kTriS];
   const int64_t t0 = j0 + kTri;
   const int64_t cbase = t0 + (int64_t)blockIdx.x * 64;  // columns (MFMA rows)
@@ -165,7 +173,8 @@ __global__ __launch_bounds__(256) void k_chol_update(double* __restrict__ Lw, in
         Lw[r + cc * ldl] = v;
     }
   }
-  if (next) chol_diag_block(Lw, ldl, t0, (int)min((int64_t)kTri, M - t0), S, dev_err, false);
+  if (next)
+    chol_diag_block(Lw, ldl, t0, (int)min((int64_t)kTri, M - t0), S, inv, dev_err, false);
 }
 
 // ------------------------------------------------------------------- QR ----
@@ -235,12 +244,14 @@ constexpr int kGramTiles = 10;                // lower 16 x 16 tiles of a 64 x 6
 constexpr int kGram = kGramTiles * 256;       // their values
 constexpr int kGramMaxBlocks = 256;
 // What the panel kernels keep between launches (doubles).
+constexpr int kInv16 = 4 * 256;               // inverses of a triangle's 16 x 16 diagonal blocks
 constexpr int kPanU1 = 0;                     // R1, row-major upper, 64 x 64
-constexpr int kPanRinv1 = kPanU1 + 4096;      // 1 / its diagonal
-constexpr int kPanZ = kPanRinv1 + 64;         // U R2, row-major upper
-constexpr int kPanRinvZ = kPanZ + 4096;
-constexpr int kPanV1 = kPanRinvZ + 64;        // V's top block transposed, row-major upper
-constexpr int kPanUS = kPanV1 + 4096;         // -U S, col-major
+constexpr int kPanInv1 = kPanU1 + 4096;
+constexpr int kPanZ = kPanInv1 + kInv16;      // U R2, row-major upper
+constexpr int kPanInvZ = kPanZ + 4096;
+constexpr int kPanV1 = kPanInvZ + kInv16;     // V's top block transposed, row-major upper
+constexpr int kPanInvV = kPanV1 + 4096;
+constexpr int kPanUS = kPanInvV + kInv16;     // -U S, col-major
 constexpr int kPanG = kPanUS + 4096;          // reduced Gram
 constexpr int kPanDoubles = kPanG + kGram;
 
@@ -337,43 +348,64 @@ __global__ __launch_bounds__(256) void k_panel_chol(int bw, double* __restrict__
     const int c = e >> 6, q = e & 63;  // U1[c][q] = L[q][c]
     pan[kPanU1 + e] = q >= c ? S[q][c] : 0.0;
   }
-  if (threadIdx.x < kTri) pan[kPanRinv1 + threadIdx.x] = 1.0 / S[threadIdx.x][threadIdx.x];
+  if (threadIdx.x < 64) tri_inv16([&](int i, int j) { return S[j][i]; }, pan + kPanInv1);
 }
 
-// dst <- src U^-1 (both col-major), a row per lane; U row-major and the
-// reciprocals of its diagonal (NULL: ones) go through LDS.  Blocks from na on
-// take problem b.
+// dst <- src U^-1 (both col-major, `bw` <= 64 columns), sixteen rows per wave at
+// a time with U (row-major) and the inverses of its diagonal blocks held as
+// operands in registers.  Blocks from na on take problem b.  Bound by the panel's
+// traffic where it has many rows; a row per lane with U broadcast from LDS took
+// 132 us at 349,000 rows (this one 94) and 18 us at 6,000 (12).
 struct PanelSolve {
   const double* src;
   int64_t lds;
   double* dst;
   int64_t ldd, rows;
   int bw;
-  const double *u, *rinv;
+  const double *u, *inv;
 };
-__global__ __launch_bounds__(256) void k_panel_solve(PanelSolve pa, PanelSolve pb, int na,
-                                                     const unsigned int* __restrict__ state) {
-  __shared__ __attribute__((aligned(16))) double u[kTri * kTri];
-  __shared__ double rinv[kTri];
+constexpr int kSolveBlocks = 512;  // of four waves: two per SIMD
+__global__ __launch_bounds__(256, 2) void k_panel_solve(PanelSolve pa, PanelSolve pb, int na,
+                                                        const unsigned int* __restrict__ state) {
   if (*state) return;
   const bool second = (int)blockIdx.x >= na;
   const PanelSolve p = second ? pb : pa;
-  const int64_t b = second ? (int)blockIdx.x - na : (int)blockIdx.x;
-  const uint32_t r = (uint32_t)min(b * 256 + threadIdx.x, p.rows - 1);
-  double x[kTri];
+  const int lane = threadIdx.x & 63, g = lane >> 4, idx = lane & 15;
+  const int64_t nt = (p.rows + 15) / 16, step = (second ? gridDim.x - na : na) * 4;
+  int64_t tile = (second ? blockIdx.x - na : blockIdx.x) * 4 + (threadIdx.x >> 6);
+  if (tile >= nt) return;
+  // columns 16 b + g + 4 r of row 16 tile + idx (past the last row: that row again,
+  // which stores the same values)
+  auto load = [&](int64_t ti, d4v (&x)[4]) {
+    const double* row = p.src + min(16 * ti + idx, p.rows - 1);
 #pragma unroll
-  for (int c = 0; c < kTri; ++c) x[c] = (p.src + (int64_t)min(c, p.bw - 1) * p.lds)[r];
-  for (int e = threadIdx.x; e < kTri * kTri / 2; e += 256)
-    reinterpret_cast<d2v*>(u)[e] = reinterpret_cast<const d2v*>(p.u)[e];
-  if (threadIdx.x < kTri) rinv[threadIdx.x] = p.rinv ? p.rinv[threadIdx.x] : 1.0;
-  __syncthreads();
+    for (int b = 0; b < 4; ++b)
 #pragma unroll
-  for (int c = 0; c < kTri; ++c) x[c] = c < p.bw ? x[c] : 0.0;
-  row_solve64(x, u, rinv);
-  // lanes past the last row hold that row too and store the same values
+      for (int r = 0; r < 4; ++r) x[b][r] = row[(int64_t)min(16 * b + g + 4 * r, p.bw - 1) * p.lds];
+  };
+  d4v cur[4], nxt[4];
+  load(tile, cur);
+  TriOps t;
+  tri_ops(t, [&](int i, int j) { return p.u[i * kTri + j]; }, [&](int e) { return p.inv[e]; });
+  for (; tile < nt; tile += step) {
+    load(min(tile + step, nt - 1), nxt);
+    __builtin_amdgcn_sched_barrier(0);
+    d4v x[4];
 #pragma unroll
-  for (int c = 0; c < kTri; ++c)
-    if (c < p.bw) (p.dst + c * p.ldd)[r] = x[c];
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) x[b][r] = 16 * b + g + 4 * r < p.bw ? cur[b][r] : 0.0;
+    tri_solve16(t, x);
+    double* row = p.dst + min(16 * tile + idx, p.rows - 1);
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int c = 16 * b + g + 4 * r;
+        if (c < p.bw) row[c * p.ldd] = x[b][r];
+        cur[b][r] = nxt[b][r];
+      }
+  }
 }
 
 // LU without pivoting of B - diag(sg) for B (64 x 64, in LDS), sg_j = -sign of
@@ -405,20 +437,19 @@ GAP_DEV void lu64_signs(double (*B)[kTriS], double* sg) {
 #pragma unroll
         for (int c = 0; c < 16; ++c) B[lane][c0 + c] = v[c];
       }
-    }
-    __syncthreads();
-    if (wave == 0 && s < 3) {  // U12 = L11^-1 B12, a column per lane
-      const int col = min(c0 + 16 + lane, kTri - 1);
-      double y[16];
+      if (s < 3) {  // U12 = L11^-1 B12, a column per lane (L11 from the rows' lanes)
+        const int col = min(c0 + 16 + lane, kTri - 1);
+        double y[16];
 #pragma unroll
-      for (int i = 0; i < 16; ++i) y[i] = B[c0 + i][col];
+        for (int i = 0; i < 16; ++i) y[i] = B[c0 + i][col];
 #pragma unroll
-      for (int i = 0; i < 16; ++i)
+        for (int i = 0; i < 16; ++i)
 #pragma unroll
-        for (int k = i + 1; k < 16; ++k) y[k] -= B[c0 + k][c0 + i] * y[i];
-      if (c0 + 16 + lane < kTri) {
+          for (int k = i + 1; k < 16; ++k) y[k] -= readlane_f64(v[i], c0 + k) * y[i];
+        if (c0 + 16 + lane < kTri) {
 #pragma unroll
-        for (int i = 1; i < 16; ++i) B[c0 + i][col] = y[i];
+          for (int i = 1; i < 16; ++i) B[c0 + i][col] = y[i];
+        }
       }
     }
     __syncthreads();
@@ -467,7 +498,9 @@ GAP_DEV void upper_product64(FA a, FB b, FP put) {
 
 // The one-block middle of the panel: R2 from the second Gram, the test that Q
 // was near enough to orthonormal, the signs and L, U of Q^'s top rows, and from
-// them R and V's top in A, tau, and Z = U R2 (V's other rows are q Z^-1).
+// them R and V's top in A, tau, Z = U R2 (V's other rows are q Z^-1) and the
+// operands of T.  Bound by latency: 55 us, half of it the 64 columns of the
+// Cholesky factor and the 64 of the LU.
 __global__ __launch_bounds__(256) void k_panel_vectors(double* __restrict__ A, int64_t ld,
                                                        int64_t rows, int bw,
                                                        const double* __restrict__ Q, int64_t ldq,
@@ -475,11 +508,20 @@ __global__ __launch_bounds__(256) void k_panel_vectors(double* __restrict__ A, i
                                                        double* __restrict__ tau,
                                                        unsigned int* __restrict__ state) {
   __shared__ double S[kTri][kTriS], B[kTri][kTriS];
-  __shared__ __attribute__((aligned(16))) double u[kTri * kTri];
-  __shared__ double rinv[kTri], sg[kTri];
+  __shared__ double u[kTri * kTri], inv[kInv16];
+  __shared__ double sg[kTri];
   __shared__ int s_bad;
   if (*state) return;  // uniform: a whole-grid condition
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane >> 4, idx = lane & 15;
   if (threadIdx.x == 0) s_bad = 0;
+  // Q's top rows, sixteen per wave, on their way while R2 is formed
+  const int64_t qr = 16 * wave + idx;
+  d4v x[4];
+#pragma unroll
+  for (int b = 0; b < 4; ++b)
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      x[b][r] = Q[(int64_t)min(16 * b + g + 4 * r, bw - 1) * ldq + min(qr, rows - 1)];
   gram_to_lds(pan + kPanG, bw, S);
   __syncthreads();
   bool far = false;
@@ -494,32 +536,32 @@ __global__ __launch_bounds__(256) void k_panel_vectors(double* __restrict__ A, i
     return;
   }
   (void)chol64_lds(S);  // diagonally dominant: no bad pivot
-  for (int e = threadIdx.x; e < kTri * kTri; e += 256) {
-    const int c = e >> 6, q = e & 63;
-    u[e] = q >= c ? S[q][c] : 0.0;  // R2
+  if (wave == 0) {
+    tri_inv16([&](int i, int j) { return S[j][i]; }, inv);
+  } else {
+    for (int e = threadIdx.x - 64; e < kTri * kTri; e += 192) {
+      const int c = e >> 6, q = e & 63;
+      u[e] = q >= c ? S[q][c] : 0.0;  // R2
+    }
   }
-  if (threadIdx.x < kTri) rinv[threadIdx.x] = 1.0 / S[threadIdx.x][threadIdx.x];
   __syncthreads();
-  if (threadIdx.x < 64) {  // Q^'s top rows, one per lane
-    const int l = threadIdx.x;
-    double x[kTri];
+  {  // Q^'s top rows
+    TriOps t;
+    tri_ops(t, [&](int i, int j) { return u[i * kTri + j]; }, [&](int e) { return inv[e]; });
 #pragma unroll
-    for (int c = 0; c < kTri; ++c)
-      x[c] = Q[(int64_t)min(c, bw - 1) * ldq + min((int64_t)l, rows - 1)];
+    for (int b = 0; b < 4; ++b)
 #pragma unroll
-    for (int c = 0; c < kTri; ++c) x[c] = c < bw && l < rows ? x[c] : 0.0;
-    row_solve64(x, u, rinv);
+      for (int r = 0; r < 4; ++r)
+        x[b][r] = 16 * b + g + 4 * r < bw && qr < rows ? x[b][r] : 0.0;
+    tri_solve16(t, x);
 #pragma unroll
-    for (int c = 0; c < kTri; ++c) B[l][c] = x[c];
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) B[qr][16 * b + g + 4 * r] = x[b][r];
   }
   __syncthreads();
   lu64_signs(B, sg);
-  // V's top rows (unit lower) and R = S R2 R1
-  for (int e = threadIdx.x; e < kTri * kTri; e += 256) {
-    const int r = e & 63, c = e >> 6;
-    if (r > c && r < rows && c < bw) A[r + c * ld] = B[r][c];
-  }
-  if (threadIdx.x < bw) tau[threadIdx.x] = -B[threadIdx.x][threadIdx.x] * sg[threadIdx.x];
+  // R = S R2 R1 and Z = U R2 (S, the LDS array, is free for Z)
   const double* u1 = pan + kPanU1;
   upper_product64([&](int i, int k) { return u[i * kTri + k]; },
                   [&](int k, int j) { return u1[k * kTri + j]; },
@@ -528,15 +570,28 @@ __global__ __launch_bounds__(256) void k_panel_vectors(double* __restrict__ A, i
                   });
   upper_product64([&](int i, int k) { return B[i][k]; },
                   [&](int k, int j) { return u[k * kTri + j]; },
-                  [&](int i, int j, double v) { pan[kPanZ + i * kTri + j] = v; });
-  if (threadIdx.x < kTri)
-    pan[kPanRinvZ + threadIdx.x] =
-        1.0 / (B[threadIdx.x][threadIdx.x] * u[threadIdx.x * (kTri + 1)]);
-  // T = (-U S) V1^-T: the rows of -U S and V1^T for the substitution
-  for (int e = threadIdx.x; e < kTri * kTri; e += 256) {
-    const int c = e >> 6, q = e & 63;
-    pan[kPanV1 + e] = q > c ? B[q][c] : (q == c ? 1.0 : 0.0);
-    pan[kPanUS + e] = q <= c ? -B[q][c] * sg[c] : 0.0;
+                  [&](int i, int j, double v) {
+                    pan[kPanZ + i * kTri + j] = v;
+                    S[i][j] = v;
+                  });
+  __syncthreads();
+  if (wave == 0) {
+    tri_inv16([&](int i, int j) { return S[i][j]; }, pan + kPanInvZ);
+  } else if (wave == 1) {
+    tri_inv16([&](int i, int j) { return i == j ? 1.0 : B[j][i]; }, pan + kPanInvV);
+  } else {
+    // V's top rows (unit lower), tau, and T = (-U S) V1^-T: the rows of -U S and
+    // V1^T for its solution
+    if (threadIdx.x - 128 < bw) {
+      const int j = threadIdx.x - 128;
+      tau[j] = -B[j][j] * sg[j];
+    }
+    for (int e = threadIdx.x - 128; e < kTri * kTri; e += 128) {
+      const int c = e >> 6, q = e & 63;
+      if (q > c && q < rows && c < bw) A[q + c * ld] = B[q][c];
+      pan[kPanV1 + e] = q > c ? B[q][c] : (q == c ? 1.0 : 0.0);
+      pan[kPanUS + e] = q <= c ? -B[q][c] * sg[c] : 0.0;
+    }
   }
 }
 
@@ -1754,38 +1809,48 @@ __global__ __launch_bounds__(1024) void k_trsv_blk(const double* __restrict__ R,
 
 // Inverses of the 64 x 64 diagonal blocks of upper-triangular matrices (col-
 // major, ld) into the diagonal blocks of Y (row-major, ldy), zero below the
-// diagonal; a lane per row of Y, which solves y R = e_r by substitution.  One
-// block per (diagonal block, matrix).
-__global__ __launch_bounds__(64) void k_trinv_diag(const double* __restrict__ R0, int64_t ld0,
-                                                   double* __restrict__ Y0,
-                                                   const double* __restrict__ R1, int64_t ld1,
-                                                   double* __restrict__ Y1, int64_t n,
-                                                   int64_t ldy, int* dev_err) {
-  __shared__ __attribute__((aligned(16))) double u[kTri * kTri];
-  __shared__ double rinv[kTri];
-  const int l = threadIdx.x;
+// diagonal: the rows of the unit matrix solved against the block, sixteen per
+// wave.  One block per (diagonal block, matrix).
+__global__ __launch_bounds__(256) void k_trinv_diag(const double* __restrict__ R0, int64_t ld0,
+                                                    double* __restrict__ Y0,
+                                                    const double* __restrict__ R1, int64_t ld1,
+                                                    double* __restrict__ Y1, int64_t n,
+                                                    int64_t ldy, int* dev_err) {
+  __shared__ double u[kTri][kTriS];
+  __shared__ double inv[kInv16];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane >> 4, idx = lane & 15;
   const int64_t j0 = (int64_t)blockIdx.x * kTri, ld = blockIdx.y ? ld1 : ld0;
   const double* R = (blockIdx.y ? R1 : R0) + j0 + j0 * ld;
   const int w = (int)min((int64_t)kTri, n - j0);
-#pragma unroll 16
-  for (int c = 0; c < kTri; ++c)  // column c, rows 0 .. c; unit rows past the matrix
-    u[l * kTri + c] = (l <= c && c < w) ? R[l + c * ld] : (l == c ? 1.0 : 0.0);
-  const double d = u[l * (kTri + 1)];
-  if (d == 0.0 || !isfinite(d)) atomicOr(dev_err, GAP_DEVERR_RANK);
-  rinv[l] = 1.0 / d;
-  __syncthreads();
-  double x[kTri];
-#pragma unroll
-  for (int c = 0; c < kTri; ++c) {
-    x[c] = c == l ? 1.0 : 0.0;
-    asm volatile("" : "+v"(x[c]));  // (64 lane masks carried through the substitution spill)
+  for (int e = threadIdx.x; e < kTri * kTri; e += 256) {  // unit rows past the matrix
+    const int r = e & 63, c = e >> 6;
+    u[r][c] = (r <= c && c < w) ? R[r + c * ld] : (r == c ? 1.0 : 0.0);
   }
-  row_solve64(x, u, rinv);
-  if (l >= w) return;
-  double* y = (blockIdx.y ? Y1 : Y0) + (j0 + l) * ldy + j0;
+  __syncthreads();
+  if (wave == 0) {
+    const double d = u[lane][lane];
+    if (d == 0.0 || !isfinite(d)) atomicOr(dev_err, GAP_DEVERR_RANK);
+    tri_inv16([&](int i, int j) { return u[i][j]; }, inv);
+  }
+  __syncthreads();
+  TriOps t;
+  tri_ops(t, [&](int i, int j) { return u[i][j]; }, [&](int e) { return inv[e]; });
+  const int row = 16 * wave + idx;
+  d4v x[4];
 #pragma unroll
-  for (int c = 0; c < kTri; ++c)
-    if (c < w) y[c] = x[c];
+  for (int b = 0; b < 4; ++b)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) x[b][r] = row == 16 * b + g + 4 * r ? 1.0 : 0.0;
+  tri_solve16(t, x);
+  if (row >= w) return;
+  double* y = (blockIdx.y ? Y1 : Y0) + (j0 + row) * ldy + j0;
+#pragma unroll
+  for (int b = 0; b < 4; ++b)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int c = 16 * b + g + 4 * r;
+      if (c < w) y[c] = c < row ? 0.0 : x[b][r];
+    }
 }
 
 // var[i] += sign * sum_j Z[i][j]^2 (row-major Z, one wave per row); with
@@ -2136,14 +2201,18 @@ void cholesky_lower(double* Lw, int64_t ldl, int64_t M, double jitter, const dou
                     int64_t ldk, int* dev_err, hipStream_t st) {
   hipLaunchKernelGGL(k_chol_init, dim3(cdiv(M, 256), (unsigned)M), dim3(256), 0, st, Lw, ldl, M,
                      jitter, Kmm, ldk);
+  double* inv = Lw + M * ldl;  // of the current diagonal block
   hipLaunchKernelGGL(k_chol_diag, dim3(1), dim3(256), 0, st, Lw, ldl, (int64_t)0,
-                     (int)std::min<int64_t>(kTri, M), dev_err);
+                     (int)std::min<int64_t>(kTri, M), inv, dev_err);
   for (int64_t j0 = 0; j0 + kTri < M; j0 += kTri) {
     const unsigned nt = cdiv(M - j0 - kTri, kTri);
-    hipLaunchKernelGGL(k_chol_panel, dim3(nt), dim3(64), 0, st, Lw, ldl, M, j0);
-    hipLaunchKernelGGL(k_chol_update, dim3(nt, nt), dim3(256), 0, st, Lw, ldl, M, j0, dev_err);
+    hipLaunchKernelGGL(k_chol_panel, dim3(nt), dim3(256), 0, st, Lw, ldl, M, j0, inv);
+    hipLaunchKernelGGL(k_chol_update, dim3(nt, nt), dim3(256), 0, st, Lw, ldl, M, j0, inv,
+                       dev_err);
   }
 }
+
+int64_t chol_doubles(int64_t M) { return M * M + 1024; }
 
 // Rows per slab of the 128-wide W = V^T C of rows [j0, m) and nct columns: at
 // most 256 slabs, of >= 2048 rows where those alone give about two blocks per
@@ -2295,17 +2364,18 @@ static void qr_panel(double* A_, int64_t ld, int64_t m, int64_t j0, int bw, int 
   };
   gram(A, ld);
   hipLaunchKernelGGL(k_panel_chol, dim3(1), dim3(256), 0, st, bw, w->pan, state, arrive);
-  const unsigned n1 = cdiv(rows, 256), n2 = rows > kTri ? cdiv(rows - kTri, 256) : 0;
-  const PanelSolve q1{A, ld, w->Q, ldq, rows, bw, w->pan + kPanU1, w->pan + kPanRinv1};
+  auto blocks = [](int64_t r) { return (unsigned)std::min<int64_t>((r + 63) / 64, kSolveBlocks); };
+  const unsigned n1 = blocks(rows), n2 = rows > kTri ? blocks(rows - kTri) : 0;
+  const PanelSolve q1{A, ld, w->Q, ldq, rows, bw, w->pan + kPanU1, w->pan + kPanInv1};
   hipLaunchKernelGGL(k_panel_solve, dim3(n1), dim3(256), 0, st, q1, q1, (int)n1, state);
   gram(w->Q, ldq);
   hipLaunchKernelGGL(k_panel_vectors, dim3(1), dim3(256), 0, st, A, ld, rows, bw, w->Q, ldq,
                      w->pan, tau, state);
   // V's other rows, and T in one block more
   const PanelSolve v{w->Q + kTri, ldq, A + kTri, ld, rows - kTri, bw, w->pan + kPanZ,
-                     w->pan + kPanRinvZ};
+                     w->pan + kPanInvZ};
   const PanelSolve t{w->pan + kPanUS, kTri, w->T + half * kTri * kTri, kTri, kTri, kTri,
-                     w->pan + kPanV1, nullptr};
+                     w->pan + kPanV1, w->pan + kPanInvV};
   hipLaunchKernelGGL(k_panel_solve, dim3(n2 + 1), dim3(256), 0, st, v, t, (int)n2, state);
   // ends at once unless the panel's columns are numerically dependent
   double *red = w->red, *piv = w->red + 2 * kTri * kPanelMaxGrid;
@@ -2446,7 +2516,7 @@ void trinv_upper2(const double* R0, int64_t ld0, double* Y0, const double* R1, i
                   double* Y1, int64_t n, int64_t ldy, double* tmp, int* dev_err, hipStream_t st) {
   if (n <= 0) return;
   const int nz = R1 ? 2 : 1;
-  hipLaunchKernelGGL(k_trinv_diag, dim3(cdiv(n, kTri), nz), dim3(64), 0, st, R0, ld0, Y0, R1, ld1,
+  hipLaunchKernelGGL(k_trinv_diag, dim3(cdiv(n, kTri), nz), dim3(256), 0, st, R0, ld0, Y0, R1, ld1,
                      Y1, n, ldy, dev_err);
   for (int64_t s = kTri; s < n; s *= 2) {
     small_trinv_level(R0, ld0, Y0, ldy, n, s, tmp, st);

@@ -1,21 +1,24 @@
 // 64 x 64 triangular building blocks in FP64: Cholesky factorisation of a block
-// held in LDS, and substitution of rows held in registers against an upper
-// triangle held in LDS.
+// held in LDS, and the solution of rows held in registers against an upper
+// triangle, on the matrix cores.
 #pragma once
-
-#include <utility>
 
 #include "common.h"
 
 constexpr int kTri = 64;
 constexpr int kTriS = kTri + 1;  // row stride of a block in LDS: columns read conflict-free
 
-// 1 / sqrt(p) for p > 0: the hardware estimate and two Newton steps.
+// 1 / sqrt(p) for p > 0 and 1 / d: the hardware estimate and one third-order
+// step (its relative error e becomes of the order of e^3, below rounding).
 GAP_DEV double rsqrt_f64(double p) {
-  double r = __builtin_amdgcn_rsq(p);
-#pragma unroll
-  for (int i = 0; i < 2; ++i) r = fma(r, 0.5 * fma(-p * r, r, 1.0), r);
-  return r;
+  const double r = __builtin_amdgcn_rsq(p);
+  const double e = fma(-p * r, r, 1.0);
+  return fma(r * e, fma(0.375, e, 0.5), r);
+}
+GAP_DEV double rcp_f64(double d) {
+  const double r = __builtin_amdgcn_rcp(d);
+  const double e = fma(-d, r, 1.0);
+  return fma(r * e, 1.0 + e, r);
 }
 
 GAP_DEV double readlane_f64(double v, int lane) {
@@ -80,74 +83,70 @@ GAP_DEV bool chol64_lds(double (*S)[kTriS]) {
   return bad;
 }
 
-// 1 / d: the hardware estimate and two Newton steps (0 and non-finite d give
-// what the estimate gives).
-GAP_DEV double rcp_f64(double d) {
-  const double r0 = __builtin_amdgcn_rcp(d);
-  double r = r0;
+// Inverses of the four 16 x 16 diagonal blocks of an upper triangle u(i, j), by
+// one wave, a row per lane: inv[256 b + 16 i + c], zero below the diagonal.
+template <class FU>
+GAP_DEV void tri_inv16(FU u, double* inv) {
+  const int lane = threadIdx.x & 63, o = lane & 48, i = lane & 15;
+  double y[16];
 #pragma unroll
-  for (int i = 0; i < 2; ++i) r = fma(r, fma(-d, r, 1.0), r);
-  return isfinite(r) ? r : r0;
+  for (int c = 0; c < 16; ++c) y[c] = c == i ? 1.0 : 0.0;
+#pragma unroll
+  for (int c = 0; c < 16; ++c) {
+    y[c] *= rcp_f64(u(o + c, o + c));
+#pragma unroll
+    for (int q = c + 1; q < 16; ++q) y[q] = fma(-y[c], u(o + c, o + q), y[q]);
+  }
+#pragma unroll
+  for (int c = 0; c < 16; ++c) inv[16 * o + 16 * i + c] = y[c];
 }
 
-// The groups of sixteen entries (c, 16 k .. 16 k + 15) of U right of its
-// diagonal, in the order row_solve64 needs them.
-struct TriGroups {
-  static constexpr int n = 156;
-  int c[n], k[n];
-  constexpr TriGroups() : c(), k() {
-    int i = 0;
-    for (int cc = 0; cc < kTri - 1; ++cc)
-      for (int kk = (cc + 1) / 16; kk < kTri / 16; ++kk, ++i) c[i] = cc, k[i] = kk;
-  }
+// Operands of x <- x U^-1 on the matrix cores for 16 rows x per wave: the 16 x 16
+// blocks of U right of and on its diagonal (negated) and the inverses of the
+// diagonal blocks.  As first operand (i = column of U, k = row): lane (g, idx)
+// holds U[16 kb + g + 4 r][16 b + idx] for r = 0 .. 3.
+struct TriOps {
+  d4v off[6], dia[4], inv[4];  // off: (kb, b) = (0,1) (0,2) (1,2) (0,3) (1,3) (2,3)
 };
-constexpr TriGroups kTriGroups;
-constexpr int kTriAhead = 3;  // groups read ahead
-
-template <int I>
-GAP_DEV void tri_read(d2v (&buf)[kTriAhead + 1][8], const d2v* u2) {
-  if constexpr (I < TriGroups::n) {
-    constexpr int c = kTriGroups.c[I], k = kTriGroups.k[I];
+template <class FU, class FI>
+GAP_DEV void tri_ops(TriOps& t, FU u, FI inv) {
+  const int lane = threadIdx.x & 63, g = lane >> 4, idx = lane & 15;
 #pragma unroll
-    for (int h = 0; h < 8; ++h)
-      if (16 * k + 2 * h + 1 > c) buf[I % (kTriAhead + 1)][h] = u2[c * (kTri / 2) + 8 * k + h];
+  for (int b = 0; b < 4; ++b) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int k = g + 4 * r;
+      t.dia[b][r] = k <= idx ? -u(16 * b + k, 16 * b + idx) : 0.0;
+      t.inv[b][r] = inv(256 * b + 16 * k + idx);
+    }
+#pragma unroll
+    for (int kb = 0; kb < b; ++kb)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        t.off[b * (b - 1) / 2 + kb][r] = -u(16 * kb + g + 4 * r, 16 * b + idx);
   }
 }
-template <int I>
-GAP_DEV void tri_step(double (&x)[kTri], d2v (&buf)[kTriAhead + 1][8], const d2v* u2,
-                      const double* rinv) {
-  constexpr int c = kTriGroups.c[I], k = kTriGroups.k[I];
-  if constexpr (k == (c + 1) / 16) x[c] *= rinv[c];
-  tri_read<I + kTriAhead>(buf, u2);
-  __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-  for (int q = 0; q < 16; ++q)
-    if (16 * k + q > c)
-      x[16 * k + q] = fma(-x[c], buf[I % (kTriAhead + 1)][q / 2][q & 1], x[16 * k + q]);
-}
-template <int... I>
-GAP_DEV void tri_steps(double (&x)[kTri], const d2v* u2, const double* rinv,
-                       std::integer_sequence<int, I...>) {
-  d2v buf[kTriAhead + 1][8];
-  tri_read<0>(buf, u2);
-  tri_read<1>(buf, u2);
-  tri_read<2>(buf, u2);
-  (tri_step<I>(x, buf, u2, rinv), ...);
-}
 
-// x <- x U^-1 for a lane's row x: U[c][q] (q >= c) at u[c * kTri + q] and the
-// reciprocal diagonal at rinv[c], in LDS (u 16-byte aligned), the same for every
-// lane.  Right-looking, so the updates of one column are independent of each
-// other, with the entries of U read three groups of sixteen ahead of their use.
-// (Left to the compiler's schedule the wave waits for a read at nearly every
-// step; scalar loads of U from global memory cost a cache miss per eight
-// entries, 57 us in all.)
-GAP_DEV void row_solve64(double (&x)[kTri], const double* u, const double* rinv) {
-  tri_steps(x, reinterpret_cast<const d2v*>(u), rinv,
-            std::make_integer_sequence<int, TriGroups::n>{});
-  x[kTri - 1] *= rinv[kTri - 1];
-  // the values are made here: sunk to a guarded store after this, the updates
-  // would leave all reads of U behind, and spill
+// x <- x U^-1 for a wave's 16 rows: x[b][r] of lane (g, idx) is row idx, column
+// 16 b + g + 4 r (the matrix core's result layout of the transpose, which is
+// also what the next product takes as its second operand).  Each 16-column block
+// is multiplied by the inverse of its diagonal block and corrected once with its
+// residual, which leaves a backward error of rounding size, as a substitution
+// does, while that block's condition is below 1e8 (it enters squared, times
+// u^2).  The substitution column by column took four times as long (33,000 cycles
+// against 72 dependent matrix instructions for the 64 columns).
+GAP_DEV void tri_solve16(const TriOps& t, d4v (&x)[4]) {
+  auto mul = [](const d4v& a, const d4v& b, d4v c) {
 #pragma unroll
-  for (int c = 0; c < kTri; ++c) asm volatile("" : "+v"(x[c]));
+    for (int r = 0; r < 4; ++r) c = mfma_f64(a[r], b[r], c);
+    return c;
+  };
+#pragma unroll
+  for (int b = 0; b < 4; ++b) {
+    d4v a = x[b];
+#pragma unroll
+    for (int kb = 0; kb < b; ++kb) a = mul(t.off[b * (b - 1) / 2 + kb], x[kb], a);
+    const d4v y = mul(t.inv[b], a, zero4());
+    x[b] = mul(t.inv[b], mul(t.dia[b], y, a), y);
+  }
 }
