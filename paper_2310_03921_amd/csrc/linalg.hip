@@ -237,8 +237,8 @@ GAP_DEV void grid_barrier_x8(unsigned int* arrive, unsigned int round, int* dev_
 // in the register-resident reduction this replaces, cost 6.8 us a column at
 // 26,000 rows and 9.7 us at 353,000 (0.43 and 0.62 ms per 64 columns, and 0.13
 // and 0.34 ms more for the updates between its 16-column steps); this takes
-// 0.15 and 0.36 ms, at the small end the latency of its one-block steps
-// (k_panel_vectors 60 us, k_panel_chol 18 us), at the large end the passes over
+// 0.11 and 0.32 ms, at the small end the latency of its one-block steps
+// (k_panel_vectors 47 us, k_panel_chol 18 us), at the large end the passes over
 // the panel.
 constexpr int kGramTiles = 10;                // lower 16 x 16 tiles of a 64 x 64 Gram
 constexpr int kGram = kGramTiles * 256;       // their values
@@ -323,26 +323,36 @@ __global__ __launch_bounds__(256) void k_panel_gram(const double* __restrict__ P
 }
 
 // The reduced Gram (layout of k_panel_gram) into the lower triangle of S, with
-// unit columns from bw on.
-GAP_DEV void gram_to_lds(const double* __restrict__ G, int bw, double (*S)[kTriS]) {
-  for (int e = threadIdx.x; e < kGram; e += 256) {
+// unit columns from bw on.  Returns whether this thread saw an entry further than
+// `far` from the unit matrix (or not a number).
+GAP_DEV bool gram_to_lds(const double* __restrict__ G, int bw, double (*S)[kTriS], double far) {
+  bool off = false;
+#pragma unroll
+  for (int e0 = 0; e0 < kGram; e0 += 256) {
+    const int e = e0 + threadIdx.x;
     const int t = e >> 8, q = (e >> 6) & 3, lane = e & 63;
     const int i = t < 1 ? 0 : t < 3 ? 1 : t < 6 ? 2 : 3, j = t - i * (i + 1) / 2;
     const int r = 16 * i + (lane >> 4) + 4 * q, c = 16 * j + (lane & 15);
-    if (r >= c) S[r][c] = r < bw ? G[e] : (r == c ? 1.0 : 0.0);
+    const double v = G[e], unit = r == c ? 1.0 : 0.0;
+    if (r >= c) {
+      S[r][c] = r < bw ? v : unit;
+      off |= r < bw && !(fabs(v - unit) < far);
+    }
   }
+  return off;
 }
 
-// R1 of the first Gram; clears the panel's state word and the barrier counters
-// of k_qr_panel_col.
-__global__ __launch_bounds__(256) void k_panel_chol(int bw, double* __restrict__ pan,
+// R1 of the first Gram; sets the panel's state word (state[half], also set where
+// the outer block's first panel is) and clears the barrier counters of
+// k_qr_panel_col.
+__global__ __launch_bounds__(256) void k_panel_chol(int bw, int half, double* __restrict__ pan,
                                                     unsigned int* __restrict__ state,
                                                     unsigned int* __restrict__ arrive) {
   __shared__ double S[kTri][kTriS];
-  gram_to_lds(pan + kPanG, bw, S);
+  (void)gram_to_lds(pan + kPanG, bw, S, INFINITY);
   __syncthreads();
   const bool bad = chol64_lds(S);
-  if (threadIdx.x == 0) *state = bad ? 1u : 0u;
+  if (threadIdx.x == 0) state[half] = bad || (half && state[0]) ? 1u : 0u;
   if (threadIdx.x < kPanelBarWords) arrive[threadIdx.x] = 0u;
   for (int e = threadIdx.x; e < kTri * kTri; e += 256) {
     const int c = e >> 6, q = e & 63;  // U1[c][q] = L[q][c]
@@ -437,19 +447,20 @@ GAP_DEV void lu64_signs(double (*B)[kTriS], double* sg) {
 #pragma unroll
         for (int c = 0; c < 16; ++c) B[lane][c0 + c] = v[c];
       }
-      if (s < 3) {  // U12 = L11^-1 B12, a column per lane (L11 from the rows' lanes)
-        const int col = min(c0 + 16 + lane, kTri - 1);
-        double y[16];
+    }
+    __syncthreads();
+    if (wave == 0 && s < 3) {  // U12 = L11^-1 B12, a column per lane
+      const int col = min(c0 + 16 + lane, kTri - 1);
+      double y[16];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) y[i] = B[c0 + i][col];
+      for (int i = 0; i < 16; ++i) y[i] = B[c0 + i][col];
 #pragma unroll
-        for (int i = 0; i < 16; ++i)
+      for (int i = 0; i < 16; ++i)
 #pragma unroll
-          for (int k = i + 1; k < 16; ++k) y[k] -= readlane_f64(v[i], c0 + k) * y[i];
-        if (c0 + 16 + lane < kTri) {
+        for (int k = i + 1; k < 16; ++k) y[k] -= B[c0 + k][c0 + i] * y[i];
+      if (c0 + 16 + lane < kTri) {
 #pragma unroll
-          for (int i = 1; i < 16; ++i) B[c0 + i][col] = y[i];
-        }
+        for (int i = 1; i < 16; ++i) B[c0 + i][col] = y[i];
       }
     }
     __syncthreads();
@@ -499,7 +510,7 @@ GAP_DEV void upper_product64(FA a, FB b, FP put) {
 // The one-block middle of the panel: R2 from the second Gram, the test that Q
 // was near enough to orthonormal, the signs and L, U of Q^'s top rows, and from
 // them R and V's top in A, tau, Z = U R2 (V's other rows are q Z^-1) and the
-// operands of T.  Bound by latency: 55 us, half of it the 64 columns of the
+// operands of T.  Bound by latency: 47 us, half of it the 64 columns of the
 // Cholesky factor and the 64 of the LU.
 __global__ __launch_bounds__(256) void k_panel_vectors(double* __restrict__ A, int64_t ld,
                                                        int64_t rows, int bw,
@@ -508,7 +519,8 @@ __global__ __launch_bounds__(256) void k_panel_vectors(double* __restrict__ A, i
                                                        double* __restrict__ tau,
                                                        unsigned int* __restrict__ state) {
   __shared__ double S[kTri][kTriS], B[kTri][kTriS];
-  __shared__ double u[kTri * kTri], inv[kInv16];
+  __shared__ __attribute__((aligned(16))) double u[kTri * kTri], u1[kTri * kTri];
+  __shared__ double inv[kInv16];
   __shared__ double sg[kTri];
   __shared__ int s_bad;
   if (*state) return;  // uniform: a whole-grid condition
@@ -522,14 +534,12 @@ __global__ __launch_bounds__(256) void k_panel_vectors(double* __restrict__ A, i
 #pragma unroll
     for (int r = 0; r < 4; ++r)
       x[b][r] = Q[(int64_t)min(16 * b + g + 4 * r, bw - 1) * ldq + min(qr, rows - 1)];
-  gram_to_lds(pan + kPanG, bw, S);
-  __syncthreads();
-  bool far = false;
-  for (int e = threadIdx.x; e < kTri * kTri; e += 256) {
-    const int r = e & 63, c = e >> 6;
-    if (r >= c) far |= !(fabs(S[r][c] - (r == c ? 1.0 : 0.0)) < 1.0 / 64);
-  }
-  if (far) s_bad = 1;
+  d2v r1[8];  // this thread's share of R1
+#pragma unroll
+  for (int i = 0; i < 8; ++i)
+    r1[i] = reinterpret_cast<const d2v*>(pan + kPanU1)[i * 256 + threadIdx.x];
+  __syncthreads();  // s_bad
+  if (gram_to_lds(pan + kPanG, bw, S, 1.0 / 64)) s_bad = 1;
   __syncthreads();
   if (s_bad) {
     if (threadIdx.x == 0) *state = 1u;
@@ -544,6 +554,8 @@ __global__ __launch_bounds__(256) void k_panel_vectors(double* __restrict__ A, i
       u[e] = q >= c ? S[q][c] : 0.0;  // R2
     }
   }
+#pragma unroll
+  for (int i = 0; i < 8; ++i) reinterpret_cast<d2v*>(u1)[i * 256 + threadIdx.x] = r1[i];
   __syncthreads();
   {  // Q^'s top rows
     TriOps t;
@@ -562,7 +574,6 @@ __global__ __launch_bounds__(256) void k_panel_vectors(double* __restrict__ A, i
   __syncthreads();
   lu64_signs(B, sg);
   // R = S R2 R1 and Z = U R2 (S, the LDS array, is free for Z)
-  const double* u1 = pan + kPanU1;
   upper_product64([&](int i, int k) { return u[i * kTri + k]; },
                   [&](int k, int j) { return u1[k * kTri + j]; },
                   [&](int i, int j, double v) {
@@ -575,104 +586,112 @@ __global__ __launch_bounds__(256) void k_panel_vectors(double* __restrict__ A, i
                     S[i][j] = v;
                   });
   __syncthreads();
-  if (wave == 0) {
-    tri_inv16([&](int i, int j) { return S[i][j]; }, pan + kPanInvZ);
-  } else if (wave == 1) {
-    tri_inv16([&](int i, int j) { return i == j ? 1.0 : B[j][i]; }, pan + kPanInvV);
-  } else {
-    // V's top rows (unit lower), tau, and T = (-U S) V1^-T: the rows of -U S and
-    // V1^T for its solution
-    if (threadIdx.x - 128 < bw) {
-      const int j = threadIdx.x - 128;
-      tau[j] = -B[j][j] * sg[j];
-    }
-    for (int e = threadIdx.x - 128; e < kTri * kTri; e += 128) {
-      const int c = e >> 6, q = e & 63;
-      if (q > c && q < rows && c < bw) A[q + c * ld] = B[q][c];
-      pan[kPanV1 + e] = q > c ? B[q][c] : (q == c ? 1.0 : 0.0);
-      pan[kPanUS + e] = q <= c ? -B[q][c] * sg[c] : 0.0;
-    }
+  if (wave == 0) tri_inv16([&](int i, int j) { return S[i][j]; }, pan + kPanInvZ);
+  if (wave == 1) tri_inv16([&](int i, int j) { return i == j ? 1.0 : B[j][i]; }, pan + kPanInvV);
+  // V's top rows (unit lower), tau, and T = (-U S) V1^-T: the rows of -U S and V1^T
+  // for its solution (the waves at an inverse join when it is done)
+  if (threadIdx.x >= 192 && threadIdx.x - 192 < bw) {
+    const int j = threadIdx.x - 192;
+    tau[j] = -B[j][j] * sg[j];
+  }
+  for (int e = threadIdx.x; e < kTri * kTri; e += 256) {
+    const int c = e >> 6, q = e & 63;
+    if (q > c && q < rows && c < bw) A[q + c * ld] = B[q][c];
+    pan[kPanV1 + e] = q > c ? B[q][c] : (q == c ? 1.0 : 0.0);
+    pan[kPanUS + e] = q <= c ? -B[q][c] * sg[c] : 0.0;
   }
 }
 
-// Householder factorisation of a panel column by column in memory, for the
-// panels whose state word is set (the launch ends at once otherwise): a
-// cooperative grid, one pass over the rows per column that applies the previous
-// reflector and accumulates the norm and dot products of the next, one grid
-// barrier per column.  Rows belong to threads for the whole kernel.  It also
-// runs as a single ordinary block.
+// Householder factorisation, column by column in memory, of an outer block's
+// columns from its first panel on whose state word is set (state[h]: panel h of
+// 64 columns; the launch ends at once if neither is).  Nothing of the block was
+// written after that panel, so its other panel is taken along.  A cooperative
+// grid: per column one pass over the rows for each group of 64 columns, which
+// applies the previous reflector and accumulates the norm and dot products of
+// the next, then one grid barrier.  Rows belong to threads for the whole kernel.
+// It also runs as a single ordinary block.
 constexpr int kColT = 256;
 __global__ __launch_bounds__(kColT) void k_qr_panel_col(double* __restrict__ A, int64_t ld,
-                                                        int64_t rows, int bw,
+                                                        int64_t rows, int ow,
                                                         double* __restrict__ red,
                                                         double* __restrict__ piv,
                                                         unsigned int* __restrict__ arrive,
                                                         const unsigned int* __restrict__ state,
                                                         double* __restrict__ tau_all,
                                                         int* __restrict__ dev_err) {
-  if (*state == 0u) return;
+  const bool first = state[0] != 0u;
+  if (!first && (ow <= kTri || state[1] == 0u)) return;
   __shared__ double s_wred[kColT / 64][kTri];
-  __shared__ double s_tw[kTri], s_pv[kTri], s_tot[kTri];
+  __shared__ double s_tw[2 * kTri], s_pv[2 * kTri], s_tot[2 * kTri];
   __shared__ double s_par[3];  // tau, beta, scale of the reflector just formed
   const int G = gridDim.x, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int64_t stride = (int64_t)G * kColT;
-  for (int k = 0; k <= bw; ++k) {
-    double part[kTri];
+  const int k0 = first ? 0 : kTri;
+  for (int k = k0; k <= ow; ++k) {
+    double* rb = red + (size_t)(k & 1) * 2 * kTri * kPanelMaxGrid;
+    double* pv = piv + (k & 1) * 2 * kTri;
+    const int p = k > k0 ? k - 1 : k;  // first column this pass touches
+    for (int o = p / kTri * kTri; o < ow; o += kTri) {
+      double part[kTri];
 #pragma unroll
-    for (int j = 0; j < kTri; ++j) part[j] = 0.0;
-    for (int64_t r = (int64_t)blockIdx.x * kColT + threadIdx.x; r < rows; r += stride) {
-      if (r < k - 1) continue;
-      double* row = A + r;
-      double a[kTri], v = 0.0, ak = 0.0;
+      for (int j = 0; j < kTri; ++j) part[j] = 0.0;
+      for (int64_t r = (int64_t)blockIdx.x * kColT + threadIdx.x; r < rows; r += stride) {
+        if (r < p) continue;
+        double* row = A + r;
+        double a[kTri];
 #pragma unroll
-      for (int j = 0; j < kTri; ++j) a[j] = (j >= k - 1 && j < bw) ? row[j * ld] : 0.0;
-      if (k > 0) {  // reflector k - 1
+        for (int j = 0; j < kTri; ++j) a[j] = (o + j >= p && o + j < ow) ? row[(o + j) * ld] : 0.0;
+        if (k > k0) {  // reflector p = k - 1, whose v an earlier group has stored
+          double v = r == p ? 1.0 : 0.0;
+          if (p >= o) {
 #pragma unroll
-        for (int j = 0; j < kTri; ++j)
-          if (j == k - 1) {
-            v = r == k - 1 ? 1.0 : a[j] * s_par[2];
-            row[j * ld] = r == k - 1 ? s_par[1] : v;
+            for (int j = 0; j < kTri; ++j)
+              if (o + j == p) {
+                v = r == p ? 1.0 : a[j] * s_par[2];
+                row[p * ld] = r == p ? s_par[1] : v;
+              }
+          } else if (r > p) {
+            v = row[p * ld];
           }
 #pragma unroll
-        for (int j = 0; j < kTri; ++j)
-          if (j >= k && j < bw) {
-            a[j] -= s_tw[j] * v;
-            row[j * ld] = a[j];
-          }
-      }
-      if (k < bw && r >= k) {
+          for (int j = 0; j < kTri; ++j)
+            if (o + j >= k && o + j < ow) {
+              a[j] -= s_tw[o + j] * v;
+              row[(o + j) * ld] = a[j];
+            }
+        }
+        if (k < ow && r == k) {
 #pragma unroll
-        for (int j = 0; j < kTri; ++j) ak = (j == k) ? a[j] : ak;
-        if (r == k) {
-          double* pv = piv + (k & 1) * kTri;
-#pragma unroll
-          for (int j = 0; j < kTri; ++j) xstore(pv + j, a[j]);
-        } else {
+          for (int j = 0; j < kTri; ++j)
+            if (o + j >= k && o + j < ow) xstore(pv + o + j, a[j]);
+        } else if (k < ow && r > k && k < o + kTri) {
+          const double ak = row[k * ld];  // (stored above, or by an earlier group)
 #pragma unroll
           for (int j = 0; j < kTri; ++j) part[j] += ak * a[j];
         }
       }
-    }
-    if (k == bw) break;
+      if (k == ow || o + kTri <= k) continue;  // uniform
 #pragma unroll
-    for (int j = 0; j < kTri; ++j) {
-      const double t = wave_sum(part[j]);
-      if (lane == 0) s_wred[wave][j] = t;
-    }
-    __syncthreads();
-    double* rb = red + (size_t)(k & 1) * kTri * kPanelMaxGrid;
-    if (threadIdx.x < kTri) {
-      double t = 0.0;
+      for (int j = 0; j < kTri; ++j) {
+        const double t = wave_sum(part[j]);
+        if (lane == 0) s_wred[wave][j] = t;
+      }
+      __syncthreads();
+      if (threadIdx.x < kTri) {
+        double t = 0.0;
 #pragma unroll
-      for (int w = 0; w < kColT / 64; ++w) t += s_wred[w][threadIdx.x];
-      xstore(rb + threadIdx.x * kPanelMaxGrid + blockIdx.x, t);
+        for (int w = 0; w < kColT / 64; ++w) t += s_wred[w][threadIdx.x];
+        xstore(rb + (o + threadIdx.x) * kPanelMaxGrid + blockIdx.x, t);
+      }
+      __syncthreads();
     }
-    grid_barrier_x8(arrive, (unsigned)(k + 1), dev_err);
-    if (threadIdx.x < kTri) {
+    if (k == ow) break;
+    grid_barrier_x8(arrive, (unsigned)(k - k0 + 1), dev_err);
+    if (threadIdx.x >= k && threadIdx.x < ow) {
       double t = 0.0;
       for (int b = 0; b < G; ++b) t += vload(rb + threadIdx.x * kPanelMaxGrid + b);
       s_tot[threadIdx.x] = t;
-      s_pv[threadIdx.x] = vload(piv + (k & 1) * kTri + threadIdx.x);
+      s_pv[threadIdx.x] = vload(pv + threadIdx.x);
     }
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -689,9 +708,9 @@ __global__ __launch_bounds__(kColT) void k_qr_panel_col(double* __restrict__ A, 
       if (blockIdx.x == 0) tau_all[k] = tau;
     }
     __syncthreads();
-    if (threadIdx.x < kTri) {
+    if (threadIdx.x < ow) {
       const int j = threadIdx.x;
-      s_tw[j] = (j > k && j < bw) ? s_par[0] * (s_pv[j] + s_par[2] * s_tot[j]) : 0.0;
+      s_tw[j] = j > k ? s_par[0] * (s_pv[j] + s_par[2] * s_tot[j]) : 0.0;
     }
     __syncthreads();
   }
@@ -726,7 +745,9 @@ constexpr int kUC = 64;   // columns per tile
 template <int KW>
 __global__ __launch_bounds__(512) void k_qr_upd(double* __restrict__ A, int64_t ld, int64_t m,
                                                 int64_t j0, int pw, int64_t c_end, int64_t nct,
-                                                const double* __restrict__ Wt) {
+                                                const double* __restrict__ Wt,
+                                                const unsigned int* __restrict__ skip) {
+  if (*skip) return;  // the reflectors are not there yet
   // padded row strides: the four lane groups of a fragment read (rows kk .. kk+3)
   // fall on different banks
   __shared__ double sV[KW][kUR + 8];
@@ -1939,11 +1960,14 @@ __global__ void k_bitonic(double* __restrict__ key, int32_t* __restrict__ idx, i
 // substitution), so every block it depends on has a smaller index and was
 // dispatched earlier; the launch is cooperative, so all blocks are resident.
 // A block folds in each dependency block c as soon as c publishes its 64
-// values (flag[c] == epoch): a 64 x 64 product with the R tile, spread over
-// 4 waves.  Then wave 0 solves the diagonal block (staged in LDS), and the
-// block publishes its values with device-scope stores before its flag
-// (cross-XCD exchange without an L2-flushing fence).  Waits are bounded and
-// set GAP_DEVERR_SYNC on expiry, after which every wait returns at once.
+// values (flag[c] == epoch): a 64 x 64 product, a quarter of R's tile per wave,
+// whose entries are in registers before the wave starts to wait.  Then wave 0
+// solves the diagonal block, a row (column) of it per lane in registers, and
+// publishes the values with device-scope stores before the flag (cross-XCD
+// exchange without an L2-flushing fence).  Waits are bounded and set
+// GAP_DEVERR_SYNC on expiry, after which every wait returns at once.  Bound by
+// the chain of blocks: 4.1 us a block, 13.6 us when the tile's loads and two
+// barriers followed each wait and each of the 64 steps divided.
 template <bool TRANS>
 __global__ __launch_bounds__(256) void k_trsv_coop(const double* __restrict__ R, int64_t ld,
                                                    int64_t n, const double* z, double* x,
@@ -1951,79 +1975,74 @@ __global__ __launch_bounds__(256) void k_trsv_coop(const double* __restrict__ R,
                                                    unsigned int epoch, int* dev_err) {
   __shared__ double T[64][65];
   __shared__ double part[4][64];
-  __shared__ double xd[64];
   const int nb = (int)((n + 63) / 64);
   const int b = TRANS ? (int)blockIdx.x : nb - 1 - (int)blockIdx.x;
   const int64_t j0 = (int64_t)b * 64;
   const int w = (int)min((int64_t)64, n - j0);
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   for (int e = tid; e < 64 * 64; e += 256) {
     const int r = e & 63, c = e >> 6;
     T[r][c] = (r < w && c < w && r <= c) ? R[(j0 + r) + (j0 + c) * ld] : 0.0;
+  }
+  const int64_t me = min(j0 + lane, n - 1);
+  const double zl = z[me];
+  __syncthreads();
+  // wave 0: this lane's row (TRANS: column) of the diagonal block
+  double row[64], dg = 1.0;
+  if (wave == 0) {
+#pragma unroll
+    for (int c = 0; c < 64; ++c) row[c] = TRANS ? T[c][lane] : T[lane][c];
+    dg = lane < w ? T[lane][lane] : 1.0;
   }
   double acc = 0.0;
   const int ndep = TRANS ? b : nb - 1 - b;
   for (int d = 0; d < ndep; ++d) {
     const int c = TRANS ? d : nb - 1 - d;  // in the order the dependencies complete
-    const int64_t c0 = (int64_t)c * 64;
-    if (tid == 0) {
-      uint64_t spins = 0;
-      while (__hip_atomic_load(flag + c, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT) != epoch) {
-        if (dev_err && (__hip_atomic_load(dev_err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) &
-                        GAP_DEVERR_SYNC))
-          break;
-        __builtin_amdgcn_s_sleep(1);
-        if (++spins > (1ull << 22)) {
-          if (dev_err) atomicOr(dev_err, GAP_DEVERR_SYNC);
-          break;
-        }
+    const int64_t c0 = (int64_t)c * 64 + wave * 16;
+    // TRANS: unknown j0 + lane needs sum_i R[c0 + i][j0 + lane] y[c0 + i], else
+    // sum_j R[j0 + lane][c0 + j] x[c0 + j]; indices past n are clamped (their
+    // value is zero, or their lane is not stored)
+    double t[16];
+#pragma unroll
+    for (int q = 0; q < 16; ++q)
+      t[q] = TRANS ? R[c0 + q + me * ld] : R[me + min(c0 + q, n - 1) * ld];
+    uint64_t spins = 0;
+    while (__hip_atomic_load(flag + c, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT) != epoch) {
+      if (dev_err && (__hip_atomic_load(dev_err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) &
+                      GAP_DEVERR_SYNC))
+        break;
+      __builtin_amdgcn_s_sleep(1);
+      if (++spins > (1ull << 22)) {
+        if (dev_err && lane == 0) atomicOr(dev_err, GAP_DEVERR_SYNC);
+        break;
       }
     }
-    __syncthreads();
-    if (tid < 64) xd[tid] = (c0 + tid < n) ? vload(x + c0 + tid) : 0.0;
-    __syncthreads();
-    if (lane < w) {
-      if (TRANS) {
-        // unknown j0 + lane needs sum_i R[c0 + i][j0 + lane] y[c0 + i]
-        const double* col = R + (j0 + lane) * ld + c0;
-#pragma unroll 4
-        for (int i = wave * 16; i < wave * 16 + 16; ++i) acc += col[i] * xd[i];
-      } else {
-        // unknown j0 + lane needs sum_j R[j0 + lane][c0 + j] x[c0 + j]
-        // columns past n (the last block) are clamped in range; xd is zero there
-        const double* row = R + (j0 + lane);
-#pragma unroll 4
-        for (int jj = wave * 16; jj < wave * 16 + 16; ++jj)
-          acc += row[min(c0 + jj, n - 1) * ld] * xd[jj];
-      }
-    }
+    const int64_t xi = c0 + (lane & 15);
+    const double xv = vload(x + min(xi, n - 1));
+    const double xz = xi < n ? xv : 0.0;
+#pragma unroll
+    for (int q = 0; q < 16; ++q) acc = fma(t[q], readlane_f64(xz, q), acc);
   }
   part[wave][lane] = acc;
   __syncthreads();
   if (wave == 0) {
-    double t = lane < w ? z[j0 + lane] - (((part[0][lane] + part[1][lane]) + part[2][lane]) +
-                                          part[3][lane])
+    double t = lane < w ? zl - (((part[0][lane] + part[1][lane]) + part[2][lane]) + part[3][lane])
                         : 0.0;
-    bool bad = false;
-    if (TRANS) {
-      for (int c = 0; c < w; ++c) {
-        const double dg = T[c][c];
-        bad |= (dg == 0.0 || !isfinite(dg));
-        const double xc = __shfl(t, c) / dg;
-        if (lane == c) t = xc;
-        else if (lane > c) t -= T[c][lane] * xc;
-      }
-    } else {
-      for (int c = w - 1; c >= 0; --c) {
-        const double dg = T[c][c];
-        bad |= (dg == 0.0 || !isfinite(dg));
-        const double xc = __shfl(t, c) / dg;
-        if (lane == c) t = xc;
-        else if (lane < c) t -= T[lane][c] * xc;
+    const bool bad = dg == 0.0 || !isfinite(dg);
+    const double rinv = 1.0 / dg;
+    // step c: the value of unknown c, then its share taken from the others (a
+    // lane's own entry and those already solved are zero in its row)
+#pragma unroll
+    for (int s = 0; s < 64; ++s) {
+      const int c = TRANS ? s : 63 - s;
+      if (c < w) {
+        const double xc = readlane_f64(t * rinv, c);
+        const double u = fma(-row[c], xc, t);
+        t = lane == c ? t : u;
       }
     }
-    if (lane < w) xstore(x + j0 + lane, t);
-    if (bad && lane == 0 && dev_err) atomicOr(dev_err, GAP_DEVERR_RANK);
+    if (lane < w) xstore(x + j0 + lane, t * rinv);
+    if (__any(bad) && lane == 0 && dev_err) atomicOr(dev_err, GAP_DEVERR_RANK);
     wait_mem();
     if (lane == 0) __hip_atomic_store(flag + b, epoch, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
   }
@@ -2250,7 +2269,7 @@ size_t qr_workspace_bytes(int64_t m, int64_t n) {
   d += (size_t)kQrOB * kQrOB;                  // T
   d += (size_t)kTri * qr_ldq(m);               // Q of a panel
   d += (size_t)kPanDoubles;                    // pan
-  d += (size_t)2 * kTri * (kPanelMaxGrid + 1); // red and piv of the column kernel
+  d += (size_t)4 * kTri * (kPanelMaxGrid + 1); // red and piv of the column kernel
   d += (size_t)n + 8;                          // tau
   return d * sizeof(double) + sizeof(unsigned int) * (kCounterWords + kTrsvMaxBlocks);  // counters, flags
 }
@@ -2270,7 +2289,7 @@ void qr_bind_workspace(void* base, int64_t m, int64_t n, QrWork* w) {
   w->W = take(kQrOB * ncols);
   w->Wt = take(kQrOB * ncols);
   w->T = take(kQrOB * kQrOB);
-  w->red = take(2 * kTri * (kPanelMaxGrid + 1));
+  w->red = take(4 * kTri * (kPanelMaxGrid + 1));
   w->tau = take(n + 8);
   w->counter = reinterpret_cast<unsigned int*>(p);
   w->flags = w->counter + kCounterWords;
@@ -2294,12 +2313,10 @@ static void qr_wy_update(double* A, int64_t ld, int64_t m, int64_t j0, int pw, i
                        pw, nct, (int64_t)kNarrowSlab, n_ct, total, per_xcd, w->part);
     reduce_rows_f64(w->part, nslab, (int64_t)pw * nct, w->W, st);
   }
-  hipLaunchKernelGGL(k_qr_larft, dim3(1), dim3(256), 0, st, w->W, nct, pw, w->tau + j0, w->T,
-                     w->counter);
   hipLaunchKernelGGL(k_qr_wt, dim3(cdiv(nct - pw, 64)), dim3(256), 0, st, w->W, nct, pw, w->T,
                      w->Wt);
-  hipLaunchKernelGGL(k_qr_upd<kQrNB>, dim3(cdiv(m - j0, kUR)), dim3(512), 0, st, A, ld, m, j0, pw, c_end,
-                     nct, w->Wt);
+  hipLaunchKernelGGL(k_qr_upd<kQrNB>, dim3(cdiv(m - j0, kUR)), dim3(512), 0, st, A, ld, m, j0, pw,
+                     c_end, nct, w->Wt, w->counter);
 }
 
 // The same update for an outer block of up to kQrOB reflectors.
@@ -2348,44 +2365,54 @@ static int col_capacity() {
   return cap;
 }
 
-// Householder factors of the bw <= 64 columns at j0, rows j0 .. m - 1, half `half`
-// of its outer block.
+// Householder factors of the bw <= 64 columns at j0, rows j0 .. m - 1, panel `half`
+// of its outer block (or its state word set and nothing written).
 static void qr_panel(double* A_, int64_t ld, int64_t m, int64_t j0, int bw, int half, QrWork* w,
-                     hipStream_t st, int* dev_err) {
+                     hipStream_t st) {
   double* A = A_ + j0 + j0 * ld;
-  double* tau = w->tau + j0;
-  int64_t rows = m - j0, ldq = qr_ldq(m);
-  unsigned int *state = w->counter + half, *arrive = w->counter + kPanelBar;
+  const int64_t rows = m - j0, ldq = qr_ldq(m);
+  unsigned int* state = w->counter + half;
   const unsigned gb = (unsigned)std::max<int64_t>(
       1, std::min<int64_t>(kGramMaxBlocks, (rows + 127) / 128));
   auto gram = [&](const double* P, int64_t ldp) {
     hipLaunchKernelGGL(k_panel_gram, dim3(gb), dim3(256), 0, st, P, ldp, rows, bw, w->part);
     reduce_rows_f64(w->part, gb, kGram, w->pan + kPanG, st);
   };
-  gram(A, ld);
-  hipLaunchKernelGGL(k_panel_chol, dim3(1), dim3(256), 0, st, bw, w->pan, state, arrive);
   auto blocks = [](int64_t r) { return (unsigned)std::min<int64_t>((r + 63) / 64, kSolveBlocks); };
   const unsigned n1 = blocks(rows), n2 = rows > kTri ? blocks(rows - kTri) : 0;
+  gram(A, ld);
+  hipLaunchKernelGGL(k_panel_chol, dim3(1), dim3(256), 0, st, bw, half, w->pan, w->counter,
+                     w->counter + kPanelBar);
   const PanelSolve q1{A, ld, w->Q, ldq, rows, bw, w->pan + kPanU1, w->pan + kPanInv1};
   hipLaunchKernelGGL(k_panel_solve, dim3(n1), dim3(256), 0, st, q1, q1, (int)n1, state);
   gram(w->Q, ldq);
   hipLaunchKernelGGL(k_panel_vectors, dim3(1), dim3(256), 0, st, A, ld, rows, bw, w->Q, ldq,
-                     w->pan, tau, state);
+                     w->pan, w->tau + j0, state);
   // V's other rows, and T in one block more
   const PanelSolve v{w->Q + kTri, ldq, A + kTri, ld, rows - kTri, bw, w->pan + kPanZ,
                      w->pan + kPanInvZ};
   const PanelSolve t{w->pan + kPanUS, kTri, w->T + half * kTri * kTri, kTri, kTri, kTri,
                      w->pan + kPanV1, w->pan + kPanInvV};
   hipLaunchKernelGGL(k_panel_solve, dim3(n2 + 1), dim3(256), 0, st, v, t, (int)n2, state);
-  // ends at once unless the panel's columns are numerically dependent
-  double *red = w->red, *piv = w->red + 2 * kTri * kPanelMaxGrid;
+}
+
+// The outer block at o0 from its first panel on that qr_panel left undone.  The
+// launch costs about 25 us even where there is none (a cooperative launch goes
+// through a queue of its own), so there is one per outer block.
+static void qr_undone(double* A_, int64_t ld, int64_t m, int64_t o0, int ow, QrWork* w,
+                      hipStream_t st, int* dev_err) {
+  double* A = A_ + o0 + o0 * ld;
+  double* tau = w->tau + o0;
+  int64_t rows = m - o0;
+  unsigned int *state = w->counter, *arrive = w->counter + kPanelBar;
+  double *red = w->red, *piv = w->red + 4 * kTri * kPanelMaxGrid;
   const int64_t G = std::min<int64_t>(col_capacity(), (rows + kColT - 1) / kColT);
-  void* args[] = {&A, &ld, &rows, &bw, &red, &piv, &arrive, &state, &tau, &dev_err};
+  void* args[] = {&A, &ld, &rows, &ow, &red, &piv, &arrive, &state, &tau, &dev_err};
   if (G < 1 || hipLaunchCooperativeKernel(reinterpret_cast<const void*>(&k_qr_panel_col),
                                           dim3((unsigned)G), dim3(kColT), args, 0,
                                           st) != hipSuccess) {
     (void)hipGetLastError();
-    hipLaunchKernelGGL(k_qr_panel_col, dim3(1), dim3(kColT), 0, st, A, ld, rows, bw, red, piv,
+    hipLaunchKernelGGL(k_qr_panel_col, dim3(1), dim3(kColT), 0, st, A, ld, rows, ow, red, piv,
                        arrive, state, tau, dev_err);
   }
 }
@@ -2402,7 +2429,7 @@ void qr_factor(double* A, int64_t ld, int64_t m, int64_t ncols, int64_t n, QrWor
     for (int64_t j0 = o0; j0 < o0 + ow; j0 += kQrNB) {
       const int bw = (int)std::min<int64_t>(kQrNB, o0 + ow - j0);
       tm->begin(TM_QR_PANEL);
-      qr_panel(A, ld, m, j0, bw, j0 > o0 ? 1 : 0, w, st, dev_err);
+      qr_panel(A, ld, m, j0, bw, j0 > o0 ? 1 : 0, w, st);
       tm->end(TM_QR_PANEL);
       if (j0 + bw >= o0 + ow) continue;
       // rest of the outer block with this 64-wide block's reflectors
@@ -2410,6 +2437,9 @@ void qr_factor(double* A, int64_t ld, int64_t m, int64_t ncols, int64_t n, QrWor
       qr_wy_update(A, ld, m, j0, bw, o0 + ow, w, st);
       tm->end(TM_QR_UPDATE);
     }
+    tm->begin(TM_QR_PANEL);
+    qr_undone(A, ld, m, o0, ow, w, st, dev_err);
+    tm->end(TM_QR_PANEL);
     if (o0 + ow >= ncols) continue;
     tm->begin(TM_QR_UPDATE);
     qr_wy_update_ob(A, ld, m, o0, ow, ncols, w, st);
