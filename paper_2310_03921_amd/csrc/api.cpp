@@ -688,6 +688,7 @@ gap_status gap_build_virial_rows(gap_handle* h, const gap_atoms* a, const gap_sp
   layout_pairs(L, N, a->n_pairs, p);
   const size_t S = L.take(sizeof(double) * std::max<int64_t>(N * ld4(M), 1));
   const size_t ke = L.take(sizeof(double) * nc * M);
+  const size_t pt = L.take(gapk::virial_part_bytes(nc, M, D));
   s = ensure_ws(h, L.off);
   if (s != GAP_OK) return s;
   run_pairs(h, a, p, false);  // pair sources (and the index checks)
@@ -699,7 +700,8 @@ gap_status gap_build_virial_rows(gap_handle* h, const gap_atoms* a, const gap_sp
   h->timer.begin(gapk::TM_FORCE);
   gapk::virial_rows_f64(a->jac, f32(a->jac_dt), a->ld_jac, D, sp->X, sp->ld_x, M,
                         at<double>(h, S), ld4(M), a->cfg_ptr, nc, a->pair_ptr,
-                        at<int32_t>(h, p.src), pair_r, N, a->n_pairs, Kv, ld, h->stream);
+                        at<int32_t>(h, p.src), pair_r, N, a->n_pairs, Kv, ld, at<double>(h, pt),
+                        h->stream);
   h->timer.end(gapk::TM_FORCE);
   HIP_TRY(h, hipGetLastError());
   return GAP_OK;

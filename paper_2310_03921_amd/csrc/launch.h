@@ -108,12 +108,13 @@ void se2b_predict_f64(const double* pair_r, const int64_t* cfg_ptr, int64_t n_cf
                       int64_t n_atoms, int64_t n_pairs, const double* x, const double* c,
                       int64_t M, double delta, double theta, double r_cut, double width,
                       double* ep, double* gp, double* e_cfg, double* forces, hipStream_t st);
-// Virial rows: K[(9 c + 3 alpha + beta), m] = - sum_{p in c} r[p][alpha] S[src(p)][m] (J[p][beta] . x_m).
+// Virial rows (part: virial_part_bytes of scratch): K[(9 c + 3 alpha + beta), m] = - sum_{p in c} r[p][alpha] S[src(p)][m] (J[p][beta] . x_m).
+size_t virial_part_bytes(int64_t n_cfg, int64_t M, int64_t D);
 void virial_rows_f64(const void* jac, bool jac_f32, int64_t ldj, int64_t D, const double* X,
                      int64_t ldx, int64_t M, const double* S, int64_t ldS, const int64_t* cfg_ptr,
                      int64_t n_cfg, const int64_t* pair_ptr, const int32_t* pair_src,
                      const double* pair_r, int64_t n_atoms, int64_t n_pairs, double* K,
-                     int64_t ldk, hipStream_t st);
+                     int64_t ldk, double* part, hipStream_t st);
 // Local-property rows: K[r][m] = delta^2 (d_{atom_idx[r]} . x_m)^zeta (atom_idx NULL:
 // atom r), column-major, or row-major [n_local][ldk] with zero row padding.
 void local_rows_f64(const void* desc, bool desc_f32, int64_t ldd, int64_t n_atoms,

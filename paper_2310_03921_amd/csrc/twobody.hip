@@ -59,18 +59,34 @@ GAP_DEV void pair_geom(const double* __restrict__ pair_r, int64_t p, const Se2b&
   u[2] = c * inv;
 }
 
-// Energy rows: block (column tile of 64, configuration); lane m of each wave,
-// waves split the configuration's pairs, fixed-order reduction over the waves.
-__global__ __launch_bounds__(256) void k_2b_energy(const double* __restrict__ pair_r,
-                                                    const int64_t* __restrict__ cfg_ptr,
-                                                    const int64_t* __restrict__ pair_ptr,
-                                                    int64_t n_atoms, int64_t n_pairs,
-                                                    const double* __restrict__ x, int64_t M,
-                                                    Se2b k, double* __restrict__ K, int64_t ldk) {
-  __shared__ double red[4][64];
+// The lanes of a wave over min(M, 64) sparse points, rounded up to a power of
+// two, and the 64 / lanes pairs side by side that leaves room for (with ten
+// points and a pair per wave at a time most lanes were idle).
+GAP_DEV int point_lanes(int64_t M) {
+  int mp = 1;
+  while (mp < 64 && mp < M) mp <<= 1;
+  return mp;
+}
+GAP_DEV double sum_pair_lanes(double v, int mp) {
+  for (int o = mp; o < 64; o <<= 1) v += __shfl_xor(v, o);
+  return v;
+}
+
+// Energy rows: block (column tile of 64, configuration); the waves and the pair
+// slots of a wave split the configuration's pairs, fixed-order reduction.
+// Bound by latency (a few hundred blocks of exponentials): sixteen waves instead
+// of four and the lanes' pair slots, 170 -> 34 us for 29k pairs and ten points.
+__global__ __launch_bounds__(1024) void k_2b_energy(const double* __restrict__ pair_r,
+                                                     const int64_t* __restrict__ cfg_ptr,
+                                                     const int64_t* __restrict__ pair_ptr,
+                                                     int64_t n_atoms, int64_t n_pairs,
+                                                     const double* __restrict__ x, int64_t M,
+                                                     Se2b k, double* __restrict__ K, int64_t ldk) {
+  __shared__ double red[16][64];
   const int64_t c = blockIdx.y;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int64_t m = (int64_t)blockIdx.x * 64 + lane;
+  const int mp = point_lanes(M), slot = wave * (64 / mp) + lane / mp;
+  const int64_t m = (int64_t)blockIdx.x * 64 + (lane & (mp - 1));
   const double xm = m < M ? x[m] : 0.0;
   const double fx = fcut(xm, k);
   const int64_t a0 = min(max(cfg_ptr[c], (int64_t)0), n_atoms);
@@ -78,20 +94,25 @@ __global__ __launch_bounds__(256) void k_2b_energy(const double* __restrict__ pa
   const int64_t p0 = min(max(pair_ptr[a0], (int64_t)0), n_pairs);
   const int64_t p1 = min(max(pair_ptr[a1], p0), n_pairs);
   double s = 0.0;
-  for (int64_t p = p0 + wave; p < p1; p += 4) {
+  for (int64_t p = p0 + slot; p < p1; p += 16 * (64 / mp)) {
     double r, fr, dfr, u[3], v, dv;
     pair_geom(pair_r, p, k, r, fr, dfr, u);
     kse(r, fr, dfr, xm, fx, k, v, dv);
     s += v;
   }
-  red[wave][lane] = s;
+  red[wave][lane] = sum_pair_lanes(s, mp);
   __syncthreads();
-  if (wave == 0 && m < M)
-    K[c + m * ldk] = 0.5 * (red[0][lane] + red[1][lane] + red[2][lane] + red[3][lane]);
+  if (wave == 0 && lane < mp && m < M) {
+    double t = 0.0;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) t += red[w][lane];
+    K[c + m * ldk] = 0.5 * t;
+  }
 }
 
-// Force rows: one wave per atom a, lane m; the atom's own pairs (a as i) and
-// the pairs pointing at it (a as j, through the target-major view).
+// Force rows: one wave per atom a, lanes over sparse points and pairs; the atom's
+// own pairs (a as i) and the pairs pointing at it (a as j, through the target-
+// major view). 72 -> 30 us for 29k pairs and ten points.
 __global__ __launch_bounds__(256) void k_2b_force(
     const double* __restrict__ pair_r, const int64_t* __restrict__ pair_ptr,
     const int64_t* __restrict__ tgt_ptr, const int32_t* __restrict__ tgt_pair, int64_t n_atoms,
@@ -99,21 +120,22 @@ __global__ __launch_bounds__(256) void k_2b_force(
     double* __restrict__ K, int64_t ldk) {
   const int64_t a = blockIdx.y * (int64_t)(blockDim.x >> 6) + (threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
-  const int64_t m = (int64_t)blockIdx.x * 64 + lane;
+  const int mp = point_lanes(M), slot = lane / mp, step = 64 / mp;
+  const int64_t m = (int64_t)blockIdx.x * 64 + (lane & (mp - 1));
   if (a >= n_atoms) return;
   const double xm = m < M ? x[m] : 0.0;
   const double fx = fcut(xm, k);
   double f[3] = {0.0, 0.0, 0.0};
   const int64_t s0 = min(max(pair_ptr[a], (int64_t)0), n_pairs);
   const int64_t s1 = min(max(pair_ptr[a + 1], s0), n_pairs);
-  for (int64_t p = s0; p < s1; ++p) {
+  for (int64_t p = s0 + slot; p < s1; p += step) {
     double r, fr, dfr, u[3], v, dv;
     pair_geom(pair_r, p, k, r, fr, dfr, u);
     kse(r, fr, dfr, xm, fx, k, v, dv);
 #pragma unroll
     for (int al = 0; al < 3; ++al) f[al] += 0.5 * dv * u[al];
   }
-  for (int64_t e = tgt_ptr[a]; e < tgt_ptr[a + 1]; ++e) {
+  for (int64_t e = tgt_ptr[a] + slot; e < tgt_ptr[a + 1]; e += step) {
     const int64_t p = tgt_pair[e];
     double r, fr, dfr, u[3], v, dv;
     pair_geom(pair_r, p, k, r, fr, dfr, u);
@@ -121,9 +143,10 @@ __global__ __launch_bounds__(256) void k_2b_force(
 #pragma unroll
     for (int al = 0; al < 3; ++al) f[al] -= 0.5 * dv * u[al];
   }
-  if (m < M) {
 #pragma unroll
-    for (int al = 0; al < 3; ++al) K[(row0 + 3 * a + al) + m * ldk] = f[al];
+  for (int al = 0; al < 3; ++al) {
+    const double t = sum_pair_lanes(f[al], mp);
+    if (slot == 0 && m < M) K[(row0 + 3 * a + al) + m * ldk] = t;
   }
 }
 
@@ -179,36 +202,38 @@ __global__ void k_2b_cfg_energy(const double* __restrict__ ep, const int64_t* __
   if (lane == 0) e_cfg[c] = s;
 }
 
-// F_a = sum_{p: i(p) = a} g_p rhat_p - sum_{p: j(p) = a} g_p rhat_p (thread per atom)
-__global__ void k_2b_forces(const double* __restrict__ gp, const double* __restrict__ pair_r,
-                            const int64_t* __restrict__ pair_ptr,
-                            const int64_t* __restrict__ tgt_ptr,
-                            const int32_t* __restrict__ tgt_pair, int64_t n_atoms,
-                            int64_t n_pairs, double* __restrict__ F) {
-  for (int64_t a = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; a < n_atoms;
-       a += (int64_t)gridDim.x * blockDim.x) {
+// F_a = sum_{p: i(p) = a} g_p rhat_p - sum_{p: j(p) = a} g_p rhat_p, sixteen lanes
+// per atom over its pairs (a thread per atom took 46 us for 2336 atoms, this 6).
+__global__ __launch_bounds__(256) void k_2b_forces(const double* __restrict__ gp,
+                                                   const double* __restrict__ pair_r,
+                                                   const int64_t* __restrict__ pair_ptr,
+                                                   const int64_t* __restrict__ tgt_ptr,
+                                                   const int32_t* __restrict__ tgt_pair,
+                                                   int64_t n_atoms, int64_t n_pairs,
+                                                   double* __restrict__ F) {
+  const int l = threadIdx.x & 15;
+  for (int64_t i0 = blockIdx.x * (int64_t)16; i0 < n_atoms; i0 += (int64_t)gridDim.x * 16) {
+    const int64_t a = i0 + (threadIdx.x >> 4);
     double f[3] = {0.0, 0.0, 0.0};
-    const int64_t s0 = min(max(pair_ptr[a], (int64_t)0), n_pairs);
-    const int64_t s1 = min(max(pair_ptr[a + 1], s0), n_pairs);
-    for (int64_t p = s0; p < s1; ++p) {
+    auto add = [&](int64_t p, double sign) {
       const double a0 = pair_r[3 * p], a1 = pair_r[3 * p + 1], a2 = pair_r[3 * p + 2];
       const double r = sqrt(a0 * a0 + a1 * a1 + a2 * a2);
-      const double s = r > 0.0 ? gp[p] / r : 0.0;
+      const double s = r > 0.0 ? sign * gp[p] / r : 0.0;
       f[0] += s * a0;
       f[1] += s * a1;
       f[2] += s * a2;
-    }
-    for (int64_t e = tgt_ptr[a]; e < tgt_ptr[a + 1]; ++e) {
-      const int64_t p = tgt_pair[e];
-      const double a0 = pair_r[3 * p], a1 = pair_r[3 * p + 1], a2 = pair_r[3 * p + 2];
-      const double r = sqrt(a0 * a0 + a1 * a1 + a2 * a2);
-      const double s = r > 0.0 ? gp[p] / r : 0.0;
-      f[0] -= s * a0;
-      f[1] -= s * a1;
-      f[2] -= s * a2;
+    };
+    if (a < n_atoms) {
+      const int64_t s0 = min(max(pair_ptr[a], (int64_t)0), n_pairs);
+      const int64_t s1 = min(max(pair_ptr[a + 1], s0), n_pairs);
+      for (int64_t p = s0 + l; p < s1; p += 16) add(p, 1.0);
+      for (int64_t e = tgt_ptr[a] + l; e < tgt_ptr[a + 1]; e += 16) add(tgt_pair[e], -1.0);
     }
 #pragma unroll
-    for (int al = 0; al < 3; ++al) F[3 * a + al] = f[al];
+    for (int al = 0; al < 3; ++al)
+#pragma unroll
+      for (int o = 1; o < 16; o <<= 1) f[al] += __shfl_xor(f[al], o);
+    if (a < n_atoms && l < 3) F[3 * a + l] = l == 0 ? f[0] : l == 1 ? f[1] : f[2];
   }
 }
 
@@ -228,7 +253,7 @@ void se2b_rows_f64(const double* pair_r, const int64_t* cfg_ptr, int64_t n_cfg,
   if (M <= 0) return;
   const Se2b k = make_k(delta, theta, r_cut, width);
   if (n_cfg > 0)
-    hipLaunchKernelGGL(k_2b_energy, dim3(cdiv(M, 64), (unsigned)n_cfg), dim3(256), 0, st, pair_r,
+    hipLaunchKernelGGL(k_2b_energy, dim3(cdiv(M, 64), (unsigned)n_cfg), dim3(1024), 0, st, pair_r,
                        cfg_ptr, pair_ptr, n_atoms, n_pairs, x, M, k, K, ldk);
   if (n_atoms > 0)
     hipLaunchKernelGGL(k_2b_force, dim3(cdiv(M, 64), cdiv(n_atoms, 4)), dim3(256), 0, st, pair_r,
@@ -255,7 +280,7 @@ void se2b_predict_f64(const double* pair_r, const int64_t* cfg_ptr, int64_t n_cf
     hipLaunchKernelGGL(k_2b_cfg_energy, dim3(cdiv(n_cfg, 4)), dim3(256), 0, st, ep, cfg_ptr,
                        pair_ptr, n_cfg, n_atoms, n_pairs, e_cfg);
   if (forces && n_atoms > 0)
-    hipLaunchKernelGGL(k_2b_forces, dim3(std::min(cdiv(n_atoms, 256), 65536u)), dim3(256), 0, st,
+    hipLaunchKernelGGL(k_2b_forces, dim3(std::min(cdiv(n_atoms, 16), 65536u)), dim3(256), 0, st,
                        gp, pair_r, pair_ptr, tgt_ptr, tgt_pair, n_atoms, n_pairs, forces);
 }
 

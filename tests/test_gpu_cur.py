@@ -84,3 +84,17 @@ def test_cur_unique_direction_first(gapx, gap):
     assert int(idx[0]) == 123
     assert abs(float(lev[123]) - 1.0) <= 1e-12
     assert abs(float(lev.sum()) - 8.0) <= 1e-10
+
+
+@pytest.mark.parametrize("n", [1, 2, 3, 4095, 4096, 4097, 9001, 40000])
+def test_cur_order_over_sort_chunks(gapx, gap, n):
+    """The whole selection is the stable order of the leverages it reports, with
+    ties (repeated atoms) by index, across the chunks of the sort."""
+    rng = np.random.default_rng(n)
+    Dm = rng.standard_normal((n, 5))
+    Dm[n // 2:] = Dm[:n - n // 2]  # ties
+    atoms = gapx.Atoms.from_host(np.array([0, n]), Dm, np.zeros(n + 1, dtype=np.int64),
+                                 np.zeros(0, dtype=np.int32), None)
+    idx, lev = gap.select_cur(atoms, n, 1e-6)
+    ref = np.argsort(-lev.cpu().numpy(), kind="stable")
+    assert np.array_equal(idx.cpu().numpy(), ref)

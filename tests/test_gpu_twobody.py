@@ -113,3 +113,17 @@ def test_two_descriptor_fit_through_fold(gapx, gap):
     close((p1["e_cfg"] + p2["e_cfg"]).cpu().numpy(), K[:b.n_cfg] @ c_ref, TOL, "energies")
     close((p1["forces"] + p2["forces"]).cpu().numpy().reshape(-1), K[b.n_cfg:] @ c_ref, TOL,
           "forces")
+
+
+@pytest.mark.parametrize("M2", [1, 2, 3, 16, 33, 64, 65])
+def test_2b_rows_over_point_lanes(gapx, gap, M2):
+    """Sparse distances from one to more than a wave's lanes: pairs side by side in a wave."""
+    w = ragged()
+    b = synth.generate(w, jac=False)
+    r = synth.pair_vectors(w, b)
+    x = synth.sparse_distances(w, M2)
+    atoms = gapx.Atoms.from_host(b.cfg_ptr, b.desc, b.pair_ptr, b.pair_j, None)
+    K = gap.build_2b_rows(atoms, k2_of(gapx, x), torch.tensor(r, device="cuda"))
+    ref = oracle.build_2b_rows(b.cfg_ptr, b.pair_ptr, b.pair_j, r, x, **PAR)
+    Kh = K[:M2, :b.n_rows].T.cpu().numpy()
+    assert np.abs(Kh - ref).max() <= TOL * max(np.abs(ref).max(), 1e-300)
