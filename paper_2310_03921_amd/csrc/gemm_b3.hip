@@ -7,8 +7,14 @@
 // A block computes a 256 x 256 tile of C with eight waves (64 x 128 each: four
 // A and eight B fragments, thirty-two accumulators), over 32-deep k blocks
 // whose split A and B halves are double-buffered in LDS in matrix-core operand
-// order (128 KB); the next k block is loaded into registers while the current
-// one feeds the matrix cores.  A 256-wide tile moves 64 bytes of operands per
+// order (128 KB).  While a k block feeds the matrix cores the next one is converted
+// and staged between its products, from registers loaded a k block earlier: a
+// wave can issue three vector instructions in the time of one product, so the
+// conversion costs the matrix cores nothing, where staging after the products left
+// them idle (65536 x 4000 x 1000, FP32: W X 1532 -> 1314 us, 1.20 PFLOP/s of
+// executed products; P-stages 1746 -> 1500 and 1723 -> 1471; W^T D 1580 -> 1442.
+// The matrix cores are busy 64% of the time at 1.8 GHz.  Reading the next block's
+// first fragments ahead of its barrier as well changed nothing).  A 256-wide tile moves 64 bytes of operands per
 // 768 BF16 flop (12,288 per k block and thread pair), so at the matrix cores'
 // rate the operand stream from L2 stays near 15 TB/s for the whole chip; a
 // 128-wide tile would need twice that.
@@ -43,14 +49,14 @@ constexpr int kPlain = 0, kPEnergy = 1, kPBack = 2;
 
 inline unsigned cdiv_u(int64_t a, int64_t b) { return (unsigned)((a + b - 1) / b); }
 
-// Staging of a 256 x 32 operand block.  The next block's loads are issued
-// before the current block's products and their registers are read only when
-// the block is written to LDS after them, so the products never wait for
-// memory: a load fetches raw values from a clamped, valid address, and what
-// lies outside the operand (rows past its end, k past the slice end) is
-// replaced by zeros, by selection, only when the block is staged, where the
-// values are also converted to FP32 and split into 16-byte hi / lo halves at
-// [tile][hi | lo][lane] (lane = row % 16 + 16 group).
+// Staging of a 256 x 32 operand block, in two halves of 128 rows.  A half's
+// loads are issued one k block before its values are converted and written to
+// LDS, so neither the products nor the conversion wait for memory: a load
+// fetches raw values from a clamped, valid address; k past the slice end is
+// replaced by zeros, by selection, when the slice's last block is staged (CHECK).
+// Rows past the operand's end repeat its last row: they feed only entries of C
+// that are not kept.  Values are converted to FP32 and split into 16-byte hi / lo
+// halves at [tile][hi | lo][lane] (lane = row % 16 + 16 group).
 template <typename TOp>
 struct Stage;
 
@@ -61,50 +67,57 @@ struct Stage;
 GAP_DEV int stage_row(int t) { return 16 * (t >> 6) + (t & 15); }
 GAP_DEV int stage_grp(int t) { return (t >> 4) & 3; }
 
+template <bool CHECK>
+GAP_DEV void stage_split(const float v[8], int kleft, bf8v* __restrict__ d) {
+  float x[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) x[e] = (!CHECK || e < kleft) ? v[e] : 0.f;
+  bf8v hi, lo;
+  split8(x, hi, lo);
+  d[0] = hi;
+  d[64] = lo;
+}
+
 // Rows (element (r, k) at p[r ld + k], ld a multiple of 4): thread t holds rows
 // stage_row(t) + 128 h, entries k0 + 8 stage_grp(t) .. + 7, as two 4-wide loads whose
-// start is clamped to the last 4-group that holds entries below K.
+// start is clamped to the last 4-group that holds entries below K.  FP64 entries
+// are rounded (settle) before the other half's are loaded: raw values of both
+// halves at once would not fit the registers.
 template <typename T>
 struct Stage<const T*> {
-  T v[2][8];
-  GAP_DEV void load(const T* __restrict__ p, int64_t ld, int64_t rows, int64_t K, int64_t r0,
-                    int64_t k0) {
-    const int t = threadIdx.x, grp = stage_grp(t);
+  const T* row[2];
+  T in[sizeof(T) == 8 ? 1 : 2][8];
+  float v8[2][8];   // FP64: the rounded entries
+  GAP_DEV void init(const T* __restrict__ p, int64_t ld, int64_t rows, int64_t r0) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+      row[h] = p + min(r0 + stage_row(threadIdx.x) + kGRowStep * h, rows - 1) * ld;
+  }
+  GAP_DEV void load(int h, int64_t k0, int64_t K) {
     const int64_t k4 = (K - 1) & ~(int64_t)3;
+    typedef T v4 __attribute__((ext_vector_type(4)));
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const T* row = p + min(r0 + stage_row(t) + kGRowStep * h, rows - 1) * ld;
+    for (int q = 0; q < 2; ++q) {
+      const int64_t kk = min(k0 + 8 * stage_grp(threadIdx.x) + 4 * q, k4);
+      const v4 x = *reinterpret_cast<const v4*>(row[h] + kk);
 #pragma unroll
-      for (int q = 0; q < 2; ++q) {
-        const int64_t kk = min(k0 + 8 * grp + 4 * q, k4);
-        if constexpr (sizeof(T) == 4) {
-          const f4v x = *reinterpret_cast<const f4v*>(row + kk);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) v[h][4 * q + e] = x[e];
-        } else {
-          const d4v x = *reinterpret_cast<const d4v*>(row + kk);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) v[h][4 * q + e] = x[e];
-        }
-      }
+      for (int e = 0; e < 4; ++e) in[sizeof(T) == 8 ? 0 : h][4 * q + e] = x[e];
     }
   }
-  GAP_DEV void store(int64_t rows, int64_t K, int64_t r0, int64_t k0,
-                     bf8v* __restrict__ dst) const {
-    const int t = threadIdx.x, grp = stage_grp(t);
+  GAP_DEV void settle(int h) {
+    if constexpr (sizeof(T) == 8) {
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int r = stage_row(t) + kGRowStep * h;
-      const bool rok = r0 + r < rows;
-      float x[8];
-#pragma unroll
-      for (int e = 0; e < 8; ++e) x[e] = (rok && k0 + 8 * grp + e < K) ? (float)v[h][e] : 0.f;
-      bf8v hi, lo;
-      split8(x, hi, lo);
-      bf8v* d = dst + (r >> 4) * 128 + (r & 15) + 16 * grp;
-      d[0] = hi;
-      d[64] = lo;
+      for (int e = 0; e < 8; ++e) v8[h][e] = (float)in[0][e];
     }
+  }
+  template <bool CHECK>
+  GAP_DEV void store(int h, int64_t k0, int64_t K, bf8v* __restrict__ dst) const {
+    const int t = threadIdx.x, grp = stage_grp(t), r = stage_row(t) + kGRowStep * h;
+    const float* v;
+    if constexpr (sizeof(T) == 8) v = v8[h];
+    else v = in[h];
+    stage_split<CHECK>(v, (int)min(K - k0 - 8 * grp, (int64_t)8),
+                       dst + (r >> 4) * 128 + (r & 15) + 16 * grp);
   }
 };
 
@@ -116,29 +129,27 @@ struct SplitRows {
 };
 template <>
 struct Stage<SplitRows> {
+  const __bf16* rh[2];
+  int64_t d;   // from hi to lo
   bf8v hi[2], lo[2];
-  GAP_DEV void load(const SplitRows& s, int64_t ld, int64_t rows, int64_t K, int64_t r0,
-                    int64_t k0) {
-    const int t = threadIdx.x, grp = stage_grp(t);
+  GAP_DEV void init(const SplitRows& s, int64_t ld, int64_t rows, int64_t r0) {
+    d = s.lo - s.hi;
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int64_t off = min(r0 + stage_row(t) + kGRowStep * h, rows - 1) * ld + k0 + 8 * grp;
-      hi[h] = *reinterpret_cast<const bf8v*>(s.hi + off);
-      lo[h] = *reinterpret_cast<const bf8v*>(s.lo + off);
-    }
+    for (int h = 0; h < 2; ++h)
+      rh[h] = s.hi + min(r0 + stage_row(threadIdx.x) + kGRowStep * h, rows - 1) * ld +
+              8 * stage_grp(threadIdx.x);
   }
-  GAP_DEV void store(int64_t rows, int64_t K, int64_t r0, int64_t k0,
-                     bf8v* __restrict__ dst) const {
-    const int t = threadIdx.x, grp = stage_grp(t);
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int r = stage_row(t) + kGRowStep * h;
-      bf8v a = hi[h], b = lo[h];
-      if (r0 + r >= rows) zero_split(a, b);
-      bf8v* d = dst + (r >> 4) * 128 + (r & 15) + 16 * grp;
-      d[0] = a;
-      d[64] = b;
-    }
+  GAP_DEV void load(int h, int64_t k0, int64_t) {
+    hi[h] = *reinterpret_cast<const bf8v*>(rh[h] + k0);
+    lo[h] = *reinterpret_cast<const bf8v*>(rh[h] + k0 + d);
+  }
+  GAP_DEV void settle(int) {}
+  template <bool CHECK>
+  GAP_DEV void store(int h, int64_t, int64_t, bf8v* __restrict__ dst) const {
+    const int t = threadIdx.x, r = stage_row(t) + kGRowStep * h;
+    bf8v* d = dst + (r >> 4) * 128 + (r & 15) + 16 * stage_grp(t);
+    d[0] = hi[h];
+    d[64] = lo[h];
   }
 };
 
@@ -146,39 +157,43 @@ struct Stage<SplitRows> {
 // holds rows (t & 127) + 128 h and k group 8 (t >> 7) .. + 7, one load per k,
 // so that for a given k a wave's lanes read 64 consecutive r (whole 256-byte
 // runs for FP32); the block lands in the same LDS places as a row operand's.
+// The k group is one per wave, so a load's address is a scalar base per k and the
+// lane's column.
 template <typename T>
 struct ColOp {
   const T* p;
 };
 template <typename T>
 struct Stage<ColOp<T>> {
+  const T* base;   // column r0
+  int64_t ld;
+  uint32_t col[2];   // byte offset of the lane's column from r0
   T v[2][8];
-  GAP_DEV void load(const ColOp<T>& op, int64_t ld, int64_t rows, int64_t K, int64_t r0,
-                    int64_t k0) {
-    const int t = threadIdx.x, grp = t >> 7;
+  static GAP_DEV int grp() { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 7); }
+  GAP_DEV void init(const ColOp<T>& op, int64_t ld_, int64_t rows, int64_t r0) {
+    base = op.p + r0;
+    ld = ld_;
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int64_t rc = min(r0 + (t & 127) + kGRowStep * h, rows - 1);
+    for (int h = 0; h < 2; ++h)
+      col[h] = (uint32_t)sizeof(T) *
+               (uint32_t)min((int64_t)(threadIdx.x & 127) + kGRowStep * h, rows - 1 - r0);
+  }
+  GAP_DEV void load(int h, int64_t k0, int64_t K) {
 #pragma unroll
-      for (int e = 0; e < 8; ++e) v[h][e] = op.p[min(k0 + 8 * grp + e, K - 1) * ld + rc];
+    for (int e = 0; e < 8; ++e) {
+      const char* pk = reinterpret_cast<const char*>(base + min(k0 + 8 * grp() + e, K - 1) * ld);
+      v[h][e] = *reinterpret_cast<const T*>(pk + col[h]);
     }
   }
-  GAP_DEV void store(int64_t rows, int64_t K, int64_t r0, int64_t k0,
-                     bf8v* __restrict__ dst) const {
-    const int t = threadIdx.x, grp = t >> 7;
+  GAP_DEV void settle(int) {}
+  template <bool CHECK>
+  GAP_DEV void store(int h, int64_t k0, int64_t K, bf8v* __restrict__ dst) const {
+    const int r = (threadIdx.x & 127) + kGRowStep * h;
+    float x[8];
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int r = (t & 127) + kGRowStep * h;
-      const bool rok = r0 + r < rows;
-      float x[8];
-#pragma unroll
-      for (int e = 0; e < 8; ++e) x[e] = (rok && k0 + 8 * grp + e < K) ? (float)v[h][e] : 0.f;
-      bf8v hi, lo;
-      split8(x, hi, lo);
-      bf8v* d = dst + (r >> 4) * 128 + (r & 15) + 16 * grp;
-      d[0] = hi;
-      d[64] = lo;
-    }
+    for (int e = 0; e < 8; ++e) x[e] = (float)v[h][e];
+    stage_split<CHECK>(x, (int)min(K - k0 - 8 * grp(), (int64_t)8),
+                       dst + (r >> 4) * 128 + (r & 15) + 16 * grp());
   }
 };
 
@@ -224,22 +239,15 @@ __global__ __launch_bounds__(kGThreads, 1) void k_gemm_b3(TA A, int64_t lda, int
 
   Stage<TA> sa;
   Stage<TB> sb;
-  if (nkb > 0) {
-    sa.load(A, lda, n_a, kz1, i0, kz0);
-    sb.load(B, ldb, n_b, kz1, j0, kz0);
-    sa.store(n_a, kz1, i0, kz0, sA(0));
-    sb.store(n_b, kz1, j0, kz0, sB(0));
-  }
-  __syncthreads();
-  for (int kb = 0; kb < nkb; ++kb) {
+  sa.init(A, lda, n_a, i0);
+  sb.init(B, ldb, n_b, j0);
+  // The products of k block kb; between them (STORE) block kb + 1 is staged from
+  // registers and (LOAD) block kb + 2 is loaded into the registers it leaves.
+  auto block = [&](int kb, auto check, auto st, auto ld) {
+    constexpr bool CHECK = decltype(check)::value, STORE = decltype(st)::value,
+                   LOAD = decltype(ld)::value;
     const int buf = kb & 1;
-    const bool more = kb + 1 < nkb;
-    const int64_t kn = kz0 + (int64_t)(kb + 1) * 32;
-    if (more) {
-      sa.load(A, lda, n_a, kz1, i0, kn);
-      sb.load(B, ldb, n_b, kz1, j0, kn);
-    }
-    __builtin_amdgcn_sched_barrier(0);
+    const int64_t k1 = kz0 + (int64_t)(kb + 1) * 32;
     const bf8v* xa = sA(buf) + lane + wr * 4 * 128;
     const bf8v* xb = sB(buf) + lane + wc * 8 * 128;
     bf8v ah[4], al[4];
@@ -251,19 +259,54 @@ __global__ __launch_bounds__(kGThreads, 1) void k_gemm_b3(TA A, int64_t lda, int
 #pragma unroll
     for (int b = 0; b < 8; ++b) {
       const bf8v bh = xb[b * 128], bl = xb[b * 128 + 64];
-#pragma unroll
-      for (int a = 0; a < 4; ++a) {
-        acc[a][b] = mfma_bf16(ah[a], bh, acc[a][b]);
-        acc[a][b] = mfma_bf16(ah[a], bl, acc[a][b]);
-        acc[a][b] = mfma_bf16(al[a], bh, acc[a][b]);
+      const int h = b / 4;
+      if (b % 4 == 0) {
+        if constexpr (STORE) sa.template store<CHECK>(h, k1, kz1, sA(buf ^ 1));
+        if (h ? LOAD : STORE) sa.settle(h ^ 1);
+        if constexpr (LOAD) sa.load(h, k1 + 32, kz1);
+      } else if (b % 2 == 0) {
+        if constexpr (STORE) sb.template store<CHECK>(h, k1, kz1, sB(buf ^ 1));
+        if constexpr (LOAD) sb.load(h, k1 + 32, kz1);
       }
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    if (more) {
-      sa.store(n_a, kz1, i0, kn, sA(buf ^ 1));
-      sb.store(n_b, kz1, j0, kn, sB(buf ^ 1));
+#pragma unroll
+      for (int a = 0; a < 4; ++a) acc[a][b] = mfma_bf16(ah[a], bh, acc[a][b]);
+#pragma unroll
+      for (int a = 0; a < 4; ++a) acc[a][b] = mfma_bf16(ah[a], bl, acc[a][b]);
+#pragma unroll
+      for (int a = 0; a < 4; ++a) acc[a][b] = mfma_bf16(al[a], bh, acc[a][b]);
     }
     __syncthreads();
+  };
+  const std::true_type yes;
+  const std::false_type no;
+  if (nkb > 0) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      sa.load(h, kz0, kz1);
+      sa.settle(h);
+      sb.load(h, kz0, kz1);
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      sa.template store<true>(h, kz0, kz1, sA(0));
+      sb.template store<true>(h, kz0, kz1, sB(0));
+    }
+    if (nkb > 1) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        sa.load(h, kz0 + 32, kz1);
+        if (h == 0) sa.settle(0);
+        sb.load(h, kz0 + 32, kz1);
+      }
+    }
+    __syncthreads();
+    int kb = 0;
+    for (; kb + 2 < nkb; ++kb) block(kb, no, yes, yes);
+    if (kb + 1 < nkb) {
+      block(kb, yes, yes, no);
+      ++kb;
+    }
+    block(kb, no, no, no);
   }
 
   // C[4 g + r][idx] of fragment (a, b): row i0 + 64 wr + 16 a + 4 g + r,

@@ -217,3 +217,25 @@ def test_fit_without_the_final_residual(gapx, gap):
     assert torch.equal(c0, c1)
     assert len(i0["resid_norm"]) == i0["refine_done"]
     assert i0["resid_norm"] == i1["resid_norm"][:-1]
+
+
+@pytest.mark.parametrize("ddt", ["f32", "f64"])
+@pytest.mark.parametrize("D,M,lo,hi", [(4, 1, 1, 1), (32, 33, 33, 33), (33, 64, 64, 66),
+                                       (64, 65, 65, 70), (97, 96, 255, 258), (129, 257, 257, 260)])
+def test_predict_and_backward_bf16x3_k_blocks(gapx, gap, D, M, lo, hi, ddt):
+    """One, two, three and more 32-deep blocks along each contraction, full and partial."""
+    w = synth.Workload("kblocks_p", 47, n_cfg=1, atoms_lo=lo, atoms_hi=hi, D=D, nb=2, M=M,
+                       zeta=2, delta=1.1, desc_dtype=ddt, jac_dtype=ddt)
+    b, X, atoms, sp = setup(gapx, w)
+    rng = np.random.default_rng(7)
+    c = rng.standard_normal(w.M)
+    ge = rng.standard_normal(b.n_atoms)
+    out = gap.predict(atoms, sp, torch.tensor(c, device="cuda"), precision="bf16x3", dEdd=True)
+    e, _, g, _ = oracle.predict(b.cfg_ptr, b.desc, b.pair_ptr, b.pair_j, b.jac, X, c, w.zeta,
+                                w.delta)
+    dd, dc, dX = gap.predict_backward(atoms, sp, torch.tensor(c, device="cuda"),
+                                      torch.tensor(ge, device="cuda"), precision="bf16x3")
+    r_dd, r_dc, r_dX = oracle.predict_backward(b.desc, X, c, ge, w.zeta, w.delta)
+    for name, got, ref in (("e_atom", out["e_atom"], e), ("dEdd", out["dEdd"], g),
+                           ("d_desc", dd, r_dd), ("d_c", dc, r_dc), ("d_X", dX, r_dX)):
+        assert relmax(got.cpu().numpy(), ref) <= MIXED_TOL, name
