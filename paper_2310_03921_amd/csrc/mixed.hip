@@ -20,30 +20,45 @@ inline unsigned cdiv(int64_t a, int64_t b) { return (unsigned)((a + b - 1) / b);
 
 // ------------------------------------------------------------------ split ----
 // X [M][ldx] FP64 -> Xh/Xl [M][ldp] (ldp = D rounded up to 32, zero padded)
-// and, when Xth is given, the transposed halves Xth/Xtl [D][ldm] (ldm = M rounded to 32).
-__global__ void k_split_x(const double* __restrict__ X, int64_t ldx, int64_t M, int64_t D,
-                          __bf16* __restrict__ Xh, __bf16* __restrict__ Xl, int64_t ldp,
-                          __bf16* __restrict__ Xth, __bf16* __restrict__ Xtl, int64_t ldm) {
-  const int64_t rows = std::max(M, (int64_t)0);
-  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < rows * ldp;
-       e += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t m = e / ldp, k = e - m * ldp;
-    const float x = (k < D) ? (float)X[m * ldx + k] : 0.f;
+// and, when Xth is given, the transposed halves Xth/Xtl [D][ldm] (ldm = M rounded
+// to 32, zero padded).  Bound by its reads and writes (8 bytes in, 8 out an entry):
+// a block turns a 64 x 64 tile through LDS, so that the transposed halves leave in
+// runs of 64 entries as well (4000 x 1000: 59 us with entry-wise transposed stores
+// and two passes of zeros, 19 here).
+__global__ __launch_bounds__(256) void k_split_x(const double* __restrict__ X, int64_t ldx,
+                                                 int64_t M, int64_t D, __bf16* __restrict__ Xh,
+                                                 __bf16* __restrict__ Xl, int64_t ldp,
+                                                 __bf16* __restrict__ Xth,
+                                                 __bf16* __restrict__ Xtl, int64_t ldm,
+                                                 int64_t n_kt) {
+  __shared__ uint32_t tile[64][65];   // [k][m], hi in the upper half
+  const int64_t m0 = blockIdx.x / n_kt * 64, k0 = blockIdx.x % n_kt * 64;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+  for (int q = 0; q < 16; ++q) {
+    const int r = 4 * q + wave;
+    const int64_t m = m0 + r, k = k0 + lane;
+    const float x = (m < M && k < D) ? (float)X[m * ldx + k] : 0.f;
     const __bf16 h = (__bf16)x;
     const __bf16 l = (__bf16)(x - (float)h);
-    Xh[e] = h;
-    Xl[e] = l;
-    if (Xth && k < D) {
-      Xth[k * ldm + m] = h;
-      Xtl[k * ldm + m] = l;
+    if (m < M && k < ldp) {
+      Xh[m * ldp + k] = h;
+      Xl[m * ldp + k] = l;
+    }
+    tile[lane][r] = (uint32_t)__builtin_bit_cast(uint16_t, h) << 16 | __builtin_bit_cast(uint16_t, l);
+  }
+  if (!Xth) return;
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < 16; ++q) {
+    const int r = 4 * q + wave;
+    const int64_t m = m0 + lane, k = k0 + r;
+    if (m < ldm && k < D) {
+      const uint32_t v = tile[r][lane];
+      Xth[k * ldm + m] = __builtin_bit_cast(__bf16, (uint16_t)(v >> 16));
+      Xtl[k * ldm + m] = __builtin_bit_cast(__bf16, (uint16_t)v);
     }
   }
-}
-
-__global__ void k_zero_bf16(__bf16* __restrict__ p, int64_t n) {
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x)
-    p[i] = (__bf16)0.0f;
 }
 
 // --------------------------------------------------------- energy rows ----
@@ -698,16 +713,11 @@ int64_t split_ld(int64_t n) { return (n + 31) / 32 * 32; }
 
 void split_x_bf16(const double* X, int64_t ldx, int64_t M, int64_t D, __bf16* Xh, __bf16* Xl,
                   __bf16* Xth, __bf16* Xtl, hipStream_t st) {
-  const int64_t ldp = split_ld(D), ldm = split_ld(M);
-  if (Xth) {
-    const int64_t nt = D * ldm;
-    const unsigned gz = std::max(1u, std::min(cdiv(nt, 256), 65536u));
-    hipLaunchKernelGGL(k_zero_bf16, dim3(gz), dim3(256), 0, st, Xth, nt);
-    hipLaunchKernelGGL(k_zero_bf16, dim3(gz), dim3(256), 0, st, Xtl, nt);
-  }
-  const unsigned g = std::max(1u, std::min(cdiv(M * ldp, 256), 65536u));
+  if (M <= 0 || D <= 0) return;
+  const int64_t ldp = split_ld(D), ldm = split_ld(M), n_kt = (ldp + 63) / 64;
+  const unsigned g = (unsigned)((ldm + 63) / 64 * n_kt);
   hipLaunchKernelGGL(k_split_x, dim3(g), dim3(256), 0, st, X, ldx, M, D, Xh, Xl, ldp, Xth, Xtl,
-                     ldm);
+                     ldm, n_kt);
 }
 
 void energy_rows_bf16x3(const void* desc, bool desc_f32, int64_t ldd, const int64_t* cfg_ptr,

@@ -85,3 +85,16 @@ def test_split_sparse_points_transposed(gap):
     assert not hi[:, D:].any() and not lo[:, D:].any()
     assert np.array_equal(ht[:, :M], rh.T) and np.array_equal(lt[:, :M], rl.T)
     assert not ht[:, M:].any() and not lt[:, M:].any()
+
+
+@pytest.mark.parametrize("M,D", [(1, 1), (31, 33), (64, 64), (65, 32), (130, 65)])
+def test_split_transposed_at_tile_edges(gap, M, D):
+    ld = (D + 3) // 4 * 4
+    x = inputs(M, D, ld, np.float64, seed=M)
+    out = gap.split_bf16x3(torch.tensor(x, device="cuda"), D, transposed=True)
+    hi, lo, ht, lt = (t.cpu().numpy().view(np.uint16) for t in out)
+    rh, rl = reference_split(x[:, :D])
+    assert np.array_equal(hi[:, :D], rh) and np.array_equal(lo[:, :D], rl)
+    assert not hi[:, D:].any() and not lo[:, D:].any()
+    assert np.array_equal(ht[:, :M], rh.T) and np.array_equal(lt[:, :M], rl.T)
+    assert not ht[:, M:].any() and not lt[:, M:].any()
