@@ -722,6 +722,18 @@ def default_handle() -> Gap:
     return _default[key]
 
 
+def _one_configuration(desc, D, dev):
+    """Atoms without pairs in one configuration.
+
+    The bounds [0, N] are formed on the device: a tensor made from a list is copied from
+    pageable memory, which waits for the stream, once a pass in each direction.
+    """
+    n = desc.shape[0]
+    return Atoms(torch.arange(2, dtype=torch.int64, device=dev).mul_(n), desc,
+                 torch.zeros(n + 1, dtype=torch.int64, device=dev),
+                 torch.zeros(0, dtype=torch.int32, device=dev), None, D)
+
+
 class GapPredict(torch.autograd.Function):
     """Per-atom energies eps_i = sum_m c_m delta^2 (d_i . x_m)^zeta with a hand-written backward.
 
@@ -736,9 +748,7 @@ class GapPredict(torch.autograd.Function):
         D = desc.shape[1]
         dev = desc.device
         desc_p = padded_rows(desc.detach(), D, device=dev)
-        atoms = Atoms(torch.tensor([0, desc.shape[0]], dtype=torch.int64, device=dev), desc_p.detach(),
-                      torch.zeros(desc.shape[0] + 1, dtype=torch.int64, device=dev),
-                      torch.zeros(0, dtype=torch.int32, device=dev), None, D)
+        atoms = _one_configuration(desc_p.detach(), D, dev)
         sp = Sparse(padded_rows(X.detach(), D, dtype=torch.float64, device=dev), D, int(zeta),
                     float(delta))
         c64 = c.detach().to(torch.float64).contiguous()
@@ -755,9 +765,7 @@ class GapPredict(torch.autograd.Function):
         D = desc.shape[1]
         dev = desc.device
         desc_p = padded_rows(desc.detach(), D, device=dev)
-        atoms = Atoms(torch.tensor([0, desc.shape[0]], dtype=torch.int64, device=dev), desc_p.detach(),
-                      torch.zeros(desc.shape[0] + 1, dtype=torch.int64, device=dev),
-                      torch.zeros(0, dtype=torch.int32, device=dev), None, D)
+        atoms = _one_configuration(desc_p.detach(), D, dev)
         sp = Sparse(padded_rows(X.detach(), D, dtype=torch.float64, device=dev), D, zeta, delta)
         dd, dc, dX = gap.predict_backward(atoms, sp, c.detach().to(torch.float64).contiguous(),
                                           g_e.detach().to(torch.float64).contiguous(), precision,

@@ -14,10 +14,10 @@
 // them idle (65536 x 4000 x 1000, FP32: W X 1532 -> 1314 us, 1.20 PFLOP/s of
 // executed products; P-stages 1746 -> 1500 and 1723 -> 1471; W^T D 1580 -> 1442.
 // The matrix cores are busy 64% of the time at 1.8 GHz.  Reading the next block's
-// first fragments ahead of its barrier as well changed nothing).  A 256-wide tile moves 64 bytes of operands per
-// 768 BF16 flop (12,288 per k block and thread pair), so at the matrix cores'
-// rate the operand stream from L2 stays near 15 TB/s for the whole chip; a
-// 128-wide tile would need twice that.
+// first fragments ahead of its barrier as well changed nothing).  A 256-wide tile
+// moves 64 bytes of operands per 768 BF16 flop (12,288 per k block and thread
+// pair), so at the matrix cores' rate the operand stream from L2 stays near
+// 15 TB/s for the whole chip; a 128-wide tile would need twice that.
 //
 // Epilogues:
 //   kPlain   C (FP64, row-major), or a split-K partial C + z * zstride;
