@@ -1617,25 +1617,32 @@ __global__ __launch_bounds__(512) void k_qr_upd3(double* __restrict__ A, int64_t
 
 // C -= V W' for a full 128-wide reflector block, one barrier per 64-column
 // tile.  Each of the eight waves owns 16 rows of the block's 128 and keeps
-// their V (128 deep) in registers for the whole kernel; -W' (Wn) is the only
+// their V (128 deep) in registers while it walks a row block; -W' (Wn) is the only
 // shared operand and goes through LDS one whole 128 x 64 tile at a time,
-// double-buffered: the next tile's Wn and C are fetched into registers at the
-// start of a tile and Wn is written to the free LDS buffer at its end.  A
-// wave's block is 16 rows x 64 columns (four matrix-core tiles sharing the V
+// double-buffered.  A wave's block is 16 rows x 64 columns (four matrix-core tiles sharing the V
 // operand).  Odd Wn rows are stored with their 16-column halves swapped so that
 // the lane groups reading rows 4t + g and 4t + g + 1 meet different banks.
 //
 // The memory traffic of a tile is issued between its matrix-core products, not
 // around them: the two waves of a SIMD run in step (one barrier per tile), so
 // work issued before or after the products leaves the matrix pipe idle.  For
-// that the previous tile's result is stored during the next tile (from a copy,
-// out), with buffer stores whose out-of-range offset drops the lanes that
-// must not write, so no store sits in a branch.
+// that the next tile's Wn and C are fetched and the previous tile's result is
+// stored in fixed steps of the products (two accumulators in turn), with buffer
+// stores whose out-of-range offset drops the lanes that must not write, so no store
+// sits in a branch.  Bound by both: 16 flop a byte at 53 TFLOP/s and 3.6 TB/s.
 //
 // Every global access is a wave-uniform base (scalar registers) plus a 32-bit
 // per-lane byte offset, and no column is clamped: the last tile is shifted left
 // to end at c_end (it needs c_end - cbeg >= 64) and stores only the columns the
 // previous tile did not.  Per-access 64-bit addresses would take 64 registers.
+//
+// The tiles of all row blocks in turn are dealt to kU5Blocks blocks, one per
+// compute unit, in even runs, so the last turn is as full as the others: with a
+// block per 128 rows, 689 of them ran as three turns of 256 (88,200 rows, 1,873
+// columns: 940 us, here 798; 56,000 rows in 410 blocks lost a fifth).  What
+// a run loads for a row block leaves in one batch, as a compute unit has no second
+// block to hide it behind.
+constexpr int kU5Blocks = 256;
 constexpr int kU5R = 128;  // rows per block (8 waves x 16)
 constexpr int kU5C = 64;   // columns per tile
 constexpr uint32_t kDropOffset = 0x80000000u;  // beyond any buffer this kernel makes
@@ -1645,102 +1652,125 @@ __global__ __launch_bounds__(512) void k_qr_upd5(double* __restrict__ A, int64_t
   __shared__ double sW[2][kQrOB][kU5C];
   const int lane = threadIdx.x & 63, g = lane >> 4, idx = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int64_t r0 = j0 + (int64_t)blockIdx.x * kU5R;
-  const int64_t rw = r0 + wave * 16 + idx;  // this lane's C row
   const int64_t cbeg = j0 + kQrOB;
   const int ntile = (int)((c_end - cbeg + kU5C - 1) / kU5C);
-  // V(rw, k) for k = 4 t + g
-  double v[kQrOB / 4];
-  {
-    const int64_t rr = rw - j0;
-#pragma unroll
-    for (int t = 0; t < kQrOB / 4; ++t) {
-      const int k = 4 * t + g;
-      double x = 0.0;
-      if (rw < m) x = (rr == k) ? 1.0 : (rr > k ? A[rw + (j0 + k) * ld] : 0.0);
-      v[t] = x;
-    }
-  }
-  // first column of a tile (the last one shifted to end at c_end)
-  auto tile_col = [&](int tile) { return min(cbeg + (int64_t)tile * kU5C, c_end - kU5C); };
-  // Wn tile: thread (wave, lane) holds rows wave + 8 h (h = 0..15), column lane
-  const uint32_t woff = (uint32_t)lane * 8u;
-  const uint32_t wbytes = (uint32_t)(kQrOB * nct * 8);
-  auto load_w = [&](int tile, double (&dst)[kQrOB / 8]) {
-    const auto rs = uniform_rsrc(Wn + (tile_col(min(tile, ntile - 1)) - j0) + (int64_t)wave * nct,
-                                 wbytes);
-#pragma unroll
-    for (int h = 0; h < kQrOB / 8; ++h) dst[h] = buf_ld(rs, woff, (uint32_t)(8 * h * nct * 8));
-  };
-  auto store_w = [&](int buf, const double (&src)[kQrOB / 8]) {
-#pragma unroll
-    for (int h = 0; h < kQrOB / 8; ++h) {
-      const int k = wave + 8 * h;
-      sW[buf][k][lane ^ ((k & 1) << 4)] = src[h];
-    }
-  };
-  // C element (rw, c0 + 16 i + 4 q + g): base column pointer uniform, the row
-  // and the lane group's column in the offset (rows past m read row m - 1)
-  const uint32_t coff = (uint32_t)((min(rw, m - 1) - r0 + g * ld) * 8);
-  const uint32_t cbytes = (uint32_t)(kU5C * ld * 8);  // a tile's extent from its base
-  // C (rows r0.., a tile's 64 columns) as four 16-column groups i: lane holds
-  // (rw, c0 + 16 i + 4 q + g) in q; reads of rows past m read row m - 1
-  auto load_ci = [&](int tile, int i, d4v& dst) {
-    const auto rs = uniform_rsrc(A + r0 + tile_col(min(tile, ntile - 1)) * ld, cbytes);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) dst[q] = buf_ld(rs, coff, (uint32_t)((16 * i + 4 * q) * ld * 8));
-  };
-  // Stores of a tile through a buffer resource based at its first column: a
-  // lane that must not write (row past m, or a column the shifted last tile
-  // shares with the previous one) gets an offset past the buffer's end, which
-  // the hardware drops.  Tile -1 (before the first) stores nothing.
-  auto store_ci = [&](int tile, int i, const d4v& src) {
-    const int64_t c0 = tile_col(max(tile, 0));
-    const int shift = tile < 0 ? kU5C : (int)(cbeg + (int64_t)tile * kU5C - c0);
-    const auto rs = uniform_rsrc(A + r0 + c0 * ld, cbytes);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const bool ok = rw < m && 16 * i + 4 * q + g >= shift;
-      buf_st(src[q], rs, ok ? coff : kDropOffset, (uint32_t)((16 * i + 4 * q) * ld * 8));
-    }
-  };
-  // a lane reads Wn row 4 t + g, columns 16 i + idx; odd rows are half-swapped
-  const int sw = (g & 1) << 4;
-  auto products = [&](d4v (&acc)[4], int t0, int t1, const double* wb) {
-#pragma unroll
-    for (int t = t0; t < t1; ++t) {
-      double a[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = wb[t * 4 * kU5C + ((i * 16) ^ sw)];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) acc[i] = mfma_f64(a[i], v[t], acc[i]);
-    }
-  };
-  d4v acc[4], nxt[4];
-  double wst[kQrOB / 8];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) load_ci(0, i, acc[i]);
-  load_w(0, wst);
-  store_w(0, wst);
-  // nothing of the prologue may be left in flight at the loop head: a pending
-  // load there would make the wait at the head of every tile wait for the
-  // previous tile's accesses as well
-  __builtin_amdgcn_s_waitcnt(0);
-  __syncthreads();
-  int buf = 0;
+  const int64_t n_all = (m - j0 + kU5R - 1) / kU5R * ntile;
+  const int64_t t_end = n_all * (blockIdx.x + 1) / gridDim.x;
 #pragma clang loop unroll(disable)
-  for (int tile = 0; tile < ntile; ++tile) {
-    load_w(tile + 1, wst);
+  for (int64_t t_at = n_all * blockIdx.x / gridDim.x; t_at < t_end;) {
+    const int tile_lo = (int)(t_at % ntile);
+    const int tile_hi = (int)min((int64_t)ntile, tile_lo + (t_end - t_at));
+    const int64_t r0 = j0 + t_at / ntile * kU5R;
+    t_at += tile_hi - tile_lo;
+    const int64_t rw = r0 + wave * 16 + idx;  // this lane's C row
+    // C element (rw, c0 + 16 i + 4 q + g): base column pointer uniform, the row
+    // and the lane group's column in the offset (rows past m read row m - 1)
+    const uint32_t coff = (uint32_t)((min(rw, m - 1) - r0 + g * ld) * 8);
+    double v[kQrOB / 4];  // V(rw, 4 t + g)
+    // first column of a tile (the last one shifted to end at c_end)
+    auto tile_col = [&](int tile) { return min(cbeg + (int64_t)tile * kU5C, c_end - kU5C); };
+    // Wn tile: thread (wave, lane) stages rows wave + 8 h (h = 0..15), column lane
+    const uint32_t woff = (uint32_t)lane * 8u;
+    const uint32_t wbytes = (uint32_t)(kQrOB * nct * 8);
+    auto load_w = [&](int tile, int h) {
+      const auto rs = uniform_rsrc(
+          Wn + (tile_col(min(tile, tile_hi - 1)) - j0) + (int64_t)wave * nct, wbytes);
+      return buf_ld(rs, woff, (uint32_t)(8 * h * nct * 8));
+    };
+    auto store_w = [&](int buf, int h, double x) {
+      const int k = wave + 8 * h;
+      sW[buf][k][lane ^ ((k & 1) << 4)] = x;
+    };
+    // C (rows r0.., a tile's 64 columns) as four 16-column groups i: lane holds
+    // (rw, c0 + 16 i + 4 q + g) in q; reads of rows past m read row m - 1
+    const uint32_t cbytes = (uint32_t)(kU5C * ld * 8);  // a tile's extent from its base
+    auto load_c = [&](int tile, int e) {
+      const auto rs = uniform_rsrc(A + r0 + tile_col(min(tile, tile_hi - 1)) * ld, cbytes);
+      return buf_ld(rs, coff, (uint32_t)(4 * e * ld * 8));
+    };
+    // Stores of a tile through a buffer resource based at its first column: a
+    // lane that must not write (row past m, or a column the shifted last tile
+    // shares with the previous one) gets an offset past the buffer's end, which
+    // the hardware drops.  The tile before the first stores nothing.
+    auto store_c = [&](int tile, int e, double x) {
+      const int64_t c0 = tile_col(max(tile, tile_lo));
+      const int shift = tile < tile_lo ? kU5C : (int)(cbeg + (int64_t)tile * kU5C - c0);
+      const bool ok = rw < m && 4 * e + g >= shift;
+      buf_st(x, uniform_rsrc(A + r0 + c0 * ld, cbytes), ok ? coff : kDropOffset,
+             (uint32_t)(4 * e * ld * 8));
+    };
+    // a lane reads Wn row 4 t + g, columns 16 i + idx; odd rows are half-swapped
+    const int sw = (g & 1) << 4;
+    d4v nxt[4], acc0[4], acc1[4];
+    double wst[8];
+    // One tile: acc = nxt - V Wn, with the accesses of its neighbours spread over
+    // the 32 steps of four products: the next tile's Wn (two halves of eight
+    // registers) and C, then the stores of the previous tile's result.
+    auto step = [&](int tile, int buf, d4v (&acc)[4], const d4v (&out)[4]) {
+      const double* wb = &sW[buf][g][idx];
+      double a[2][4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) load_ci(tile + 1, i, nxt[i]);
-    products(acc, 0, kQrOB / 4, &sW[buf][g][idx]);
-    store_w(buf ^ 1, wst);
+      for (int i = 0; i < 4; ++i) a[0][i] = wb[(i * 16) ^ sw];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) store_ci(tile, i, acc[i]);
-    lds_barrier();
-    buf ^= 1;
+      for (int t = 0; t < kQrOB / 4; ++t) {
+        if (t + 1 < kQrOB / 4) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) acc[i] = nxt[i];
+          for (int i = 0; i < 4; ++i) a[(t + 1) & 1][i] = wb[(t + 1) * 4 * kU5C + ((i * 16) ^ sw)];
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          acc[i] = mfma_f64(a[t & 1][i], v[t], t == 0 ? nxt[i] : acc[i]);
+        if (t < 8) wst[t] = load_w(tile + 1, t);
+        if (t >= 1 && t < 17) nxt[(t - 1) / 4][(t - 1) % 4] = load_c(tile + 1, t - 1);
+        if (t >= 16 && t < 24) {
+          store_w(buf ^ 1, t - 16, wst[t - 16]);
+          wst[t - 16] = load_w(tile + 1, t - 8);
+        }
+        if (t >= 8 && t < 24) store_c(tile - 1, t - 8, out[(t - 8) / 4][(t - 8) % 4]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+#pragma unroll
+      for (int h = 0; h < 8; ++h) store_w(buf ^ 1, 8 + h, wst[h]);
+      lds_barrier();
+    };
+    {
+      double w0[16];
+#pragma unroll
+      for (int h = 0; h < 16; ++h) w0[h] = load_w(tile_lo, h);
+#pragma unroll
+      for (int t = 0; t < kQrOB / 4; ++t)
+        v[t] = buf_ld(uniform_rsrc(A + r0 + (j0 + 4 * t) * ld, (uint32_t)(4 * ld * 8)), coff, 0u);
+#pragma unroll
+      for (int e = 0; e < 16; ++e) nxt[e / 4][e % 4] = load_c(tile_lo, e);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int h = 0; h < 16; ++h) store_w(0, h, w0[h]);
+      const int64_t rr = rw - j0;
+#pragma unroll
+      for (int t = 0; t < kQrOB / 4; ++t) {
+        const int k = 4 * t + g;
+        v[t] = rw >= m || rr < k ? 0.0 : (rr == k ? 1.0 : v[t]);
+      }
+    }
+    // nothing of the prologue may be left in flight at the loop head: a pending
+    // load there would make the wait at the head of every tile wait for the
+    // previous tile's accesses as well
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    int tile = tile_lo;
+#pragma clang loop unroll(disable)
+    for (; tile + 1 < tile_hi; tile += 2) {
+      step(tile, 0, acc0, acc1);
+      step(tile + 1, 1, acc1, acc0);
+    }
+    if (tile < tile_hi) {
+      step(tile, 0, acc0, acc1);
+#pragma unroll
+      for (int e = 0; e < 16; ++e) store_c(tile, e, acc0[e / 4][e % 4]);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 16; ++e) store_c(tile - 1, e, acc1[e / 4][e % 4]);
+    }
   }
 }
 
@@ -2268,17 +2298,17 @@ void cholesky_lower(double* Lw, int64_t ldl, int64_t M, double jitter, const dou
 
 int64_t chol_doubles(int64_t M) { return M * M + 1024; }
 
-// Rows per slab of the 128-wide W = V^T C of rows [j0, m) and nct columns: at
-// most 256 slabs, of >= 2048 rows where those alone give about two blocks per
-// compute unit, else shorter ones (>= 256 rows, whose partials still cost less
-// than reading V and C) until they do.  With 2048-row slabs a factorisation of
-// 6,000 rows and 200 columns ran this product on 8 blocks in 305 us; 50 blocks
-// take 48 us.
+// Rows per slab of the 128-wide W = V^T C of rows [j0, m) and nct columns: as many
+// slabs as give at most kVtcSlots blocks, two on each compute unit, so that all
+// run at once and end together (blocks of one length: 688 of them take two full
+// turns, and even 520 took 1.6 times as long as 504), and slabs of >= 256 rows,
+// whose partials still cost less than reading V and C.  88,200 rows, 2,001 columns: 902 us
+// in 688 blocks, 808 in 512.
+constexpr int64_t kVtcSlots = 512;
 static int64_t qr_slab_rows(int64_t m, int64_t j0, int64_t nct) {
   const int64_t rows = m - j0, n_ct = (nct + kVC - 1) / kVC;
-  const int64_t large = std::max<int64_t>((m + 255) / 256, 2048);
-  const int64_t fill = std::max<int64_t>(rows * n_ct / 512, 256);
-  return (std::min(large, fill) + 31) / 32 * 32;
+  const int64_t n = std::max<int64_t>(kVtcSlots / n_ct, 1);
+  return (std::max<int64_t>((rows + n - 1) / n, 256) + 31) / 32 * 32;
 }
 
 static int64_t qr_ldq(int64_t m) { return (m + 3) & ~int64_t(3); }
@@ -2378,8 +2408,10 @@ static void qr_wy_update_ob(double* A, int64_t ld, int64_t m, int64_t j0, int pw
   // the barrier-light kernel needs a full block, a full tile of trailing
   // columns and a 64-column tile of C within 31-bit offsets
   if (pw == kQrOB && nct - pw >= kU5C && ld < (int64_t)(1 << 22))
-    hipLaunchKernelGGL(k_qr_upd5, dim3(cdiv(m - j0, kU5R)), dim3(512), 0, st, A, ld, m, j0,
-                       c_end, nct, w->Wt);
+    hipLaunchKernelGGL(k_qr_upd5,
+                       dim3((unsigned)std::min<int64_t>(
+                           kU5Blocks, (int64_t)cdiv(m - j0, kU5R) * cdiv(nct - pw, kU5C))),
+                       dim3(512), 0, st, A, ld, m, j0, c_end, nct, w->Wt);
   else
     hipLaunchKernelGGL(k_qr_upd3, dim3(cdiv(m - j0, kU3R)), dim3(512), 0, st, A, ld, m, j0, pw,
                        c_end, nct, w->Wt);

@@ -86,3 +86,18 @@ def test_zero_column_is_reported(gapx, gap):
     with pytest.raises(gapx.GapError) as e:
         gap.lstsq(device_matrix(gapx, K, rng.standard_normal(500)), 500, 90)
     assert e.value.status == gapx.GAP_E_RANK
+
+
+@pytest.mark.parametrize("m,n", [(12700, 300), (33000, 193), (40001, 256)])
+def test_trailing_update_runs_over_row_blocks(gapx, gap, m, n):
+    """More 128 x 64 tiles of the trailing columns than compute units: a block's run
+    of tiles starts and ends inside row blocks."""
+    print(f"m {m} n {n}", flush=True)
+    rng = np.random.default_rng([m, n])
+    K = rng.standard_normal((m, n))
+    y = rng.standard_normal(m)
+    A = device_matrix(gapx, K, y)
+    x, _ = gap.lstsq(A, m, n)
+    ref = np.linalg.lstsq(K, y, rcond=None)[0]
+    assert np.linalg.norm(x.cpu().numpy() - ref) <= 1e-10 * np.linalg.norm(ref) * np.linalg.cond(K)
+    assert factor_error(A, K) <= 1e-12
