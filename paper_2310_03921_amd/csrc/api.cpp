@@ -526,13 +526,13 @@ gap_status build_knm_impl(gap_handle* h, const gap_atoms* a, const gap_sparse* s
   layout_pairs(L, N, a->n_pairs, p, true);
   const size_t S = L.take(sizeof(double) * std::max<int64_t>(N * ld4(M), 1));
   SplitWs sw;
-  size_t jh = 0, jl = 0;
+  size_t jx = 0;
   bool presplit = false;
   if (prec == GAP_BF16X3) {
     layout_split(L, M, D, false, sw);
     const size_t jbytes = (size_t)3 * a->n_pairs * gapk::split_ld(D) * 2;
     // Pre-split the Jacobians once for descriptors of up to 256 entries (the
-    // twelve-wave kernel then streams hi / lo halves with no split in its
+    // force-row kernel then streams hi / lo halves with no split in its
     // loop) when both halves fit in the workspace with room to spare.  Longer
     // descriptors stream the FP32 / FP64 rows and split them in registers:
     // measured on the 576k-atom fit, the wide kernel on pre-split rows took
@@ -542,10 +542,7 @@ gap_status build_knm_impl(gap_handle* h, const gap_atoms* a, const gap_sparse* s
     double room = std::min(0.85 * (double)(free_b + h->ws_bytes), (double)((size_t)16 << 30));
     if (h->ws_limit > 0) room = std::min(room, (double)h->ws_limit);
     presplit = a->n_pairs > 0 && D <= 256 && (double)(L.off + 2 * jbytes) * 1.125 <= room;
-    if (presplit) {
-      jh = L.take(jbytes);
-      jl = L.take(jbytes);
-    }
+    if (presplit) jx = L.take(2 * jbytes);
   }
   s = ensure_ws(h, L.off);
   if (s != GAP_OK) return s;
@@ -559,8 +556,8 @@ gap_status build_knm_impl(gap_handle* h, const gap_atoms* a, const gap_sparse* s
     run_split(h, sp, sw, false);
     if (presplit) {
       h->timer.begin(gapk::TM_SPLIT);
-      gapk::split_j_bf16(a->jac, f32(a->jac_dt), a->ld_jac, a->n_pairs, D, at<__bf16>(h, jh),
-                         at<__bf16>(h, jl), h->stream);
+      gapk::split_j_bf16(a->jac, f32(a->jac_dt), a->ld_jac, a->n_pairs, D, at<__bf16>(h, jx),
+                         h->stream);
       h->timer.end(gapk::TM_SPLIT);
     }
     h->timer.begin(gapk::TM_ENERGY);
@@ -574,7 +571,7 @@ gap_status build_knm_impl(gap_handle* h, const gap_atoms* a, const gap_sparse* s
     bool done = false;
     if (presplit)
       done = gapk::force_rows_bf16x3_split(
-          at<__bf16>(h, jh), at<__bf16>(h, jl), D, at<__bf16>(h, sw.xh), at<__bf16>(h, sw.xl), M,
+          at<__bf16>(h, jx), D, at<__bf16>(h, sw.xh), at<__bf16>(h, sw.xl), M,
           at<float>(h, S), ld8(M), at<int64_t>(h, p.tgt_ptr), at<int32_t>(h, p.tgt_pair),
           at<int32_t>(h, p.src), at<int32_t>(h, p.order), N, a->n_pairs, a->n_cfg, Knm, ld,
           h->stream);

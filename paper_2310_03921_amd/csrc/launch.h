@@ -219,14 +219,14 @@ void force_rows_bf16x3(const void* jac, bool jac_f32, int64_t ldj, int64_t D, co
                        const int64_t* tgt_ptr, const int32_t* tgt_pair, const int32_t* pair_src,
                        const int32_t* order, int64_t n_atoms, int64_t n_pairs, int64_t row0,
                        double* K, int64_t ldk, hipStream_t st);
-// J -> hi/lo halves [3 n_pairs][split_ld(D)] each.
+// J -> rows [3 n_pairs] of split_ld(D) / 32 blocks of 32 hi and 32 lo entries.
 void split_j_bf16(const void* jac, bool jac_f32, int64_t ldj, int64_t n_pairs, int64_t D,
-                  __bf16* Jh, __bf16* Jl, hipStream_t st);
+                  __bf16* J, hipStream_t st);
 // Any row-major rows x D array (ld % 4 == 0) -> hi/lo halves [rows][split_ld(D)].
 void split_rows_bf16(const void* x, bool x_f32, int64_t ld, int64_t rows, int64_t D,
                      __bf16* hi, __bf16* lo, hipStream_t st);
 // Force rows from pre-split Jacobians (returns false when D is too large for it).
-bool force_rows_bf16x3_split(const __bf16* Jh, const __bf16* Jl, int64_t D, const __bf16* Xh,
+bool force_rows_bf16x3_split(const __bf16* J, int64_t D, const __bf16* Xh,
                              const __bf16* Xl, int64_t M, const float* S, int64_t ldS,
                              const int64_t* tgt_ptr, const int32_t* tgt_pair,
                              const int32_t* pair_src, const int32_t* order, int64_t n_atoms,

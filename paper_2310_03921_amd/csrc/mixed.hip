@@ -557,12 +557,12 @@ void launch_b3w(JS js, int64_t D, const __bf16* Xh, const __bf16* Xl, int64_t ld
                      n_ct, n_tgb, nkb);
 }
 
-// Jacobian rows split once into hi/lo halves, [n_pairs][3][ldp] each (ldp = D
-// rounded up to 32, zero padded), so the force-row kernel streams 4 bytes per
-// element and does no splitting in its inner loop.
+// Rows split into hi/lo halves, zero padded from D to ldp (D rounded up to 32), 4 bytes
+// an element: 32-entry block q of row r at Jh and Jl + r * ldr + q * ldb.
 template <typename TJ>
 __global__ void k_split_j(const TJ* __restrict__ J, int64_t ldj, int64_t rows, int64_t D,
-                          __bf16* __restrict__ Jh, __bf16* __restrict__ Jl, int64_t ldp) {
+                          __bf16* __restrict__ Jh, __bf16* __restrict__ Jl, int64_t ldp,
+                          int64_t ldr, int64_t ldb) {
   const int64_t per_row = ldp / 8;
   for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < rows * per_row;
        e += (int64_t)gridDim.x * blockDim.x) {
@@ -571,25 +571,30 @@ __global__ void k_split_j(const TJ* __restrict__ J, int64_t ldj, int64_t rows, i
     load8f(J + r * ldj, k, D, x);
     bf8v h, l;
     split8(x, h, l);
-    *reinterpret_cast<bf8v*>(Jh + r * ldp + k) = h;
-    *reinterpret_cast<bf8v*>(Jl + r * ldp + k) = l;
+    const int64_t o = r * ldr + k / 32 * ldb + k % 32;
+    *reinterpret_cast<bf8v*>(Jh + o) = h;
+    *reinterpret_cast<bf8v*>(Jl + o) = l;
   }
 }
 
-// Twelve-wave BF16x3 force rows on pre-split Jacobians: wave w handles
-// component alpha = w % 3 of slot group w / 3 (16 targets), 128 columns whose
-// split X halves sit in LDS in matrix-core order.  Pair metadata, the next
-// pair's first Jacobian block and the S values of the current step are
-// fetched ahead, as in the FP64 form.
+// BF16x3 force rows on pre-split Jacobians (up to 256 descriptor entries): four
+// waves, each holding 16 targets (a slot group) for all three components and 128
+// columns, whose split X halves sit in LDS in matrix-core order for the whole
+// block.  Every B fragment read from LDS feeds nine matrix-core products: with
+// twelve waves of one component each it fed three, and the LDS reads alone took
+// longer than the products (28,672 atoms, 858k pairs, M 2000, D 252: 10.1 ms, 8.1 so).  A
+// wave has its SIMD to itself and issues an instruction only every few cycles, so
+// besides its products it does as little as possible: the hi and lo halves of a row
+// lie in one 128-byte line per k block, read straight into operand order, kDepth
+// blocks ahead.
 template <int NKB>
-__global__ __launch_bounds__(768) void k_force_rows_b3s(
-    const __bf16* __restrict__ Jh, const __bf16* __restrict__ Jl, int64_t ldp, int64_t D,
+__global__ __launch_bounds__(256, 1) void k_force_rows_b3s(
+    const __bf16* __restrict__ J, int64_t ldp, int64_t D,
     const __bf16* __restrict__ Xh, const __bf16* __restrict__ Xl, int64_t M,
     const float* __restrict__ S, int64_t ldS, const int64_t* __restrict__ tgt_ptr,
     const int32_t* __restrict__ tgt_pair, const int32_t* __restrict__ pair_src,
     const int32_t* __restrict__ order, int64_t n_atoms, int64_t n_pairs, int64_t row0,
     double* __restrict__ K, int64_t ldk, int64_t n_ct, int64_t n_grp) {
-  constexpr int nkb = NKB;  // 32-deep k blocks (compile time: straight-line, exact waits)
   // No guarded load on the hot path (a guarded load compiles to a branch whose
   // join waits for it at once): every load reads a valid address, and invalid
   // steps are cancelled by a zero S factor.  A slot past its degree (or a
@@ -597,97 +602,130 @@ __global__ __launch_bounds__(768) void k_force_rows_b3s(
   // split Jacobian rows are zero-padded to ldp, so no k clamp is needed.  Lane
   // idx of column tile u owns column 8 idx + u, so a lane's eight S values for
   // one source are 32 contiguous bytes (S rows zero-padded to ldS).
-  // X halves in LDS: [nkb][kNCF][hi | lo][64 lanes] of 16 bytes, so each 16-byte
+  // X halves in LDS: [NKB][kNCF][hi | lo][64 lanes] of 16 bytes, so each 16-byte
   // LDS read of the wave is contiguous (no bank conflict)
-  extern __shared__ SplitPair xs3[];
+  extern __shared__ bf8v xs3[];
   int64_t ct, tgb;
   if (!xcd_group_tile(n_grp, n_ct, tgb, ct)) return;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane >> 4, idx = lane & 15;
-  const int alpha = wave % 3, grp = wave / 3;
   const int64_t colbase = ct * (16 * kNCF);
-  for (int e = threadIdx.x; e < nkb * kNCF * 64; e += 768) {
+  for (int e = threadIdx.x; e < NKB * kNCF * 64; e += 256) {
     const int kb = e / (kNCF * 64), rem = e % (kNCF * 64);
     const int u = rem / 64, ln = rem % 64;
     const int64_t col = colbase + kNCF * (ln & 15) + u;
-    SplitPair sp;
+    bf8v h, l;
     if (col < M) {
       const int64_t k = (int64_t)kb * 32 + 8 * (ln >> 4);
-      sp.h = *reinterpret_cast<const bf8v*>(Xh + col * ldp + k);
-      sp.l = *reinterpret_cast<const bf8v*>(Xl + col * ldp + k);
+      h = *reinterpret_cast<const bf8v*>(Xh + col * ldp + k);
+      l = *reinterpret_cast<const bf8v*>(Xl + col * ldp + k);
     } else {
-      zero_split(sp.h, sp.l);
+      zero_split(h, l);
     }
-    bf8v* t = reinterpret_cast<bf8v*>(xs3) + (size_t)(e >> 6) * 128 + (e & 63);
-    t[0] = sp.h;
-    t[64] = sp.l;
+    bf8v* t = xs3 + (size_t)(e >> 6) * 128 + (e & 63);
+    t[0] = h;
+    t[64] = l;
   }
   __syncthreads();
-  const int64_t slot = (tgb * 4 + grp) * 16 + idx;
+  const int64_t slot = (tgb * 4 + wave) * 16 + idx;
   const int target = slot < n_atoms ? order[slot] : -1;
   const int64_t seg0 = target >= 0 ? tgt_ptr[target] : 0;
   const int deg = target >= 0 ? (int)(tgt_ptr[target + 1] - seg0) : 0;
   const int maxdeg = wave_max16(deg);
   const int64_t last = min(seg0 + max(deg - 1, 0), n_pairs - 1);
   auto pair_slot = [&](int t) -> int64_t { return min(seg0 + t, last); };
-  auto rowoff = [&](int p) -> int64_t { return ((int64_t)p * 3 + alpha) * ldp + 8 * g; };
   const int64_t cl0 = colbase + kNCF * idx;           // first column of this lane
   const int64_t scol = min(cl0, ldS - kNCF);          // clamped (valid) S offset
-  f4v acc[kNCF];
+  float colok[kNCF];
 #pragma unroll
-  for (int u = 0; u < kNCF; ++u) acc[u] = zero4f();
-  const bf8v* xb = reinterpret_cast<const bf8v*>(xs3) + lane;
+  for (int u = 0; u < kNCF; ++u) colok[u] = (cl0 + u < M) ? 1.f : 0.f;
+  f4v acc[3][kNCF];
+#pragma unroll
+  for (int a = 0; a < 3; ++a)
+#pragma unroll
+    for (int u = 0; u < kNCF; ++u) acc[a][u] = zero4f();
   if (maxdeg > 0) {
-    // pair metadata one step ahead of its use
+    // kDepth k blocks of the Jacobian rows in flight: slot kb % kDepth holds block
+    // kb until its products are issued, then block kb + kDepth, or from the last
+    // blocks of a step on the next step's first ones
+    constexpr int kDepth = NKB < 3 ? NKB : 3;
+    // pair indices two steps ahead of their use, sources one
     int pair = tgt_pair[pair_slot(0)];
     int pair_n = tgt_pair[pair_slot(1)];
     int src = pair_src[pair];
-    int64_t ro = rowoff(pair);
-    bf8v ah = *reinterpret_cast<const bf8v*>(Jh + ro);
-    bf8v al = *reinterpret_cast<const bf8v*>(Jl + ro);
+    const __bf16* jr = J + (int64_t)pair * 6 * ldp + 8 * g;
+    bf8v ah[kDepth][3], al[kDepth][3];
+#pragma unroll
+    for (int d = 0; d < kDepth; ++d)
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        ah[d][a] = *reinterpret_cast<const bf8v*>(jr + a * 2 * ldp + 64 * d);
+        al[d][a] = *reinterpret_cast<const bf8v*>(jr + a * 2 * ldp + 64 * d + 32);
+      }
     for (int t = 0; t < maxdeg; ++t) {
       const int pair_nn = tgt_pair[pair_slot(t + 2)];
       const int src_n = pair_src[pair_n];
-      const int64_t ro_n = rowoff(pair_n);
+      const __bf16* jn = J + (int64_t)pair_n * 6 * ldp + 8 * g;
       // S of this step's sources (rows 4 g + r of the output tile)
       f4v s_lo[4], s_hi[4];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int src_r = __shfl(src, 4 * g + r);
-        const float* sp = S + (int64_t)max(src_r, 0) * ldS + scol;
-        s_lo[r] = *reinterpret_cast<const f4v*>(sp);
-        s_hi[r] = *reinterpret_cast<const f4v*>(sp + 4);
-      }
-      f4v G[kNCF];
-#pragma unroll
-      for (int u = 0; u < kNCF; ++u) G[u] = zero4f();
-#pragma unroll 1
-      for (int kb = 0; kb < nkb; ++kb) {
-        const int64_t nro = (kb + 1 < nkb) ? ro + (int64_t)(kb + 1) * 32 : ro_n;
-        const bf8v nh = *reinterpret_cast<const bf8v*>(Jh + nro);
-        const bf8v nl = *reinterpret_cast<const bf8v*>(Jl + nro);
-#pragma unroll
-        for (int u = 0; u < kNCF; ++u) {
-          const bf8v bh = xb[(kb * kNCF + u) * 128], bl = xb[(kb * kNCF + u) * 128 + 64];
-          G[u] = mfma_bf16(ah, bh, G[u]);
-          G[u] = mfma_bf16(ah, bl, G[u]);
-          G[u] = mfma_bf16(al, bh, G[u]);
-        }
-        ah = nh;
-        al = nl;
-      }
+      float ok[4];
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int src_r = __shfl(src, 4 * g + r);
         const int deg_r = __shfl(deg, 4 * g + r);
-        const float ok = (t < deg_r && src_r >= 0) ? 1.f : 0.f;
+        ok[r] = (t < deg_r && src_r >= 0) ? 1.f : 0.f;
+        const float* sp = S + (int64_t)max(src_r, 0) * ldS + scol;
+        s_lo[r] = *reinterpret_cast<const f4v*>(sp);
+        s_hi[r] = *reinterpret_cast<const f4v*>(sp + 4);
+      }
+      // (a new address each step: the reads do not change with t, and 512 registers
+      // of them would be kept across the loop)
+      int x_at = lane;
+      asm volatile("" : "+v"(x_at));
+      const bf8v* xb = xs3 + x_at;
+      f4v G[3][kNCF];
+      auto add = [&](int u) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const float sv = (u < 4 ? s_lo[r][u & 3] : s_hi[r][u & 3]) * (ok[r] * colok[u]);
+#pragma unroll
+          for (int a = 0; a < 3; ++a) acc[a][u][r] += sv * G[a][u][r];
+        }
+      };
+#pragma unroll
+      for (int a = 0; a < 3; ++a)
+#pragma unroll
+        for (int u = 0; u < kNCF; ++u) G[a][u] = zero4f();
+#pragma unroll
+      for (int kb = 0; kb < NKB; ++kb) {
+        const int d = kb % kDepth;
+        // X halves one tile ahead of their products
+        const bf8v* xk = xb + (size_t)kb * kNCF * 128;
+        bf8v bh = xk[0], bl = xk[64];
 #pragma unroll
         for (int u = 0; u < kNCF; ++u) {
-          const float sv = (u < 4 ? s_lo[r][u & 3] : s_hi[r][u & 3]) *
-                           ((cl0 + u < M) ? ok : 0.f);
-          acc[u][r] += sv * G[u][r];
+          const bf8v ch = bh, cl = bl;
+          if (u + 1 < kNCF) {
+            bh = xk[(u + 1) * 128];
+            bl = xk[(u + 1) * 128 + 64];
+          }
+#pragma unroll
+          for (int a = 0; a < 3; ++a) G[a][u] = mfma_bf16(ah[d][a], ch, G[a][u]);
+#pragma unroll
+          for (int a = 0; a < 3; ++a) G[a][u] = mfma_bf16(ah[d][a], cl, G[a][u]);
+#pragma unroll
+          for (int a = 0; a < 3; ++a) G[a][u] = mfma_bf16(al[d][a], ch, G[a][u]);
+          // the last block: sums of the tile before, between this tile's products
+          if (kb == NKB - 1 && u > 0) add(u - 1);
+        }
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+          const __bf16* p = kb + kDepth < NKB ? jr + 64 * (kb + kDepth) : jn + 64 * d;
+          ah[d][a] = *reinterpret_cast<const bf8v*>(p + a * 2 * ldp);
+          al[d][a] = *reinterpret_cast<const bf8v*>(p + a * 2 * ldp + 32);
         }
       }
-      ro = ro_n;
+      add(kNCF - 1);
+      jr = jn;
       pair_n = pair_nn;
       src = src_n;
     }
@@ -697,8 +735,12 @@ __global__ __launch_bounds__(768) void k_force_rows_b3s(
     const int tr = __shfl(target, 4 * g + r);
     if (tr < 0) continue;
 #pragma unroll
-    for (int u = 0; u < kNCF; ++u)
-      if (cl0 + u < M) K[(row0 + 3 * (int64_t)tr + alpha) + (cl0 + u) * ldk] = -(double)acc[u][r];
+    for (int u = 0; u < kNCF; ++u) {
+      if (cl0 + u >= M) continue;
+#pragma unroll
+      for (int a = 0; a < 3; ++a)
+        K[(row0 + 3 * (int64_t)tr + a) + (cl0 + u) * ldk] = -(double)acc[a][u][r];
+    }
   }
 }
 
@@ -794,25 +836,30 @@ void force_rows_bf16x3(const void* jac, bool jac_f32, int64_t ldj, int64_t D, co
   }
 }
 
-void split_j_bf16(const void* jac, bool jac_f32, int64_t ldj, int64_t n_pairs, int64_t D,
-                  __bf16* Jh, __bf16* Jl, hipStream_t st) {
-  split_rows_bf16(jac, jac_f32, ldj, 3 * n_pairs, D, Jh, Jl, st);
-}
-
-void split_rows_bf16(const void* jac, bool jac_f32, int64_t ldj, int64_t rows, int64_t D,
-                     __bf16* Jh, __bf16* Jl, hipStream_t st) {
+static void launch_split(const void* x, bool x_f32, int64_t ld, int64_t rows, int64_t D,
+                         __bf16* hi, __bf16* lo, int64_t ldr, int64_t ldb, hipStream_t st) {
   if (rows <= 0) return;
   const int64_t ldp = split_ld(D);
   const unsigned g = std::max(1u, std::min(cdiv(rows * (ldp / 8), 256), 65536u));
-  if (jac_f32)
-    hipLaunchKernelGGL(k_split_j<float>, dim3(g), dim3(256), 0, st, tp<float>(jac), ldj, rows, D,
-                       Jh, Jl, ldp);
+  if (x_f32)
+    hipLaunchKernelGGL(k_split_j<float>, dim3(g), dim3(256), 0, st, tp<float>(x), ld, rows, D, hi,
+                       lo, ldp, ldr, ldb);
   else
-    hipLaunchKernelGGL(k_split_j<double>, dim3(g), dim3(256), 0, st, tp<double>(jac), ldj, rows, D,
-                       Jh, Jl, ldp);
+    hipLaunchKernelGGL(k_split_j<double>, dim3(g), dim3(256), 0, st, tp<double>(x), ld, rows, D,
+                       hi, lo, ldp, ldr, ldb);
 }
 
-bool force_rows_bf16x3_split(const __bf16* Jh, const __bf16* Jl, int64_t D, const __bf16* Xh,
+void split_j_bf16(const void* jac, bool jac_f32, int64_t ldj, int64_t n_pairs, int64_t D,
+                  __bf16* J, hipStream_t st) {
+  launch_split(jac, jac_f32, ldj, 3 * n_pairs, D, J, J + 32, 2 * split_ld(D), 64, st);
+}
+
+void split_rows_bf16(const void* x, bool x_f32, int64_t ld, int64_t rows, int64_t D, __bf16* hi,
+                     __bf16* lo, hipStream_t st) {
+  launch_split(x, x_f32, ld, rows, D, hi, lo, split_ld(D), 32, st);
+}
+
+bool force_rows_bf16x3_split(const __bf16* J, int64_t D, const __bf16* Xh,
                              const __bf16* Xl, int64_t M, const float* S, int64_t ldS,
                              const int64_t* tgt_ptr, const int32_t* tgt_pair,
                              const int32_t* pair_src, const int32_t* order, int64_t n_atoms,
@@ -834,7 +881,7 @@ bool force_rows_bf16x3_split(const __bf16* Jh, const __bf16* Jl, int64_t D, cons
                                 (int)((size_t)kMaxKb32 * kNCF * 64 * sizeof(SplitPair)));
       attr[nkb] = true;
     }
-    hipLaunchKernelGGL(kern, dim3(blocks), dim3(768), lds, st, Jh, Jl, ldp, D, Xh,
+    hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), lds, st, J, ldp, D, Xh,
                        Xl, M, S, ldS, tgt_ptr, tgt_pair, pair_src, order, n_atoms, n_pairs, row0,
                        K, ldk, n_ct, n_tgb);
   };

@@ -239,3 +239,20 @@ def test_predict_and_backward_bf16x3_k_blocks(gapx, gap, D, M, lo, hi, ddt):
     for name, got, ref in (("e_atom", out["e_atom"], e), ("dEdd", out["dEdd"], g),
                            ("d_desc", dd, r_dd), ("d_c", dc, r_dc), ("d_X", dX, r_dX)):
         assert relmax(got.cpu().numpy(), ref) <= MIXED_TOL, name
+
+
+@pytest.mark.parametrize("D,M,lo,hi", [(4, 3, 1, 9), (33, 20, 5, 15), (64, 65, 16, 40),
+                                       (96, 128, 30, 34), (125, 129, 17, 50), (160, 64, 8, 30),
+                                       (180, 130, 20, 40), (222, 40, 10, 40), (256, 127, 16, 33)])
+@pytest.mark.parametrize("jdt", ["f32", "f64"])
+def test_knm_bf16x3_presplit_k_blocks(gapx, gap, D, M, lo, hi, jdt):
+    """Force rows from split Jacobians of one to eight 32-entry blocks: target groups
+    and column tiles full and partial, targets without pairs."""
+    w = synth.Workload("presplit_k", 51, n_cfg=7, atoms_lo=lo, atoms_hi=hi, D=D, nb=5, M=M,
+                       zeta=3, delta=1.3, precision="bf16x3", jac_dtype=jdt, desc_dtype=jdt)
+    b, X, atoms, sp = setup(gapx, w)
+    A = gap.build_knm(atoms, sp, precision="bf16x3")
+    got = A[:w.M, :b.n_rows].T.cpu().numpy()
+    ref = oracle.build_knm(b.cfg_ptr, b.desc, b.pair_ptr, b.pair_j, b.jac, X, w.zeta, w.delta)
+    assert relmax(got[:b.n_cfg], ref[:b.n_cfg]) <= MIXED_TOL
+    assert relmax(got[b.n_cfg:], ref[b.n_cfg:]) <= MIXED_TOL
