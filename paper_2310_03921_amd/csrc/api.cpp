@@ -1401,8 +1401,8 @@ gap_status gap_predict_backward(gap_handle* h, const gap_atoms* a, const gap_spa
                      at<__bf16>(h, sw.xl), M, D, sp->zeta, sp->delta, c, g_e, at<float>(h, W32),
                      ldw, nullptr, at<double>(h, dcp), h->stream);
     if (d_c)
-      gapk::sum_parts_f64(at<double>(h, dcp), gapk::gemm_b3_row_blocks(N), M, d_c, 1, M, M,
-                          h->stream);
+      // (a thread per point walked up to 256 row tiles' sums alone: 100 us)
+      gapk::reduce_rows_f64(at<double>(h, dcp), gapk::gemm_b3_row_blocks(N), M, d_c, h->stream);
     if (d_desc)
       gapk::gemm_b3_wx(at<float>(h, W32), ldw, N, M, at<__bf16>(h, sw.xth),
                        at<__bf16>(h, sw.xtl), D, d_desc, D, h->stream);
