@@ -319,7 +319,7 @@ void sumsq_add_f64(const double* x, int64_t n, double* out, hipStream_t st);
 void trinv_upper2(const double* R0, int64_t ld0, double* Y0, const double* R1, int64_t ld1,
                   double* Y1, int64_t n, int64_t ldy, double* tmp, int* dev_err, hipStream_t st);
 // var[i] = base + sign * ||Z[i][0:m]||^2 with base var[i] (init 0), delta^2 (d_i . d_i)^zeta
-// (init 1) or 0 (init 2).
+// (init 1) or 0 (init 2); init 3: as 1, then plus var[i].
 void var_rows(const double* Z, int64_t ldz, int64_t n, int64_t m, double sign, const void* desc,
               bool desc_f32, int64_t ldd, int64_t D, int zeta, double delta, int init,
               double* var, hipStream_t st);

@@ -1922,7 +1922,7 @@ __global__ __launch_bounds__(256) void k_var_rows(const double* __restrict__ Z, 
   }
   s = wave_sum(s);
   double kii = 0.0;
-  if (init == 1) {
+  if (init & 1) {
     double t = 0.0;
     for (int64_t k = lane; k < D; k += 64) {
       const double d = (double)desc[i * ldd + k];
@@ -1933,7 +1933,10 @@ __global__ __launch_bounds__(256) void k_var_rows(const double* __restrict__ Z, 
     for (int q = 0; q < zeta; ++q) p *= t;
     kii = delta * delta * p;
   }
-  if (lane == 0) var[i] = (init ? kii : var[i]) + sign * s;
+  if (lane == 0) {
+    const double v = (init ? kii : var[i]) + sign * s;
+    var[i] = init == 3 ? v + var[i] : v;
+  }
 }
 
 // Descriptors as FP64 rows [n][ldo] with zero row padding (columns D .. ldo - 1).

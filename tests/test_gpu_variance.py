@@ -70,3 +70,22 @@ def test_variance_from_fold_state_ragged(gapx, gap):
     gap.fold_rows(T, M, n, torch.tensor(y, device="cuda"), torch.tensor(sig, device="cuda"))
     var = gap.predict_variance(atoms, sp, Kmm_d, w.jitter, T)
     check(var.cpu().numpy(), b, X, K, Kmm, y, sig, w)
+
+
+@pytest.mark.parametrize("M", [511, 512, 577])
+def test_variance_with_the_factorisation_beside_it(gapx, gap, M):
+    """Around the size from which U and its inverse are formed on the side stream; two
+    calls that follow each other without a wait."""
+    w = synth.Workload("side_chol", 37, n_cfg=11, atoms_lo=55, atoms_hi=70, D=60, nb=2, M=M,
+                       zeta=4, delta=1.3)
+    b, X, K, Kmm, y, sig = problem(w)
+    atoms = gapx.Atoms.from_host(b.cfg_ptr, b.desc, b.pair_ptr, b.pair_j, b.jac)
+    sp = gapx.Sparse.from_host(X, w.zeta, w.delta)
+    Kmm_d = gap.build_kmm(sp)
+    A = gap.build_knm(atoms, sp)
+    gap.fit(A, b.n_rows, Kmm_d, torch.tensor(y, device="cuda"), torch.tensor(sig, device="cuda"),
+            w.jitter, sp)
+    outs = [gap.predict_variance(atoms, sp, Kmm_d, w.jitter, A) for _ in range(2)]
+    for var in outs:
+        check(var.cpu().numpy(), b, X, K, Kmm, y, sig, w)
+    assert torch.equal(outs[0], outs[1])
