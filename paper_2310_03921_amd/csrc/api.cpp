@@ -252,11 +252,6 @@ void layout_predict(Layout& L, const gap_atoms* a, const gap_sparse* sp, bool ne
   if (need_forces) layout_pairs(L, N, a->n_pairs, w.pairs);
 }
 
-// Pairs from which predict transposes them on the side stream beside its products:
-// the fork and the join cost about 25 us (a call of 1,900 pairs went from 41 to 66 us,
-// one of 69k stayed as it was), the transposition of 464k pairs 60 (1556 -> 1520 us).
-constexpr int64_t kSidePairs = 1 << 17;
-
 void run_predict(gap_handle* h, const gap_atoms* a, const gap_sparse* sp, const double* c,
                  const PredictWs& w, double* e_atom, double* e_cfg, double* dEdd,
                  double* forces, bool bf16 = false, const int32_t* species = nullptr,
@@ -267,13 +262,6 @@ void run_predict(gap_handle* h, const gap_atoms* a, const gap_sparse* sp, const 
   double* W = (need_g && !bf16) ? at<double>(h, w.W) : nullptr;
   float* W32 = bf16 ? at<float>(h, w.W) : nullptr;
   const int64_t ldw = ld4(M);
-  const bool side_pairs = forces && a->n_pairs >= kSidePairs;
-  if (side_pairs) {
-    (void)hipEventRecord(h->ev_fork, h->stream);
-    (void)hipStreamWaitEvent(h->side, h->ev_fork, 0);
-    run_pairs(h, a, w.pairs, false, h->side);
-    (void)hipEventRecord(h->ev_join, h->side);
-  }
   auto wx = [&](double* out, int64_t ldo) {
     if (bf16)
       gapk::gemm_b3_wx(W32, ldw, N, M, at<__bf16>(h, w.split.xth), at<__bf16>(h, w.split.xtl), D,
@@ -302,10 +290,7 @@ void run_predict(gap_handle* h, const gap_atoms* a, const gap_sparse* sp, const 
     const int64_t ldg = ld4(D);
     wx(g, ldg);
     if (dEdd) gapk::copy_rows_f64(g, ldg, dEdd, D, N, D, h->stream);
-    if (side_pairs)
-      (void)hipStreamWaitEvent(h->stream, h->ev_join, 0);
-    else
-      run_pairs(h, a, w.pairs, false);
+    run_pairs(h, a, w.pairs, false);
     gapk::forces_f64(a->jac, f32(a->jac_dt), a->ld_jac, D, g, ldg, at<int32_t>(h, w.pairs.src), N,
                      a->n_pairs, at<int64_t>(h, w.pairs.tgt_ptr),
                      at<int32_t>(h, w.pairs.tgt_pair), at<double>(h, w.f_pair), forces,

@@ -79,23 +79,3 @@ def test_force_rows_over_blocks_of_targets(gapx, gap, n_atoms):
     ref = oracle.build_knm(cfg, desc, pair_ptr, pair_j, jac, X, 2, 1.0)
     got = K[:M, :len(ref)].T.cpu().numpy()
     assert np.abs(got - ref).max() <= 1e-10 * np.abs(ref).max()
-
-
-@pytest.mark.parametrize("n_pairs", [(1 << 17) - 1, 1 << 17, 150001])
-def test_predict_with_the_transposition_beside_it(gapx, gap, n_pairs):
-    """Forces around the pair count from which predict transposes on its side stream, in
-    calls that follow each other without a wait; sums of ~33 FP64 products of order one
-    per atom and component: 1e-10 of the largest force, as everywhere."""
-    n, D, M = 4001, 4, 5
-    rng = np.random.default_rng(n_pairs)
-    pair_ptr, pair_j = pair_list(n, n_pairs)
-    desc = rng.standard_normal((n, D))
-    jac = rng.standard_normal((n_pairs, 3, D))
-    X, zeta, delta = desc[:M].copy(), 2, 1.1
-    atoms = gapx.Atoms.from_host(np.array([0, n]), desc, pair_ptr, pair_j, jac)
-    sp = gapx.Sparse.from_host(X, zeta, delta)
-    cs = [rng.standard_normal(M) for _ in range(3)]
-    outs = [gap.predict(atoms, sp, torch.tensor(c, device="cuda"), forces=True) for c in cs]
-    for c, out in zip(cs, outs):
-        _, _, _, F = oracle.predict(np.array([0, n]), desc, pair_ptr, pair_j, jac, X, c, zeta, delta)
-        assert np.abs(out["forces"].cpu().numpy() - F).max() <= 1e-10 * np.abs(F).max()
