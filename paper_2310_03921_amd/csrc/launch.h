@@ -276,7 +276,7 @@ struct QrWork {
   double* T;          // nb x nb
   double* Q;          // a panel's orthonormal columns, 64 x (m rounded up to 4)
   double* pan;        // a panel's small matrices
-  double* red;        // reduction partials and pivot rows of the column-by-column panel
+  double* red;        // reduction partials and pivot rows of panels taken column by column
   double* tau;        // tau of every reflector [n]
   unsigned int* counter;
   unsigned int* flags;  // per-block completion flags of the multi-block triangular solves

@@ -6,8 +6,8 @@
 // Householder QR, right-looking and blocked (compact WY, Q = I - V T V^T):
 //   panel: 64 columns at once, by Cholesky QR twice and the reconstruction of
 //          the Householder vectors (all products on FP64 MFMA, three small
-//          one-block steps); a column-by-column cooperative kernel takes a
-//          panel whose columns are numerically dependent.
+//          one-block steps); a cooperative kernel that adds shifted rounds takes
+//          a panel whose columns are numerically dependent.
 //   trailing update: W = V^T C (split over row slabs on FP64 MFMA, then a
 //          fixed-order reduction), T from the Gram V^T V and tau, and
 //          C -= V (T^T W) on FP64 MFMA.  b rides along as the last column.
@@ -25,7 +25,7 @@ constexpr int kQrNB = 64;      // outer block width (compact-WY trailing update)
 constexpr int kTrsvMaxBlocks = 256;  // multi-block triangular solve: n <= 64 * 256
 constexpr int kPanelMaxGrid = 256;
 // Workspace counter words: [0], [1] the states of an outer block's two panels (1:
-// the panel needs the column-by-column kernel), [kPanelBar ..) that kernel's eight arrival counters.
+// the panel is left to k_qr_panel_dep), [kPanelBar ..) that kernel's eight arrival counters.
 constexpr int kPanelBar = 64;
 constexpr int kPanelBarWords = 8 * 16;
 constexpr int kCounterWords = 256;
@@ -46,6 +46,27 @@ GAP_DEV void xstore(double* p, double v) {
   __hip_atomic_store(reinterpret_cast<uint64_t*>(p), __builtin_bit_cast(uint64_t, v),
                      __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+// A value the compiler takes as new, so that what is derived from it is formed where
+// it is used and not kept in registers from one phase of a long kernel to the next.
+GAP_DEV int64_t fresh(int64_t x) {
+  asm volatile("" : "+s"(x));
+  return x;
+}
+template <typename T>
+GAP_DEV T* fresh(T* p) {
+  asm volatile("" : "+s"(p));
+  return p;
+}
+GAP_DEV int fresh(int x) {
+  asm volatile("" : "+s"(x));
+  return x;
+}
+GAP_DEV int fresh_thread() {
+  int t = threadIdx.x;
+  asm volatile("" : "+v"(t));
+  return t;
+}
+GAP_DEV int fresh_lane() { return fresh_thread() & 63; }
 // Wait until every memory operation this wave issued has completed.
 GAP_DEV void wait_mem() { __builtin_amdgcn_s_waitcnt(0); }
 
@@ -233,7 +254,7 @@ GAP_DEV void grid_barrier_x8(unsigned int* arrive, unsigned int round, int* dev_
 // matrix and solutions agree with LAPACK's to rounding for condition numbers up
 // to 1e12 over all columns).  A panel that fails the test (its columns dependent
 // to about 1e-8, a zero column, an overflow) is left as it is and factored by
-// k_qr_panel_col.  One grid barrier and one reduction over blocks per column, as
+// k_qr_panel_dep.  One grid barrier and one reduction over blocks per column, as
 // in the register-resident reduction this replaces, cost 6.8 us a column at
 // 26,000 rows and 9.7 us at 353,000 (0.43 and 0.62 ms per 64 columns, and 0.13
 // and 0.34 ms more for the updates between its 16-column steps); this takes
@@ -255,22 +276,19 @@ constexpr int kPanUS = kPanInvV + kInv16;     // -U S, col-major
 constexpr int kPanG = kPanUS + 4096;          // reduced Gram
 constexpr int kPanDoubles = kPanG + kGram;
 
-// Gram partials of up to 64 columns (col-major, rows 16-byte groups aligned):
-// wave w of the grid takes the 16-row chunks w, w + waves, ...; a lane holds
-// four consecutive rows of its column of each 16-column tile, which serve as
-// both operands; the block's four waves add up in LDS.
-__global__ __launch_bounds__(256) void k_panel_gram(const double* __restrict__ P, int64_t ld,
-                                                    int64_t rows, int bw,
-                                                    double* __restrict__ part) {
-  __shared__ double red[3][kGram];
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane >> 4, idx = lane & 15;
+// Gram of up to 64 columns (col-major, rows 16-byte groups aligned) over the
+// 16-row chunks c, c + nw, ...: a lane holds four consecutive rows of its column of
+// each 16-column tile, which serve as both operands.
+GAP_DEV void gram_chunks(const double* __restrict__ P, int64_t ld, int64_t rows, int bw, int64_t c,
+                         int64_t nw, d4v (&acc)[kGramTiles],
+                         int lane = threadIdx.x & 63) {
+  const int g = lane >> 4, idx = lane & 15;
   const double* col[4];
 #pragma unroll
   for (int u = 0; u < 4; ++u) col[u] = P + (int64_t)min(16 * u + idx, bw - 1) * ld + 4 * g;
-  d4v acc[kGramTiles];
 #pragma unroll
   for (int t = 0; t < kGramTiles; ++t) acc[t] = zero4();
-  const int64_t nch = (rows + 15) / 16, full = rows / 16, nw = (int64_t)gridDim.x * 4;
+  const int64_t nch = (rows + 15) / 16, full = rows / 16;
   auto products = [&](const d4v (&a)[4]) {
     int t = 0;
 #pragma unroll
@@ -280,7 +298,6 @@ __global__ __launch_bounds__(256) void k_panel_gram(const double* __restrict__ P
 #pragma unroll
         for (int q = 0; q < 4; ++q) acc[t] = mfma_f64(a[i][q], a[j][q], acc[t]);
   };
-  int64_t c = (int64_t)blockIdx.x * 4 + wave;
   d4v cur[4], nxt[4];
   if (c < full) {
 #pragma unroll
@@ -303,11 +320,18 @@ __global__ __launch_bounds__(256) void k_panel_gram(const double* __restrict__ P
       for (int q = 0; q < 4; ++q) cur[u][q] = q < left ? col[u][16 * c + q] : 0.0;
     products(cur);
   }
+}
+
+// Sum of the block's four waves' Grams, in wave order, handed to put(e, value) by wave 0.
+template <class FP>
+GAP_DEV void gram_block_sum(const d4v (&acc)[kGramTiles], double* red, FP put,
+                            int lane = threadIdx.x & 63) {
+  const int wave = threadIdx.x >> 6;
   if (wave > 0) {
 #pragma unroll
     for (int t = 0; t < kGramTiles; ++t)
 #pragma unroll
-      for (int q = 0; q < 4; ++q) red[wave - 1][t * 256 + q * 64 + lane] = acc[t][q];
+      for (int q = 0; q < 4; ++q) red[(wave - 1) * kGram + t * 256 + q * 64 + lane] = acc[t][q];
   }
   __syncthreads();
   if (wave == 0) {
@@ -316,27 +340,41 @@ __global__ __launch_bounds__(256) void k_panel_gram(const double* __restrict__ P
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const int e = t * 256 + q * 64 + lane;
-        part[(int64_t)blockIdx.x * kGram + e] =
-            ((acc[t][q] + red[0][e]) + red[1][e]) + red[2][e];
+        put(e, ((acc[t][q] + red[e]) + red[kGram + e]) + red[2 * kGram + e]);
       }
   }
 }
 
-// The reduced Gram (layout of k_panel_gram) into the lower triangle of S, with
-// unit columns from bw on.  Returns whether this thread saw an entry further than
-// `far` from the unit matrix (or not a number).
-GAP_DEV bool gram_to_lds(const double* __restrict__ G, int bw, double (*S)[kTriS], double far) {
+__global__ __launch_bounds__(256) void k_panel_gram(const double* __restrict__ P, int64_t ld,
+                                                    int64_t rows, int bw,
+                                                    double* __restrict__ part) {
+  __shared__ double red[3 * kGram];
+  d4v acc[kGramTiles];
+  gram_chunks(P, ld, rows, bw, (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6),
+              (int64_t)gridDim.x * 4, acc);
+  gram_block_sum(acc, red,
+                 [&](int e, double v) { part[(int64_t)blockIdx.x * kGram + e] = v; });
+}
+
+// The reduced Gram (value e of gram_block_sum's layout: load(e)) into the lower
+// triangle of S, with unit columns from bw on.  Returns whether this thread saw an
+// entry further than `far` from the unit matrix (or not a number).
+template <class FL>
+GAP_DEV bool gram_to_lds(FL load, int bw, double (*S)[kTriS], double far,
+                         int tid = threadIdx.x) {
   bool off = false;
+  double v[kGramTiles];
 #pragma unroll
-  for (int e0 = 0; e0 < kGram; e0 += 256) {
-    const int e = e0 + threadIdx.x;
-    const int t = e >> 8, q = (e >> 6) & 3, lane = e & 63;
+  for (int t = 0; t < kGramTiles; ++t) v[t] = load(256 * t + tid);
+#pragma unroll
+  for (int t = 0; t < kGramTiles; ++t) {
+    const int q = (tid >> 6) & 3, lane = tid & 63;
     const int i = t < 1 ? 0 : t < 3 ? 1 : t < 6 ? 2 : 3, j = t - i * (i + 1) / 2;
     const int r = 16 * i + (lane >> 4) + 4 * q, c = 16 * j + (lane & 15);
-    const double v = G[e], unit = r == c ? 1.0 : 0.0;
+    const double unit = r == c ? 1.0 : 0.0;
     if (r >= c) {
-      S[r][c] = r < bw ? v : unit;
-      off |= r < bw && !(fabs(v - unit) < far);
+      S[r][c] = r < bw ? v[t] : unit;
+      off |= r < bw && !(fabs(v[t] - unit) < far);
     }
   }
   return off;
@@ -344,12 +382,12 @@ GAP_DEV bool gram_to_lds(const double* __restrict__ G, int bw, double (*S)[kTriS
 
 // R1 of the first Gram; sets the panel's state word (state[half], also set where
 // the outer block's first panel is) and clears the barrier counters of
-// k_qr_panel_col.
+// k_qr_panel_dep.
 __global__ __launch_bounds__(256) void k_panel_chol(int bw, int half, double* __restrict__ pan,
                                                     unsigned int* __restrict__ state,
                                                     unsigned int* __restrict__ arrive) {
   __shared__ double S[kTri][kTriS];
-  (void)gram_to_lds(pan + kPanG, bw, S, INFINITY);
+  (void)gram_to_lds([&](int e) { return pan[kPanG + e]; }, bw, S, INFINITY);
   __syncthreads();
   const bool bad = chol64_lds(S);
   if (threadIdx.x == 0) state[half] = bad || (half && state[0]) ? 1u : 0u;
@@ -374,15 +412,12 @@ struct PanelSolve {
   int bw;
   const double *u, *inv;
 };
-constexpr int kSolveBlocks = 512;  // of four waves: two per SIMD
-__global__ __launch_bounds__(256, 2) void k_panel_solve(PanelSolve pa, PanelSolve pb, int na,
-                                                        const unsigned int* __restrict__ state) {
-  if (*state) return;
-  const bool second = (int)blockIdx.x >= na;
-  const PanelSolve p = second ? pb : pa;
-  const int lane = threadIdx.x & 63, g = lane >> 4, idx = lane & 15;
-  const int64_t nt = (p.rows + 15) / 16, step = (second ? gridDim.x - na : na) * 4;
-  int64_t tile = (second ? blockIdx.x - na : blockIdx.x) * 4 + (threadIdx.x >> 6);
+// Tiles tile, tile + step, ... of sixteen rows; u(i, j) and inv(e): the triangle.
+template <class FU, class FI>
+GAP_DEV void solve_tiles(const PanelSolve& p, FU u, FI inv, int64_t tile, int64_t step,
+                         int lane = threadIdx.x & 63) {
+  const int g = lane >> 4, idx = lane & 15;
+  const int64_t nt = (p.rows + 15) / 16;
   if (tile >= nt) return;
   // columns 16 b + g + 4 r of row 16 tile + idx (past the last row: that row again,
   // which stores the same values)
@@ -396,7 +431,7 @@ __global__ __launch_bounds__(256, 2) void k_panel_solve(PanelSolve pa, PanelSolv
   d4v cur[4], nxt[4];
   load(tile, cur);
   TriOps t;
-  tri_ops(t, [&](int i, int j) { return p.u[i * kTri + j]; }, [&](int e) { return p.inv[e]; });
+  tri_ops(t, u, inv, lane);
   for (; tile < nt; tile += step) {
     load(min(tile + step, nt - 1), nxt);
     __builtin_amdgcn_sched_barrier(0);
@@ -417,13 +452,24 @@ __global__ __launch_bounds__(256, 2) void k_panel_solve(PanelSolve pa, PanelSolv
       }
   }
 }
+constexpr int kSolveBlocks = 512;  // of four waves: two per SIMD
+__global__ __launch_bounds__(256, 2) void k_panel_solve(PanelSolve pa, PanelSolve pb, int na,
+                                                        const unsigned int* __restrict__ state) {
+  if (*state) return;
+  const bool second = (int)blockIdx.x >= na;
+  const PanelSolve p = second ? pb : pa;
+  solve_tiles(p, [&](int i, int j) { return p.u[i * kTri + j]; },
+              [&](int e) { return p.inv[e]; },
+              (int64_t)(second ? blockIdx.x - na : blockIdx.x) * 4 + (threadIdx.x >> 6),
+              (int64_t)(second ? gridDim.x - na : na) * 4);
+}
 
 // LU without pivoting of B - diag(sg) for B (64 x 64, in LDS), sg_j = -sign of
 // the pivot: U in and above the diagonal, unit L below.  256 threads, four steps
 // of 16 columns: one wave factors them with a row per lane, then solves the
 // rows to their right with a column per lane; the four waves update the rest.
-GAP_DEV void lu64_signs(double (*B)[kTriS], double* sg) {
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+GAP_DEV void lu64_signs(double (*B)[kTriS], double* sg, int lane) {
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int g = lane >> 4, idx = lane & 15;
   for (int s = 0; s < 4; ++s) {
     const int c0 = 16 * s;
@@ -485,8 +531,8 @@ GAP_DEV void lu64_signs(double (*B)[kTriS], double* sg) {
 // functions a(i, k) (i <= k) and b(k, j) (k <= j), handed to put(i, j, value)
 // for every i <= j; 256 threads.
 template <class FA, class FB, class FP>
-GAP_DEV void upper_product64(FA a, FB b, FP put) {
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+GAP_DEV void upper_product64(FA a, FB b, FP put, int lane) {
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int g = lane >> 4, idx = lane & 15;
   int t = 0;
   for (int ti = 0; ti < 4; ++ti)
@@ -507,21 +553,94 @@ GAP_DEV void upper_product64(FA a, FB b, FP put) {
     }
 }
 
-// The one-block middle of the panel: R2 from the second Gram, the test that Q
-// was near enough to orthonormal, the signs and L, U of Q^'s top rows, and from
-// them R and V's top in A, tau, Z = U R2 (V's other rows are q Z^-1) and the
-// operands of T.  Bound by latency: 47 us, half of it the 64 columns of the
-// Cholesky factor and the 64 of the LU.
+// LDS of a panel's middle.
+struct PanelLds {
+  double S[kTri][kTriS], B[kTri][kTriS];
+  __attribute__((aligned(16))) double u[kTri * kTri], u1[kTri * kTri];
+  double inv[kInv16];
+  double sg[kTri];
+};
+
+// The middle of the panel, by a workgroup: R2 from the second Gram (in S), the
+// signs and L, U of Q^'s top rows (Q's in x: sixteen per wave, columns 16 b + g +
+// 4 r of row idx), and from them R in A (if `out`) and Z = U R2 in S and put_z
+// (V's other rows are q Z^-1).  put_u1 stores R1 in u1.  Leaves L and U in B and
+// the signs in sg.
+template <class FP, class FZ>
+GAP_DEV void panel_middle(PanelLds& s, d4v (&x)[4], FP put_u1, FZ put_z, double* __restrict__ A,
+                          int64_t ld, int64_t rows, int bw, bool out, int lane = threadIdx.x & 63) {
+  const int wave = threadIdx.x >> 6, g = lane >> 4, idx = lane & 15;
+  const int64_t qr = 16 * wave + idx;
+  (void)chol64_lds(s.S, lane);  // diagonally dominant: no bad pivot
+  if (wave == 0) {
+    tri_inv16([&](int i, int j) { return s.S[j][i]; }, s.inv, lane);
+  } else {
+    for (int e = 64 * (wave - 1) + lane; e < kTri * kTri; e += 192) {
+      const int c = e >> 6, q = e & 63;
+      s.u[e] = q >= c ? s.S[q][c] : 0.0;  // R2
+    }
+  }
+  put_u1();
+  __syncthreads();
+  {  // Q^'s top rows
+    TriOps t;
+    tri_ops(t, [&](int i, int j) { return s.u[i * kTri + j]; }, [&](int e) { return s.inv[e]; },
+            lane);
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        x[b][r] = 16 * b + g + 4 * r < bw && qr < rows ? x[b][r] : 0.0;
+    tri_solve16(t, x);
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) s.B[qr][16 * b + g + 4 * r] = x[b][r];
+  }
+  __syncthreads();
+  lu64_signs(s.B, s.sg, lane);
+  // R = S R2 R1 and Z = U R2 (S, the LDS array, is free for Z)
+  if (out)
+    upper_product64([&](int i, int k) { return s.u[i * kTri + k]; },
+                    [&](int k, int j) { return s.u1[k * kTri + j]; },
+                    [&](int i, int j, double v) {
+                      if (j < bw) A[i + j * ld] = s.sg[i] * v;
+                    },
+                    lane);
+  upper_product64([&](int i, int k) { return s.B[i][k]; },
+                  [&](int k, int j) { return s.u[k * kTri + j]; },
+                  [&](int i, int j, double v) {
+                    put_z(i * kTri + j, v);
+                    s.S[i][j] = v;
+                  },
+                  lane);
+  __syncthreads();
+}
+
+// V's top rows (unit lower) into A, and tau, from the L and U that panel_middle left.
+GAP_DEV void panel_top(const PanelLds& s, double* __restrict__ A, int64_t ld, int64_t rows, int bw,
+                       double* __restrict__ tau) {
+  if (threadIdx.x >= 192 && threadIdx.x - 192 < bw) {
+    const int j = threadIdx.x - 192;
+    tau[j] = -s.B[j][j] * s.sg[j];
+  }
+  for (int e = threadIdx.x; e < kTri * kTri; e += 256) {
+    const int c = e >> 6, q = e & 63;
+    if (q > c && q < rows && c < bw) A[q + c * ld] = s.B[q][c];
+  }
+}
+
+// The one-block middle launch: the test that Q was near enough to orthonormal, then
+// R, tau and V's top in A, and the operands of V's other rows and of T.  Bound by
+// latency: 47 us, half of it the 64 columns of the Cholesky factor and the 64 of
+// the LU.
 __global__ __launch_bounds__(256) void k_panel_vectors(double* __restrict__ A, int64_t ld,
                                                        int64_t rows, int bw,
                                                        const double* __restrict__ Q, int64_t ldq,
                                                        double* __restrict__ pan,
                                                        double* __restrict__ tau,
                                                        unsigned int* __restrict__ state) {
-  __shared__ double S[kTri][kTriS], B[kTri][kTriS];
-  __shared__ __attribute__((aligned(16))) double u[kTri * kTri], u1[kTri * kTri];
-  __shared__ double inv[kInv16];
-  __shared__ double sg[kTri];
+  __shared__ PanelLds s;
   __shared__ int s_bad;
   if (*state) return;  // uniform: a whole-grid condition
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane >> 4, idx = lane & 15;
@@ -539,105 +658,97 @@ __global__ __launch_bounds__(256) void k_panel_vectors(double* __restrict__ A, i
   for (int i = 0; i < 8; ++i)
     r1[i] = reinterpret_cast<const d2v*>(pan + kPanU1)[i * 256 + threadIdx.x];
   __syncthreads();  // s_bad
-  if (gram_to_lds(pan + kPanG, bw, S, 1.0 / 64)) s_bad = 1;
+  if (gram_to_lds([&](int e) { return pan[kPanG + e]; }, bw, s.S, 1.0 / 64)) s_bad = 1;
   __syncthreads();
   if (s_bad) {
     if (threadIdx.x == 0) *state = 1u;
     return;
   }
-  (void)chol64_lds(S);  // diagonally dominant: no bad pivot
-  if (wave == 0) {
-    tri_inv16([&](int i, int j) { return S[j][i]; }, inv);
-  } else {
-    for (int e = threadIdx.x - 64; e < kTri * kTri; e += 192) {
-      const int c = e >> 6, q = e & 63;
-      u[e] = q >= c ? S[q][c] : 0.0;  // R2
-    }
-  }
+  panel_middle(
+      s, x,
+      [&] {
 #pragma unroll
-  for (int i = 0; i < 8; ++i) reinterpret_cast<d2v*>(u1)[i * 256 + threadIdx.x] = r1[i];
-  __syncthreads();
-  {  // Q^'s top rows
-    TriOps t;
-    tri_ops(t, [&](int i, int j) { return u[i * kTri + j]; }, [&](int e) { return inv[e]; });
-#pragma unroll
-    for (int b = 0; b < 4; ++b)
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-        x[b][r] = 16 * b + g + 4 * r < bw && qr < rows ? x[b][r] : 0.0;
-    tri_solve16(t, x);
-#pragma unroll
-    for (int b = 0; b < 4; ++b)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) B[qr][16 * b + g + 4 * r] = x[b][r];
-  }
-  __syncthreads();
-  lu64_signs(B, sg);
-  // R = S R2 R1 and Z = U R2 (S, the LDS array, is free for Z)
-  upper_product64([&](int i, int k) { return u[i * kTri + k]; },
-                  [&](int k, int j) { return u1[k * kTri + j]; },
-                  [&](int i, int j, double v) {
-                    if (j < bw) A[i + j * ld] = sg[i] * v;
-                  });
-  upper_product64([&](int i, int k) { return B[i][k]; },
-                  [&](int k, int j) { return u[k * kTri + j]; },
-                  [&](int i, int j, double v) {
-                    pan[kPanZ + i * kTri + j] = v;
-                    S[i][j] = v;
-                  });
-  __syncthreads();
-  if (wave == 0) tri_inv16([&](int i, int j) { return S[i][j]; }, pan + kPanInvZ);
-  if (wave == 1) tri_inv16([&](int i, int j) { return i == j ? 1.0 : B[j][i]; }, pan + kPanInvV);
-  // V's top rows (unit lower), tau, and T = (-U S) V1^-T: the rows of -U S and V1^T
-  // for its solution (the waves at an inverse join when it is done)
-  if (threadIdx.x >= 192 && threadIdx.x - 192 < bw) {
-    const int j = threadIdx.x - 192;
-    tau[j] = -B[j][j] * sg[j];
-  }
+        for (int i = 0; i < 8; ++i) reinterpret_cast<d2v*>(s.u1)[i * 256 + threadIdx.x] = r1[i];
+      },
+      [&](int e, double v) { pan[kPanZ + e] = v; }, A, ld, rows, bw, true);
+  if (wave == 0) tri_inv16([&](int i, int j) { return s.S[i][j]; }, pan + kPanInvZ);
+  if (wave == 1) tri_inv16([&](int i, int j) { return i == j ? 1.0 : s.B[j][i]; }, pan + kPanInvV);
+  // (the waves at an inverse join when it is done) and T = (-U S) V1^-T: the rows of
+  // -U S and V1^T for its solution
+  panel_top(s, A, ld, rows, bw, tau);
   for (int e = threadIdx.x; e < kTri * kTri; e += 256) {
     const int c = e >> 6, q = e & 63;
-    if (q > c && q < rows && c < bw) A[q + c * ld] = B[q][c];
-    pan[kPanV1 + e] = q > c ? B[q][c] : (q == c ? 1.0 : 0.0);
-    pan[kPanUS + e] = q <= c ? -B[q][c] * sg[c] : 0.0;
+    pan[kPanV1 + e] = q > c ? s.B[q][c] : (q == c ? 1.0 : 0.0);
+    pan[kPanUS + e] = q <= c ? -s.B[q][c] * s.sg[c] : 0.0;
   }
 }
 
-// Householder factorisation, column by column in memory, of an outer block's
-// columns from its first panel on whose state word is set (state[h]: panel h of
-// 64 columns; the launch ends at once if neither is).  Nothing of the block was
-// written after that panel, so its other panel is taken along.  A cooperative
-// grid: per column one pass over the rows for each group of 64 columns, which
-// applies the previous reflector and accumulates the norm and dot products of
-// the next, then one grid barrier.  Rows belong to threads for the whole kernel.
-// It also runs as a single ordinary block.
+// ---------------------------------------------- numerically dependent panels ----
+// k_qr_panel_dep factors an outer block's columns from its first panel on whose
+// state word is set (state[h]: panel h of 64 columns; the launch ends at once if
+// neither is).  Nothing of the block was written after that panel, so its other
+// panel is taken along.  A cooperative grid (it also runs as a single ordinary
+// block) that does what the panel kernels do, with more rounds of Cholesky QR:
+//   G = X^T X, R = chol(G + kDepShift diag(G)), X <- X R^-1,
+// from X = P until G is within 1/64 of the unit matrix.  The shift keeps the Cholesky
+// factor defined whatever the columns (the Gram's own rounding is below it) and X's
+// columns at most of length one, so a round lengthens what is left of a column
+// outside the span of the others by up to 1 / sqrt(kDepShift) = 3e6 and adds
+// a column-wise error of rounding size: two rounds for columns that depend up to
+// 1e-9, or equal ones (whose rounding errors the rounds lengthen, as the
+// column-by-column reduction does); at most three were seen.  Where that fails (a
+// zero column, columns equal in a way that leaves no rounding error, an overflow)
+// panel_columns goes through the rest of the block column by column.
+// A 64-row group of the block belongs to one workgroup for the whole kernel, and
+// a 16-row tile to one wave except in panel_columns, so rows are exchanged through
+// memory by nobody; Grams, Q's top rows and V^T C go by device-scope atomics, and
+// every workgroup forms the small factors for itself.
+// A fit of 88,000 rows and 2,000 points with equal points in every 128: 330 ms when
+// such blocks went column by column alone (a pass over up to 128 columns and a grid
+// barrier per column), 29.2 now, 22.9 without equal points; 5,600 rows and 300
+// points: 20.6, 2.1 and 1.4.  (48 and 5.1 with every panel by a reduction of sixteen
+// columns in registers.)  Bound by the latency of its grid barriers and of the one-
+// block steps each round repeats.
 constexpr int kColT = 256;
-__global__ __launch_bounds__(kColT) void k_qr_panel_col(double* __restrict__ A, int64_t ld,
-                                                        int64_t rows, int ow,
-                                                        double* __restrict__ red,
-                                                        double* __restrict__ piv,
-                                                        unsigned int* __restrict__ arrive,
-                                                        const unsigned int* __restrict__ state,
-                                                        double* __restrict__ tau_all,
-                                                        int* __restrict__ dev_err) {
-  const bool first = state[0] != 0u;
-  if (!first && (ow <= kTri || state[1] == 0u)) return;
+constexpr double kDepShift = 0x1p-43;
+constexpr int kDepRounds = 5;
+
+struct DepArgs {
+  double* A;  // the outer block at its diagonal, col-major
+  int64_t ld, rows;
+  int ow;     // its columns
+  double* Q;  // [64][ldq]
+  int64_t ldq;
+  double* part;  // [grid][4096] partial sums
+  double* pan;
+  double *red, *piv;  // of panel_columns
+  unsigned int* arrive;
+  const unsigned int* state;
+  double* tau;
+  int* dev_err;
+};
+
+// Columns k0 .. ow - 1 one by one: per column one pass over the rows for each group
+// of 64 columns, which applies the previous reflector and accumulates the norm and
+// dot products of the next, then one grid barrier (`bar`: those completed).
+GAP_DEV void panel_columns(const DepArgs& d, int k0, unsigned bar) {
   __shared__ double s_wred[kColT / 64][kTri];
   __shared__ double s_tw[2 * kTri], s_pv[2 * kTri], s_tot[2 * kTri];
   __shared__ double s_par[3];  // tau, beta, scale of the reflector just formed
-  const int G = gridDim.x, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int64_t stride = (int64_t)G * kColT;
-  const int k0 = first ? 0 : kTri;
+  const int G = gridDim.x, wave = threadIdx.x >> 6, lane = fresh_lane(), ow = d.ow;
+  const int64_t ld = fresh(d.ld);
   for (int k = k0; k <= ow; ++k) {
-    double* rb = red + (size_t)(k & 1) * 2 * kTri * kPanelMaxGrid;
-    double* pv = piv + (k & 1) * 2 * kTri;
+    double* rb = d.red + (size_t)(k & 1) * 2 * kTri * kPanelMaxGrid;
+    double* pv = d.piv + (k & 1) * 2 * kTri;
     const int p = k > k0 ? k - 1 : k;  // first column this pass touches
     for (int o = p / kTri * kTri; o < ow; o += kTri) {
       double part[kTri];
 #pragma unroll
       for (int j = 0; j < kTri; ++j) part[j] = 0.0;
-      for (int64_t r = (int64_t)blockIdx.x * kColT + threadIdx.x; r < rows; r += stride) {
+      for (int64_t r = ((int64_t)blockIdx.x + (int64_t)G * wave) * 64 + lane; r < d.rows;
+           r += (int64_t)G * kColT) {
         if (r < p) continue;
-        double* row = A + r;
+        double* row = d.A + r;
         double a[kTri];
 #pragma unroll
         for (int j = 0; j < kTri; ++j) a[j] = (o + j >= p && o + j < ow) ? row[(o + j) * ld] : 0.0;
@@ -686,7 +797,7 @@ __global__ __launch_bounds__(kColT) void k_qr_panel_col(double* __restrict__ A, 
       __syncthreads();
     }
     if (k == ow) break;
-    grid_barrier_x8(arrive, (unsigned)(k - k0 + 1), dev_err);
+    grid_barrier_x8(d.arrive, ++bar, d.dev_err);
     if (threadIdx.x >= k && threadIdx.x < ow) {
       double t = 0.0;
       for (int b = 0; b < G; ++b) t += vload(rb + threadIdx.x * kPanelMaxGrid + b);
@@ -705,7 +816,7 @@ __global__ __launch_bounds__(kColT) void k_qr_panel_col(double* __restrict__ A, 
       s_par[0] = tau;
       s_par[1] = beta;
       s_par[2] = scale;
-      if (blockIdx.x == 0) tau_all[k] = tau;
+      if (blockIdx.x == 0) d.tau[k] = tau;
     }
     __syncthreads();
     if (threadIdx.x < ow) {
@@ -713,6 +824,261 @@ __global__ __launch_bounds__(kColT) void k_qr_panel_col(double* __restrict__ A, 
       s_tw[j] = j > k ? s_par[0] * (s_pv[j] + s_par[2] * s_tot[j]) : 0.0;
     }
     __syncthreads();
+  }
+}
+
+// tot[e] = sum over the grid's blocks of part[block][e], e < n, in a fixed order: the
+// blocks share the sums, sixteen lanes each.  Between two grid barriers.
+GAP_DEV void grid_sum(const double* part, int n, double* tot) {
+  const int G = gridDim.x, l = threadIdx.x & 15;
+  for (int e = blockIdx.x + G * (threadIdx.x >> 4); e < n; e += G * (kColT / 16)) {
+    double t = 0.0;
+#pragma unroll 8
+    for (int b = l; b < G; b += 16) t += vload(part + (int64_t)b * n + e);
+#pragma unroll
+    for (int o = 1; o < 16; o <<= 1) t += __shfl_xor(t, o);
+    if (l == 0) xstore(tot + e, t);
+  }
+}
+
+// C -= V T^T V^T C for the cw columns C after a full first panel: V in A (unit lower
+// trapezoidal), T (row-major) in s.u, s.u1 free.  Tiles tile0, tile0 + nw, ... are
+// this wave's.
+GAP_DEV void dep_update(const DepArgs& d, PanelLds& s, int cw, int64_t tile0, int64_t nw,
+                        unsigned& bar) {
+  const int wave = threadIdx.x >> 6, lane = fresh_lane(), g = lane >> 4, idx = lane & 15;
+  const int64_t nt = (d.rows + 15) / 16, ld = fresh(d.ld);
+  double* C = d.A + kTri * ld;
+  auto unit_lower = [](int64_t r, int c, double v) { return r == c ? 1.0 : (r > c ? v : 0.0); };
+  // W = V^T C: lane (g, idx) holds rows 4 g .. + 3 of a tile's columns 16 u + idx
+  d4v w[4][4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) w[i][j] = zero4();
+  for (int64_t t = tile0; t < nt; t += nw) {
+    const int64_t r0 = 16 * t + 4 * g;
+    d4v v[4], c[4];
+    if (16 * t + 16 <= d.rows) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        v[u] = *reinterpret_cast<const d4v*>(d.A + r0 + (16 * u + idx) * ld);
+        c[u] = *reinterpret_cast<const d4v*>(C + r0 + min(16 * u + idx, cw - 1) * ld);
+      }
+    } else {
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int64_t r = min(r0 + q, d.rows - 1);
+          v[u][q] = r0 + q < d.rows ? d.A[r + (16 * u + idx) * ld] : 0.0;
+          c[u][q] = r0 + q < d.rows ? C[r + min(16 * u + idx, cw - 1) * ld] : 0.0;
+        }
+    }
+    if (t < 4) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v[u][q] = unit_lower(r0 + q, 16 * u + idx, v[u][q]);
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) w[i][j] = mfma_f64(v[i][q], c[j][q], w[i][j]);
+  }
+  for (int k = 0; k < 4; ++k) {  // the waves in turn
+    if (wave == k) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            double* p = s.u1 + ((i * 4 + j) * 4 + r) * 64 + lane;
+            *p = k ? *p + w[i][j][r] : w[i][j][r];
+          }
+    }
+    __syncthreads();
+  }
+  for (int e = threadIdx.x; e < kTri * kTri; e += kColT)
+    xstore(d.part + (int64_t)blockIdx.x * kTri * kTri + e, s.u1[e]);
+  grid_barrier_x8(d.arrive, ++bar, d.dev_err);
+  grid_sum(d.part, kTri * kTri, d.pan + kPanZ);
+  grid_barrier_x8(d.arrive, ++bar, d.dev_err);
+  {  // Wt = -T^T W in s.u1, row-major: columns 16 wave .. + 15
+    d4v x[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        x[t][r] = vload(d.pan + kPanZ + ((t * 4 + wave) * 4 + r) * 64 + lane);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      d4v y = zero4();
+#pragma unroll
+      for (int t = 0; t <= u; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          y = mfma_f64(-s.u[(16 * t + g + 4 * r) * kTri + 16 * u + idx], x[t][r], y);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) s.u1[(16 * u + g + 4 * r) * kTri + 16 * wave + idx] = y[r];
+    }
+  }
+  __syncthreads();
+  // C += V Wt: lane (g, idx) holds columns 16 b + g + 4 r of row idx (past the last
+  // row: that row again, which stores the same values)
+  for (int64_t t = tile0; t < nt; t += nw) {
+    const int64_t row = min(16 * t + idx, d.rows - 1);
+    d4v v[4], c[4];
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int k = 16 * b + g + 4 * r;
+        v[b][r] = unit_lower(row, k, d.A[row + k * ld]);
+        c[b][r] = C[row + min(k, cw - 1) * ld];
+      }
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+      for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          c[b] = mfma_f64(s.u1[(16 * kb + g + 4 * r) * kTri + 16 * b + idx], v[kb][r], c[b]);
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int k = 16 * b + g + 4 * r;
+        if (k < cw) C[row + k * ld] = c[b][r];
+      }
+  }
+  __syncthreads();
+}
+
+__global__ __launch_bounds__(kColT) void k_qr_panel_dep(DepArgs d) {
+  const bool first = d.state[0] != 0u;
+  if (!first && (d.ow <= kTri || d.state[1] == 0u)) return;
+  __shared__ PanelLds s;
+  __shared__ double inv_v[kInv16];
+  __shared__ int s_flag;
+  const int wave = threadIdx.x >> 6;
+  const int64_t nw = (int64_t)gridDim.x * 4;
+  // this wave's first tile of sixteen rows from tile `lo` on (its tiles: step nw)
+  auto my_tile = [&](int lo) {
+    int64_t t = (int64_t)blockIdx.x * 4 + wave;
+    while (t < lo) t += nw;
+    return t;
+  };
+  // `v` of any thread, in all threads of the block
+  auto any_of = [&](bool v) {
+    __syncthreads();
+    if (threadIdx.x == 0) s_flag = 0;
+    __syncthreads();
+    if (v) s_flag = 1;
+    __syncthreads();
+    return s_flag != 0;
+  };
+  unsigned bar = 0;
+  for (int h = first ? 0 : 1; h * kTri < d.ow; ++h) {
+    const int bw = min(kTri, d.ow - h * kTri);
+    double* P = d.A + (int64_t)h * kTri * d.ld;          // the panel's columns, block rows
+    const bool owner = (int)blockIdx.x == h % (int)gridDim.x;  // of its top 64 rows
+    double *tot = d.pan + kPanG, *top = d.pan + kPanV1;
+    for (int round = 0;; ++round) {
+      const double* X = round ? d.Q : P;
+      const int64_t ldx = round ? d.ldq : d.ld;
+      d4v acc[kGramTiles];
+      gram_chunks(fresh(X), fresh(ldx), d.rows, bw, my_tile(4 * h), nw, acc,
+                  fresh_lane());
+      gram_block_sum(acc, &s.S[0][0], [&](int e, double v) {  // (S and B)
+        xstore(d.part + (int64_t)blockIdx.x * kGram + e, v);
+      }, fresh_lane());
+      grid_barrier_x8(d.arrive, ++bar, d.dev_err);
+      grid_sum(d.part, kGram, tot);
+      grid_barrier_x8(d.arrive, ++bar, d.dev_err);
+      const bool far = any_of(gram_to_lds([&](int e) { return vload(tot + e); }, bw, s.S, 1.0 / 64,
+                                          fresh_thread()));
+      if (round > 0 && !far) break;
+      if (threadIdx.x < kTri) s.S[threadIdx.x][threadIdx.x] *= 1.0 + kDepShift;
+      __syncthreads();
+      const bool bad = chol64_lds(s.S, fresh_lane());
+      if (any_of(threadIdx.x == 0 && bad) || round == kDepRounds) {
+        panel_columns(d, h * kTri, bar);
+        return;
+      }
+      if (wave == 0) tri_inv16([&](int i, int j) { return s.S[j][i]; }, s.inv, fresh_lane());
+      // the product of the rounds' factors
+      if (round > 0) {
+        upper_product64([&](int i, int k) { return s.S[k][i]; },
+                        [&](int k, int j) { return s.u1[k * kTri + j]; },
+                        [&](int i, int j, double v) { s.u[i * kTri + j] = v; }, fresh_lane());
+        __syncthreads();
+      }
+      for (int e = fresh_thread(); e < kTri * kTri; e += kColT) {
+        const int i = e >> 6, j = e & 63;
+        s.u1[e] = i > j ? 0.0 : (round ? s.u[e] : s.S[j][i]);
+      }
+      __syncthreads();
+      const PanelSolve q{fresh(X), fresh(ldx), fresh(d.Q), fresh(d.ldq), d.rows, fresh(bw), nullptr, nullptr};
+      solve_tiles(q, [&](int i, int j) { return s.S[j][i]; }, [&](int e) { return s.inv[e]; },
+                  my_tile(4 * h), nw, fresh_lane());
+      if (owner) {  // Q's top rows, this wave's own
+        const int lane = fresh_lane(), g = lane >> 4, idx = lane & 15;
+        const int64_t row = h * kTri + 16 * wave + idx;
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int c = 16 * b + g + 4 * r;
+            xstore(top + (16 * wave + idx) * kTri + c,
+                   d.Q[min(c, bw - 1) * d.ldq + min(row, d.rows - 1)]);
+          }
+      }
+      __syncthreads();  // S is read no more
+    }
+    const int lane = fresh_lane(), g = lane >> 4, idx = lane & 15;
+    d4v x[4];
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        x[b][r] = vload(top + (16 * wave + idx) * kTri + 16 * b + g + 4 * r);
+    double* Ad = P + h * kTri;  // at the panel's diagonal
+    const int64_t rows_h = d.rows - h * kTri;
+    panel_middle(s, x, [] {}, [](int, double) {}, Ad, d.ld, rows_h, bw, owner, lane);
+    if (wave == 0) tri_inv16([&](int i, int j) { return s.S[i][j]; }, s.inv, lane);
+    if (wave == 1)
+      tri_inv16([&](int i, int j) { return i == j ? 1.0 : s.B[j][i]; }, inv_v, lane);
+    if (owner) panel_top(s, Ad, d.ld, rows_h, bw, d.tau + h * kTri);
+    __syncthreads();
+    const PanelSolve v{fresh(d.Q), fresh(d.ldq), fresh(P), fresh(d.ld), d.rows, fresh(bw), nullptr, nullptr};
+    solve_tiles(v, [&](int i, int j) { return s.S[i][j]; }, [&](int e) { return s.inv[e]; },
+                my_tile(4 * (h + 1)), nw, fresh_lane());
+    const int cw = d.ow - (h + 1) * kTri;
+    if (cw <= 0) continue;
+    {  // T = (-U S) V1^-T in u (the launch after this one forms it from V and tau)
+      const int row = 16 * wave + idx;
+#pragma unroll
+      for (int b = 0; b < 4; ++b)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int c = 16 * b + g + 4 * r;
+          x[b][r] = row <= c ? -s.B[row][c] * s.sg[c] : 0.0;
+        }
+      TriOps t;
+      tri_ops(t, [&](int i, int j) { return i == j ? 1.0 : s.B[j][i]; },
+              [&](int e) { return inv_v[e]; }, lane);
+      tri_solve16(t, x);
+#pragma unroll
+      for (int b = 0; b < 4; ++b)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) s.u[row * kTri + 16 * b + g + 4 * r] = x[b][r];
+    }
+    __syncthreads();
+    dep_update(d, s, cw, my_tile(0), nw, bar);
   }
 }
 
@@ -1377,7 +1743,7 @@ __global__ __launch_bounds__(256, 2) void k_qr_vtc5(const double* __restrict__ A
     }
 }
 
-// T of a 64-wide half whose panel was factored column by column (its state word
+// T of a 64-wide half whose panel was factored by k_qr_panel_dep (its state word
 // is set; other panels bring their T along), from the Gram G = V^T V held in W
 // (row l at W + l * nct): T[0:i, i] = -tau_i T[0:i, 0:i] G[0:i, i], T[i][i] =
 // tau_i.  Col-major, ld 64, one block per half; zero below the diagonal.
@@ -2321,7 +2687,7 @@ static int64_t qr_ldq(int64_t m) { return (m + 3) & ~int64_t(3); }
 // columns).  Both the workspace size and its binding use this one count.
 static int64_t qr_part_elems(int64_t m, int64_t n) {
   int64_t e = std::max(((m + kNarrowSlab - 1) / kNarrowSlab + 1) * (int64_t)kQrNB * 2 * kQrNB,
-                       (int64_t)kGramMaxBlocks * kGram);
+                       (int64_t)std::max(kGramMaxBlocks * kGram, kPanelMaxGrid * kTri * kTri));
   for (int64_t j0 = 0; j0 < n; j0 += kQrOB) {
     const int64_t nct = n + 1 - j0, slab = qr_slab_rows(m, j0, nct);
     e = std::max(e, (m - j0 + slab - 1) / slab * kQrOB * nct);
@@ -2337,7 +2703,7 @@ size_t qr_workspace_bytes(int64_t m, int64_t n) {
   d += (size_t)kQrOB * kQrOB;                  // T
   d += (size_t)kTri * qr_ldq(m);               // Q of a panel
   d += (size_t)kPanDoubles;                    // pan
-  d += (size_t)4 * kTri * (kPanelMaxGrid + 1); // red and piv of the column kernel
+  d += (size_t)4 * kTri * (kPanelMaxGrid + 1); // red and piv of panel_columns
   d += (size_t)n + 8;                          // tau
   return d * sizeof(double) + sizeof(unsigned int) * (kCounterWords + kTrsvMaxBlocks);  // counters, flags
 }
@@ -2420,18 +2786,17 @@ static void qr_wy_update_ob(double* A, int64_t ld, int64_t m, int64_t j0, int pw
                        c_end, nct, w->Wt);
 }
 
-// Number of k_qr_panel_col blocks that are co-resident on the current device (0 if unknown).
-static int col_capacity() {
-  static int cap = -1;
-  if (cap < 0) {
-    cap = 0;
+// Number of k_qr_panel_dep blocks that are co-resident on the current device (0 if unknown).
+static int dep_capacity() {
+  static const int cap = [] {
     int dev = 0, nb = 0;
     hipDeviceProp_t p;
     if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&p, dev) == hipSuccess &&
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_qr_panel_col, kColT, 0) == hipSuccess &&
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_qr_panel_dep, kColT, 0) == hipSuccess &&
         nb > 0)
-      cap = std::min(nb * p.multiProcessorCount, kPanelMaxGrid);
-  }
+      return std::min(nb * p.multiProcessorCount, kPanelMaxGrid);
+    return 0;
+  }();
   return cap;
 }
 
@@ -2469,21 +2834,19 @@ static void qr_panel(double* A_, int64_t ld, int64_t m, int64_t j0, int bw, int 
 // The outer block at o0 from its first panel on that qr_panel left undone.  The
 // launch costs about 25 us even where there is none (a cooperative launch goes
 // through a queue of its own), so there is one per outer block.
-static void qr_undone(double* A_, int64_t ld, int64_t m, int64_t o0, int ow, QrWork* w,
+static void qr_undone(double* A, int64_t ld, int64_t m, int64_t o0, int ow, QrWork* w,
                       hipStream_t st, int* dev_err) {
-  double* A = A_ + o0 + o0 * ld;
-  double* tau = w->tau + o0;
-  int64_t rows = m - o0;
-  unsigned int *state = w->counter, *arrive = w->counter + kPanelBar;
-  double *red = w->red, *piv = w->red + 4 * kTri * kPanelMaxGrid;
-  const int64_t G = std::min<int64_t>(col_capacity(), (rows + kColT - 1) / kColT);
-  void* args[] = {&A, &ld, &rows, &ow, &red, &piv, &arrive, &state, &tau, &dev_err};
-  if (G < 1 || hipLaunchCooperativeKernel(reinterpret_cast<const void*>(&k_qr_panel_col),
+  const int64_t rows = m - o0;
+  DepArgs d{A + o0 + o0 * ld, ld, rows, ow, w->Q, qr_ldq(m), w->part, w->pan,
+            w->red, w->red + 4 * kTri * kPanelMaxGrid, w->counter + kPanelBar, w->counter,
+            w->tau + o0, dev_err};
+  const int64_t G = std::min<int64_t>(dep_capacity(), (rows + 127) / 128);
+  void* args[] = {&d};
+  if (G < 1 || hipLaunchCooperativeKernel(reinterpret_cast<const void*>(&k_qr_panel_dep),
                                           dim3((unsigned)G), dim3(kColT), args, 0,
                                           st) != hipSuccess) {
     (void)hipGetLastError();
-    hipLaunchKernelGGL(k_qr_panel_col, dim3(1), dim3(kColT), 0, st, A, ld, rows, ow, red, piv,
-                       arrive, state, tau, dev_err);
+    hipLaunchKernelGGL(k_qr_panel_dep, dim3(1), dim3(kColT), 0, st, d);
   }
 }
 

@@ -38,8 +38,8 @@ GAP_DEV double readlane_f64(double v, int lane) {
 // wave 0 only.  The one-wave form it replaces, whose lanes formed each dot
 // product from LDS, took 44 us a block; this one 19 us, launch and loads
 // included, and 11 us on top of a Cholesky update that goes on to it.
-GAP_DEV bool chol64_lds(double (*S)[kTriS]) {
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+GAP_DEV bool chol64_lds(double (*S)[kTriS], int lane = threadIdx.x & 63) {
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int g = lane >> 4, idx = lane & 15;
   bool bad = false;
   for (int s = 0; s < 4; ++s) {
@@ -86,8 +86,8 @@ GAP_DEV bool chol64_lds(double (*S)[kTriS]) {
 // Inverses of the four 16 x 16 diagonal blocks of an upper triangle u(i, j), by
 // one wave, a row per lane: inv[256 b + 16 i + c], zero below the diagonal.
 template <class FU>
-GAP_DEV void tri_inv16(FU u, double* inv) {
-  const int lane = threadIdx.x & 63, o = lane & 48, i = lane & 15;
+GAP_DEV void tri_inv16(FU u, double* inv, int lane = threadIdx.x & 63) {
+  const int o = lane & 48, i = lane & 15;
   double y[16];
 #pragma unroll
   for (int c = 0; c < 16; ++c) y[c] = c == i ? 1.0 : 0.0;
@@ -109,8 +109,8 @@ struct TriOps {
   d4v off[6], dia[4], inv[4];  // off: (kb, b) = (0,1) (0,2) (1,2) (0,3) (1,3) (2,3)
 };
 template <class FU, class FI>
-GAP_DEV void tri_ops(TriOps& t, FU u, FI inv) {
-  const int lane = threadIdx.x & 63, g = lane >> 4, idx = lane & 15;
+GAP_DEV void tri_ops(TriOps& t, FU u, FI inv, int lane = threadIdx.x & 63) {
+  const int g = lane >> 4, idx = lane & 15;
 #pragma unroll
   for (int b = 0; b < 4; ++b) {
 #pragma unroll

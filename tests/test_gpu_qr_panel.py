@@ -101,3 +101,71 @@ def test_trailing_update_runs_over_row_blocks(gapx, gap, m, n):
     ref = np.linalg.lstsq(K, y, rcond=None)[0]
     assert np.linalg.norm(x.cpu().numpy() - ref) <= 1e-10 * np.linalg.norm(ref) * np.linalg.cond(K)
     assert factor_error(A, K) <= 1e-12
+
+
+def column_error(A, K):
+    """max |R^T R - K^T K|_ij / (|k_i| |k_j|): the bound column by column, which Householder
+    QR meets whatever the scales of the columns are."""
+    n = K.shape[1]
+    R = np.triu(A[:n, :n].T.cpu().numpy())
+    norms = np.linalg.norm(K, axis=0)
+    norms[norms == 0] = 1.0
+    return np.abs((R / norms).T @ (R / norms) - (K / norms).T @ (K / norms)).max()
+
+
+def solve_dependent(gapx, gap, K, y, rank_ok):
+    A = device_matrix(gapx, K, y)
+    try:
+        x, _ = gap.lstsq(A, *K.shape)
+    except gapx.GapError as e:
+        assert rank_ok and e.status == gapx.GAP_E_RANK
+        x = None
+    return A, x
+
+
+@pytest.mark.parametrize("m,n,pairs", [
+    (128, 128, ((70, 100),)), (130, 66, ((65, 64),)), (5000, 128, ((70, 100),)),
+    (5000, 300, ((70, 100),)), (5000, 300, ((198, 228),)), (5003, 256, ((70, 100), (198, 228))),
+    (33001, 193, ((127, 64), (192, 150))), (700, 300, ((3, 40), (64 + 128, 65 + 128)))])
+@pytest.mark.parametrize("eps", [1e-9, 1e-13, 0.0])
+def test_second_panel_alone_is_dependent(gapx, gap, m, n, pairs, eps):
+    """The second 64 columns of a 128-wide block fail alone, in the first and in a later
+    block, with trailing columns behind them and without, and over twelve decades of
+    column scales."""
+    print(f"m {m} n {n} pairs {pairs} eps {eps}", flush=True)
+    rng = np.random.default_rng([m, n])
+    K = rng.standard_normal((m, n)) + (np.eye(m, n) * 3 if m < 2 * n else 0)
+    for a, b in pairs:
+        K[:, a] = K[:, b] + eps * rng.standard_normal(m)
+    K *= 10.0 ** rng.uniform(-6, 6, n)
+    y = rng.standard_normal(m)
+    A, x = solve_dependent(gapx, gap, K, y, eps == 0.0)
+    assert column_error(A, K) <= 1e-12
+    if x is not None:
+        # x minimises a problem whose columns are changed by rounding: K^T r column by column
+        x = x.cpu().numpy()
+        size = np.linalg.norm(K, axis=0)
+        r = y - K @ x
+        assert (np.abs(K.T @ r) / size).max() <= 1e-12 * ((size * np.abs(x)).sum()
+                                                           + np.linalg.norm(y))
+
+
+@pytest.mark.parametrize("m,n,zero,same", [
+    (500, 90, (70,), ()), (500, 90, (3,), ()), (5000, 300, (70,), (3, 40)),
+    (33001, 140, (100,), (3, 40)), (100, 100, (99,), (0, 1)), (5000, 200, (), range(0, 200)),
+    (5000, 130, (129,), (64, 127))])
+def test_columns_that_no_round_can_tell_apart(gapx, gap, m, n, zero, same):
+    """Zero columns, alone and behind a panel of equal columns, and a matrix of one column
+    repeated, all ones (no rounding error tells them apart): R still reproduces K^T K."""
+    print(f"m {m} n {n} zero {zero} same {same}", flush=True)
+    rng = np.random.default_rng([m, n])
+    K = rng.standard_normal((m, n)) + (np.eye(m, n) * 3 if m < 2 * n else 0)
+    if len(same) == n:
+        K[:] = 1.0
+    for a in same:
+        K[:, a] = K[:, same[0]]
+    for a in zero:
+        K[:, a] = 0.0
+    A, x = solve_dependent(gapx, gap, K, rng.standard_normal(m), True)
+    assert x is None or not zero
+    assert column_error(A, K) <= 1e-12
