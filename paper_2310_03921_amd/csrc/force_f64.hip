@@ -154,16 +154,18 @@ GAP_DEV void ldj4(const float* p, double out[4]) {
 // There is no guarded load on the hot path.
 // A load under a condition compiles to a branch whose join waits for the load
 // at once, which would serialise the Jacobian stream; here every load reads a
-// valid address and invalid data is cancelled arithmetically:
+// valid address and what it must not contribute is left out afterwards:
 //  - k blocks beyond D read the row's last 4 elements and meet zero rows of X
 //    (RAGGED, D % 4 != 0: the row's padding may hold anything, so entries past D
 //    are replaced by zero where they are used);
-//  - a slot past its degree (or a target past n_atoms) reads a valid pair of
-//    the same target (or pair 0) and its step result is multiplied by a zero S;
-//  - S is read at a clamped (source, column) and multiplied by the validity.
-// Matrix data are finite, so garbage * 0 == 0.  Results equal those of the
-// guarded form up to the order of FP64 additions (identical here: the zero
-// contributions add exact zeros).
+//  - a slot past its degree (or a target past n_atoms) reads a valid pair, of the
+//    same target or of another, and S at a clamped source: the sum is selected,
+//    not scaled by zero, so a Jacobian or S that is not finite stays with its
+//    own target's rows (a column past M is never stored).
+// With NG = 4 the sums are those of the guarded form, in its order.  With NG = 1 a
+// target's pairs are dealt to four waves, whose sums are added in wave order: the
+// last bits then differ from NG = 4's, so they depend on the call's size through
+// kForceSplit, but not on the run.
 constexpr int kLdsMaxKb = 16;  // D <= 256
 constexpr int kLdsNC = 4;      // 16-column tiles per block
 template <typename TJ, bool RAGGED, int NG>
@@ -281,14 +283,21 @@ __global__ __launch_bounds__(768) void k_force_rows_lds(
         const int src_r = __shfl(src, g + 4 * r);
         sv[r] = *reinterpret_cast<const dNv*>(S + (int64_t)max(src_r, 0) * ldS + scol);
       }
+      if (__all(t < deg && src >= 0)) {  // most steps: the group's degrees are alike
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int src_r = __shfl(src, g + 4 * r);
-        const int deg_r = __shfl(deg, g + 4 * r);
-        const bool ok_r = t < deg_r && src_r >= 0;
+        for (int r = 0; r < 4; ++r)
 #pragma unroll
-        for (int u = 0; u < NC; ++u)
-          acc[u][r] += sv[r][u] * ((ok_r && colr[u] < M) ? 1.0 : 0.0) * G[u][r];
+          for (int u = 0; u < NC; ++u) acc[u][r] += sv[r][u] * G[u][r];
+      } else {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int src_r = __shfl(src, g + 4 * r);
+          const int deg_r = __shfl(deg, g + 4 * r);
+          const bool ok_r = t < deg_r && src_r >= 0;
+#pragma unroll
+          for (int u = 0; u < NC; ++u)
+            acc[u][r] = ok_r ? acc[u][r] + sv[r][u] * G[u][r] : acc[u][r];
+        }
       }
       jr = jn;
       pair_n = pair_nn;

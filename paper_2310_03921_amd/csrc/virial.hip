@@ -170,12 +170,12 @@ GAP_DEV void ldj4(const float* p, double out[4]) {
 // its lifetime, stored in the matrix core's operand order (as in the force-row
 // kernel): twelve waves, wave w taking Jacobian component beta = w % 3 of pair
 // stream w / 3, so three waves share a SIMD.  Every load in the pair loop reads
-// a valid address (pairs past the configuration read its last pair, k blocks
-// past D the row's last four elements against zero rows of X) and invalid data
-// are cancelled by zero weights, or for D % 4 != 0 (RAGGED), where the row's
-// padding may hold anything, replaced by zero; the next k block's (or the next
-// chunk's first) Jacobian fragment is loaded before the current block's matrix
-// work.
+// a valid address (pairs past the configuration read its last pair, whose second
+// share of the sums is left out by selection; k blocks past D the row's last four
+// elements against zero rows of X, or for D % 4 != 0 (RAGGED), where the row's
+// padding may hold anything, zeros in their place; columns past M are never
+// stored); the next k block's (or the next chunk's first) Jacobian fragment is
+// loaded before the current block's matrix work.
 constexpr int kVNC = 4;  // 16-column tiles per block
 constexpr int kVNG = 4;  // pair streams
 constexpr int kVMaxKb = 16;  // D <= 256
@@ -219,9 +219,6 @@ __global__ __launch_bounds__(192 * kVNG) void k_virial_rows_lds(
 #pragma unroll
     for (int q = 0; q < 4; ++q) a[q] = kb * 16 + 4 * g + q < D ? a[q] : 0.0;
   };
-  double cm[kVNC];
-#pragma unroll
-  for (int u = 0; u < kVNC; ++u) cm[u] = colbase + kVNC * idx + u < M ? 1.0 : 0.0;
   const int64_t scol = min(colbase + kVNC * idx, ldS - kVNC);
   double acc[3][kVNC];
 #pragma unroll
@@ -283,14 +280,13 @@ __global__ __launch_bounds__(192 * kVNG) void k_virial_rows_lds(
         const int64_t pr = p0 + g + 4 * r;
         const int64_t pc = min(pr, p_hi - 1);
         const int32_t src = pair_src[pc];
-        const double ok = (pr < p_hi && src >= 0 && src < n_atoms) ? 1.0 : 0.0;
+        const bool ok = pr < p_hi && src >= 0 && src < n_atoms;
         const int64_t sr = min(max((int64_t)src, (int64_t)0), n_atoms - 1);
         const d4v sv = *reinterpret_cast<const d4v*>(S + sr * ldS + scol);
-        const double rv[3] = {ok * pair_r[3 * pc], ok * pair_r[3 * pc + 1],
-                              ok * pair_r[3 * pc + 2]};
+        const double rv[3] = {pair_r[3 * pc], pair_r[3 * pc + 1], pair_r[3 * pc + 2]};
 #pragma unroll
         for (int u = 0; u < kVNC; ++u) {
-          const double w = sv[u] * cm[u] * G[u][r];
+          const double w = ok ? sv[u] * G[u][r] : 0.0;
 #pragma unroll
           for (int al = 0; al < 3; ++al) acc[al][u] += rv[al] * w;
         }
