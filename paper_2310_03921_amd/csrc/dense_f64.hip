@@ -649,6 +649,14 @@ __global__ __launch_bounds__(256, 3) void k_pstage_q(
   }
 }
 
+// W[i][c] = 0 for c0 <= c < ldw
+__global__ void k_zero_columns(double* __restrict__ W, int64_t n, int64_t ldw, int64_t c0) {
+  const int64_t w = ldw - c0;
+  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < n * w;
+       e += (int64_t)gridDim.x * blockDim.x)
+    W[e / w * ldw + c0 + e % w] = 0.0;
+}
+
 // e[i] = sum over the column groups g of part[g][i]: sixteen groups of lanes
 // per sixteen atoms take the groups in turn, then add up in a fixed order.
 __global__ __launch_bounds__(256) void k_sum_groups(const double* __restrict__ part, int64_t ng,
@@ -914,6 +922,11 @@ void pstage_f64(int mode, const void* rows, bool rows_f32, int64_t ldd, int64_t 
     };
     D % 4 ? pick(std::true_type{}) : pick(std::false_type{});
   }
+  // the kernels' tiles pad the rows to their last tile's end, a caller's rows may be longer
+  const int64_t padded = ng * (pstage_small(n, M) ? 32 : 128);
+  if (W && ldw > padded)
+    hipLaunchKernelGGL(k_zero_columns, dim3(std::min(cdiv(n * (ldw - padded), 256), 65536u)),
+                       dim3(256), 0, st, W, n, ldw, padded);
   if (mode == 0 && e_atom)
     hipLaunchKernelGGL(k_sum_groups, dim3(std::max(1u, std::min(cdiv(n, 16), 65536u))), dim3(256),
                        0, st, e_part, ng, n, e_atom);

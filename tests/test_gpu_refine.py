@@ -194,3 +194,17 @@ def test_refine_host_checks(gapx, gap):
     assert L.gap_refine_solve(gap._h, p(R), w.M, w.M, p(Kd), 0.0, p(g), p(c)) == gapx.GAP_E_RANK
     Kmm_d = gap.build_kmm(sp)
     assert relmax(Kmm_d.cpu().numpy().T, Kmm) <= TOL
+
+
+@pytest.mark.parametrize("n,M,ldS", [(70, 40, 64), (70, 40, 128), (70, 40, 300), (70, 128, 132),
+                                     (24700, 40, 260), (24700, 127, 128)])
+def test_weights_pad_every_row_with_zeros(gapx, gap, n, M, ldS):
+    """S of a caller's own row length: columns M .. ldS - 1 are zero, whatever they held."""
+    rng = np.random.default_rng([n, M])
+    d, X = rng.standard_normal((n, 12)), rng.standard_normal((M, 12))
+    atoms = gapx.Atoms.from_host(np.array([0, n]), d, np.zeros(n + 1, np.int64),
+                                 np.zeros(0, np.int32), None)
+    S = torch.full((n, ldS), float("nan"), dtype=torch.float64, device="cuda")
+    gap.refine_weights(atoms, gapx.Sparse.from_host(X, 3, 1.1), out=S)
+    assert (S[:, M:] == 0).all()
+    assert relmax(S[:, :M].cpu().numpy(), 1.1**2 * 3 * (d @ X.T)**2) <= TOL
