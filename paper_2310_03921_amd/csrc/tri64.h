@@ -133,7 +133,10 @@ GAP_DEV void tri_ops(TriOps& t, FU u, FI inv, int lane = threadIdx.x & 63) {
 // is multiplied by the inverse of its diagonal block and corrected once with its
 // residual, which leaves a backward error of rounding size, as a substitution
 // does, while that block's condition is below 1e8 (it enters squared, times
-// u^2).  The substitution column by column took four times as long (33,000 cycles
+// u^2): a Cholesky factor of a matrix that was found positive definite, and panels
+// whose Gram passed its test.  For the rows of the unit matrix (an inverse) the error
+// is a substitution's at any condition: 1.0 to 1.4 u |Y||U||Y| entry by entry, where a
+// substitution has 0.8 to 2.9, for block conditions up to 2e14.  The substitution column by column took four times as long (33,000 cycles
 // against 72 dependent matrix instructions for the 64 columns).
 GAP_DEV void tri_solve16(const TriOps& t, d4v (&x)[4]) {
   auto mul = [](const d4v& a, const d4v& b, d4v c) {

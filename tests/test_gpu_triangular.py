@@ -67,3 +67,43 @@ def test_variance_over_inverse_levels(gapx, gap, M, N):
                                torch.tensor(Kmm, device="cuda"), 1e-3,
                                torch.tensor(buf, device="cuda"))
     assert np.abs(var.cpu().numpy() - ref).max() <= 1e-10
+
+
+def inverse_rows(U):
+    """U^-1 of an upper triangle by substitution, in U's own precision."""
+    n = len(U)
+    Y = np.eye(n, dtype=U.dtype)
+    for c in range(n):
+        Y[:, c] /= U[c, c]
+        Y[:, c + 1:] -= np.outer(Y[:, c], U[c, c + 1:])
+    return Y
+
+
+@pytest.mark.parametrize("M", [16, 64, 200])
+@pytest.mark.parametrize("eps", [1e-4, 1e-8, 1e-12])
+def test_variance_with_an_ill_conditioned_factor(gapx, gap, M, eps):
+    """R of columns equal up to eps, inside a 16-column block and across blocks (block
+    conditions up to 1e13): against extended precision, within what a substitution may
+    be off, |dY| <= M u |Y||R||Y| entry by entry, carried through |k Y|^2."""
+    rng = np.random.default_rng([M, 7])
+    X, d = points(M), points(40 + 1000)[:40]
+    Kmm = oracle.build_kmm(X, 2, 1.0)
+    B = rng.standard_normal((2 * M, M))
+    for a, b in ((1, 0), (9, 4), (M - 1, 2)):
+        B[:, a] = B[:, b] + eps * rng.standard_normal(2 * M)
+    R = np.linalg.qr(B)[1]
+    Y = inverse_rows(R.astype(np.longdouble))
+    U = np.linalg.cholesky(Kmm + 1e-3 * np.eye(M)).T.astype(np.longdouble)
+    k = (np.longdouble(1) * d @ X.T) ** 2
+    z = k @ Y
+    kii = (d * d).sum(1) ** 2
+    ref = kii - ((k @ inverse_rows(U)) ** 2).sum(1) + (z ** 2).sum(1)
+    u = 2.0 ** -53
+    dz = M * u * (np.abs(k) @ np.abs(Y) @ np.abs(R) @ np.abs(Y))
+    bound = (2 * np.abs(z) * dz + dz ** 2).sum(1) + M * u * (z ** 2).sum(1) + 1e-10
+    atoms = gapx.Atoms.from_host(np.array([0, 40]), d, np.zeros(41, np.int64),
+                                 np.zeros(0, np.int32), None)
+    var = gap.predict_variance(atoms, gapx.Sparse.from_host(X, 2, 1.0),
+                               torch.tensor(Kmm, device="cuda"), 1e-3,
+                               torch.tensor(np.ascontiguousarray(R.T), device="cuda"))
+    assert (np.abs(var.cpu().numpy() - ref) <= bound).all()
