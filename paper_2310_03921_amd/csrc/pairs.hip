@@ -26,7 +26,7 @@ namespace {
 
 constexpr int kDegBuckets = 1024;
 constexpr int kScanPer = 4096;      // counts scanned by one block
-constexpr int kWaveRankMax = 2048;  // segments up to this length are rank-sorted by one wave
+constexpr int64_t kRankPerPair = 4;  // a segment is rank-sorted while n^2 <= this times the pairs
 constexpr int kSmallAtoms = 1024;   // limits of the one-block form
 constexpr int kSmallPer = 12;       // pairs per thread
 constexpr int kSmallPairs = 1024 * kSmallPer;
@@ -75,16 +75,16 @@ GAP_DEV int wave_rank(int32_t v, int n) {
   return r;
 }
 
-// Rank sort of one segment of n distinct values by one wave, in -> out.
-GAP_DEV void wave_sort_segment(const int32_t* in, int n_, int32_t* __restrict__ out) {
+// Rank sort of one segment of n distinct values by one wave, in -> out (n uniform):
+// up to 64 values, and any number.
+GAP_DEV void wave_sort_short(const int32_t* in, int n, int32_t* __restrict__ out) {
   const int lane = threadIdx.x & 63;
-  const int n = __builtin_amdgcn_readfirstlane(n_);
-  if (n <= 64) {
-    const int32_t v = lane < n ? in[lane] : 0;
-    const int r = wave_rank(v, n);
-    if (lane < n) out[r] = v;
-    return;
-  }
+  const int32_t v = lane < n ? in[lane] : 0;
+  const int r = wave_rank(v, n);
+  if (lane < n) out[r] = v;
+}
+GAP_DEV void wave_sort_segment(const int32_t* in, int n, int32_t* __restrict__ out) {
+  const int lane = threadIdx.x & 63;
   for (int a = 0; a < n; a += 64) {
     const int32_t v = a + lane < n ? in[a + lane] : 0;
     int r = 0;
@@ -95,6 +95,41 @@ GAP_DEV void wave_sort_segment(const int32_t* in, int n_, int32_t* __restrict__ 
     }
     if (a + lane < n) out[r] = v;
   }
+}
+
+// The same from the list of pairs in order: those of target j, 256 pairs a step.
+GAP_DEV void wave_scan_segment(const int32_t* __restrict__ pair_j, int64_t n_pairs, int32_t j,
+                               int32_t* __restrict__ out) {
+  const int lane = threadIdx.x & 63;
+  int32_t at = 0;
+  for (int64_t p0 = 0; p0 < n_pairs; p0 += 256) {
+    int32_t v[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v[q] = pair_j[min(p0 + 64 * q + lane, n_pairs - 1)];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const bool mine = v[q] == j && p0 + 64 * q + lane < n_pairs;
+      const uint64_t m = __ballot(mine);
+      if (mine) out[at + __popcll(m & ((1ull << lane) - 1))] = (int32_t)(p0 + 64 * q + lane);
+      at += __popcll(m);
+    }
+  }
+}
+
+// Increasing pair order in target j's segment of n pairs, in -> out, by one wave:
+// by rank, 0.65 ns per n^2 (a step of 64 lane reads for 64 x 64 values), or by a pass over
+// the whole list, 2 to 9 ns a pair, where that is shorter.  (A line at n = 2048 made
+// 20,000 targets of 2,500 pairs each pass over all 50M: 804 ms, 23 by rank; and one
+// target of 2,000 among 100,000 pairs took 2.6 ms by rank, 0.26 by a pass.)
+GAP_DEV void wave_order_segment(const int32_t* in, int n_, int32_t* __restrict__ out,
+                                const int32_t* __restrict__ pair_j, int64_t n_pairs, int32_t j) {
+  const int n = __builtin_amdgcn_readfirstlane(n_);
+  if (n <= 64)
+    wave_sort_short(in, n, out);
+  else if ((int64_t)n * n <= kRankPerPair * n_pairs)
+    wave_sort_segment(in, n, out);
+  else
+    wave_scan_segment(pair_j, n_pairs, j, out);
 }
 
 // The whole transposition in one block, for lists that fit its LDS and
@@ -145,10 +180,23 @@ __global__ __launch_bounds__(1024) void k_pairs_small(
   for (int q = 0; q < kSmallPer; ++q)
     if (pos[q] >= 0) list[start[jv[q]] + pos[q]] = t + 1024 * q;
   __syncthreads();
+  bool longer = false;
+  int lo = start[wave], hi = start[wave + 1];  // (entries past n_atoms hold the total)
   for (int j = wave; j < n_atoms; j += 16) {
-    const int lo = start[j];
-    wave_sort_segment(list + lo, start[j + 1] - lo, tgt_pair + lo);
+    const int jn = min(j + 16, kSmallAtoms - 1), lo_n = start[jn], hi_n = start[jn + 1];
+    const int n = __builtin_amdgcn_readfirstlane(hi - lo);
+    if (n <= 64)
+      wave_sort_short(list + lo, n, tgt_pair + lo);
+    else
+      longer = true;
+    lo = lo_n;
+    hi = hi_n;
   }
+  if (longer)  // (apart: they are rare, and their code would slow the loop above)
+    for (int j = wave; j < n_atoms; j += 16) {
+      const int at = start[j], n = __builtin_amdgcn_readfirstlane(start[j + 1] - at);
+      if (n > 64) wave_order_segment(list + at, n, tgt_pair + at, pair_j, n_pairs, j);
+    }
   for (int p = start[1024] + t; p < n_pairs; p += 1024) tgt_pair[p] = 0;  // dropped pairs
   if (order != nullptr && t < n_atoms) {
     const int32_t d = min(c, kDegBuckets - 1);
@@ -243,9 +291,8 @@ __global__ void k_place_pairs(const int32_t* __restrict__ pair_j, int64_t n_pair
 
 // Restore increasing pair order in every segment, list -> tgt_pair: one wave
 // per target ranks its values in registers (a serial insertion sort by one
-// thread per target took 1.27 ms for 116,000 targets of 30 pairs).  A segment
-// longer than kWaveRankMax is rebuilt by its wave from the pair list in order
-// instead (a pass over the list, not the square of the segment).  Entries past
+// thread per target took 1.27 ms for 116,000 targets of 30 pairs), or rebuilds a
+// long segment from the list (wave_order_segment).  Entries past
 // the last segment (pairs dropped for an out-of-range target) hold pair 0, a
 // valid index for readers that clamp a slot to the end of the list.
 __global__ __launch_bounds__(256) void k_sort_segments(const int64_t* __restrict__ tgt_ptr,
@@ -253,22 +300,12 @@ __global__ __launch_bounds__(256) void k_sort_segments(const int64_t* __restrict
                                                        const int32_t* __restrict__ pair_j,
                                                        const int32_t* __restrict__ list,
                                                        int32_t* __restrict__ tgt_pair) {
-  const int lane = threadIdx.x & 63;
   const int64_t nw = (int64_t)gridDim.x * 4;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   for (int64_t j = (int64_t)blockIdx.x * 4 + wave; j < n_atoms; j += nw) {
-    const int64_t lo = tgt_ptr[j], n = tgt_ptr[j + 1] - lo;
-    if (n <= kWaveRankMax) {
-      wave_sort_segment(list + lo, (int)n, tgt_pair + lo);
-      continue;
-    }
-    int64_t out = lo;
-    for (int64_t p0 = 0; p0 < n_pairs; p0 += 64) {
-      const bool mine = p0 + lane < n_pairs && pair_j[p0 + lane] == (int32_t)j;
-      const uint64_t m = __ballot(mine);
-      if (mine) tgt_pair[out + __popcll(m & ((1ull << lane) - 1))] = (int32_t)(p0 + lane);
-      out += __popcll(m);
-    }
+    const int64_t lo = tgt_ptr[j];
+    wave_order_segment(list + lo, (int)(tgt_ptr[j + 1] - lo), tgt_pair + lo, pair_j, n_pairs,
+                       (int32_t)j);
   }
   for (int64_t p = tgt_ptr[n_atoms] + blockIdx.x * (int64_t)256 + threadIdx.x; p < n_pairs;
        p += (int64_t)gridDim.x * 256)

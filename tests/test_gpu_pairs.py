@@ -79,3 +79,18 @@ def test_force_rows_over_blocks_of_targets(gapx, gap, n_atoms):
     ref = oracle.build_knm(cfg, desc, pair_ptr, pair_j, jac, X, 2, 1.0)
     got = K[:M, :len(ref)].T.cpu().numpy()
     assert np.abs(got - ref).max() <= 1e-10 * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("n_atoms,n_pairs,heavy", [
+    (2, 12288, (6144,)), (1, 12288, ()), (40, 12288, (220, 221, 222, 223)), (3, 300, (64, 65, 66)),
+    (3000, 50000, (446, 447, 448, 449, 64, 65)), (1100, 40961, (3000, 400, 404, 405)),
+    (1500, 1048577, (2047, 2048, 2049, 300000))])
+def test_segment_order_where_its_two_forms_meet(gapx, gap, n_atoms, n_pairs, heavy):
+    """Segments of n pairs around n^2 = 4 n_pairs, in the one-block form and the general
+    one, and lists that are no multiple of the 256 pairs of a step."""
+    print(f"n_atoms {n_atoms} n_pairs {n_pairs}", flush=True)
+    pair_ptr, pair_j = pair_list(n_atoms, n_pairs, heavy)
+    tptr, tpair = gap.pair_transpose(atoms_of(gapx, pair_ptr, pair_j))
+    order = np.argsort(pair_j, kind="stable")
+    assert np.array_equal(tptr.cpu().numpy(), np.searchsorted(pair_j[order], np.arange(n_atoms + 1)))
+    assert np.array_equal(tpair.cpu().numpy(), order)
