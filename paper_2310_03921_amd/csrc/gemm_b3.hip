@@ -465,10 +465,13 @@ __global__ void k_sum_parts(const double* __restrict__ part, int64_t nz, int64_t
   }
 }
 
+// Entries of k in each of nz slices, whole k blocks: so they may be fewer than nz.
+inline int64_t k_per_slice(int64_t K, int nz) { return ((K + nz - 1) / nz + 31) / 32 * 32; }
+
 template <typename TA, typename TB, int EPI>
 void launch_gemm(TA A, int64_t lda, int64_t n_a, TB B, int64_t ldb, int64_t n_b, int64_t K,
                  int nz, const EpiArgs& ep, hipStream_t st) {
-  const int64_t kpz = ((K + nz - 1) / nz + 31) / 32 * 32;
+  const int64_t kpz = k_per_slice(K, nz);
   const dim3 grid(xcd_group_tile_blocks(cdiv_u(n_a, kGT), cdiv_u(n_b, kGT)),
                   (unsigned)cdiv_u(K, kpz));
   static bool attr = false;
@@ -530,6 +533,14 @@ void gemm_b3_wx(const float* W, int64_t ldw, int64_t n, int64_t M, const __bf16*
                                                1, ep, st);
 }
 
+void sum_parts_f64(const double* part, int64_t nz, int64_t stride, double* out, int64_t rows,
+                   int64_t ldo, int64_t cols, hipStream_t st) {
+  if (rows <= 0 || cols <= 0) return;
+  const unsigned g = std::max(1u, std::min(cdiv_u(rows * cols, 256), 65536u));
+  hipLaunchKernelGGL(k_sum_parts, dim3(g), dim3(256), 0, st, part, nz, rows * cols, stride, out,
+                     rows, ldo, cols);
+}
+
 void gemm_b3_wtd(const float* W, int64_t ldw, int64_t M, int64_t n, const void* desc,
                  bool desc_f32, int64_t ldd, int64_t D, double* part, int nz, double* out,
                  int64_t ldo, hipStream_t st) {
@@ -539,25 +550,15 @@ void gemm_b3_wtd(const float* W, int64_t ldw, int64_t M, int64_t n, const void* 
   ep.ldc = D;
   ep.zstride = M * D;
   // out[m][d] = sum_i W[i][m] desc[i][d]: both operands are column views (k = i)
-  if (desc_f32)
-    launch_gemm<ColOp<float>, ColOp<float>, kPlain>(ColOp<float>{W}, ldw, M,
-                                                    ColOp<float>{static_cast<const float*>(desc)},
-                                                    ldd, D, n, nz, ep, st);
-  else
+  const ColOp<float> w{W};
+  if (n > 0 && desc_f32)
+    launch_gemm<ColOp<float>, ColOp<float>, kPlain>(
+        w, ldw, M, ColOp<float>{static_cast<const float*>(desc)}, ldd, D, n, nz, ep, st);
+  else if (n > 0)
     launch_gemm<ColOp<float>, ColOp<double>, kPlain>(
-        ColOp<float>{W}, ldw, M, ColOp<double>{static_cast<const double*>(desc)}, ldd, D, n, nz, ep,
-        st);
-  const unsigned g = std::max(1u, std::min(cdiv_u(M * D, 256), 65536u));
-  hipLaunchKernelGGL(k_sum_parts, dim3(g), dim3(256), 0, st, part, (int64_t)nz, M * D, M * D, out,
-                     M, ldo, D);
-}
-
-void sum_parts_f64(const double* part, int64_t nz, int64_t stride, double* out, int64_t rows,
-                   int64_t ldo, int64_t cols, hipStream_t st) {
-  if (rows <= 0 || cols <= 0) return;
-  const unsigned g = std::max(1u, std::min(cdiv_u(rows * cols, 256), 65536u));
-  hipLaunchKernelGGL(k_sum_parts, dim3(g), dim3(256), 0, st, part, nz, rows * cols, stride, out,
-                     rows, ldo, cols);
+        w, ldw, M, ColOp<double>{static_cast<const double*>(desc)}, ldd, D, n, nz, ep, st);
+  const int64_t slices = n > 0 ? cdiv_u(n, k_per_slice(n, nz)) : 0;
+  sum_parts_f64(part, slices, M * D, out, M, ldo, D, st);
 }
 
 }  // namespace gapk

@@ -7,6 +7,8 @@ carry relative errors of order 1e-5; the bounds below leave a factor ~10.
 After refinement with an exact FP64 residual, c must match the FP64 solution
 to the FP64 bound (1e-10).
 """
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -256,3 +258,47 @@ def test_knm_bf16x3_presplit_k_blocks(gapx, gap, D, M, lo, hi, jdt):
     ref = oracle.build_knm(b.cfg_ptr, b.desc, b.pair_ptr, b.pair_j, b.jac, X, w.zeta, w.delta)
     assert relmax(got[:b.n_cfg], ref[:b.n_cfg]) <= MIXED_TOL
     assert relmax(got[b.n_cfg:], ref[b.n_cfg:]) <= MIXED_TOL
+
+
+@pytest.mark.parametrize("n", [16416, 1025, 8224])
+def test_backward_bf16x3_over_slices_of_atoms(gapx, gap, n):
+    """d_X sums the slices of the atom range that were computed, where rounding their length
+    up to 32 atoms makes them fewer than asked for: after a call that left other
+    partial sums in the workspace."""
+    print(f"n {n}", flush=True)
+    rng = np.random.default_rng(n)
+    M, D = 20, 12
+    X = rng.standard_normal((M, D))
+    sp = gapx.Sparse.from_host(X, 2, 1.0)
+    c = rng.standard_normal(M)
+
+    def backward(k):
+        d, ge = rng.standard_normal((k, D)), rng.standard_normal(k)
+        atoms = gapx.Atoms.from_host(np.array([0, k]), d, np.zeros(k + 1, np.int64),
+                                     np.zeros(0, np.int32), None)
+        return d, ge, gap.predict_backward(atoms, sp, torch.tensor(c, device="cuda"),
+                                           torch.tensor(ge, device="cuda"), precision="bf16x3")
+
+    backward(16384)
+    d, ge, got = backward(n)
+    ref = oracle.predict_backward(d, X, c, ge, 2, 1.0)
+    for name, g, r in zip(("d_desc", "d_c", "d_X"), got, ref):
+        g, r = g.cpu().numpy(), np.asarray(r).reshape(g.shape)
+        assert np.abs(g - r).max() <= MIXED_TOL * np.abs(r).max(), name
+
+
+def test_backward_bf16x3_without_atoms(gapx, gap):
+    """No atoms (and pointers that are not NULL): the gradients of c and X are zero."""
+    M, D = 20, 12
+    atoms = gapx.Atoms.from_host(np.array([0, 0]), np.zeros((0, D)), np.zeros(1, np.int64),
+                                 np.zeros(0, np.int32), None)
+    sp = gapx.Sparse.from_host(np.ones((M, D)), 2, 1.0)
+    a, s = atoms.struct(), sp.struct()
+    c, ge = (torch.ones(k, dtype=torch.float64, device="cuda") for k in (M, 4))
+    dc = torch.full((M,), 7.0, dtype=torch.float64, device="cuda")
+    dX = torch.full((M, D), 7.0, dtype=torch.float64, device="cuda")
+    ptr = lambda t: ctypes.c_void_p(t.data_ptr())
+    st = gapx.lib().gap_predict_backward(gap._h, ctypes.byref(a), ctypes.byref(s), ptr(c),
+                                         gapx.PRECISION["bf16x3"], ptr(ge), None, ptr(dc), ptr(dX))
+    gap.sync()
+    assert st == 0 and (dc == 0).all() and (dX == 0).all()
