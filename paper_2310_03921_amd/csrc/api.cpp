@@ -451,8 +451,8 @@ gap_status gap_workspace_query(gap_handle* h, const gap_atoms* a, const gap_spar
   const int64_t n_rows = a->n_cfg + 3 * N;
   Layout L;
   PairWs p;
-  layout_pairs(L, N, a->n_pairs, p);
-  L.take(sizeof(double) * N * M);  // S
+  layout_pairs(L, N, a->n_pairs, p, true);
+  L.take(sizeof(double) * N * ld4(M));  // S
   size_t knm = L.off;
   Layout F;
   F.take(sizeof(double) * gapk::chol_doubles(M));
@@ -752,8 +752,8 @@ gap_status gap_predict_variance(gap_handle* h, const gap_atoms* a, const gap_spa
   gapk::local_rows_f64(a->desc, f32(a->desc_dt), a->ld_desc, N, nullptr, N, sp->X, sp->ld_x, M,
                        D, sp->zeta, sp->delta, at<double>(h, Ks), ldm, h->dev_err, h->stream,
                        true);
-  gapk::trinv_upper2(R, ldr, at<double>(h, Yr), nullptr, 0, nullptr, M, ldm, at<double>(h, tp),
-                     h->dev_err, h->stream);
+  gapk::trinv_upper(R, ldr, at<double>(h, Yr), M, ldm, at<double>(h, tp), h->dev_err,
+                    h->stream);
   gapk::gemm_wx_f64(at<double>(h, Ks), ldm, N, M, at<double>(h, Yr), ldm, M, at<double>(h, pt),
                     at<double>(h, Zb), ldm, h->stream, true);
   gapk::var_rows(at<double>(h, Zb), ldm, N, M, 1.0, a->desc, f32(a->desc_dt), a->ld_desc, D,
@@ -761,8 +761,8 @@ gap_status gap_predict_variance(gap_handle* h, const gap_atoms* a, const gap_spa
   gapk::cholesky_lower(at<double>(h, Lw), M, M, jitter, Kmm, M, h->dev_err, st_u);
   gapk::stack_u(at<double>(h, Ub), M, 0, M, at<double>(h, Lw), M, st_u);
   // (L is done with; the inverse's products take at most M^2 / 2 of its place)
-  gapk::trinv_upper2(at<double>(h, Ub), M, at<double>(h, Yu), nullptr, 0, nullptr, M, ldm,
-                     at<double>(h, Lw), h->dev_err, st_u);
+  gapk::trinv_upper(at<double>(h, Ub), M, at<double>(h, Yu), M, ldm,
+                    at<double>(h, Lw), h->dev_err, st_u);
   if (side) HIP_TRY(h, hipEventRecord(h->ev_join, h->side));
   if (side) HIP_TRY(h, hipStreamWaitEvent(h->stream, h->ev_join, 0));
   // var_i = k_ii - ||k_i^T U^-1||^2 + ||k_i^T R^-1||^2
@@ -815,8 +815,8 @@ gap_status gap_select_cur(gap_handle* h, const gap_atoms* a, int64_t n_sparse, d
   gapk::cholesky_lower(at<double>(h, Lw), D, D, jitter, at<double>(h, Gw), D, h->dev_err,
                        h->stream);
   gapk::stack_u(at<double>(h, Ub), D, 0, D, at<double>(h, Lw), D, h->stream);
-  gapk::trinv_upper2(at<double>(h, Ub), D, at<double>(h, Yu), nullptr, 0, nullptr, D, ldd,
-                     at<double>(h, tp), h->dev_err, h->stream);
+  gapk::trinv_upper(at<double>(h, Ub), D, at<double>(h, Yu), D, ldd,
+                    at<double>(h, tp), h->dev_err, h->stream);
   gapk::gemm_wx_f64(dd, ldd, N, D, at<double>(h, Yu), ldd, D, at<double>(h, pt), at<double>(h, Zb),
                     ldd, h->stream, true);
   gapk::var_rows(at<double>(h, Zb), ldd, N, D, 1.0, dd, false, ldd, D, 1, 1.0, 2, lev, h->stream);

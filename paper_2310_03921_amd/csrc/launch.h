@@ -315,9 +315,9 @@ void norm2_f64(const double* x, int64_t n, double* out, hipStream_t st);
 // out[0] += x . x
 void sumsq_add_f64(const double* x, int64_t n, double* out, hipStream_t st);
 // Y = R^-1 (R upper n x n col-major) as a row-major Y[i * ldy + c], zero below
-// the diagonal, for one or two matrices (R1 NULL: one); tmp: n * ldy doubles.
-void trinv_upper2(const double* R0, int64_t ld0, double* Y0, const double* R1, int64_t ld1,
-                  double* Y1, int64_t n, int64_t ldy, double* tmp, int* dev_err, hipStream_t st);
+// the diagonal; tmp: n * ldy doubles.
+void trinv_upper(const double* R, int64_t ld, double* Y, int64_t n, int64_t ldy, double* tmp,
+                 int* dev_err, hipStream_t st);
 // var[i] = base + sign * ||Z[i][0:m]||^2 with base var[i] (init 0), delta^2 (d_i . d_i)^zeta
 // (init 1) or 0 (init 2); init 3: as 1, then plus var[i].
 void var_rows(const double* Z, int64_t ldz, int64_t n, int64_t m, double sign, const void* desc,

@@ -9,8 +9,9 @@
 //          one-block steps); a cooperative kernel that adds shifted rounds takes
 //          a panel whose columns are numerically dependent.
 //   trailing update: W = V^T C (split over row slabs on FP64 MFMA, then a
-//          fixed-order reduction), T from the Gram V^T V and tau, and
-//          C -= V (T^T W) on FP64 MFMA.  b rides along as the last column.
+//          fixed-order reduction) and C -= V (T^T W) on FP64 MFMA, T from the
+//          panel (from the Gram V^T V and tau where a panel was numerically
+//          dependent).  b rides along as the last column.
 #include <algorithm>
 
 #include "launch.h"
@@ -2224,20 +2225,18 @@ __global__ __launch_bounds__(1024) void k_trsv_blk(const double* __restrict__ R,
   for (int64_t i = threadIdx.x; i < n; i += 1024) x[i] = xs[i];
 }
 
-// Inverses of the 64 x 64 diagonal blocks of upper-triangular matrices (col-
+// Inverses of the 64 x 64 diagonal blocks of an upper-triangular matrix (col-
 // major, ld) into the diagonal blocks of Y (row-major, ldy), zero below the
 // diagonal: the rows of the unit matrix solved against the block, sixteen per
-// wave.  One block per (diagonal block, matrix).
-__global__ __launch_bounds__(256) void k_trinv_diag(const double* __restrict__ R0, int64_t ld0,
-                                                    double* __restrict__ Y0,
-                                                    const double* __restrict__ R1, int64_t ld1,
-                                                    double* __restrict__ Y1, int64_t n,
+// wave.  One block per diagonal block.
+__global__ __launch_bounds__(256) void k_trinv_diag(const double* __restrict__ R0, int64_t ld,
+                                                    double* __restrict__ Y, int64_t n,
                                                     int64_t ldy, int* dev_err) {
   __shared__ double u[kTri][kTriS];
   __shared__ double inv[kInv16];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane >> 4, idx = lane & 15;
-  const int64_t j0 = (int64_t)blockIdx.x * kTri, ld = blockIdx.y ? ld1 : ld0;
-  const double* R = (blockIdx.y ? R1 : R0) + j0 + j0 * ld;
+  const int64_t j0 = (int64_t)blockIdx.x * kTri;
+  const double* R = R0 + j0 + j0 * ld;
   const int w = (int)min((int64_t)kTri, n - j0);
   for (int e = threadIdx.x; e < kTri * kTri; e += 256) {  // unit rows past the matrix
     const int r = e & 63, c = e >> 6;
@@ -2260,7 +2259,7 @@ __global__ __launch_bounds__(256) void k_trinv_diag(const double* __restrict__ R
     for (int r = 0; r < 4; ++r) x[b][r] = row == 16 * b + g + 4 * r ? 1.0 : 0.0;
   tri_solve16(t, x);
   if (row >= w) return;
-  double* y = (blockIdx.y ? Y1 : Y0) + (j0 + row) * ldy + j0;
+  double* y = Y + (j0 + row) * ldy + j0;
 #pragma unroll
   for (int b = 0; b < 4; ++b)
 #pragma unroll
@@ -2270,8 +2269,9 @@ __global__ __launch_bounds__(256) void k_trinv_diag(const double* __restrict__ R
     }
 }
 
-// var[i] += sign * sum_j Z[i][j]^2 (row-major Z, one wave per row); with
-// init, var[i] starts at delta^2 (d_i . d_i)^zeta instead.
+// var[i] = base + sign * sum_j Z[i][j]^2 (row-major Z, one wave per row), the base
+// var[i] (init 0), delta^2 (d_i . d_i)^zeta (1) or zero (2); init 3: as 1, and then
+// var[i] is added.
 template <typename TD>
 __global__ __launch_bounds__(256) void k_var_rows(const double* __restrict__ Z, int64_t ldz,
                                                   int64_t n, int64_t m, double sign,
@@ -2682,9 +2682,10 @@ static int64_t qr_slab_rows(int64_t m, int64_t j0, int64_t nct) {
 
 static int64_t qr_ldq(int64_t m) { return (m + 3) & ~int64_t(3); }
 
-// Elements of the split-K partials buffer: the Gram partials of a panel, those of the 128-wide updates, or
-// of the 16- and 64-wide ones over short slabs (at most 64 reflectors x 128
-// columns).  Both the workspace size and its binding use this one count.
+// Elements of the split-K partials buffer: the Gram partials of a panel, those of a
+// dependent panel (64 x 64 per block), those of the 64-wide updates over short slabs
+// (64 reflectors x 128 columns), or those of the 128-wide updates.  Both the workspace
+// size and its binding use this one count.
 static int64_t qr_part_elems(int64_t m, int64_t n) {
   int64_t e = std::max(((m + kNarrowSlab - 1) / kNarrowSlab + 1) * (int64_t)kQrNB * 2 * kQrNB,
                        (int64_t)std::max(kGramMaxBlocks * kGram, kPanelMaxGrid * kTri * kTri));
@@ -2730,8 +2731,8 @@ void qr_bind_workspace(void* base, int64_t m, int64_t n, QrWork* w) {
 }
 
 // Compact-WY update of columns [c0, c_end) with the pw reflectors stored in
-// columns [j0, j0 + pw): W = V^T A[j0:m, j0:c_end) (Gram V^T V included),
-// T from the Gram and tau, then A[j0:m, c0:c_end) -= V (T^T W).
+// columns [j0, j0 + pw): W = V^T A[j0:m, j0:c_end), then A[j0:m, j0 + pw:c_end) -=
+// V (T^T W) with the panel's T.
 static void qr_wy_update(double* A, int64_t ld, int64_t m, int64_t j0, int pw, int64_t c_end,
                          QrWork* w, hipStream_t st) {
   const int64_t nct = c_end - j0;
@@ -2969,22 +2970,18 @@ void sumsq_add_f64(const double* x, int64_t n, double* out, hipStream_t st) {
   hipLaunchKernelGGL(k_sumsq_add, dim3(1), dim3(1024), 0, st, x, n, out);
 }
 
-// Y_z = R_z^-1 for two upper-triangular matrices of order n (R_1 may be NULL),
-// by doubling: with the inverses of two neighbouring s x s diagonal blocks,
+// Y = R^-1 for an upper-triangular matrix of order n, by doubling: with the inverses
+// of two neighbouring s x s diagonal blocks,
 //   [R11 R12; 0 R22]^-1 = [Y11, -Y11 R12 Y22; 0, Y22],
 // two products per level for all pairs of blocks at once (tmp: n * ldy doubles).
 // A substitution per column and workgroup, the form this replaces, re-read the
-// whole triangle for every column: 2.3 ms at n = 2000, now 0.35 ms for both.
-void trinv_upper2(const double* R0, int64_t ld0, double* Y0, const double* R1, int64_t ld1,
-                  double* Y1, int64_t n, int64_t ldy, double* tmp, int* dev_err, hipStream_t st) {
+// whole triangle for every column: 2.3 ms at n = 2000, now 0.17.
+void trinv_upper(const double* R, int64_t ld, double* Y, int64_t n, int64_t ldy, double* tmp,
+                 int* dev_err, hipStream_t st) {
   if (n <= 0) return;
-  const int nz = R1 ? 2 : 1;
-  hipLaunchKernelGGL(k_trinv_diag, dim3(cdiv(n, kTri), nz), dim3(256), 0, st, R0, ld0, Y0, R1, ld1,
-                     Y1, n, ldy, dev_err);
-  for (int64_t s = kTri; s < n; s *= 2) {
-    small_trinv_level(R0, ld0, Y0, ldy, n, s, tmp, st);
-    if (R1) small_trinv_level(R1, ld1, Y1, ldy, n, s, tmp, st);
-  }
+  hipLaunchKernelGGL(k_trinv_diag, dim3(cdiv(n, kTri)), dim3(256), 0, st, R, ld, Y, n, ldy,
+                     dev_err);
+  for (int64_t s = kTri; s < n; s *= 2) small_trinv_level(R, ld, Y, ldy, n, s, tmp, st);
 }
 
 void var_rows(const double* Z, int64_t ldz, int64_t n, int64_t m, double sign, const void* desc,
