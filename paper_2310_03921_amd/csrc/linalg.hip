@@ -7,11 +7,12 @@
 //   panel: 64 columns at once, by Cholesky QR twice and the reconstruction of
 //          the Householder vectors (all products on FP64 MFMA, three small
 //          one-block steps); a cooperative kernel that adds shifted rounds takes
-//          a panel whose columns are numerically dependent.
+//          a panel whose columns are numerically dependent, and one that holds
+//          the columns in registers a last block of up to sixteen.
 //   trailing update: W = V^T C (split over row slabs on FP64 MFMA, then a
 //          fixed-order reduction) and C -= V (T^T W) on FP64 MFMA, T from the
-//          panel (from the Gram V^T V and tau where a panel was numerically
-//          dependent).  b rides along as the last column.
+//          panel (from the Gram V^T V and tau where one of the other two
+//          kernels took it).  b rides along as the last column.
 #include <algorithm>
 
 #include "launch.h"
@@ -1083,6 +1084,192 @@ __global__ __launch_bounds__(kColT) void k_qr_panel_dep(DepArgs d) {
   }
 }
 
+// ------------------------------------------------------- narrow blocks ----
+// Householder factorisation of an outer block of width <= kRRW with the whole
+// panel held in registers across a cooperative grid: thread t of block b owns
+// the panel rows (b * 512 + t) + q * (grid * 512), q < kRRQ.  Every column
+// step applies the previous reflector to the thread's rows, forms per-block
+// partial sums of the next column's norm and dot products, publishes them, and
+// waits at a grid barrier; every block then reduces all partials in the same
+// fixed order, so all blocks derive identical reflector parameters without a
+// second barrier.  Partials alternate between two buffers so a block that is
+// one step ahead never overwrites values a slower block is still reading.
+// For a block this narrow the eight launches of a 64-column panel and its one-block
+// steps of 64 columns cost more (four columns, 600 rows: 94 us of kernels against 25;
+// 400,000 rows: 290 against 41; a least-squares call of 60 rows 242 against 170).
+static_assert(kPanelMaxGrid <= 256, "the panel reduction reads at most 4 partials per lane");
+constexpr int kRRW = 16;    // panel width
+constexpr int kRRQ = 4;     // rows per thread
+constexpr int kRRT = 512;   // threads per block
+static_assert(kRRW == 16, "the panel's wave reduction is a 16-value butterfly");
+__global__ __launch_bounds__(kRRT) void k_qr_panel_rr(double* __restrict__ A, int64_t ld,
+                                                      int64_t m, int pw,
+                                                      double* __restrict__ red,
+                                                      double* __restrict__ piv,
+                                                      unsigned int* __restrict__ arrive,
+                                                      double* __restrict__ tau_all,
+                                                      unsigned int* __restrict__ state,
+                                                      int* __restrict__ dev_err) {
+  __shared__ double s_wred[kRRT / 64][kRRW];
+  __shared__ double s_tot[kRRW];
+  __shared__ double s_tw[kRRW];
+  __shared__ double s_par[3];  // tau, beta, scale of the reflector just formed
+  __shared__ double s_pv[kRRW];  // the pivot row of the current column
+  const int G = gridDim.x;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int64_t stride = (int64_t)G * kRRT;
+  int64_t lrow[kRRQ];  // row, or -1
+  double a[kRRQ][kRRW];
+#pragma unroll
+  for (int q = 0; q < kRRQ; ++q) {
+    const int64_t lr = (int64_t)blockIdx.x * kRRT + threadIdx.x + q * stride;
+    lrow[q] = (lr < m) ? lr : -1;
+#pragma unroll
+    for (int j = 0; j < kRRW; ++j)
+      a[q][j] = (lrow[q] >= 0 && j < pw) ? A[lr + j * ld] : 0.0;
+  }
+  double beta_p = 0.0, scale_p = 0.0;
+  for (int k = 0; k <= pw; ++k) {
+    // 1. apply reflector k-1 to rows >= k-1.  Register arrays are indexed by
+    //    absolute column only (selects against k), never by a k-relative
+    //    index, which would force them out of registers.  tw[j] is zero for
+    //    j <= k-1, and v is zero on rows above the reflector, so the update
+    //    needs no condition.
+    if (k > 0) {
+      double tw[kRRW];
+#pragma unroll
+      for (int j = 0; j < kRRW; ++j) tw[j] = s_tw[j];
+#pragma unroll
+      for (int q = 0; q < kRRQ; ++q) {
+        const bool at = lrow[q] == k - 1, below = lrow[q] > k - 1;
+        double ak1 = 0.0;
+#pragma unroll
+        for (int j = 0; j < kRRW; ++j) ak1 = (j == k - 1) ? a[q][j] : ak1;
+        const double v = at ? 1.0 : (below ? ak1 * scale_p : 0.0);
+        const double nk1 = at ? beta_p : (below ? v : ak1);
+#pragma unroll
+        for (int j = 0; j < kRRW; ++j) {
+          a[q][j] = (j == k - 1) ? nk1 : a[q][j];
+          a[q][j] -= tw[j] * v;
+        }
+      }
+    }
+    if (k == pw) break;
+    // 2. partial sums for column k over rows > k, by absolute column:
+    //    part[k] = sum a_k^2, part[j] = sum a_k a_j (j > k); pivot row published
+    double part[kRRW];
+#pragma unroll
+    for (int j = 0; j < kRRW; ++j) part[j] = 0.0;
+#pragma unroll
+    for (int q = 0; q < kRRQ; ++q) {
+      double ak = 0.0;
+#pragma unroll
+      for (int j = 0; j < kRRW; ++j) ak = (j == k) ? a[q][j] : ak;
+      ak = (lrow[q] > k) ? ak : 0.0;
+      // columns j < k are summed too (no select per register) and never used
+#pragma unroll
+      for (int j = 0; j < kRRW; ++j) part[j] += ak * a[q][j];
+      if (lrow[q] == k) {
+        double* pv = piv + (k & 1) * kRRW;
+#pragma unroll
+        for (int j = 0; j < kRRW; ++j) xstore(pv + j, a[q][j]);
+      }
+    }
+    // wave sums of the 16 partials by a halving butterfly (17 lane exchanges
+    // instead of 16 separate 6-step reductions): lane l ends with the total of
+    // column 8 b5 + 4 b4 + 2 b3 + b2 of its lane bits
+    {
+      double t8[8], t4[4], t2[2], t1;
+      const bool u5 = lane & 32, u4 = lane & 16, u3 = lane & 8, u2 = lane & 4;
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        t8[i] = (u5 ? part[i + 8] : part[i]) + __shfl_xor(u5 ? part[i] : part[i + 8], 32);
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        t4[i] = (u4 ? t8[i + 4] : t8[i]) + __shfl_xor(u4 ? t8[i] : t8[i + 4], 16);
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+        t2[i] = (u3 ? t4[i + 2] : t4[i]) + __shfl_xor(u3 ? t4[i] : t4[i + 2], 8);
+      t1 = (u2 ? t2[1] : t2[0]) + __shfl_xor(u2 ? t2[0] : t2[1], 4);
+      t1 += __shfl_xor(t1, 2);
+      t1 += __shfl_xor(t1, 1);
+      const int jj = (u5 ? 8 : 0) + (u4 ? 4 : 0) + (u3 ? 2 : 0) + (u2 ? 1 : 0);
+      if ((lane & 3) == 0 && jj >= k && jj < pw) s_wred[wave][jj - k] = t1;
+    }
+    const int ncnt = pw - k;
+    __syncthreads();
+    double* rb = red + (size_t)(k & 1) * kRRW * G;
+    if (threadIdx.x < ncnt) {
+      double s = 0.0;
+#pragma unroll
+      for (int w = 0; w < kRRT / 64; ++w) s += s_wred[w][threadIdx.x];
+      xstore(rb + (int64_t)threadIdx.x * G + blockIdx.x, s);
+    }
+    grid_barrier_x8(arrive, (unsigned)(k + 1), dev_err);
+    // the pivot row, read together with the partials below (one round trip)
+    const double* pv = piv + (k & 1) * kRRW;
+    if (threadIdx.x < kRRW) s_pv[threadIdx.x] = vload(pv + threadIdx.x);
+    // 3. every block reduces all partials in the same order.  A wave reads the
+    //    G <= 256 partials of its two columns (wave, wave + 8) with all eight
+    //    loads in flight together (clamped addresses, out-of-range ones scaled
+    //    by zero), so the reads cost one memory round trip, not one per load.
+    if (wave < ncnt) {
+      const int v0 = wave, v1 = min(wave + kRRT / 64, ncnt - 1);
+      double x0[4], x1[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int b = min(lane + 64 * i, G - 1);
+        x0[i] = vload(rb + (int64_t)v0 * G + b);
+        x1[i] = vload(rb + (int64_t)v1 * G + b);
+      }
+      double s0 = 0.0, s1 = 0.0;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const double w = (lane + 64 * i < G) ? 1.0 : 0.0;
+        s0 += w * x0[i];
+        s1 += w * x1[i];
+      }
+      s0 = wave_sum(s0);
+      s1 = wave_sum(s1);
+      if (lane == 0) {
+        s_tot[v0] = s0;
+        if (wave + kRRT / 64 < ncnt) s_tot[wave + kRRT / 64] = s1;
+      }
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      const double alpha = s_pv[k];
+      const double xnorm = sqrt(s_tot[0]);
+      double tau = 0.0, beta = alpha, scale = 0.0;
+      if (xnorm > 0.0) {
+        beta = -copysign(hypot(alpha, xnorm), alpha);
+        tau = (beta - alpha) / beta;
+        scale = 1.0 / (alpha - beta);
+      }
+      s_par[0] = tau;
+      s_par[1] = beta;
+      s_par[2] = scale;
+      if (blockIdx.x == 0) tau_all[k] = tau;
+    }
+    __syncthreads();
+    if (threadIdx.x < kRRW) {
+      const int j = threadIdx.x;
+      s_tw[j] = (j > k && j < pw) ? s_par[0] * (s_pv[j] + s_par[2] * s_tot[j - k]) : 0.0;
+    }
+    beta_p = s_par[1];
+    scale_p = s_par[2];
+    __syncthreads();
+  }
+  if (blockIdx.x == 0 && threadIdx.x == 0) *state = 1u;  // T is formed from V and tau
+#pragma unroll
+  for (int q = 0; q < kRRQ; ++q) {
+    if (lrow[q] < 0) continue;
+#pragma unroll
+    for (int j = 0; j < kRRW; ++j)
+      if (j < pw) A[lrow[q] + j * ld] = a[q][j];
+  }
+}
+
 // sum_{q0 <= q < q1} a(q) b(q) with four independent partial sums, so that the
 // LDS reads of four terms are in flight together (a single running sum waits
 // for each read in turn)
@@ -1744,8 +1931,8 @@ __global__ __launch_bounds__(256, 2) void k_qr_vtc5(const double* __restrict__ A
     }
 }
 
-// T of a 64-wide half whose panel was factored by k_qr_panel_dep (its state word
-// is set; other panels bring their T along), from the Gram G = V^T V held in W
+// T of a 64-wide half whose panel was factored by k_qr_panel_dep or k_qr_panel_rr (its
+// state word is set; other panels bring their T along), from the Gram G = V^T V held in W
 // (row l at W + l * nct): T[0:i, i] = -tau_i T[0:i, 0:i] G[0:i, i], T[i][i] =
 // tau_i.  Col-major, ld 64, one block per half; zero below the diagonal.
 __global__ __launch_bounds__(256) void k_qr_larft(const double* __restrict__ W, int64_t nct,
@@ -2851,16 +3038,54 @@ static void qr_undone(double* A, int64_t ld, int64_t m, int64_t o0, int ow, QrWo
   }
 }
 
+// Blocks of k_qr_panel_rr for `rows` rows: as few as hold the panel (every column costs
+// one grid barrier and a reduction over the blocks' partials), 0 if they cannot be
+// co-resident.
+static int64_t rr_blocks(int64_t rows) {
+  static const int cap = [] {
+    int dev = 0, nb = 0;
+    hipDeviceProp_t p;
+    if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&p, dev) == hipSuccess &&
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_qr_panel_rr, kRRT, 0) == hipSuccess &&
+        nb > 0)
+      return std::min(nb * p.multiProcessorCount, kPanelMaxGrid);
+    return 0;
+  }();
+  const int64_t G = (rows + kRRT * kRRQ - 1) / (kRRT * kRRQ);
+  return G <= cap ? G : 0;
+}
+
+// An outer block of ow <= kRRW columns; false if the wide panels have to take it.
+static bool qr_narrow(double* A, int64_t ld, int64_t m, int64_t o0, int ow, QrWork* w,
+                      hipStream_t st, int* dev_err) {
+  int64_t rows = m - o0;
+  const int64_t G = ow <= kRRW ? rr_blocks(rows) : 0;
+  if (G < 1) return false;
+  hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(256), 0, st, w->counter, (int64_t)kCounterWords, 0u);
+  double *P = A + o0 + o0 * ld, *piv = w->red + 4 * kTri * kPanelMaxGrid, *tau = w->tau + o0;
+  unsigned int* arrive = w->counter + kPanelBar;
+  void* args[] = {&P, &ld, &rows, &ow, &w->red, &piv, &arrive, &tau, &w->counter, &dev_err};
+  if (hipLaunchCooperativeKernel(reinterpret_cast<const void*>(&k_qr_panel_rr),
+                                 dim3((unsigned)G), dim3(kRRT), args, 0, st) == hipSuccess)
+    return true;
+  (void)hipGetLastError();
+  return false;
+}
+
 void qr_factor(double* A, int64_t ld, int64_t m, int64_t ncols, int64_t n, QrWork* w,
                hipStream_t st, int* dev_err, Timer* tm) {
   Timer dummy;
   if (!tm) tm = &dummy;
   // Two levels: 64-wide panels inside 128-wide outer blocks (one 64-wide compact-
   // WY update of the outer block's second half), one 128-wide update of the
-  // trailing matrix per outer block.
+  // trailing matrix per outer block; a last outer block of up to sixteen columns is
+  // one panel of its own kind.
   for (int64_t o0 = 0; o0 < n; o0 += kQrOB) {
     const int ow = (int)std::min<int64_t>(kQrOB, n - o0);
-    for (int64_t j0 = o0; j0 < o0 + ow; j0 += kQrNB) {
+    tm->begin(TM_QR_PANEL);
+    const bool narrow = qr_narrow(A, ld, m, o0, ow, w, st, dev_err);
+    tm->end(TM_QR_PANEL);
+    for (int64_t j0 = o0; !narrow && j0 < o0 + ow; j0 += kQrNB) {
       const int bw = (int)std::min<int64_t>(kQrNB, o0 + ow - j0);
       tm->begin(TM_QR_PANEL);
       qr_panel(A, ld, m, j0, bw, j0 > o0 ? 1 : 0, w, st);
@@ -2871,9 +3096,11 @@ void qr_factor(double* A, int64_t ld, int64_t m, int64_t ncols, int64_t n, QrWor
       qr_wy_update(A, ld, m, j0, bw, o0 + ow, w, st);
       tm->end(TM_QR_UPDATE);
     }
-    tm->begin(TM_QR_PANEL);
-    qr_undone(A, ld, m, o0, ow, w, st, dev_err);
-    tm->end(TM_QR_PANEL);
+    if (!narrow) {
+      tm->begin(TM_QR_PANEL);
+      qr_undone(A, ld, m, o0, ow, w, st, dev_err);
+      tm->end(TM_QR_PANEL);
+    }
     if (o0 + ow >= ncols) continue;
     tm->begin(TM_QR_UPDATE);
     qr_wy_update_ob(A, ld, m, o0, ow, ncols, w, st);

@@ -169,3 +169,25 @@ def test_columns_that_no_round_can_tell_apart(gapx, gap, m, n, zero, same):
     A, x = solve_dependent(gapx, gap, K, rng.standard_normal(m), True)
     assert x is None or not zero
     assert column_error(A, K) <= 1e-12
+
+
+@pytest.mark.parametrize("m,n", [(2, 2), (16, 16), (60, 9), (2048, 16), (2049, 15), (5000, 17),
+                                 (4100, 144), (4100, 145), (300, 133), (524288, 3), (524289, 3)])
+@pytest.mark.parametrize("same", [False, True])
+def test_narrow_last_block(gapx, gap, m, n, same):
+    """A last block of up to sixteen columns has its own panel while its rows fit the
+    device's registers; with equal columns among the last sixteen as well."""
+    print(f"m {m} n {n} same {same}", flush=True)
+    rng = np.random.default_rng([m, n])
+    K = rng.standard_normal((m, n)) + (np.eye(m, n) * 3 if m < 2 * n else 0)
+    if same:
+        K[:, n - 1] = K[:, n - 2]
+    K *= 10.0 ** rng.uniform(-6, 6, n)
+    y = rng.standard_normal(m)
+    A, x = solve_dependent(gapx, gap, K, y, same)
+    assert column_error(A, K) <= 1e-12
+    if x is not None:
+        x = x.cpu().numpy()
+        size = np.linalg.norm(K, axis=0)
+        assert (np.abs(K.T @ (y - K @ x)) / size).max() <= 1e-12 * (
+            (size * np.abs(x)).sum() + np.linalg.norm(y))
