@@ -76,6 +76,8 @@ GAP_DEV double sum_pair_lanes(double v, int mp) {
 // slots of a wave split the configuration's pairs, fixed-order reduction.
 // Bound by latency (a few hundred blocks of exponentials): sixteen waves instead
 // of four and the lanes' pair slots, 170 -> 34 us for 29k pairs and ten points.
+// Where the blocks alone fill the device (k2bWide) four waves finish a block's pairs
+// with less left idle.
 __global__ __launch_bounds__(1024) void k_2b_energy(const double* __restrict__ pair_r,
                                                      const int64_t* __restrict__ cfg_ptr,
                                                      const int64_t* __restrict__ pair_ptr,
@@ -94,7 +96,8 @@ __global__ __launch_bounds__(1024) void k_2b_energy(const double* __restrict__ p
   const int64_t p0 = min(max(pair_ptr[a0], (int64_t)0), n_pairs);
   const int64_t p1 = min(max(pair_ptr[a1], p0), n_pairs);
   double s = 0.0;
-  for (int64_t p = p0 + slot; p < p1; p += 16 * (64 / mp)) {
+  const int nw = blockDim.x >> 6;
+  for (int64_t p = p0 + slot; p < p1; p += nw * (64 / mp)) {
     double r, fr, dfr, u[3], v, dv;
     pair_geom(pair_r, p, k, r, fr, dfr, u);
     kse(r, fr, dfr, xm, fx, k, v, dv);
@@ -104,8 +107,7 @@ __global__ __launch_bounds__(1024) void k_2b_energy(const double* __restrict__ p
   __syncthreads();
   if (wave == 0 && lane < mp && m < M) {
     double t = 0.0;
-#pragma unroll
-    for (int w = 0; w < 16; ++w) t += red[w][lane];
+    for (int w = 0; w < nw; ++w) t += red[w][lane];
     K[c + m * ldk] = 0.5 * t;
   }
 }
@@ -245,6 +247,11 @@ Se2b make_k(double delta, double theta, double r_cut, double width) {
 
 }  // namespace
 
+// Blocks of k_2b_energy from which a block has four waves instead of sixteen.  (us for all
+// rows, sixteen / four waves: 3,428 blocks of 7 pairs 103 / 84; 8,570 of 84 pairs 525 / 461;
+// 21,425 of 56 pairs 927 / 778.)
+constexpr int64_t k2bWide = 2048;
+
 void se2b_rows_f64(const double* pair_r, const int64_t* cfg_ptr, int64_t n_cfg,
                    const int64_t* pair_ptr, const int64_t* tgt_ptr, const int32_t* tgt_pair,
                    int64_t n_atoms, int64_t n_pairs, const double* x, int64_t M, double delta,
@@ -253,7 +260,8 @@ void se2b_rows_f64(const double* pair_r, const int64_t* cfg_ptr, int64_t n_cfg,
   if (M <= 0) return;
   const Se2b k = make_k(delta, theta, r_cut, width);
   if (n_cfg > 0)
-    hipLaunchKernelGGL(k_2b_energy, dim3(cdiv(M, 64), (unsigned)n_cfg), dim3(1024), 0, st, pair_r,
+    hipLaunchKernelGGL(k_2b_energy, dim3(cdiv(M, 64), (unsigned)n_cfg),
+                       dim3(n_cfg * cdiv(M, 64) < k2bWide ? 1024 : 256), 0, st, pair_r,
                        cfg_ptr, pair_ptr, n_atoms, n_pairs, x, M, k, K, ldk);
   if (n_atoms > 0)
     hipLaunchKernelGGL(k_2b_force, dim3(cdiv(M, 64), cdiv(n_atoms, 4)), dim3(256), 0, st, pair_r,

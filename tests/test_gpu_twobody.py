@@ -127,3 +127,16 @@ def test_2b_rows_over_point_lanes(gapx, gap, M2):
     ref = oracle.build_2b_rows(b.cfg_ptr, b.pair_ptr, b.pair_j, r, x, **PAR)
     Kh = K[:M2, :b.n_rows].T.cpu().numpy()
     assert np.abs(Kh - ref).max() <= TOL * max(np.abs(ref).max(), 1e-300)
+
+
+@pytest.mark.parametrize("n_cfg,M2", [(2047, 5), (2048, 5), (1023, 70), (1025, 70)])
+def test_2b_rows_over_many_configurations(gapx, gap, n_cfg, M2):
+    """Energy rows of more blocks than fill the device, whose blocks have fewer waves."""
+    w = synth.Workload("many", 43, n_cfg=n_cfg, atoms_lo=1, atoms_hi=4, D=8, nb=3, M=4)
+    b = synth.generate(w, jac=False)
+    r = synth.pair_vectors(w, b)
+    x = synth.sparse_distances(w, M2)
+    atoms = gapx.Atoms.from_host(b.cfg_ptr, b.desc, b.pair_ptr, b.pair_j, None)
+    K = gap.build_2b_rows(atoms, k2_of(gapx, x), torch.tensor(r, device="cuda"))
+    ref = oracle.build_2b_rows(b.cfg_ptr, b.pair_ptr, b.pair_j, r, x, **PAR)
+    close(K[:M2, :b.n_cfg].T.cpu().numpy(), ref[:b.n_cfg], TOL, "2b energy rows")
