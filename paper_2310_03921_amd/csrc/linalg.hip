@@ -114,7 +114,7 @@ GAP_DEV void chol_diag_block(double* __restrict__ Lw, int64_t ldl, int64_t j0, i
       if (r >= c) S[r][c] = r < nbj ? Lw[(j0 + r) + (j0 + c) * ldl] : (r == c ? 1.0 : 0.0);
     }
   __syncthreads();
-  const bool bad = chol64_lds(S);
+  const bool bad = chol64_lds(S, (nbj + 15) / 16);
   if (bad && threadIdx.x == 0) atomicOr(dev_err, GAP_DEVERR_NOT_PD);
   if (threadIdx.x < 64) tri_inv16([&](int i, int j) { return S[j][i]; }, inv);
   for (int e = threadIdx.x; e < kTri * kTri; e += 256) {
@@ -391,7 +391,7 @@ __global__ __launch_bounds__(256) void k_panel_chol(int bw, int half, double* __
   __shared__ double S[kTri][kTriS];
   (void)gram_to_lds([&](int e) { return pan[kPanG + e]; }, bw, S, INFINITY);
   __syncthreads();
-  const bool bad = chol64_lds(S);
+  const bool bad = chol64_lds(S, (bw + 15) / 16);
   if (threadIdx.x == 0) state[half] = bad || (half && state[0]) ? 1u : 0u;
   if (threadIdx.x < kPanelBarWords) arrive[threadIdx.x] = 0u;
   for (int e = threadIdx.x; e < kTri * kTri; e += 256) {
@@ -467,13 +467,17 @@ __global__ __launch_bounds__(256, 2) void k_panel_solve(PanelSolve pa, PanelSolv
 }
 
 // LU without pivoting of B - diag(sg) for B (64 x 64, in LDS), sg_j = -sign of
-// the pivot: U in and above the diagonal, unit L below.  256 threads, four steps
-// of 16 columns: one wave factors them with a row per lane, then solves the
+// the pivot: U in and above the diagonal, unit L below.  256 threads, nb steps
+// of 16 columns (zero columns of B from 16 nb on: U is 1 there): one wave factors them with a row per lane, then solves the
 // rows to their right with a column per lane; the four waves update the rest.
-GAP_DEV void lu64_signs(double (*B)[kTriS], double* sg, int lane) {
+GAP_DEV void lu64_signs(double (*B)[kTriS], double* sg, int nb, int lane) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int g = lane >> 4, idx = lane & 15;
-  for (int s = 0; s < 4; ++s) {
+  if (wave == 1 && lane >= 16 * nb) {
+    B[lane][lane] = 1.0;
+    sg[lane] = -1.0;
+  }
+  for (int s = 0; s < nb; ++s) {
     const int c0 = 16 * s;
     if (wave == 0) {
       double v[16];
@@ -497,7 +501,7 @@ GAP_DEV void lu64_signs(double (*B)[kTriS], double* sg, int lane) {
       }
     }
     __syncthreads();
-    if (wave == 0 && s < 3) {  // U12 = L11^-1 B12, a column per lane
+    if (wave == 0 && s + 1 < nb) {  // U12 = L11^-1 B12, a column per lane
       const int col = min(c0 + 16 + lane, kTri - 1);
       double y[16];
 #pragma unroll
@@ -514,7 +518,7 @@ GAP_DEV void lu64_signs(double (*B)[kTriS], double* sg, int lane) {
     __syncthreads();
     int t = 0;
     for (int ti = s + 1; ti < 4; ++ti)
-      for (int tj = s + 1; tj < 4; ++tj, ++t) {
+      for (int tj = s + 1; tj < nb; ++tj, ++t) {
         if ((t & 3) != wave) continue;
         d4v acc;
 #pragma unroll
@@ -573,7 +577,8 @@ GAP_DEV void panel_middle(PanelLds& s, d4v (&x)[4], FP put_u1, FZ put_z, double*
                           int64_t ld, int64_t rows, int bw, bool out, int lane = threadIdx.x & 63) {
   const int wave = threadIdx.x >> 6, g = lane >> 4, idx = lane & 15;
   const int64_t qr = 16 * wave + idx;
-  (void)chol64_lds(s.S, lane);  // diagonally dominant: no bad pivot
+  const int nb = (bw + 15) / 16;
+  (void)chol64_lds(s.S, nb, lane);  // diagonally dominant: no bad pivot
   if (wave == 0) {
     tri_inv16([&](int i, int j) { return s.S[j][i]; }, s.inv, lane);
   } else {
@@ -600,7 +605,7 @@ GAP_DEV void panel_middle(PanelLds& s, d4v (&x)[4], FP put_u1, FZ put_z, double*
       for (int r = 0; r < 4; ++r) s.B[qr][16 * b + g + 4 * r] = x[b][r];
   }
   __syncthreads();
-  lu64_signs(s.B, s.sg, lane);
+  lu64_signs(s.B, s.sg, nb, lane);
   // R = S R2 R1 and Z = U R2 (S, the LDS array, is free for Z)
   if (out)
     upper_product64([&](int i, int k) { return s.u[i * kTri + k]; },
@@ -1006,7 +1011,7 @@ __global__ __launch_bounds__(kColT) void k_qr_panel_dep(DepArgs d) {
       if (round > 0 && !far) break;
       if (threadIdx.x < kTri) s.S[threadIdx.x][threadIdx.x] *= 1.0 + kDepShift;
       __syncthreads();
-      const bool bad = chol64_lds(s.S, fresh_lane());
+      const bool bad = chol64_lds(s.S, (bw + 15) / 16, fresh_lane());
       if (any_of(threadIdx.x == 0 && bad) || round == kDepRounds) {
         panel_columns(d, h * kTri, bar);
         return;
@@ -2436,6 +2441,11 @@ __global__ __launch_bounds__(256) void k_trinv_diag(const double* __restrict__ R
     tri_inv16([&](int i, int j) { return u[i][j]; }, inv);
   }
   __syncthreads();
+  if (w <= 16) {  // that is all of it
+    const int r = threadIdx.x >> 4, c = threadIdx.x & 15;
+    if (r < w && c < w) Y[(j0 + r) * ldy + j0 + c] = inv[threadIdx.x];
+    return;
+  }
   TriOps t;
   tri_ops(t, [&](int i, int j) { return u[i][j]; }, [&](int e) { return inv[e]; });
   const int row = 16 * wave + idx;

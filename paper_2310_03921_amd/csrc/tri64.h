@@ -29,8 +29,8 @@ GAP_DEV double readlane_f64(double v, int lane) {
 }
 
 // Lower Cholesky factor of the 64 x 64 block S (lower triangle read and
-// overwritten), by a workgroup of 256 threads; S is complete on return.  Four
-// steps of 16 columns: one wave factors the columns with a row per lane (the
+// overwritten; unit columns from 16 nb on), by a workgroup of 256 threads; S is
+// complete on return.  nb steps of 16 columns: one wave factors the columns with a row per lane (the
 // pivot's reciprocal root and the rows of L it needs come by readlane, so the
 // chain per column has no LDS access, square root or division), then the four
 // waves update the rest on the matrix cores.  Returns whether a pivot was not
@@ -38,11 +38,11 @@ GAP_DEV double readlane_f64(double v, int lane) {
 // wave 0 only.  The one-wave form it replaces, whose lanes formed each dot
 // product from LDS, took 44 us a block; this one 19 us, launch and loads
 // included, and 11 us on top of a Cholesky update that goes on to it.
-GAP_DEV bool chol64_lds(double (*S)[kTriS], int lane = threadIdx.x & 63) {
+GAP_DEV bool chol64_lds(double (*S)[kTriS], int nb = 4, int lane = threadIdx.x & 63) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int g = lane >> 4, idx = lane & 15;
   bool bad = false;
-  for (int s = 0; s < 4; ++s) {
+  for (int s = 0; s < nb; ++s) {
     const int c0 = 16 * s;
     if (wave == 0) {
       double v[16];
@@ -64,9 +64,9 @@ GAP_DEV bool chol64_lds(double (*S)[kTriS], int lane = threadIdx.x & 63) {
         if (lane >= c0 + c) S[lane][c0 + c] = v[c];
     }
     __syncthreads();
-    // tiles (ti, tj), s < tj <= ti < 4, dealt to the waves
+    // tiles (ti, tj), s < tj <= ti < nb, dealt to the waves
     int t = 0;
-    for (int ti = s + 1; ti < 4; ++ti)
+    for (int ti = s + 1; ti < nb; ++ti)
       for (int tj = s + 1; tj <= ti; ++tj, ++t) {
         if ((t & 3) != wave) continue;
         d4v acc;
