@@ -685,7 +685,7 @@ gap_status gap_build_virial_rows(gap_handle* h, const gap_atoms* a, const gap_sp
   layout_pairs(L, N, a->n_pairs, p);
   const size_t S = L.take(sizeof(double) * std::max<int64_t>(N * ld4(M), 1));
   const size_t ke = L.take(sizeof(double) * nc * M);
-  const size_t pt = L.take(gapk::virial_part_bytes(nc, M, D));
+  const size_t pt = L.take(gapk::virial_part_bytes(nc, a->n_pairs, M, D));
   s = ensure_ws(h, L.off);
   if (s != GAP_OK) return s;
   run_pairs(h, a, p, false);  // pair sources (and the index checks)

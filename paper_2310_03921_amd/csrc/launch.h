@@ -109,7 +109,7 @@ void se2b_predict_f64(const double* pair_r, const int64_t* cfg_ptr, int64_t n_cf
                       int64_t M, double delta, double theta, double r_cut, double width,
                       double* ep, double* gp, double* e_cfg, double* forces, hipStream_t st);
 // Virial rows (part: virial_part_bytes of scratch): K[(9 c + 3 alpha + beta), m] = - sum_{p in c} r[p][alpha] S[src(p)][m] (J[p][beta] . x_m).
-size_t virial_part_bytes(int64_t n_cfg, int64_t M, int64_t D);
+size_t virial_part_bytes(int64_t n_cfg, int64_t n_pairs, int64_t M, int64_t D);
 void virial_rows_f64(const void* jac, bool jac_f32, int64_t ldj, int64_t D, const double* X,
                      int64_t ldx, int64_t M, const double* S, int64_t ldS, const int64_t* cfg_ptr,
                      int64_t n_cfg, const int64_t* pair_ptr, const int32_t* pair_src,

@@ -329,14 +329,18 @@ __global__ __launch_bounds__(192 * kVNG) void k_virial_rows_lds(
 // points runs as long as the largest configuration, so where these are few they
 // are cut into up to eight slices, summed in slice order (60 configurations of up
 // to 70 atoms, M 301, D 150: 729 us in 300 blocks, 636 in 2 x 300, 571 in 3 x 300,
-// 532 in 6 x 300, 568 in 13 x 300).
-static int64_t virial_slices(int64_t n_cfg, int64_t M, int64_t D) {
-  const int64_t blocks = n_cfg * ((M + 63) / 64);
+// 532 in 6 x 300, 568 in 13 x 300).  A slice takes at least one step of 64 pairs on
+// average, and two where the blocks of one slice already take half the device: with less
+// they only load the points once more each (12 configurations of 65 pairs, D 252, M 1000:
+// 144 us in one slice, 196 in eight; of 518, M 301, 60 blocks: 177 in four, 166 in eight).
+static int64_t virial_slices(int64_t n_cfg, int64_t n_pairs, int64_t M, int64_t D) {
+  const int64_t blocks = std::max<int64_t>(n_cfg * ((M + 63) / 64), 1);
   if (D > 16 * kVMaxKb || blocks >= 1024) return 1;
-  return std::max<int64_t>(1, std::min<int64_t>(8, 2048 / std::max<int64_t>(blocks, 1)));
+  const int64_t slice = 16 * kVNG * (blocks < 128 ? 1 : 2) * std::max<int64_t>(n_cfg, 1);
+  return std::max<int64_t>(1, std::min<int64_t>({8, 2048 / blocks, n_pairs / slice}));
 }
-size_t virial_part_bytes(int64_t n_cfg, int64_t M, int64_t D) {
-  const int64_t ns = virial_slices(n_cfg, M, D);
+size_t virial_part_bytes(int64_t n_cfg, int64_t n_pairs, int64_t M, int64_t D) {
+  const int64_t ns = virial_slices(n_cfg, n_pairs, M, D);
   return ns > 1 ? sizeof(double) * ns * 9 * n_cfg * M : 0;
 }
 
@@ -354,7 +358,7 @@ void virial_rows_f64(const void* jac, bool jac_f32, int64_t ldj, int64_t D, cons
   if (D <= 16 * kVMaxKb) {  // (S rows are padded to a multiple of four)
     const int nkb = 2 * (int)((D + 31) / 32);  // even, 16-deep blocks
     const size_t tile = (size_t)kVNC * 64 * 4 * sizeof(double);
-    const int64_t ns = virial_slices(n_cfg, M, D);
+    const int64_t ns = virial_slices(n_cfg, n_pairs, M, D);
     double* out = ns > 1 ? part : K;
     const int64_t ldo = ns > 1 ? 9 * n_cfg : ldk;
     grid.y = (unsigned)ns;

@@ -103,3 +103,21 @@ def test_rows_at_descriptor_edges(gapx, gap, D):
     K = gap.build_knm(atoms, sp)[:w.M, :b.n_rows].T.cpu().numpy()
     kref = oracle.build_knm(b.cfg_ptr, b.desc, b.pair_ptr, pair_j, b.jac, X, w.zeta, w.delta)
     assert np.abs(K - kref).max() <= 1e-10 * np.abs(kref).max()
+
+
+@pytest.mark.parametrize("n_cfg,per,M", [(1, 63, 40), (1, 64, 40), (1, 128, 70), (3, 129, 300),
+                                         (40, 65, 300), (40, 260, 300), (2, 1000, 9)])
+def test_rows_over_slices_of_pairs(gapx, gap, n_cfg, per, M):
+    """Configurations of `per` pairs on average, around the one or two steps of 64 that a
+    slice takes at least, their pairs cut at random."""
+    rng = np.random.default_rng([n_cfg, per, M])
+    N, D, P = 4 * n_cfg, 21, n_cfg * per
+    cut = np.sort(rng.integers(0, P + 1, size=N - 1))
+    pair_ptr = np.concatenate([[0], cut, [P]]).astype(np.int64)
+    cfg = np.arange(0, N + 1, 4)
+    desc, X = rng.standard_normal((N, D)), rng.standard_normal((M, D))
+    jac, r = rng.standard_normal((P, 3, D)), rng.standard_normal((P, 3))
+    atoms = gapx.Atoms.from_host(cfg, desc, pair_ptr, rng.integers(0, N, P).astype(np.int32), jac)
+    K = gap.build_virial_rows(atoms, gapx.Sparse.from_host(X, 2, 1.0), torch.tensor(r, device="cuda"))
+    ref = oracle.build_virial_rows(cfg, desc, pair_ptr, jac, r, X, 2, 1.0)
+    assert np.abs(K[:M, :9 * n_cfg].T.cpu().numpy() - ref).max() <= 1e-10 * np.abs(ref).max()
