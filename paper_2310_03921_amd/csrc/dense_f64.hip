@@ -789,6 +789,7 @@ __global__ __launch_bounds__(1024) void k_reduce_rows(const double* __restrict__
   const int64_t m = (int64_t)blockIdx.x * 64 + lane;
   double s = 0.0;
   if (m < M)
+#pragma unroll 4
     for (int64_t p = wave; p < nparts; p += 16) s += part[p * M + m];
   ps[wave][lane] = s;
   __syncthreads();
