@@ -900,7 +900,7 @@ void pstage_f64(int mode, const void* rows, bool rows_f32, int64_t ldd, int64_t 
                 double* e_part, double* dc_part, hipStream_t st, const double* Sx, int64_t ldsx) {
   if (n <= 0 || M <= 0) return;
   const int64_t ng = pstage_groups(n, M);
-  double* ep = e_atom ? e_part : nullptr;
+  double* ep = ng == 1 ? e_atom : e_atom ? e_part : nullptr;  // (one group's sums are the energies)
   if (pstage_small(n, M)) {
     small_pstage_f64(mode, rows, rows_f32, ldd, n, X, ldx, M, D, zeta, delta, c, g_e, W, ldw, ep,
                      dc_part, Sx, ldsx, st);
@@ -928,7 +928,7 @@ void pstage_f64(int mode, const void* rows, bool rows_f32, int64_t ldd, int64_t 
   if (W && ldw > padded)
     hipLaunchKernelGGL(k_zero_columns, dim3(std::min(cdiv(n * (ldw - padded), 256), 65536u)),
                        dim3(256), 0, st, W, n, ldw, padded);
-  if (mode == 0 && e_atom)
+  if (mode == 0 && e_atom && ng > 1)
     hipLaunchKernelGGL(k_sum_groups, dim3(std::max(1u, std::min(cdiv(n, 16), 65536u))), dim3(256),
                        0, st, e_part, ng, n, e_atom);
 }
