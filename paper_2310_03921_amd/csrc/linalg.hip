@@ -261,7 +261,7 @@ GAP_DEV void grid_barrier_x8(unsigned int* arrive, unsigned int round, int* dev_
 // 26,000 rows and 9.7 us at 353,000 (0.43 and 0.62 ms per 64 columns, and 0.13
 // and 0.34 ms more for the updates between its 16-column steps); this takes
 // 0.11 and 0.32 ms, at the small end the latency of its one-block steps
-// (k_panel_vectors 47 us, k_panel_chol 18 us), at the large end the passes over
+// (k_panel_vectors 45 us, k_panel_chol 16 us), at the large end the passes over
 // the panel.
 constexpr int kGramTiles = 10;                // lower 16 x 16 tiles of a 64 x 64 Gram
 constexpr int kGram = kGramTiles * 256;       // their values
@@ -639,7 +639,7 @@ GAP_DEV void panel_top(const PanelLds& s, double* __restrict__ A, int64_t ld, in
 
 // The one-block middle launch: the test that Q was near enough to orthonormal, then
 // R, tau and V's top in A, and the operands of V's other rows and of T.  Bound by
-// latency: 47 us, half of it the 64 columns of the Cholesky factor and the 64 of
+// latency: 45 us, half of it the 64 columns of the Cholesky factor and the 64 of
 // the LU.
 __global__ __launch_bounds__(256) void k_panel_vectors(double* __restrict__ A, int64_t ld,
                                                        int64_t rows, int bw,
@@ -695,7 +695,8 @@ __global__ __launch_bounds__(256) void k_panel_vectors(double* __restrict__ A, i
 // state word is set (state[h]: panel h of 64 columns; the launch ends at once if
 // neither is).  Nothing of the block was written after that panel, so its other
 // panel is taken along.  A cooperative grid (it also runs as a single ordinary
-// block) that does what the panel kernels do, with more rounds of Cholesky QR:
+// block) that does what the panel kernels do, with more rounds of Cholesky QR, shifted
+// (Fukaya, Kannan, Nakatsukasa, Yamamoto, Yanagisawa, SIAM J. Sci. Comput. 2020):
 //   G = X^T X, R = chol(G + kDepShift diag(G)), X <- X R^-1,
 // from X = P until G is within 1/64 of the unit matrix.  The shift keeps the Cholesky
 // factor defined whatever the columns (the Gram's own rounding is below it) and X's
