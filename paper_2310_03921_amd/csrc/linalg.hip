@@ -708,8 +708,8 @@ __global__ __launch_bounds__(256) void k_panel_vectors(double* __restrict__ A, i
 // zero column, columns equal in a way that leaves no rounding error, an overflow)
 // panel_columns goes through the rest of the block column by column.
 // A 64-row group of the block belongs to one workgroup for the whole kernel, and
-// a 16-row tile to one wave except in panel_columns, so rows are exchanged through
-// memory by nobody; Grams, Q's top rows and V^T C go by device-scope atomics, and
+// a 16-row tile to one wave except in panel_columns, so no row passes from one
+// workgroup to another; Grams, Q's top rows and V^T C go by device-scope atomics, and
 // every workgroup forms the small factors for itself.
 // A fit of 88,000 rows and 2,000 points with equal points in every 128: 330 ms when
 // such blocks went column by column alone (a pass over up to 128 columns and a grid
