@@ -274,23 +274,35 @@ __global__ __launch_bounds__(192 * kVNG) void k_virial_rows_lds(
             for (int u = 0; u < kVNC; ++u) G[u] = mfma_f64(fb[s4], b[u][s4], G[u]);
         }
       }
-      // C layout: lane holds pairs p0 + g + 4 r of its four columns
+      // C layout: lane holds pairs p0 + g + 4 r of its four columns.  The gathers of all
+      // four are issued before the first is used (the scheduler, left to itself, does them
+      // one after the other to save registers that a block of twelve waves has anyway:
+      // 30,000 atoms of 30 pairs, D 252, M 2000, 44.55 ms against 43.81).
+      int32_t src[4];
+      d4v sv[4];
+      double rv[4][3];
+      bool ok[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) src[r] = pair_src[min(p0 + g + 4 * r, p_hi - 1)];
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int64_t pr = p0 + g + 4 * r;
-        const int64_t pc = min(pr, p_hi - 1);
-        const int32_t src = pair_src[pc];
-        const bool ok = pr < p_hi && src >= 0 && src < n_atoms;
-        const int64_t sr = min(max((int64_t)src, (int64_t)0), n_atoms - 1);
-        const d4v sv = *reinterpret_cast<const d4v*>(S + sr * ldS + scol);
-        const double rv[3] = {pair_r[3 * pc], pair_r[3 * pc + 1], pair_r[3 * pc + 2]};
+        const int64_t pr = p0 + g + 4 * r, pc = min(pr, p_hi - 1);
+        ok[r] = pr < p_hi && src[r] >= 0 && src[r] < n_atoms;
+        const int64_t sr = min(max((int64_t)src[r], (int64_t)0), n_atoms - 1);
+        sv[r] = *reinterpret_cast<const d4v*>(S + sr * ldS + scol);
+#pragma unroll
+        for (int al = 0; al < 3; ++al) rv[r][al] = pair_r[3 * pc + al];
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
 #pragma unroll
         for (int u = 0; u < kVNC; ++u) {
-          const double w = ok ? sv[u] * G[u][r] : 0.0;
+          const double w = ok[r] ? sv[r][u] * G[u][r] : 0.0;
 #pragma unroll
-          for (int al = 0; al < 3; ++al) acc[al][u] += rv[al] * w;
+          for (int al = 0; al < 3; ++al) acc[al][u] += rv[r][al] * w;
         }
-      }
       jr = jn;
     }
   }
