@@ -15,6 +15,8 @@
 // Within one degree the order is increasing atom index, so the 16 targets of
 // a wavefront usually come from one or two neighbouring configurations and
 // their incoming pairs' Jacobian rows lie close together in memory.
+#include <cmath>
+
 #include <algorithm>
 
 #include "common.h"
@@ -27,6 +29,12 @@ namespace {
 constexpr int kDegBuckets = 1024;
 constexpr int kScanPer = 4096;      // counts scanned by one block
 constexpr int64_t kRankPerPair = 4;  // a segment is rank-sorted while n^2 <= this times the pairs
+// The longest segment of n_pairs pairs that is rank-sorted (one wave holds 64 at no cost).
+inline int rank_longest(int64_t n_pairs) {
+  int64_t n = (int64_t)std::sqrt((double)(kRankPerPair * n_pairs));
+  if (n * n > kRankPerPair * n_pairs) --n;
+  return (int)std::max<int64_t>(n, 64);
+}
 constexpr int kSmallAtoms = 1024;   // limits of the one-block form
 constexpr int kSmallPer = 12;       // pairs per thread
 constexpr int kSmallPairs = 1024 * kSmallPer;
@@ -67,20 +75,27 @@ GAP_DEV T block_scan_1024(T v, T* wave_tot) {
   return v + base;
 }
 
-// Rank of this lane's value v (one of the n valid values of the wave, lanes
-// 0 .. n - 1) among the wave's values.
-GAP_DEV int wave_rank(int32_t v, int n) {
+// How many of lanes 0 .. n - 1's w (n <= 64; the lanes from n on hold INT32_MAX) are
+// below this lane's v, PER lanes a step.  Four take fewer instructions, one a shorter chain
+// of them: over many blocks four are faster (580,000 targets of 70 pairs: the transposition
+// 2.31 ms, 3.36 with one), for the four waves a SIMD of the one-block form one is (217
+// targets of 41 pairs: the kernel 26.9 us, 28.0 with four).
+template <int PER>
+GAP_DEV int wave_below(int32_t w, int32_t v, int n) {
   int r = 0;
-  for (int q = 0; q < n; ++q) r += __builtin_amdgcn_readlane(v, q) < v ? 1 : 0;
+  for (int q = 0; q < n; q += PER)
+#pragma unroll
+    for (int e = 0; e < PER; ++e) r += __builtin_amdgcn_readlane(w, q + e) < v ? 1 : 0;
   return r;
 }
 
 // Rank sort of one segment of n distinct values by one wave, in -> out (n uniform):
 // up to 64 values, and any number.
+template <int PER>
 GAP_DEV void wave_sort_short(const int32_t* in, int n, int32_t* __restrict__ out) {
   const int lane = threadIdx.x & 63;
-  const int32_t v = lane < n ? in[lane] : 0;
-  const int r = wave_rank(v, n);
+  const int32_t v = lane < n ? in[lane] : INT32_MAX;
+  const int r = wave_below<PER>(v, v, n);
   if (lane < n) out[r] = v;
 }
 GAP_DEV void wave_sort_segment(const int32_t* in, int n, int32_t* __restrict__ out) {
@@ -90,14 +105,19 @@ GAP_DEV void wave_sort_segment(const int32_t* in, int n, int32_t* __restrict__ o
     int r = 0;
     for (int b = 0; b < n; b += 64) {
       const int32_t w = b + lane < n ? in[b + lane] : INT32_MAX;  // never below a pair index
-      const int nb = min(64, n - b);
-      for (int q = 0; q < nb; ++q) r += __builtin_amdgcn_readlane(w, q) < v ? 1 : 0;
+      r += wave_below<4>(w, v, min(64, n - b));
     }
     if (a + lane < n) out[r] = v;
   }
 }
 
 // The same from the list of pairs in order: those of target j, 256 pairs a step.
+// A rank sort takes 0.3 ns per n^2 (a step of 64 lane reads for 64 x 64 values), this pass
+// 2 to 9 ns a pair of the whole list, so a segment passes where n^2 is above four times the
+// pairs.  (One target of 600 or 640 among 100,000 pairs: 0.13 ms by rank, 0.17 by a pass.
+// A line at n = 2048 made 20,000 targets of 2,500 pairs each pass over all 50M: 804 ms, 18
+// by rank; and one target of 2,000 among 100,000 pairs took 2.6 ms by rank at one lane a
+// step, 0.24 by a pass.)
 GAP_DEV void wave_scan_segment(const int32_t* __restrict__ pair_j, int64_t n_pairs, int32_t j,
                                int32_t* __restrict__ out) {
   const int lane = threadIdx.x & 63;
@@ -116,22 +136,6 @@ GAP_DEV void wave_scan_segment(const int32_t* __restrict__ pair_j, int64_t n_pai
   }
 }
 
-// Increasing pair order in target j's segment of n pairs, in -> out, by one wave:
-// by rank, 0.65 ns per n^2 (a step of 64 lane reads for 64 x 64 values), or by a pass over
-// the whole list, 2 to 9 ns a pair, where that is shorter.  (A line at n = 2048 made
-// 20,000 targets of 2,500 pairs each pass over all 50M: 804 ms, 23 by rank; and one
-// target of 2,000 among 100,000 pairs took 2.6 ms by rank, 0.26 by a pass.)
-GAP_DEV void wave_order_segment(const int32_t* in, int n_, int32_t* __restrict__ out,
-                                const int32_t* __restrict__ pair_j, int64_t n_pairs, int32_t j) {
-  const int n = __builtin_amdgcn_readfirstlane(n_);
-  if (n <= 64)
-    wave_sort_short(in, n, out);
-  else if ((int64_t)n * n <= kRankPerPair * n_pairs)
-    wave_sort_segment(in, n, out);
-  else
-    wave_scan_segment(pair_j, n_pairs, j, out);
-}
-
 // The whole transposition in one block, for lists that fit its LDS and
 // registers: a molecular-dynamics cell of 64 atoms and 1,900 pairs took nine
 // launches and 189 us as separate kernels (most of it the serial sort of each
@@ -140,15 +144,17 @@ GAP_DEV void wave_order_segment(const int32_t* in, int n_, int32_t* __restrict__
 // trip to memory for the pair list, then LDS.
 __global__ __launch_bounds__(1024) void k_pairs_small(
     const int64_t* __restrict__ pair_ptr, const int32_t* __restrict__ pair_j, int n_atoms,
-    int n_pairs, int64_t* __restrict__ tgt_ptr, int32_t* __restrict__ tgt_pair,
+    int n_pairs, int rank_max, int64_t* __restrict__ tgt_ptr, int32_t* __restrict__ tgt_pair,
     int32_t* __restrict__ pair_src, int32_t* __restrict__ order, int* dev_err) {
   __shared__ int32_t cnt[kSmallAtoms], start[kSmallAtoms + 1], wave_tot[16];
   __shared__ int32_t list[kSmallPairs];
+  __shared__ int longer;  // some segment holds more than 64 pairs
   const int t = threadIdx.x, wave = t >> 6;
   int32_t jv[kSmallPer];
 #pragma unroll
   for (int q = 0; q < kSmallPer; ++q) jv[q] = pair_j[min(t + 1024 * q, max(n_pairs, 1) - 1)];
   cnt[t] = 0;
+  if (t == 0) longer = 0;
 #pragma unroll
   for (int q = 0; q < kSmallPer; ++q)
     if (t + 1024 * q < n_pairs) pair_src[t + 1024 * q] = -1;
@@ -170,6 +176,7 @@ __global__ __launch_bounds__(1024) void k_pairs_small(
     write_pair_src(pair_ptr, i, n_pairs, pair_src, dev_err);
   __syncthreads();
   const int32_t c = t < n_atoms ? cnt[t] : 0;
+  if (c > 64) longer = 1;
   const int32_t incl = block_scan_1024(c, wave_tot);
   start[t] = incl - c;
   if (t == 1023) start[1024] = incl;
@@ -180,22 +187,21 @@ __global__ __launch_bounds__(1024) void k_pairs_small(
   for (int q = 0; q < kSmallPer; ++q)
     if (pos[q] >= 0) list[start[jv[q]] + pos[q]] = t + 1024 * q;
   __syncthreads();
-  bool longer = false;
   int lo = start[wave], hi = start[wave + 1];  // (entries past n_atoms hold the total)
   for (int j = wave; j < n_atoms; j += 16) {
     const int jn = min(j + 16, kSmallAtoms - 1), lo_n = start[jn], hi_n = start[jn + 1];
     const int n = __builtin_amdgcn_readfirstlane(hi - lo);
-    if (n <= 64)
-      wave_sort_short(list + lo, n, tgt_pair + lo);
-    else
-      longer = true;
+    if (n <= 64) wave_sort_short<1>(list + lo, n, tgt_pair + lo);
     lo = lo_n;
     hi = hi_n;
   }
-  if (longer)  // (apart: they are rare, and their code would slow the loop above)
+  if (__builtin_expect(longer, 0))  // (apart: their code would slow the loop above)
     for (int j = wave; j < n_atoms; j += 16) {
       const int at = start[j], n = __builtin_amdgcn_readfirstlane(start[j + 1] - at);
-      if (n > 64) wave_order_segment(list + at, n, tgt_pair + at, pair_j, n_pairs, j);
+      if (n > rank_max)
+        wave_scan_segment(pair_j, n_pairs, j, tgt_pair + at);
+      else if (n > 64)
+        wave_sort_segment(list + at, n, tgt_pair + at);
     }
   for (int p = start[1024] + t; p < n_pairs; p += 1024) tgt_pair[p] = 0;  // dropped pairs
   if (order != nullptr && t < n_atoms) {
@@ -291,22 +297,35 @@ __global__ void k_place_pairs(const int32_t* __restrict__ pair_j, int64_t n_pair
 
 // Restore increasing pair order in every segment, list -> tgt_pair: one wave
 // per target ranks its values in registers (a serial insertion sort by one
-// thread per target took 1.27 ms for 116,000 targets of 30 pairs), or rebuilds a
-// long segment from the list (wave_order_segment).  Entries past
+// thread per target took 1.27 ms for 116,000 targets of 30 pairs); segments longer
+// than rank_max are rebuilt from the list, in a loop of their own.  Entries past
 // the last segment (pairs dropped for an out-of-range target) hold pair 0, a
 // valid index for readers that clamp a slot to the end of the list.
 __global__ __launch_bounds__(256) void k_sort_segments(const int64_t* __restrict__ tgt_ptr,
                                                        int64_t n_atoms, int64_t n_pairs,
+                                                       int rank_max,
                                                        const int32_t* __restrict__ pair_j,
                                                        const int32_t* __restrict__ list,
                                                        int32_t* __restrict__ tgt_pair) {
   const int64_t nw = (int64_t)gridDim.x * 4;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  bool longer = false;
   for (int64_t j = (int64_t)blockIdx.x * 4 + wave; j < n_atoms; j += nw) {
     const int64_t lo = tgt_ptr[j];
-    wave_order_segment(list + lo, (int)(tgt_ptr[j + 1] - lo), tgt_pair + lo, pair_j, n_pairs,
-                       (int32_t)j);
+    const int n = __builtin_amdgcn_readfirstlane((int)(tgt_ptr[j + 1] - lo));
+    if (n <= 64)
+      wave_sort_short<4>(list + lo, n, tgt_pair + lo);
+    else if (n <= rank_max)
+      wave_sort_segment(list + lo, n, tgt_pair + lo);
+    else
+      longer = true;
   }
+  if (longer)
+    for (int64_t j = (int64_t)blockIdx.x * 4 + wave; j < n_atoms; j += nw) {
+      const int64_t lo = tgt_ptr[j];
+      if (__builtin_amdgcn_readfirstlane((int)(tgt_ptr[j + 1] - lo)) > rank_max)
+        wave_scan_segment(pair_j, n_pairs, (int32_t)j, tgt_pair + lo);
+    }
   for (int64_t p = tgt_ptr[n_atoms] + blockIdx.x * (int64_t)256 + threadIdx.x; p < n_pairs;
        p += (int64_t)gridDim.x * 256)
     tgt_pair[p] = 0;
@@ -397,9 +416,10 @@ void pair_transpose(const int64_t* pair_ptr, const int32_t* pair_j, int64_t n_at
                     int64_t n_pairs, int64_t* tgt_ptr, int32_t* tgt_pair, int32_t* pair_src,
                     int32_t* order, int32_t* scratch, int32_t* list, int* dev_err,
                     hipStream_t st) {
+  const int rank_max = rank_longest(n_pairs);
   if (n_pairs > 0 && n_atoms > 0 && n_atoms <= kSmallAtoms && n_pairs <= kSmallPairs) {
     hipLaunchKernelGGL(k_pairs_small, dim3(1), dim3(1024), 0, st, pair_ptr, pair_j, (int)n_atoms,
-                       (int)n_pairs, tgt_ptr, tgt_pair, pair_src, order, dev_err);
+                       (int)n_pairs, rank_max, tgt_ptr, tgt_pair, pair_src, order, dev_err);
     return;
   }
   int32_t* cnt = scratch;                               // n_atoms
@@ -416,7 +436,7 @@ void pair_transpose(const int64_t* pair_ptr, const int32_t* pair_j, int64_t n_at
     hipLaunchKernelGGL(k_place_pairs, dim3(grid_for(n_pairs)), dim3(256), 0, st, pair_j, n_pairs,
                        n_atoms, tgt_ptr, tgt_pair, list);
     hipLaunchKernelGGL(k_sort_segments, dim3(grid_for(n_atoms, 4)), dim3(256), 0, st, tgt_ptr,
-                       n_atoms, n_pairs, pair_j, list, tgt_pair);
+                       n_atoms, n_pairs, rank_max, pair_j, list, tgt_pair);
   }
   if (order != nullptr && n_atoms > 0) {
     const unsigned nb = (unsigned)((n_atoms + 1023) / 1024);

@@ -94,3 +94,13 @@ def test_segment_order_where_its_two_forms_meet(gapx, gap, n_atoms, n_pairs, hea
     order = np.argsort(pair_j, kind="stable")
     assert np.array_equal(tptr.cpu().numpy(), np.searchsorted(pair_j[order], np.arange(n_atoms + 1)))
     assert np.array_equal(tpair.cpu().numpy(), order)
+
+
+@pytest.mark.parametrize("n_atoms", [150, 1300])
+def test_every_short_segment(gapx, gap, n_atoms):
+    """Segments of 0 to 140 pairs, in the one-block form and the general one."""
+    pair_ptr, pair_j = pair_list(n_atoms, 12288, tuple(range(141)))
+    tptr, tpair = gap.pair_transpose(atoms_of(gapx, pair_ptr, pair_j))
+    order = np.argsort(pair_j, kind="stable")
+    assert np.array_equal(tptr.cpu().numpy(), np.searchsorted(pair_j[order], np.arange(n_atoms + 1)))
+    assert np.array_equal(tpair.cpu().numpy(), order)
